@@ -89,7 +89,7 @@ def _n_layers(case):
     return {"hmm": case["n"] - 1, "btree": case["n"] - 2}.get(case["family"], 0)
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
     """Device tensors of one head and one batch.  h is what a normalised hidden state looks like (unit
     variance), W gives logits of standard deviation 2 (a byte model's predictions are peaked), the layers are those
     of a head that was initialised at the identity and has moved away from it (about 0.6 on the diagonal)."""
@@ -114,20 +114,31 @@ def prepare(case, seed):
             layers = eye.expand(L, r, r).contiguous()
         else:
             layers = eye + gauss(L, r, r, dtype=torch.float32)
-    head = Head(case["family"], h, W, Wsum, layers, R)
-    if case["packed"]:
-        head.pack_W()
-    state = {"case": case, "head": head, "seed": seed & 0x7fffffff,
-             "targets": torch.randint(0, min(v, 256), (B, n), generator=gen, device=dev, dtype=torch.int32)}
+    x = {"h": h, "W": W, "Wsum": Wsum, "layers": layers, "R": R,
+         "targets": torch.randint(0, min(v, 256), (B, n), generator=gen, device=dev, dtype=torch.int32)}
     if case["op"] in ("greedy", "decode"):
-        state["p"] = torch.softmax(gauss(B, n + 1, v, std=2.0, dtype=torch.float32), dim=-1).contiguous()
-    if case["op"] == "decode":
-        state["table"] = torch.empty(B, n, r, v, device=dev, dtype=torch.float32)
+        x["p"] = torch.softmax(gauss(B, n + 1, v, std=2.0, dtype=torch.float32), dim=-1).contiguous()
     if case["op"] == "train":
         # discounted loss over the positions whose window is whole
         valid = (torch.rand(B, n, generator=gen, device=dev) < 0.9).float()
-        state["coef"] = (0.8 ** torch.arange(n, device=dev, dtype=torch.float32) * valid / valid.sum()).contiguous()
-        f32 = {"dtype": torch.float32, "device": dev}
+        x["coef"] = (0.8 ** torch.arange(n, device=dev, dtype=torch.float32) * valid / valid.sum()).contiguous()
+    return x
+
+
+def prepare(case, seed):
+    """The head and what its program keeps beside it: buffers for the table, for the gradients."""
+    x = _inputs(case, seed)
+    h, W, Wsum, layers, R = (x[k] for k in ("h", "W", "Wsum", "layers", "R"))
+    B, d, n, r, v = (case[k] for k in "Bdnrv")
+    head = Head(case["family"], h, W, Wsum, layers, R)
+    if case["packed"]:
+        head.pack_W()
+    f32 = {"dtype": torch.float32, "device": h.device}
+    state = {"case": case, "head": head, "seed": seed & 0x7fffffff}
+    state.update({k: x[k] for k in ("targets", "p", "coef") if k in x})
+    if case["op"] == "decode":
+        state["table"] = torch.empty(B, n, r, v, **f32)
+    if case["op"] == "train":
         state["grads"] = {"loss": torch.empty(B, **f32), "dh": torch.empty(B, d, **f32), "dW": torch.empty(n, r, v, d, **f32),
                           "dWsum": None if Wsum is None else torch.empty(r, d, **f32),
                           "dlayers": None if layers is None else torch.empty_like(layers),
@@ -196,3 +207,119 @@ def tolerance(case):
     if case["op"] == "train":
         return {"rel": 7e-3, "max": 0.4} if case["dtype"] == "bf16" else {"rel": 2e-5}
     return {"rel": 1e-6}
+
+
+# ---- the same values in 64 bits, in plain torch -------------------------------------------------------------
+
+def _lse_step(A, x):
+    """log sum_j exp(A[.., k, j]) exp(x[b, j]); A [k, j] shared or [b, k, j] of each position."""
+    m = x.amax(dim=-1, keepdim=True)
+    w = torch.exp(x - m)
+    y = w @ torch.exp(A).T if A.dim() == 2 else (torch.exp(A) * w[:, None, :]).sum(dim=-1)
+    return m + torch.log(y)
+
+
+def _joint(family, e, logw, logA):
+    """log of the circuit's value from the log evidence e [B, n, r]; layer l of logA is logA[l] or logA[:, l]."""
+    n = e.shape[1]
+    layer = (lambda l: logA[l]) if logA is None or logA.dim() == 3 else (lambda l: logA[:, l])
+    if family == "ff":
+        return e[:, :, 0].sum(dim=1)
+    if family == "cp":
+        return torch.logsumexp(logw + e.sum(dim=1), dim=-1)
+    if family == "hmm":
+        alpha = logw + e[:, 0]
+        for i in range(1, n):
+            alpha = e[:, i] + _lse_step(layer(i - 1).transpose(-1, -2), alpha)
+        return torch.logsumexp(alpha, dim=-1)
+    node = [None] * (n - 1) + [e[:, i] for i in range(n)]
+    for m in range(n - 2, 0, -1):
+        node[m] = _lse_step(layer(m - 1), node[2 * m + 1] + node[2 * m + 2])
+    return torch.logsumexp(logw + node[1] + node[2], dim=-1)
+
+
+def _prefix(family, e, logw, logA):
+    n = e.shape[1]
+    past = torch.tril(torch.ones(n, n, dtype=e.dtype, device=e.device))
+    return torch.stack([_joint(family, e * past[i][None, :, None], logw, logA) for i in range(n)], dim=1)
+
+
+def _leaf_marginals(family, logw, logA, n, B):
+    """log of the marginal of the latent that selects the input units of each token: [B, n, r]."""
+    if family == "ff":
+        return torch.zeros(B, n, 1, dtype=torch.float64, device="cuda:0")
+    if family == "cp":
+        return logw[:, None, :].expand(B, n, logw.shape[-1])
+    layer = (lambda l: logA[l].transpose(-1, -2)) if logA is None or logA.dim() == 3 else (lambda l: logA[:, l].transpose(-1, -2))
+    if family == "hmm":
+        z = [logw]
+        for i in range(1, n):
+            z.append(_lse_step(layer(i - 1), z[-1]))
+        return torch.stack(z, dim=1)
+    z = [logw]
+    for m in range(1, n - 1):
+        z.append(_lse_step(layer(m - 1), z[(m - 1) // 2]))
+    return torch.stack([z[(n - 2 + i) // 2] for i in range(n)], dim=1)
+
+
+def exact(case, seed):
+    """The values of run() that do not depend on a draw."""
+    op, family = case["op"], case["family"]
+    if op in ("greedy", "draft_score"):
+        return None         # whole values, and the scores of what was drawn
+    x = _inputs(case, seed)
+    B, d, n, r, v = (case[k] for k in "Bdnrv")
+    up = lambda t: None if t is None else t.double()
+    h, W, tg = x["h"].double(), x["W"], x["targets"].long()
+    s = None if x["Wsum"] is None else (h @ up(x["Wsum"]).T).requires_grad_(op == "train")
+    lay = up(x["layers"])
+    if x["R"] is not None:
+        L = x["R"].shape[0]
+        lay = lay + torch.stack([h @ up(x["R"][l]).reshape(r * r, d).T for l in range(L)], dim=1).view(B, L, r, r)
+    if lay is not None:
+        lay = lay.detach().requires_grad_(op == "train")
+    logw = None if s is None else torch.log_softmax(s, dim=-1)
+    logA = None if lay is None else torch.log_softmax(lay, dim=-1)
+
+    def logphi(i, j):
+        return torch.log_softmax(h @ W[i, j].double().T, dim=-1)
+
+    if op == "decode":
+        return None, None, torch.stack([torch.stack([logphi(i, j) for j in range(r)], dim=1) for i in range(n)], dim=1), None, None
+    if op == "univariate":
+        m = _leaf_marginals(family, logw, logA, n, B)
+        out = torch.full((B, n, v), -math.inf, dtype=torch.float64, device=h.device)
+        for i in range(n):
+            for j in range(r):
+                out[:, i] = torch.logaddexp(out[:, i], m[:, i, j, None] + logphi(i, j))
+        return out
+    e = torch.stack([torch.stack([logphi(i, j).gather(1, tg[:, i, None])[:, 0] for j in range(r)], dim=1) for i in range(n)], dim=1)
+    if op == "loglik":
+        return _joint(family, e, logw, logA)
+    if op == "prefix":
+        return _prefix(family, e, logw, logA)
+    e.requires_grad_(True)
+    P = _prefix(family, e, logw, logA)
+    loss = (x["coef"].double() * (torch.nn.functional.pad(P[:, :-1], (1, 0)) - P)).sum(dim=1)
+    loss.sum().backward()
+    out = {"loss": loss.detach(), "dh": torch.zeros(B, d, dtype=torch.float64, device=h.device),
+           "dW": torch.empty(n, r, v, d, dtype=torch.float64, device=h.device)}
+    for i in range(n):
+        for j in range(r):
+            g = -torch.exp(logphi(i, j))
+            g.scatter_add_(1, tg[:, i, None], torch.ones_like(g[:, :1]))
+            g *= e.grad[:, i, j, None]
+            out["dW"][i, j] = g.T @ h
+            out["dh"] += g @ W[i, j].double()
+    if s is not None:
+        out["dWsum"] = s.grad.T @ h
+        out["dh"] += s.grad @ up(x["Wsum"])
+    if x["R"] is not None:
+        g = lay.grad.view(B, -1, r * r)
+        out["dR"] = torch.stack([(g[:, l].T @ h).view(r, r, d) for l in range(L)])
+        out["dlayers"] = lay.grad.sum(dim=0)
+        for l in range(L):
+            out["dh"] += g[:, l] @ up(x["R"][l]).reshape(r * r, d)
+    elif lay is not None:
+        out["dlayers"] = lay.grad
+    return out
