@@ -81,6 +81,21 @@ bool stage_major_h_pays(const mtpc_head* hd) {
   return hd->B > 64 && row % H_STAGE_BYTES == 0 && row * (unsigned long long)hd->B < (1ull << 32);
 }
 
+// fp32 operands of the 256-position tiles as planes of three bf16 terms (launch_unembed), where a pass over all
+// of W is then faster: per round of tiles over the CUs SPLIT_TILE_US against F32_TILE_US (a 320 x 256 tile, 1024
+// columns; B = 2048, n r = 256, d = 3072: 3.56 against 7.29 ms), against that stand the split of W (4 bytes read
+// and 6 written per element: 0.43 ms there, 4.9 TB/s) and four short launches.
+constexpr double SPLIT_TILE_US = 148, F32_TILE_US = 304;
+bool split_pays(const mtpc_head* hd) {
+  if (hd->dtype != MTPC_F32 || hd->B <= 64) return false;
+  if ((unsigned long long)hd->B * hd->d * 6 >= (1ull << 32)) return false;      // one 32-bit buffer resource
+  const double rows = hd->v > 256 ? 320 : hd->v > 128 ? 256 : 128;
+  const double rounds = std::ceil((double)((hd->B + 255) / 256) * hd->n * hd->r / 256.0);
+  const double tile = rounds * rows / 320.0 * hd->d / 1024.0;
+  const double split = (double)hd->n * hd->r * hd->v * hd->d * 10.0 / 4.9e6 + 15.0;
+  return tile * SPLIT_TILE_US + split < tile * F32_TILE_US;
+}
+
 // most windows per position whose rows B*T*n still index with an int
 long long hd_rows_limit(const mtpc_head* hd) {
   if (!hd || hd->B < 1 || hd->n < 1) return 0x7fffffffLL;      // rejected later by check_head
@@ -91,6 +106,8 @@ struct Plan {           // byte offsets into the workspace
   size_t logw, lay_nat, lay_circ, e, zleaf, lat, logm, table, total;
   size_t hs;            // stage-major copy of h for the 256-position tiles of the fused kernel
   bool has_hs;
+  size_t Wq, hq, wild;  // fp32 as three bf16 terms: planes of W and h, flag (launch_unembed)
+  bool has_split;
   size_t lean_total;    // univariate marginals: the plan without the table
   size_t bk_count, bk_slot, bk_rowoff, bk_tileoff, bk_tilebucket, bk_list;
   size_t rowlogits;     // compact table of the few-drafts path   // buckets of the token draws (large batches)
@@ -140,7 +157,7 @@ mtpc_status check_layers(int family, const mtpc_head* hd, const mtpc_sumlayers* 
 }
 
 Plan make_plan(int family, int op, const mtpc_head* hd, const mtpc_sumlayers* ly, int S, int mode,
-               bool want_prefix, bool caller_table = false) {
+               bool want_prefix, bool caller_table = false, bool split = true) {
   Plan p{};
   const size_t B = hd->B, n = hd->n, r = hd->r;
   const int L = n_layers(family, hd->n);
@@ -186,6 +203,15 @@ Plan make_plan(int family, int op, const mtpc_head* hd, const mtpc_sumlayers* ly
   p.zleaf = sample ? take(B * (size_t)S * n * 4) : 0;
   p.lat = sample ? take(B * (size_t)S * (size_t)(n_latents(family, hd->n) + 1) * 4) : 0;
   p.logm = uni ? take(B * n * r * 4) : 0;
+  // the calls that run the fused kernel over all of W (below: not those that draw through buckets or rows)
+  const bool full_pass = op == MTPC_OP_LOGLIK || op == MTPC_OP_WINDOWS || (uni ? r == 1 || table_fits(hd) : op == MTPC_OP_MARGINALS) ||
+                         (sample && (want_prefix || caller_table || !buckets_pay(hd, S, want_prefix)));
+  if (split && full_pass && split_pays(hd)) {
+    p.has_split = true;
+    p.wild = take(4);
+    p.hq = take(B * (size_t)hd->d * 6);
+    p.Wq = take(n * r * (size_t)hd->v * hd->d * 6);
+  }
   p.lean_total = off;
   if (uni && r > 1 && table_fits(hd)) {       // last, so that a caller may leave it out (see prepare)
     p.has_table = true;
@@ -230,6 +256,9 @@ mtpc_status prepare(int family, int op, const mtpc_head* hd, const mtpc_sumlayer
   plan = make_plan(family, op, hd, ly, S, mode, want_prefix, caller_table);
   if (!hd->workspace) return MTPC_ERR_NULL;
   if ((uintptr_t)hd->workspace & 15) return MTPC_ERR_WORKSPACE;
+  if (plan.has_split && op == MTPC_OP_SAMPLE && hd->workspace_bytes < plan.total)
+    // (the static scratch, or a caller's workspace of another size: sampling runs without the bf16 terms)
+    plan = make_plan(family, op, hd, ly, S, mode, want_prefix, caller_table, false);
   if (hd->workspace_bytes < plan.total) {
     // univariate marginals run without the table when the workspace has no room for it
     const bool uni = op == MTPC_OP_MARGINALS && mode == MTPC_MARG_UNIVARIATE;
@@ -252,6 +281,13 @@ UnembedArgs unembed_args(const mtpc_head* hd) {
   u.Wp_stage = hd->W_stage_bytes == 0 ? PACK_STAGE_BYTES : hd->W_stage_bytes;
   u.B = hd->B; u.d = hd->d; u.v = hd->v; u.n = hd->n; u.r = hd->r;
   return u;
+}
+
+// the scratch of the bf16 terms (when the plan has room for it) into the arguments
+void split_scratch(const mtpc_head* hd, const Plan& p, UnembedArgs& u) {
+  if (!p.has_split) return;
+  char* ws = (char*)hd->workspace;
+  u.Wq = ws + p.Wq; u.hq = ws + p.hq; u.wild = (int*)(ws + p.wild);
 }
 
 // the stage-major copy of h into the workspace (when the plan has room for it) and into the arguments
@@ -325,6 +361,7 @@ mtpc_status run_evidence_op(int family, const mtpc_head* hd, const mtpc_sumlayer
   if (s != MTPC_OK) return s;
   UnembedArgs u = unembed_args(hd);
   u.targets = targets; u.T = 1; u.e = (float*)(ws + p.e);
+  split_scratch(hd, p, u);
   HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, u, st));
   {
     ProfScope prof(st);
@@ -363,6 +400,7 @@ mtpc_status run_univariate(int family, const mtpc_head* hd, const mtpc_sumlayers
   if (family == MTPC_FF || p.has_table) {
     UnembedArgs t = unembed_args(hd);
     t.logphi = family == MTPC_FF ? out : (float*)(ws + p.table);
+    split_scratch(hd, p, t);
     HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, t, st));
     {
       ProfScope prof(st);
@@ -469,6 +507,7 @@ mtpc_status run_sample(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
   } else {
     UnembedArgs u = unembed_args(hd);
     u.logphi = table;
+    split_scratch(hd, p, u);
     HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, u, st));
     hs_ready = u.hs;
     if (draw == Draw::InKernel) {
@@ -490,6 +529,7 @@ mtpc_status run_sample(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
   if (want_prefix && !table_scores) {
     UnembedArgs u2 = unembed_args(hd);
     u2.targets = drafts; u2.T = S; u2.e = (float*)(ws + p.e);
+    split_scratch(hd, p, u2);
     if (hs_ready != nullptr) u2.hs = hs_ready;
     else HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, u2, st));
     ProfScope prof(st);
@@ -525,6 +565,7 @@ mtpc_status run_window_scores(int family, const mtpc_head* hd, const mtpc_sumlay
   if (s != MTPC_OK) return s;
   UnembedArgs u = unembed_args(hd);
   u.targets = x; u.T = T; u.targets2 = x2; u.T2 = T2; u.e = (float*)(ws + p.e);
+  split_scratch(hd, p, u);
   HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, u, st));
   {
     ProfScope prof(st);
@@ -605,9 +646,12 @@ struct BwdPlan {
   int Lst;                  // stored layers (1: one matrix shared by all steps)
   int steps;                // reverse-pass steps with a layer (HMM: n-1; tree: program length)
   long long M, Mx, Mlay, Mtot, ldM, ldb;
+  // fp32 as three bf16 terms: in the forward pass (split_pays) and in the two contractions
+  bool split_fwd, split;
+  size_t Wq, hq, wild, dslT;
 };
 
-BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly, bool keep_phi) {
+BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly, bool keep_phi, bool split = true) {
   BwdPlan q{};
   q.keep_phi = keep_phi;
   const size_t esz = hd->dtype == MTPC_BF16 ? 2 : 4;
@@ -628,14 +672,28 @@ BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly,
   q.logw = take(B * r * 4);
   q.e = take(B * n * r * 4);
   q.Ge = take(B * n * r * 4);
-  q.dLT = take((size_t)(q.ctx ? q.ldM : q.Mx) * q.ldb * esz);
-  q.dL = take(B * q.ldM * esz);
-  q.WT = take((size_t)hd->d * q.ldM * esz);
+  // The contractions take the terms wherever one 32-bit buffer resource spans each operand and every element of
+  // the logit gradient is written by one kernel (layers computed from h have columns from elsewhere)
+  const unsigned long long lim = 1ull << 32;
+  q.split = split && keep_phi && hd->dtype == MTPC_F32 && hd->B > 64 && !q.ctx && (unsigned long long)q.M * q.ldb * 6 < lim &&
+            (unsigned long long)B * q.ldM * 6 < lim && (unsigned long long)hd->d * q.ldM * 6 < lim &&
+            (unsigned long long)hd->d * q.ldb * 6 < lim;
+  q.split_fwd = q.split && split_pays(hd);
+  const size_t osz = q.split ? 6 : esz;       // bytes per element of the contractions' operands
+  q.dLT = take((size_t)(q.ctx ? q.ldM : q.split ? q.M : q.Mx) * q.ldb * osz);
+  q.dslT = q.split ? take((size_t)(q.Mx - q.M) * q.ldb * esz) : q.dLT + (size_t)q.M * q.ldb * esz;
+  q.dL = take(B * q.ldM * osz);
+  q.WT = take((size_t)hd->d * q.ldM * osz);
   q.hT = take((size_t)hd->d * q.ldb * esz);
+  if (q.split_fwd) {
+    q.wild = take(4);
+    q.hq = take(B * (size_t)hd->d * 6);
+    q.Wq = take((size_t)q.M * hd->d * 6);
+  }
   q.has_hs = stage_major_h_pays(hd);
   q.hs = q.has_hs ? take(B * (size_t)hd->d * esz) : 0;
-  q.has_hTs = (unsigned long long)hd->d * q.ldb * esz < (1ull << 32);
-  q.hTs = q.has_hTs ? take((size_t)hd->d * q.ldb * esz) : 0;
+  q.has_hTs = (unsigned long long)hd->d * q.ldb * osz < (1ull << 32);
+  q.hTs = q.has_hTs ? take((size_t)hd->d * q.ldb * osz) : 0;
   q.steps = family == MTPC_BTREE ? tree_program_steps(hd->n, 1) : L;
   if (L > 0) {
     const size_t lay = ((q.ctx || q.perpos) ? B : 1) * (size_t)q.Lst * r * r * 4;
@@ -706,6 +764,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   BwdPlan q = make_bwd_plan(family, hd, ly, true);
   if (!hd->workspace) return MTPC_ERR_NULL;
   if ((uintptr_t)hd->workspace & 15) return MTPC_ERR_WORKSPACE;
+  if (hd->workspace_bytes < q.total && q.split) q = make_bwd_plan(family, hd, ly, true, false);
   if (hd->workspace_bytes < q.total) q = make_bwd_plan(family, hd, ly, false);
   if (hd->workspace_bytes < q.total) return MTPC_ERR_WORKSPACE;
   if (q.ldM * 4 > 0x7fffffffLL / 320 || q.ldb * 4 > 0x7fffffffLL / 320) return MTPC_ERR_UNSUPPORTED;
@@ -734,6 +793,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   UnembedArgs u = unembed_args(hd);
   u.targets = targets; u.T = 1; u.e = (float*)(ws + q.e);
   if (q.keep_phi) { u.phiT = (float*)(ws + q.phi); u.ld_phi = q.ldb; }
+  if (q.split_fwd) { u.Wq = ws + q.Wq; u.hq = ws + q.hq; u.wild = (int*)(ws + q.wild); }
   HIP_TRY(stage_major_h(hd, q.has_hs, q.hs, u, st));
   HIP_TRY(launch_unembed(u, hd->dtype, st));
 
@@ -743,7 +803,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   c.e = (const float*)(ws + q.e);
   c.logw = family == MTPC_FF ? nullptr : (const float*)(ws + q.logw);
   c.coef = coef; c.Ge = (float*)(ws + q.Ge);
-  c.dslT = family == MTPC_FF ? nullptr : (void*)(ws + q.dLT + (size_t)q.M * q.ldb * esz);
+  c.dslT = family == MTPC_FF ? nullptr : (void*)(ws + q.dslT);
   c.ldb = q.ldb; c.bf16 = hd->dtype == MTPC_BF16; c.loss = loss;
   if (L > 0) {
     c.lay_nat = (const float*)(ws + q.lay_nat);
@@ -771,8 +831,8 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   // ---- logit gradient in both layouts: dLT [.][ldb] and dL = dLT^T [B][ldM]
   // (stage-major, as the contractions read their 320-row operands, when this kernel writes every element of
   // both - no layer-logit columns from elsewhere - and one 32-bit buffer resource spans each)
-  const bool grads_staged = q.keep_phi && !ctx && (unsigned long long)q.M * q.ldb * esz < (1ull << 32) &&
-                            (unsigned long long)hd->B * q.ldM * esz < (1ull << 32);
+  const bool grads_staged = q.split || (q.keep_phi && !ctx && (unsigned long long)q.M * q.ldb * esz < (1ull << 32) &&
+                                        (unsigned long long)hd->B * q.ldM * esz < (1ull << 32));
   TransposeArgs t{};
   if (q.keep_phi) {
     GradPhiArgs g{};
@@ -782,6 +842,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
     g.dl_end = ctx ? q.Mlay : q.ldM;           // the layer-logit columns are written by the reverse pass
     g.dLT = ws + q.dLT; g.dL = ws + q.dL;
     g.staged = grads_staged;
+    g.planes = q.split; g.dslT = ws + q.dslT;
     HIP_TRY(launch_grad_from_phi(g, hd->dtype, st));
   } else {
     GradLogitsArgs g{};
@@ -806,6 +867,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   // (64-byte stages, [ldM * esz / 64][d][64 bytes]) when one 32-bit buffer resource spans it
   const bool wt_staged = (unsigned long long)hd->d * q.ldM * esz < (1ull << 32);
   t.stage_rows = wt_staged ? hd->d : 0;
+  t.planes = q.split;
   t.src = hd->W; t.ld_src = hd->d; t.R = (int)q.M; t.C = hd->d;
   t.dst = ws + q.WT; t.ld_dst = q.ldM; t.col0 = 0; t.Rpad = (int)(family == MTPC_FF ? q.ldM : q.M);
   HIP_TRY(launch_transpose(t, hd->dtype, st));
@@ -819,11 +881,14 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
     t.col0 = q.Mlay; t.Rpad = (int)(q.ldM - q.Mlay);
     HIP_TRY(launch_transpose(t, hd->dtype, st));
   }
-  t.stage_rows = 0;                           // hT also feeds the small dWsum kernel: plain, plus a stage-major copy
+  t.stage_rows = t.planes = 0;                // hT also feeds the small dWsum kernel: plain, plus a stage-major copy
   t.src = hd->h; t.ld_src = hd->ld_h; t.R = hd->B; t.C = hd->d;
   t.dst = ws + q.hT; t.ld_dst = q.ldb; t.col0 = 0; t.Rpad = (int)q.ldb;
   HIP_TRY(launch_transpose(t, hd->dtype, st));
-  if (q.has_hTs)
+  if (q.split) {
+    t.dst = ws + q.hTs; t.stage_rows = hd->d; t.planes = 1;
+    HIP_TRY(launch_transpose(t, hd->dtype, st));
+  } else if (q.has_hTs)
     HIP_TRY(launch_pack_rows(ws + q.hT, ws + q.hTs, 1, hd->d, (int)(q.ldb * esz), q.ldb * (long long)esz, H_STAGE_BYTES, st));
 
   // ---- the two contractions
@@ -832,6 +897,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   m.Bm = ws + q.WT; m.ldb = q.ldM; m.N = hd->d; m.K = (int)q.ldM;
   m.Bs = wt_staged ? ws + q.WT : nullptr;
   m.As = grads_staged ? ws + q.dL : nullptr; m.As_rows = hd->B;
+  m.planes = q.split;
   m.C = dh; m.ldc = hd->d; m.split = hd->B; m.n2 = 0; m.C2 = nullptr; m.split3 = 0x7fffffff; m.C3 = nullptr;
   m.ksplit = q.ksplit; m.kchunk = q.kchunk; m.partial = q.ksplit > 1 ? (float*)(ws + q.partial) : nullptr;
   HIP_TRY(launch_gemm_tn(m, hd->dtype, st));
@@ -850,7 +916,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   m.split3 = ctx ? (int)q.Mlay : 0x7fffffff; m.C3 = dR;
   HIP_TRY(launch_gemm_tn(m, hd->dtype, st));
   if (own_dwsum)
-    HIP_TRY(launch_dwsum(ws + q.dLT + (size_t)q.M * q.ldb * esz, ws + q.hT, q.ldb, hd->r, hd->d, hd->dtype, dWsum, st));
+    HIP_TRY(launch_dwsum(ws + q.dslT, ws + q.hT, q.ldb, hd->r, hd->d, hd->dtype, dWsum, st));
   return MTPC_OK;
 }
 

@@ -87,12 +87,72 @@ __global__ __launch_bounds__(256) void k_transpose_vec(const TransposeArgs a) {
   }
 }
 
+// fp32 matrices into planes of three bf16 terms (split3) of the transpose, stage-major with a.stage_rows rows:
+// [3 columns/32][stage_rows][64 bytes].  64 x 64 tiles through LDS; a thread splits eight neighbours along the
+// contraction, 16 bytes of each plane (element by element where a column block starts or ends inside them).
+__global__ __launch_bounds__(256) void k_transpose_planes(const TransposeArgs a) {
+  __shared__ float tile[64][64 + 1];
+  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
+  const float* src = (const float*)a.src;
+  unsigned short* dst = (unsigned short*)a.dst;
+  {
+    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int r = r0 + ty + 4 * k, c = c0 + tx;
+      tile[ty + 4 * k][tx] = (r < a.R && c < a.C) ? src[(long long)r * a.ld_src + c] : 0.f;
+    }
+  }
+  __syncthreads();
+  // four threads write the 64 bytes of a row of one plane
+  const int ch = threadIdx.x & 3, cc = threadIdx.x >> 2;
+  const int c = c0 + cc;
+  if (c >= a.C) return;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int rl = half * 32 + ch * 8, r = r0 + rl;
+    if (r >= a.Rpad) continue;
+    struct alignas(16) Oct { unsigned short v[8]; } o[3];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      unsigned short q[3];
+      split3(tile[rl + t][cc], q);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) o[p].v[t] = q[p];
+    }
+    const long long k = a.col0 + r;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      if ((k & 7) == 0 && r + 8 <= a.Rpad) {
+        *(Oct*)(dst + ((k / 32 * 3 + p) * a.stage_rows + c) * 32 + k % 32) = o[p];
+      } else {
+        for (int t = 0; t < 8; ++t)
+          if (r + t < a.Rpad) dst[(((k + t) / 32 * 3 + p) * a.stage_rows + c) * 32 + (k + t) % 32] = o[p].v[t];
+      }
+    }
+  }
+}
+
 // 64 (m) x 128 (b) tiles: logit gradient from the stored probabilities, written in both
 // layouts (dLT along b straight away, dL along m after a transpose through LDS).  A thread
 // moves four neighbouring elements at a time (16-byte loads, 8- or 16-byte stores).
-template <typename T>
+// PLANES (fp32): both layouts as planes of three bf16 terms, as tile_gemm_run_split reads them.
+template <typename T, bool PLANES = false>
 __global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a) {
   struct alignas(4 * sizeof(T)) Quad { T v[4]; };
+  // four neighbours along K, to row `row` of a staged matrix of `rows` rows
+  auto put_planes = [](void* dst, long long k, long long rows, long long row, const Quad& x) {
+    struct alignas(8) Half { unsigned short v[4]; } o[3];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      unsigned short q[3];
+      split3((float)x.v[c], q);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) o[p].v[c] = q[p];
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *(Half*)((unsigned short*)dst + ((k / 32 * 3 + p) * rows + row) * 32 + k % 32) = o[p];
+  };
   __shared__ T tile[64][128 + 4];
   const long long m0 = (long long)blockIdx.y * 64;
   const int b0 = blockIdx.x * 128;
@@ -134,10 +194,11 @@ __global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a) {
       for (int c = 0; c < 4; ++c)
         if (b + c < a.B && x[c] != -1) out.v[c] = conv(g[c] * ((av == x[c] ? 1.f : 0.f) - pv[c]));
       constexpr int EPS = 64 / (int)sizeof(T);     // elements of a row per stage (b is a multiple of 4)
-      if (a.staged) *(Quad*)(dLT + ((long long)(b / EPS) * a.M + m) * EPS + b % EPS) = out;
+      if constexpr (PLANES) put_planes(a.dLT, b, a.M, m, out);
+      else if (a.staged) *(Quad*)(dLT + ((long long)(b / EPS) * a.M + m) * EPS + b % EPS) = out;
       else *(Quad*)(dLT + m * a.ldb + b) = out;
     } else if (m < a.Mx && col_ok) {
-      out = *(const Quad*)(dLT + m * a.ldb + b);   // sum-unit rows, written by the reverse pass
+      out = *(const Quad*)((const T*)a.dslT + (m - a.M) * a.ldb + b);   // sum-unit rows, written by the reverse pass
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) tile[ml][4 * tx + c] = out.v[c];
@@ -153,7 +214,8 @@ __global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) out.v[c] = tile[4 * mq + c][bl];
       constexpr int EPS = 64 / (int)sizeof(T);
-      if (a.staged) *(Quad*)(dL + ((m / EPS) * a.B + (b0 + bl)) * EPS + m % EPS) = out;
+      if constexpr (PLANES) put_planes(a.dL, m, a.B, b0 + bl, out);
+      else if (a.staged) *(Quad*)(dL + ((m / EPS) * a.B + (b0 + bl)) * EPS + m % EPS) = out;
       else *(Quad*)(dL + (long long)(b0 + bl) * a.ldM + m) = out;
     }
   }
@@ -686,6 +748,11 @@ __global__ __launch_bounds__(256) void k_fill_zero(float* p, long long n) {
 hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t st) {
   if (a.C < 1 || a.Rpad < 1) return hipSuccess;
   const dim3 grid((a.C + 63) / 64, (a.Rpad + 63) / 64);
+  if (a.planes) {
+    if (dtype != MTPC_F32 || a.stage_rows <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_transpose_planes, grid, dim3(256), 0, st, a);
+    return hipGetLastError();
+  }
   const int esz = dtype == MTPC_BF16 ? 2 : 4, ve = 16 / esz;
   const bool vec = a.ld_src % ve == 0 && a.ld_dst % ve == 0 && a.col0 % ve == 0 &&
                    (((uintptr_t)a.src | (uintptr_t)a.dst) & 15) == 0;
@@ -702,6 +769,7 @@ hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t st) {
 hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st) {
   const dim3 grid((unsigned)((a.ldb + 127) / 128), (unsigned)((a.ldM + 63) / 64));
   if (dtype == MTPC_BF16) hipLaunchKernelGGL(k_grad_from_phi<unsigned short>, grid, dim3(256), 0, st, a);
+  else if (a.planes) hipLaunchKernelGGL((k_grad_from_phi<float, true>), grid, dim3(256), 0, st, a);
   else hipLaunchKernelGGL(k_grad_from_phi<float>, grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }

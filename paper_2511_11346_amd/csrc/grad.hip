@@ -107,7 +107,8 @@ hipError_t launch_unembed_grad(const GradLogitsArgs& a, int dtype, hipStream_t s
 }
 
 // ---------------------------------------------------------------------------
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool ASTAGED>
+// SPLIT: fp32 operands as planes of three bf16 terms (tile_gemm_run_split), both stage-major.
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool ASTAGED, bool SPLIT = false>
 __global__ __launch_bounds__(WV * WB * 64)
 void k_gemm_tn(const GemmArgs a) {
   using TL = Tile<WV, WB, VB, PB, SB, NS>;
@@ -138,8 +139,14 @@ void k_gemm_tn(const GemmArgs a) {
     t.klen = min(a.kchunk, a.K - t.k0);
     return t;
   };
-  TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, ASTAGED> feed;
+  TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, ASTAGED, false, 0, SPLIT> feed;
   auto open = [&](const Where& t) {
+    if constexpr (SPLIT) {
+      const long long s0 = (long long)(t.k0 / 32) * 3;             // (chunks are multiples of 64 columns)
+      feed.open((const char*)a.As + s0 * a.As_rows * 64, 0, a.Bm, 0, a.N, 3 * t.klen, t.rows, 0, t.b0, smem, nullptr, 0, 1,
+                (const char*)a.Bs + s0 * a.N * 64, a.As_rows, t.slab * TL::TV);
+      return;
+    }
     // (the chunk [k0, k0 + klen) of a stage-major operand is the run of its stages k0 * ESZ / 64 onwards)
     const char* bs = (a.Bs != nullptr && SB == 64) ? (const char*)a.Bs + (long long)t.k0 * ESZ / 64 * a.N * 64 : nullptr;
     if constexpr (ASTAGED)
@@ -153,7 +160,8 @@ void k_gemm_tn(const GemmArgs a) {
   open(cur);
   for (int w = blockIdx.x;;) {
     typename FR::blk_t acc[NPB][NVB];
-    tile_gemm_run(feed, cur.klen, smem, acc);
+    if constexpr (SPLIT) tile_gemm_run_split(feed, cur.klen, smem, acc);
+    else tile_gemm_run(feed, cur.klen, smem, acc);
     const int wnext = w + (int)gridDim.x;
     Where nxt = cur;
     if (wnext < total) {
@@ -215,12 +223,14 @@ void k_gemm_tn(const GemmArgs a) {
   }
 }
 
-template <int WV, int WB, int VB, int PB, bool BF16, bool ASTAGED = false>
+template <int WV, int WB, int VB, int PB, bool BF16, bool ASTAGED = false, bool SPLIT = false>
 static hipError_t launch_gemm_cfg(const GemmArgs& a, hipStream_t st) {
   using TL = Tile<WV, WB, VB, PB, 64, 4>;
+  if constexpr (!BF16 && !ASTAGED)
+    if (a.planes) return launch_gemm_cfg<WV, WB, VB, PB, true, true, true>(a, st);
   if constexpr (!ASTAGED)
     if (a.As != nullptr) return launch_gemm_cfg<WV, WB, VB, PB, BF16, true>(a, st);
-  constexpr auto kern = k_gemm_tn<WV, WB, VB, PB, 64, 4, BF16, ASTAGED>;
+  constexpr auto kern = k_gemm_tn<WV, WB, VB, PB, 64, 4, BF16, ASTAGED, SPLIT>;
   if (hipError_t e = allow_lds<kern>(TL::SMEM); e != hipSuccess) return e;
   const int nslab = (a.M + TL::TV - 1) / TL::TV, nbt = (a.N + TL::TP - 1) / TL::TP;
   int grid = nslab * nbt * max(a.ksplit, 1);

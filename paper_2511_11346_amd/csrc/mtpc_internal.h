@@ -40,6 +40,12 @@ struct UnembedArgs {
   float* logphi;        // [B][n][r][v] normalised logits of every slab, or nullptr
   float* phiT;          // [n*r*v][ld_phi] softmax probabilities, transposed, or nullptr (evidence kernel only)
   long long ld_phi;
+  // fp32 operands of 256-position tiles, multiplied as three bf16 terms each (split_pays): scratch that
+  // launch_unembed fills with the planes of W, [n*r][3 d/32][v][64 bytes], and of h, [3 d/32][B][64 bytes], and
+  // a flag it sets when an operand is infinite or NaN (the fp32 instruction takes over then).  Or nullptr
+  void* Wq;
+  void* hq;
+  int* wild;
 };
 
 // Univariate marginals: M[b][i][a] = log sum_j m[b][i][j] phi[b][i][j][a].
@@ -266,6 +272,10 @@ struct GradPhiArgs {
   // rows m < M of dLT as [ldb * esz / 64][M][64 bytes] (the sum-unit rows M..Mx-1 stay where they are, behind
   // it), dL as [ldM * esz / 64][B][64 bytes] (then dl_end = ldM: every column is written here)
   int staged;
+  // 1 (fp32, staged): both as planes of three bf16 terms, stages of 32 columns per term (tile_gemm_run_split):
+  // dLT [3 ldb/32][M][64 bytes], dL [3 ldM/32][B][64 bytes]
+  int planes;
+  const void* dslT;     // the sum-unit rows M..Mx-1 of dLT, [Mx - M][ldb] in the dtype of h
 };
 hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st);
 
@@ -287,6 +297,7 @@ struct GemmArgs {
   // columns and write their partial tile to partial[ks][M][ldc]; a second kernel adds the
   // partials in a fixed order into C (single output buffer only)
   int ksplit; int kchunk; float* partial;
+  int planes;           // fp32 only: As and Bs hold three bf16 terms per value, [3 K/32][rows][64 bytes]
 };
 hipError_t launch_gemm_tn(const GemmArgs& a, int dtype, hipStream_t st);
 // number of K splits that fills the 256 CUs best for an M x N output (1: none)
@@ -312,6 +323,8 @@ struct TransposeArgs {
   // 0: dst[c][col0 + r].  Else the destination is stage-major in 64-byte stages with this many rows,
   // [columns * esz / 64][stage_rows][64 bytes] (the form the contraction kernels read an operand in)
   int stage_rows;
+  // 1 (fp32, stage_rows set): three bf16 terms per value, [3 columns/32][stage_rows][64 bytes]
+  int planes;
 };
 hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t st);
 
@@ -412,6 +425,24 @@ __device__ __forceinline__ float philox_uniform(uint32_t seed_lo, uint32_t seed_
   uint32_t sel = slot & 3u;
   uint32_t word = sel == 0 ? w[0] : sel == 1 ? w[1] : sel == 2 ? w[2] : w[3];
   return (float)(word >> 8) * 5.9604644775390625e-8f;
+}
+
+// x as the exact sum of three bf16 terms (8 significant bits each: 24 in all), the next one the nearest bf16 of
+// what is left.  A finite x keeps finite terms (next to the largest value the nearest bf16 would be infinite:
+// the one below is taken); an infinite or NaN x is its own first term, the others are 0.
+// Terms below 2^-126 lose low bits, which matters to values below 2^-110 only.
+__device__ __forceinline__ void split3(float x, unsigned short (&t)[3]) {
+  auto bits = [](float y) { return (unsigned)__builtin_bit_cast(unsigned short, (__bf16)y) << 16; };
+  const unsigned ux = __float_as_uint(x);
+  const bool finite = (ux & 0x7f800000u) != 0x7f800000u;
+  unsigned u1 = bits(x);
+  if ((u1 & 0x7f800000u) == 0x7f800000u && finite) u1 = ux & 0xffff0000u;
+  const float r1 = finite ? x - __uint_as_float(u1) : 0.f;
+  const unsigned u2 = bits(r1);
+  const float r2 = r1 - __uint_as_float(u2);
+  t[0] = (unsigned short)(u1 >> 16);
+  t[1] = (unsigned short)(u2 >> 16);
+  t[2] = (unsigned short)(bits(r2) >> 16);
 }
 
 __device__ __forceinline__ float neg_inf() { return -__builtin_inff(); }

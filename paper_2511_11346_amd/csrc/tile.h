@@ -169,12 +169,17 @@ __device__ __forceinline__ int swz(int row) {
 // 1^f(8+k) must differ: f = (0, 3, 2, 1).
 __device__ __forceinline__ int swz16(int row) { return (0 - (row >> 2)) & 3; }
 
+// Ring buffers of the plane stages of tile_gemm_run_split: first terms alternate between two.
+constexpr int SPLIT_SLOT_A0 = 0, SPLIT_SLOT_C = 2, SPLIT_SLOT_B = 3;
+
 // Where the operands of one tile come from, and the direct-to-LDS loads that bring them in: open()
 // describes the tile and issues the first NS-1 stages of its ring, tile_gemm_run() multiplies.  Apart,
 // so that a workgroup that walks several tiles can open the next one (the ring is free once the run
 // has returned) before it turns to the epilogue of the one it has just multiplied.
+// SPLIT: the operands are fp32 matrices as planes of three bf16 terms (see tile_gemm_run_split); only the
+// first two planes are issued here.
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER = false, bool M16 = false,
-          bool WPACK = false, bool STREAMW = false, int PH = 0>
+          bool WPACK = false, bool STREAMW = false, int PH = 0, bool SPLIT = false>
 struct TileFeed {
   using TL = Tile<WV, WB, VB, PB, SB, NS, PH>;
   static constexpr int ESZ = BF16 ? 2 : 4;
@@ -255,9 +260,14 @@ struct TileFeed {
     // has to be told where they come out of a select)
     hstep = (unsigned)__builtin_amdgcn_readfirstlane((int)(hpk ? (unsigned)B * SB : (unsigned)SB));
     wstep = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(wall ? wrows_total : v) * SB));
-    const int KI = d * ESZ / SB;
-    for (int s = 0; s < NS - 1; ++s)
-      if (s < KI) issue(s);
+    if constexpr (SPLIT) {
+      issue(SPLIT_SLOT_A0);
+      issue(SPLIT_SLOT_B);
+    } else {
+      const int KI = d * ESZ / SB;
+      for (int s = 0; s < NS - 1; ++s)
+        if (s < KI) issue(s);
+    }
   }
 };
 
@@ -485,6 +495,111 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
     }
   }
   __syncthreads();     // all waves are done reading the ring
+}
+
+// The product of two fp32 operands on the bf16 matrix pipes.  An fp32 value is the exact sum of three bf16
+// terms x1 + x2 + x3, each the nearest bf16 of what the ones before leave (see split3), and
+//   x y = x1 y1 + x1 y2 + x2 y2 + x2 y1 + x3 y1 + x1 y3 + (x2 y3 + x3 y2 + x3 y3),
+// where what is left out is below 2^-25 |x y|, less than the rounding of one fp32 multiply-add.  The six
+// products cost 6 / 16 of the fp32 instruction's time; products and sums are fp32 as there, with one rounding
+// per 32 terms of K instead of one per 1 or 2.
+// Both operands are stage-major (TileFeed with WPACK and hs) in 64-byte stages that hold 32 columns of ONE
+// term: stages 3k, 3k+1, 3k+2 are terms 1, 2, 3 of columns 32k .. 32k+31.  d: fp32 columns.
+// Schedule: the ping-pong clusters of tile_gemm_run, six per 32 columns; a cluster re-reads only the operand
+// that changes (56 fragment reads per 240 products instead of 84).  Of the four ring buffers two alternate
+// for the first terms, which are needed to the end of their columns; loads are issued four or five clusters
+// before their first use.  One stage of loads feeds two clusters, where the bf16 kernel loads one for each.
+template <int WV, int WB, int VB, int PB, int SB, int NS>
+__device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB, NS, true, false, true, true, false, 0, true>& feed,
+                                                    int d, char* smem, f32x4_t (&acc)[2 * PB][2 * VB]) {
+  using TL = Tile<WV, WB, VB, PB, SB, NS>;
+  static_assert(TL::NW == 8 && SB == 64 && NS == 4, "ping-pong of two wave groups over four ring buffers");
+  const int lane = threadIdx.x & 63, wave = feed.wave;
+  const int wv = wave % WV, wb = wave / WV;
+  const int l15 = lane & 15, lq = lane >> 4;
+  const int sw16 = swz16(l15);
+  const int a16 = (wv * VB * 32 + l15) * SB + ((lq ^ sw16) << 4);
+  const int b16 = (TL::TV + wb * TL::WP + l15) * SB + ((lq ^ sw16) << 4);
+#pragma unroll
+  for (int pb = 0; pb < 2 * PB; ++pb)
+#pragma unroll
+    for (int vb = 0; vb < 2 * VB; ++vb) acc[pb][vb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  i32x4_t ga[2 * VB], gb[2 * PB];
+  auto read_a = [&](int slot) {
+    const char* cur = smem + slot * TL::STAGE;
+#pragma unroll
+    for (int vb = 0; vb < 2 * VB; ++vb) ga[vb] = *(const i32x4_t*)(cur + a16 + vb * 16 * SB);
+  };
+  auto read_b = [&](int slot) {
+    const char* cur = smem + slot * TL::STAGE;
+#pragma unroll
+    for (int pb = 0; pb < 2 * PB; ++pb) gb[pb] = *(const i32x4_t*)(cur + b16 + pb * 16 * SB);
+  };
+  auto barrier = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto compute = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int pb = 0; pb < 2 * PB; ++pb)
+#pragma unroll
+      for (int vb = 0; vb < 2 * VB; ++vb) {
+        mma_step<true>(acc[pb][vb], ga[vb], gb[pb]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int KI = d / 32;
+  MTPC_WAIT_VMCNT(TL::PER);                 // the first terms of the first columns have landed
+  __syncthreads();
+  // ALLOW: loads of this wave that may still be on their way when the next cluster reads (negative: that
+  // cluster reads no new buffer).  Group 1 waits at the end of its memory cluster, group 0 after its products:
+  // either way before the barrier that lets the other group read.
+  auto run = [&](auto grp) {
+    constexpr int G = decltype(grp)::value;
+    auto rest = [&](auto allow) {           // what follows the reads and loads of a memory cluster
+      constexpr int ALLOW = decltype(allow)::value;
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (G == 1 && ALLOW >= 0) MTPC_WAIT_VMCNT(ALLOW >= 0 ? ALLOW : 0);
+      barrier();
+      compute();
+      if constexpr (G == 0 && ALLOW >= 0) MTPC_WAIT_VMCNT(ALLOW >= 0 ? ALLOW : 0);
+      barrier();
+    };
+    auto columns = [&](int k, auto lastk) { // the six products of 32 columns; the last ones issue no more
+      constexpr bool LAST = decltype(lastk)::value;
+      const int a = k & 1;
+      read_a(a); read_b(a);                 // x1 y1.  Third terms and the next first terms go where nobody reads
+      feed.issue(SPLIT_SLOT_C);             // any more since the last barrier
+      rest(std::integral_constant<int, TL::PER>{});            // second terms landed
+      read_b(SPLIT_SLOT_B);                 // x1 y2
+      if constexpr (!LAST) feed.issue(a ^ 1);
+      rest(std::integral_constant<int, -1>{});
+      read_a(SPLIT_SLOT_B);                 // x2 y2
+      rest(std::integral_constant<int, -1>{});
+      read_b(a);                            // x2 y1: the buffer of the second terms is free
+      if constexpr (!LAST) feed.issue(SPLIT_SLOT_B);
+      rest(std::integral_constant<int, LAST ? 0 : 2 * TL::PER>{});   // third terms landed
+      read_a(SPLIT_SLOT_C);                 // x3 y1
+      rest(std::integral_constant<int, -1>{});
+      read_a(a); read_b(SPLIT_SLOT_C);      // x1 y3
+      rest(std::integral_constant<int, LAST ? -1 : TL::PER>{});      // the next first terms landed
+    };
+    for (int k = 0; k < KI - 1; ++k) columns(k, std::false_type{});
+    columns(KI - 1, std::true_type{});
+  };
+  if (wave >> 2) {
+    __syncthreads();                        // start one cluster late
+    run(std::integral_constant<int, 1>{});
+  } else {
+    run(std::integral_constant<int, 0>{});
+    __syncthreads();                        // pairs with the late start of the other group
+  }
+  __syncthreads();                          // all waves are done reading the ring
 }
 
 // D = W_slab x h_tile^T for one workgroup; on return every wave holds its VB x PB

@@ -246,9 +246,14 @@ __device__ __forceinline__ void tile_draws_cols(const f32x4_t (&acc)[NPB][VB * 2
 template <int WB, bool SAMPLE>
 constexpr bool unembed_walks_tiles() { return !SAMPLE && WB != 1; }
 
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false>
+// SPLIT: fp32 operands as planes of three bf16 terms (tile_gemm_run_split); everything but the product is
+// the bf16 kernel's.
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false>
 __global__ __launch_bounds__(WV * WB * 64)
 void k_unembed(const UnembedArgs a) {
+  // of the two launches over the same fp32 operands one does the work (see launch_split)
+  if constexpr (SPLIT || !BF16)
+    if (a.wild != nullptr && (*a.wild != 0) == SPLIT) return;
   using TL = Tile<WV, WB, VB, PB, SB, NS>;
   constexpr bool M16 = use_m16<WV, WB, SB, NS, BF16>();
   using FR = Frag<M16>;
@@ -266,14 +271,16 @@ void k_unembed(const UnembedArgs a) {
   // softmax statistics are taken, instead of after a workgroup launch with the matrix pipe idle.
   // Every other instantiation has one tile per workgroup and leaves the loop after it.
   constexpr bool WALK = unembed_walks_tiles<WB, SAMPLE>();
-  using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, WB == 1>;
-  const void* const hstaged = (WB != 1 && SB == H_STAGE_BYTES) ? a.hs : nullptr;
+  using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, WB == 1, 0, SPLIT>;
+  const void* const hstaged = SPLIT ? a.hq : (WB != 1 && SB == H_STAGE_BYTES) ? a.hs : nullptr;
+  const void* const Wfeed = SPLIT ? a.Wq : WPACK ? a.Wp : a.W;
+  const int dfeed = SPLIT ? 3 * a.d : a.d;            // bf16 columns of the planes
   const int ntiles = nbt * nslab;
   int slab, bt;
   tile_of_block(blockIdx.x, nbt, nslab, slab, bt);
   Feed feed;
   // the decode-sized tiles (one wave column) are launched with one tile of positions: W is a stream
-  feed.open(WPACK ? a.Wp : a.W, a.d, a.h, a.ld_h, a.B, a.d, a.v, slab, bt * TL::TP, smem, nullptr, 0, 1, hstaged);
+  feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab, bt * TL::TP, smem, nullptr, 0, 1, hstaged);
   for (int w = blockIdx.x;;) {
   const int b0 = bt * TL::TP;
   const int wi = slab / a.r, wj = slab - wi * a.r;
@@ -299,13 +306,14 @@ void k_unembed(const UnembedArgs a) {
   }
 
   typename FR::blk_t acc[NPB][NVB];
-  tile_gemm_run(feed, a.d, smem, acc);
+  if constexpr (SPLIT) tile_gemm_run_split(feed, a.d, smem, acc);
+  else tile_gemm_run(feed, a.d, smem, acc);
   const int wnext = w + (int)gridDim.x;
   int slab_next = 0, bt_next = 0;
   if constexpr (WALK)
     if (wnext < ntiles) {
       tile_of_block(wnext, nbt, nslab, slab_next, bt_next);
-      feed.open(WPACK ? a.Wp : a.W, a.d, a.h, a.ld_h, a.B, a.d, a.v, slab_next, bt_next * TL::TP, smem, nullptr, 0, 1, hstaged);
+      feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab_next, bt_next * TL::TP, smem, nullptr, 0, 1, hstaged);
     }
 
   if constexpr (!SAMPLE) if (a.targets != nullptr) {
@@ -921,10 +929,10 @@ hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t st)
   return dtype == MTPC_BF16 ? launch_uni_dt<true>(a, st) : launch_uni_dt<false>(a, st);
 }
 
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false>
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false>
 static hipError_t launch_cfg(const UnembedArgs& a, hipStream_t st) {
   using TL = Tile<WV, WB, VB, PB, SB, NS>;
-  constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK>;
+  constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK, SPLIT>;
   if (hipError_t e = allow_lds<kern>(TL::SMEM); e != hipSuccess) return e;
   const int nbt = (a.B + TL::TP - 1) / TL::TP;
   int grid = nbt * a.n * a.r;
@@ -1001,8 +1009,60 @@ hipError_t launch_pack_rows(const void* src, void* dst, long long slabs, int v, 
   return hipGetLastError();
 }
 
+// fp32 rows as planes of three bf16 terms (split3), stage-major: per matrix [3 d/32][v][64 bytes], stage 3k+p
+// holding term p of columns 32k..32k+31.  One thread splits 8 columns: four threads read one 128-byte line and
+// write 64 contiguous bytes of each plane, neighbouring rows follow.  Sets *wild when a value is infinite or NaN.
+__global__ __launch_bounds__(256) void k_split_rows(const char* __restrict__ src, char* __restrict__ dst, long long slabs, int v,
+                                                    int d, long long row_stride, int* wild) {
+  const long long per_slab = (long long)v * (d / 8);
+  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (t >= slabs * per_slab) return;
+  const long long slab = t / per_slab;
+  const int u = (int)(t - slab * per_slab);
+  const int k = u / (v * 4), w = u - k * v * 4, row = w >> 2, ch = w & 3;
+  const char* s = src + (slab * v + row) * row_stride + (long long)k * 128 + ch * 32;
+  const f32x4_t x0 = __builtin_nontemporal_load((const f32x4_t*)s), x1 = __builtin_nontemporal_load((const f32x4_t*)(s + 16));
+  struct alignas(16) Oct { unsigned short v[8]; } o[3];
+  bool bad = false;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const float x = c < 4 ? x0[c & 3] : x1[c & 3];
+    bad |= !(fabsf(x) <= 3.402823466e38f);
+    unsigned short q[3];
+    split3(x, q);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) o[p].v[c] = q[p];
+  }
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+    *(Oct*)(dst + ((slab * (3LL * (d / 32)) + 3LL * k + p) * v + row) * 64 + ch * 16) = o[p];
+  if (bad) *wild = 1;
+}
+
+__global__ void k_clear_flag(int* flag) { *flag = 0; }
+
+// fp32 operands through their bf16 terms.  Infinite or NaN operands stay with the fp32 instruction, whose sums
+// such values enter once instead of term by term: which of the two launches does the work is known on the
+// device only, the other one's workgroups leave at once (about 5 us).
+template <bool SAMPLE>
+static hipError_t launch_split(const UnembedArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, st, a.wild);
+  auto split = [&](const void* src, void* dst, long long slabs, int v, long long ld) {
+    const long long chunks = slabs * v * (a.d / 8);
+    hipLaunchKernelGGL(k_split_rows, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, st, (const char*)src, (char*)dst,
+                       slabs, v, a.d, ld * 4, a.wild);
+  };
+  split(a.h, a.hq, 1, a.B, a.ld_h);
+  split(a.W, a.Wq, (long long)a.n * a.r, a.v, a.d);
+  hipError_t e = a.v > 256   ? launch_cfg<2, 4, 5, 2, 64, 4, true, SAMPLE, true, true>(a, st)
+                 : a.v > 128 ? launch_cfg<2, 4, 4, 2, 64, 4, true, SAMPLE, true, true>(a, st)
+                             : launch_cfg<2, 4, 2, 2, 64, 4, true, SAMPLE, true, true>(a, st);
+  return e != hipSuccess ? e : launch_dt<false, SAMPLE>(a, st);
+}
+
 hipError_t launch_unembed(const UnembedArgs& a, int dtype, hipStream_t st) {
   const bool sample = a.zleaf != nullptr;
+  if (dtype == MTPC_F32 && a.Wq != nullptr) return sample ? launch_split<true>(a, st) : launch_split<false>(a, st);
   if (dtype == MTPC_BF16)
     return sample ? launch_dt<true, true>(a, st) : launch_dt<true, false>(a, st);
   return sample ? launch_dt<false, true>(a, st) : launch_dt<false, false>(a, st);

@@ -76,6 +76,9 @@ hipError_t launch_unembed(const UnembedArgs& a, int dtype, hipStream_t) {
   need(a.W, (u64)a.n * a.r * a.v * a.d * esz(dtype), "unembed W");
   opt(a.Wp, (u64)a.n * a.r * a.v * a.d * esz(dtype), "unembed stage-major W");
   opt(a.hs, (u64)a.B * a.d * esz(dtype), "unembed stage-major h");
+  opt(a.Wq, (u64)a.n * a.r * a.v * a.d * 6, "unembed bf16 terms of W");
+  opt(a.hq, (u64)a.B * a.d * 6, "unembed bf16 terms of h");
+  opt(a.wild, 4, "unembed flag");
   if (a.targets) {
     need(a.targets, (u64)a.B * a.T * a.n * 4, "unembed targets");
     opt(a.targets2, (u64)a.B * a.T2 * a.n * 4, "unembed targets2");
@@ -213,6 +216,11 @@ hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t) {
   need(a.Ge, (u64)a.B * a.n * a.r * 4, "grad Ge");
   need(a.dLT, (u64)a.Mx * a.ldb * esz(dtype), "grad dLT");
   need(a.dL, (u64)a.B * a.ldM * esz(dtype), "grad dL");
+  if (a.planes) {
+    need(a.dLT, (u64)a.M * a.ldb * 6, "grad dLT, bf16 terms");
+    need(a.dL, (u64)a.B * a.ldM * 6, "grad dL, bf16 terms");
+  }
+  if (a.Mx > a.M) need(a.dslT, (u64)(a.Mx - a.M) * a.ldb * esz(dtype), "grad sum-unit rows");
   return ok();
 }
 hipError_t launch_gemm_tn(const GemmArgs& a, int dtype, hipStream_t) {
@@ -222,6 +230,10 @@ hipError_t launch_gemm_tn(const GemmArgs& a, int dtype, hipStream_t) {
   if (a.As) {
     if (a.As_rows < a.M) { std::fprintf(stderr, "gemm: stage-major A with too few rows\n"); std::abort(); }
     need(a.As, (u64)a.As_rows * a.K * esz(dtype), "gemm A, stage-major");
+  }
+  if (a.planes) {
+    need(a.As, (u64)a.As_rows * a.K * 6, "gemm A, bf16 terms");
+    need(a.Bs, (u64)a.N * a.K * 6, "gemm B, bf16 terms");
   }
   const int r1 = a.M < a.split ? a.M : a.split;
   need(a.C, strided(r1, a.ldc, a.N, 4), "gemm C");
@@ -237,6 +249,7 @@ hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t) {
     const u64 eps = 64 / esz(dtype);
     if (a.stage_rows < a.C) { std::fprintf(stderr, "transpose: bad stage-major destination\n"); std::abort(); }
     need(a.dst, ((u64)a.col0 + a.Rpad + eps - 1) / eps * a.stage_rows * 64, "transpose dst, stage-major");
+    if (a.planes) need(a.dst, ((u64)a.col0 + a.Rpad + 31) / 32 * a.stage_rows * 192, "transpose dst, bf16 terms");
   } else {
     need((const char*)a.dst + (u64)a.col0 * esz(dtype), strided(a.C, a.ld_dst, a.Rpad, esz(dtype)), "transpose dst");
   }

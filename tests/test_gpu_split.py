@@ -1,0 +1,82 @@
+"""GPU parity of the fp32 products through three bf16 terms per value (the 256-position tiles) against the
+same sums in 64 bits.
+
+Tolerance.  The terms are exact and the six products kept leave out less than 2^-25 |x y|, so a logit of d
+terms is off by the rounding of its fp32 sums, as on the fp32 matrix pipes: at most (6 d / 32 + d) 2^-24 sum |x y|
+(worst case, every rounding the same way; d <= 1056 and sum |x y| < 60 here: 3e-3, seen 1e-6).  The bound used,
+5e-6 on log-probabilities and 2e-5 of the largest gradient entry, is the one the fp32 tests of the
+same outputs have."""
+import numpy as np
+import pytest
+import torch
+
+import mtpc_inputs as mi
+from oracle import backward as bw
+from oracle import mtpc_oracle as oc
+from gpu_util import make_head
+from test_gpu_backward import check_grad
+
+pytestmark = pytest.mark.gpu
+
+
+# edges of the vocabulary and position tiles, one column block, an odd and an even number of them, rows of h apart
+SIZES = [(65, 512, 2, 3, 33), (70, 544, 3, 2, 128), (256, 512, 2, 2, 129), (257, 512, 2, 3, 256),
+         (300, 1056, 2, 2, 268), (129, 1024, 1, 4, 320)]
+
+
+@pytest.mark.parametrize("B,d,n,r,v", SIZES)
+def test_evidence_table_and_draws(B, d, n, r, v):
+    inp = mi.make_inputs("cp", B=B, d=d, n=n, r=r, v=v, dtype="f32", seed=B + v, h_scale=1.0)
+    head = make_head(inp)
+    logphi, logw, _ = oc._params("cp", inp.h, inp.W, inp.Wsum, None)
+    want = oc.prefix_marginals_from("cp", logphi, logw, None, inp.targets)
+    got = head.prefix_marginals(torch.from_numpy(inp.targets).cuda()).cpu().numpy()
+    assert np.abs(got - want).max() < 5e-6
+    table = torch.full((B, n, r, v), float("nan"), device="cuda")
+    drafts, lat, scores = head.sample(2, seed=5, want_prefix=True, logphi=table)
+    assert np.abs(table.cpu().numpy() - logphi).max() < 5e-6
+    want = oc.prefix_marginals_from("cp", logphi, logw, None, drafts[:, 1].cpu().numpy())
+    assert np.abs(scores[:, 1].cpu().numpy() - want).max() < 5e-6
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4028235e38, -3.4e38, 1e-38])
+def test_values_at_the_ends_of_the_range(value):
+    """An infinite or NaN weight gives what fp32 sums give; the largest finite ones stay finite terms."""
+    B, d, n, r, v = 65, 512, 1, 3, 40
+    inp = mi.make_inputs("cp", B=B, d=d, n=n, r=r, v=v, dtype="f32", seed=9, h_scale=1.0)
+    inp.h = np.abs(inp.h) + 0.5
+    inp.W[0, 1, 7, 5] = value
+    # (times 0 for the largest: the softmax of a logit of 1e37 is beyond fp32, with any product kernel)
+    inp.h[:, 5] = 0.0 if value == 3.4028235e38 else 0.25
+    logits = np.einsum("nrvd,bd->bnrv", inp.W.astype(np.float64), inp.h.astype(np.float64))
+    m = logits.max(axis=-1, keepdims=True)
+    m[np.isneginf(m)] = 0
+    with np.errstate(invalid="ignore"):
+        want = logits - m - np.log(np.exp(logits - m).sum(axis=-1, keepdims=True))
+    got = make_head(inp)
+    table = torch.empty(B, n, r, v, device="cuda")
+    got.sample(1, seed=5, want_prefix=True, logphi=table)
+    got = table.cpu().numpy().astype(np.float64)
+    other = np.ones((B, n, r, v), bool)
+    other[:, 0, 1] = False
+    assert np.abs(got - want)[other].max() < 1e-4        # (|logits| up to 400 here)
+    with np.errstate(invalid="ignore"):
+        same = (got == want) | (np.isnan(got) & np.isnan(want)) | (np.abs(got - want) <= 1e-4 + 1e-6 * np.abs(want))
+    # (a unit with a NaN logit has no distribution: all that its softmax promises is that this entry is NaN)
+    assert (same if not np.isnan(value) else same[:, 0, 1, 7]).all()
+
+
+@pytest.mark.parametrize("family,B,d,n,r,v", [("cp", 65, 96, 2, 3, 33), ("hmm", 300, 544, 3, 5, 129), ("ff", 257, 512, 3, 1, 268),
+                                              ("btree", 97, 512, 4, 6, 320)])
+def test_training_step(family, B, d, n, r, v):
+    inp = mi.make_inputs(family, B=B, d=d, n=n, r=r, v=v, dtype="f32", seed=B, h_scale=1.0)
+    coef = bw.loss_coefficients(0.8, np.random.default_rng(B).random((B, n)) > 0.15)
+    head = make_head(inp)
+    tg = torch.from_numpy(inp.targets.astype(np.int32)).cuda()
+    out = head.loss_backward(tg, torch.from_numpy(coef.astype(np.float32)).cuda())
+    ref = bw.loss_and_gradients(family, inp.h, inp.W, inp.Wsum, inp.layers, inp.targets, coef.astype(np.float32))
+    for k in ("dh", "dW", "dWsum", "dlayers"):
+        if out[k] is not None:
+            check_grad(k, out[k], ref[k], "f32")
+    again = head.loss_backward(tg, torch.from_numpy(coef.astype(np.float32)).cuda())
+    assert all(torch.equal(again[k], out[k]) for k in out if out[k] is not None)
