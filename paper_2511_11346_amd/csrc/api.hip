@@ -89,11 +89,12 @@ constexpr double SPLIT_TILE_US = 148, F32_TILE_US = 304;
 bool split_pays(const mtpc_head* hd) {
   if (hd->dtype != MTPC_F32 || hd->B <= 64) return false;
   if ((unsigned long long)hd->B * hd->d * 6 >= (1ull << 32)) return false;      // one 32-bit buffer resource
-  const double rows = hd->v > 256 ? 320 : hd->v > 128 ? 256 : 128;
+  const double frows = hd->v > 256 ? 320 : hd->v > 192 ? 256 : hd->v > 128 ? 192 : 128;
+  const double srows = (hd->v > 256 && hd->v <= 272) ? 272 : frows;            // (launch_train)
   const double rounds = std::ceil((double)((hd->B + 255) / 256) * hd->n * hd->r / 256.0);
-  const double tile = rounds * rows / 320.0 * hd->d / 1024.0;
+  const double tile = rounds / 320.0 * hd->d / 1024.0;
   const double split = (double)hd->n * hd->r * hd->v * hd->d * 10.0 / 4.9e6 + 15.0;
-  return tile * SPLIT_TILE_US + split < tile * F32_TILE_US;
+  return tile * srows * SPLIT_TILE_US + split < tile * frows * F32_TILE_US;
 }
 
 // most windows per position whose rows B*T*n still index with an int

@@ -18,11 +18,18 @@ constexpr int NSLOT = 16;         // positions sampled per pass of the draw loop
 
 // PH: one more block of 16 position columns per wave (kernels on the 16x16 MFMA blocks only), for tiles
 // whose width is not a multiple of 32 columns per wave.
-template <int WV, int WB, int VB, int PB, int SB, int NS, int PH = 0>
+// VH: so many 16-row blocks fewer than WV * VB * 2 in all (the same kernels, two waves along the vocabulary):
+// the first wave of a column keeps 2 VB - VH / 2 of them, the second one less when VH is odd.  Wave groups 0-3
+// and 4-7 are then the two halves of the rows, so that every SIMD has one wave of each half and the rows that
+// are not there cost no SIMD any time.
+template <int WV, int WB, int VB, int PB, int SB, int NS, int PH = 0, int VH = 0>
 struct Tile {
   static constexpr int NW = WV * WB;
   static constexpr int NT = NW * 64;
-  static constexpr int TV = WV * VB * 32;
+  static constexpr int TV = WV * VB * 32 - VH * 16;
+  static constexpr int WROWS = VB * 32 - VH / 2 * 16;  // rows of a wave (the last one may have 16 fewer)
+  static __device__ __forceinline__ int wv(int wave) { return VH ? wave >> 2 : wave % WV; }
+  static __device__ __forceinline__ int wb(int wave) { return VH ? wave & 3 : wave / WV; }
   static constexpr int WP = PB * 32 + PH * 16;         // position columns of a wave
   static constexpr int TP = WB * WP;
   static constexpr int ROWS = TV + TP;
@@ -30,13 +37,18 @@ struct Tile {
   static constexpr int RPL = 64 / CPR;                 // rows covered by one 1 KiB wave-load
   static constexpr int NWL = ROWS / RPL;               // wave-loads per stage
   static constexpr int LPW = (NWL + NW - 1) / NW;      // wave-loads per wave per stage (some waves: LPW-1)
-  static constexpr int PER = (NWL % NW == 0) ? LPW : LPW - 1;   // loads every wave surely issues
+  // A last load that one wave alone would issue is dealt in quarters of 16 lanes over the four waves of its group:
+  // a branch that tells the waves of a group apart would sit in the K loop (with it, and the registers it cost, the
+  // 272-row tile of fp32 terms took 5.3 ms where the 320-row one takes 3.6).
+  static constexpr bool QUARTERS = NW == 8 && (NWL % NW == 1 || NWL % NW == 5);
+  static constexpr int PER = (NWL % NW == 0 || (QUARTERS && NWL % NW == 5)) ? LPW : LPW - 1;   // loads every wave surely issues
   static constexpr int KS = SB / 32;                   // MFMA k-substeps (2 chunks each) per stage
   static constexpr int STAGE = ROWS * SB;
   static constexpr int VPL = (TV + 63) / 64;           // values per lane in the draw scan
   static constexpr int RED_OFF = NS * STAGE;           // float2 red[WV][TP]
   static constexpr int MISC_OFF = RED_OFF + WV * TP * 8;   // int cnt, list[TP], slot[TP]
   static constexpr int SMEM = MISC_OFF + 16 + TP * 8;
+  static_assert(VH == 0 || (WV == 2 && WB == 4), "two halves of the rows, one per wave group");
   static_assert(SB == 64 || SB == 128, "stage bytes");
   static_assert(NS >= 2 && ROWS % RPL == 0, "ring geometry");
   static_assert(NSLOT * VPL * 64 * 4 <= NS * STAGE, "draw buffer must fit in the stage buffers");
@@ -135,6 +147,14 @@ __device__ __forceinline__ void load_to_lds(unsigned voff, i32x4_t srd, unsigned
                  :: "v"(voff), "s"(srd), "s"(soff), "s"(lds_base) : "memory");
 }
 
+// The same for the lanes of `mask` only (wave-uniform): lane L's data still lands at lds_base + 16*L.  All
+// lanes must be active.
+__device__ __forceinline__ void load_to_lds_masked(unsigned voff, i32x4_t srd, unsigned soff, unsigned lds_base,
+                                                   unsigned long long mask) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 exec, %4\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds\n\ts_mov_b64 exec, -1"
+               :: "v"(voff), "s"(srd), "s"(soff), "s"(lds_base), "s"(mask) : "memory");
+}
+
 // Raw buffer resource over [base, base + bytes): reads beyond it return zero.
 __device__ __forceinline__ i32x4_t make_srd(const void* base, unsigned bytes) {
   const unsigned long long a = (unsigned long long)base;
@@ -179,9 +199,9 @@ constexpr int SPLIT_SLOT_A0 = 0, SPLIT_SLOT_C = 2, SPLIT_SLOT_B = 3;
 // SPLIT: the operands are fp32 matrices as planes of three bf16 terms (see tile_gemm_run_split); only the
 // first two planes are issued here.
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER = false, bool M16 = false,
-          bool WPACK = false, bool STREAMW = false, int PH = 0, bool SPLIT = false>
+          bool WPACK = false, bool STREAMW = false, int PH = 0, bool SPLIT = false, int VH = 0>
 struct TileFeed {
-  using TL = Tile<WV, WB, VB, PB, SB, NS, PH>;
+  using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
   static constexpr int ESZ = BF16 ? 2 : 4;
   static constexpr int CPR = TL::CPR;
   i32x4_t srdW, srdH;
@@ -195,7 +215,17 @@ struct TileFeed {
 
   __device__ __forceinline__ void issue_one(int q, int buf) {   // q-th wave-load of this wave for one stage
     __builtin_assume(wave >= 0 && wave < TL::NW);    // (which loads are W's and which exist is then known per q, mostly)
-    const int wl = wave + q * TL::NW;
+    int wl = wave + q * TL::NW;
+    if constexpr (TL::QUARTERS) {
+      static_assert(!STREAMW, "tiles of one wave column");
+      if (q == TL::LPW - 1) {
+        const bool share = (wave >> 2) == (TL::NWL % TL::NW == 5 ? 1 : 0);       // the group of the last load
+        if (share) {
+          load_to_lds_masked(voff[q], srdH, kofsH, lds0 + buf * TL::STAGE + (TL::NWL - 1) * 1024, 0xffffull << ((wave & 3) * 16));
+          return;
+        }
+      }
+    }
     if (q < TL::PER || wl < TL::NWL) {
       // a wave-load never straddles the W / h boundary (TV is a multiple of RPL)
       const bool isW = wl * TL::RPL < TL::TV;
@@ -273,19 +303,19 @@ struct TileFeed {
 
 // The product of a tile whose feed is open: on return every wave holds its VB x PB accumulator blocks and
 // all waves have passed a barrier (the ring is free).
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER, bool M16, bool WPACK, bool STREAMW, int PH>
-__device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH>& feed,
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER, bool M16, bool WPACK, bool STREAMW, int PH, int VH>
+__device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, false, VH>& feed,
                                               int d, char* smem,
-                                              typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB]) {
-  using TL = Tile<WV, WB, VB, PB, SB, NS, PH>;
-  static_assert(PH == 0 || M16, "half blocks of position columns: 16x16 MFMA blocks only");
+                                              typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB - VH / 2]) {
+  using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
+  static_assert((PH == 0 && VH == 0) || M16, "half blocks: 16x16 MFMA blocks only");
   using FR = Frag<M16>;
   static_assert(!M16 || (BF16 && NS >= 3 && TL::NW == 8 && SB == 64),
                 "16x16 blocks: bf16, two waves per SIMD, one MFMA k-step per 64-byte stage");
   constexpr int ESZ = BF16 ? 2 : 4;
   constexpr int CPR = TL::CPR, KS = TL::KS;
   const int tid = threadIdx.x, lane = tid & 63, wave = feed.wave;
-  const int wv = wave % WV, wb = wave / WV;
+  const int wv = TL::wv(wave), wb = TL::wb(wave);
   const int l31 = lane & 31, lhalf = lane >> 5;
   const int hrows = feed.hrows;
   auto issue_one = [&](int q, int buf) { feed.issue_one(q, buf); };
@@ -295,7 +325,7 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
 #pragma unroll
   for (int pb = 0; pb < PB * FR::SUB + PH; ++pb)
 #pragma unroll
-    for (int vb = 0; vb < VB * FR::SUB; ++vb)
+    for (int vb = 0; vb < VB * FR::SUB - VH / 2; ++vb)
 #pragma unroll
       for (int i = 0; i < FR::NI; ++i) acc[pb][vb][i] = 0.f;
 
@@ -369,22 +399,23 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
     // whole 64-byte stage is one k-step of 2 VB x 2 PB MFMAs
     const int l15 = lane & 15, lq = lane >> 4;
     const int sw16 = swz16(l15);
-    const int a16 = (wv * VB * 32 + l15) * SB + ((lq ^ sw16) << 4);
+    const int a16 = (wv * TL::WROWS + l15) * SB + ((lq ^ sw16) << 4);
+    constexpr int NVB16 = 2 * VB - VH / 2;     // 16-row blocks of a wave (group 1: one fewer when VH is odd)
     constexpr int NPB16 = 2 * PB + PH;
     const int b16 = (TL::TV + wb * TL::WP + l15) * SB + ((lq ^ sw16) << 4);
-    i32x4_t ga[2 * VB], gb[NPB16];
+    i32x4_t ga[NVB16], gb[NPB16];
     bool act16[NPB16];
 #pragma unroll
     for (int pb = 0; pb < NPB16; ++pb) act16[pb] = !GATHER || wb * TL::WP + pb * 16 < hrows;
     // memory cluster of stage `it`: its fragments, and (LOAD) the loads of stage it+NS-1 into the
     // buffer of stage it-1 (last read before the previous barrier)
-    auto mem_cluster = [&](int it, auto load) {
+    auto mem_cluster = [&](int it, auto load, auto nvb) {
       const char* cur = smem + (it % NS) * TL::STAGE;
       if constexpr (M16) {
 #pragma unroll
         for (int pb = 0; pb < NPB16; ++pb) gb[pb] = *(const i32x4_t*)(cur + b16 + pb * 16 * SB);
 #pragma unroll
-        for (int vb = 0; vb < 2 * VB; ++vb) ga[vb] = *(const i32x4_t*)(cur + a16 + vb * 16 * SB);
+        for (int vb = 0; vb < decltype(nvb)::value; ++vb) ga[vb] = *(const i32x4_t*)(cur + a16 + vb * 16 * SB);
       } else {
         load_frags(cur, 0, 0);
         load_frags(cur, 1, 1);
@@ -394,7 +425,7 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
     };
     // (a branch between two MFMAs costs about as much as an MFMA: empty position blocks are
     // skipped a whole row of products at a time)
-    auto compute_cluster = [&]() {
+    auto compute_cluster = [&](auto nvb) {
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_setprio(1);
       if constexpr (M16) {
@@ -402,7 +433,7 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
         for (int pb = 0; pb < NPB16; ++pb)
           if (!GATHER || act16[pb]) {
 #pragma unroll
-            for (int vb = 0; vb < 2 * VB; ++vb) {
+            for (int vb = 0; vb < decltype(nvb)::value; ++vb) {
               mma_step<BF16>(acc[pb][vb], ga[vb], gb[pb]);
               __builtin_amdgcn_sched_barrier(0);
             }
@@ -428,21 +459,22 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
     // at the end of its memory cluster, group 0 after its compute cluster.
     auto run = [&](auto grp) {
       constexpr int G = decltype(grp)::value;
+      constexpr std::integral_constant<int, NVB16 - (G == 1 ? VH % 2 : 0)> nvb{};
       const int KM = max(KI - (NS - 1), 0);
       int it = 0;
       for (; it < KM; ++it) {
-        mem_cluster(it, std::true_type{});
+        mem_cluster(it, std::true_type{}, nvb);
         if constexpr (G == 1) MTPC_WAIT_VMCNT((NS - 2) * TL::PER);
         barrier();
-        compute_cluster();
+        compute_cluster(nvb);
         if constexpr (G == 0) MTPC_WAIT_VMCNT((NS - 2) * TL::PER);
         barrier();
       }
       for (; it < KI; ++it) {
-        mem_cluster(it, std::false_type{});
+        mem_cluster(it, std::false_type{}, nvb);
         if constexpr (G == 1) MTPC_WAIT_VMCNT(0);
         barrier();
-        compute_cluster();
+        compute_cluster(nvb);
         if constexpr (G == 0) MTPC_WAIT_VMCNT(0);
         barrier();
       }
@@ -509,26 +541,27 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
 // that changes (56 fragment reads per 240 products instead of 84).  Of the four ring buffers two alternate
 // for the first terms, which are needed to the end of their columns; loads are issued four or five clusters
 // before their first use.  One stage of loads feeds two clusters, where the bf16 kernel loads one for each.
-template <int WV, int WB, int VB, int PB, int SB, int NS>
-__device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB, NS, true, false, true, true, false, 0, true>& feed,
-                                                    int d, char* smem, f32x4_t (&acc)[2 * PB][2 * VB]) {
-  using TL = Tile<WV, WB, VB, PB, SB, NS>;
+template <int WV, int WB, int VB, int PB, int SB, int NS, int VH>
+__device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB, NS, true, false, true, true, false, 0, true, VH>& feed,
+                                                    int d, char* smem, f32x4_t (&acc)[2 * PB][2 * VB - VH / 2]) {
+  using TL = Tile<WV, WB, VB, PB, SB, NS, 0, VH>;
+  constexpr int NVB16 = 2 * VB - VH / 2;
   static_assert(TL::NW == 8 && SB == 64 && NS == 4, "ping-pong of two wave groups over four ring buffers");
   const int lane = threadIdx.x & 63, wave = feed.wave;
-  const int wv = wave % WV, wb = wave / WV;
+  const int wv = TL::wv(wave), wb = TL::wb(wave);
   const int l15 = lane & 15, lq = lane >> 4;
   const int sw16 = swz16(l15);
-  const int a16 = (wv * VB * 32 + l15) * SB + ((lq ^ sw16) << 4);
+  const int a16 = (wv * TL::WROWS + l15) * SB + ((lq ^ sw16) << 4);
   const int b16 = (TL::TV + wb * TL::WP + l15) * SB + ((lq ^ sw16) << 4);
 #pragma unroll
   for (int pb = 0; pb < 2 * PB; ++pb)
 #pragma unroll
-    for (int vb = 0; vb < 2 * VB; ++vb) acc[pb][vb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  i32x4_t ga[2 * VB], gb[2 * PB];
-  auto read_a = [&](int slot) {
+    for (int vb = 0; vb < NVB16; ++vb) acc[pb][vb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  i32x4_t ga[NVB16], gb[2 * PB];
+  auto read_a = [&](int slot, auto nvb) {
     const char* cur = smem + slot * TL::STAGE;
 #pragma unroll
-    for (int vb = 0; vb < 2 * VB; ++vb) ga[vb] = *(const i32x4_t*)(cur + a16 + vb * 16 * SB);
+    for (int vb = 0; vb < decltype(nvb)::value; ++vb) ga[vb] = *(const i32x4_t*)(cur + a16 + vb * 16 * SB);
   };
   auto read_b = [&](int slot) {
     const char* cur = smem + slot * TL::STAGE;
@@ -540,13 +573,13 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto compute = [&]() {
+  auto compute = [&](auto nvb) {
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int pb = 0; pb < 2 * PB; ++pb)
 #pragma unroll
-      for (int vb = 0; vb < 2 * VB; ++vb) {
+      for (int vb = 0; vb < decltype(nvb)::value; ++vb) {
         mma_step<true>(acc[pb][vb], ga[vb], gb[pb]);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -561,32 +594,33 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
   // either way before the barrier that lets the other group read.
   auto run = [&](auto grp) {
     constexpr int G = decltype(grp)::value;
+    constexpr std::integral_constant<int, NVB16 - (G == 1 ? VH % 2 : 0)> nvb{};
     auto rest = [&](auto allow) {           // what follows the reads and loads of a memory cluster
       constexpr int ALLOW = decltype(allow)::value;
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (G == 1 && ALLOW >= 0) MTPC_WAIT_VMCNT(ALLOW >= 0 ? ALLOW : 0);
       barrier();
-      compute();
+      compute(nvb);
       if constexpr (G == 0 && ALLOW >= 0) MTPC_WAIT_VMCNT(ALLOW >= 0 ? ALLOW : 0);
       barrier();
     };
     auto columns = [&](int k, auto lastk) { // the six products of 32 columns; the last ones issue no more
       constexpr bool LAST = decltype(lastk)::value;
       const int a = k & 1;
-      read_a(a); read_b(a);                 // x1 y1.  Third terms and the next first terms go where nobody reads
+      read_a(a, nvb); read_b(a);                 // x1 y1.  Third terms and the next first terms go where nobody reads
       feed.issue(SPLIT_SLOT_C);             // any more since the last barrier
       rest(std::integral_constant<int, TL::PER>{});            // second terms landed
       read_b(SPLIT_SLOT_B);                 // x1 y2
       if constexpr (!LAST) feed.issue(a ^ 1);
       rest(std::integral_constant<int, -1>{});
-      read_a(SPLIT_SLOT_B);                 // x2 y2
+      read_a(SPLIT_SLOT_B, nvb);                 // x2 y2
       rest(std::integral_constant<int, -1>{});
       read_b(a);                            // x2 y1: the buffer of the second terms is free
       if constexpr (!LAST) feed.issue(SPLIT_SLOT_B);
       rest(std::integral_constant<int, LAST ? 0 : 2 * TL::PER>{});   // third terms landed
-      read_a(SPLIT_SLOT_C);                 // x3 y1
+      read_a(SPLIT_SLOT_C, nvb);                 // x3 y1
       rest(std::integral_constant<int, -1>{});
-      read_a(a); read_b(SPLIT_SLOT_C);      // x1 y3
+      read_a(a, nvb); read_b(SPLIT_SLOT_C);      // x1 y3
       rest(std::integral_constant<int, LAST ? -1 : TL::PER>{});      // the next first terms landed
     };
     for (int k = 0; k < KI - 1; ++k) columns(k, std::false_type{});
@@ -618,13 +652,13 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
 // STREAMW: every byte of W is read once by the whole launch (one tile of positions): loaded with the
 // non-temporal hint.
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER = false, bool M16 = false,
-          bool WPACK = false, bool STREAMW = false, int PH = 0>
+          bool WPACK = false, bool STREAMW = false, int PH = 0, int VH = 0>
 __device__ __forceinline__ void tile_gemm(const void* Wp, long long ld_w, const void* hp, long long ld_h,
                                           int B, int d, int v, int slab, int b0, char* smem,
-                                          typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB],
+                                          typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB - VH / 2],
                                           const int* rows = nullptr, int nrows = 0, int rdiv = 1,
                                           const void* hs = nullptr, int wrows_total = 0, int wrow0 = 0) {
-  TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH> feed;
+  TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, false, VH> feed;
   feed.open(Wp, ld_w, hp, ld_h, B, d, v, slab, b0, smem, rows, nrows, rdiv, hs, wrows_total, wrow0);
   tile_gemm_run(feed, d, smem, acc);
 }
@@ -632,23 +666,23 @@ __device__ __forceinline__ void tile_gemm(const void* Wp, long long ld_w, const 
 // Softmax statistics of every position column of the tile: max and log-sum-exp
 // over the v vocabulary rows.  With FR = Frag<M16>, lane (lcol, lgrp) of wave (wv, wb) holds, for
 // position column p = wb*PB*32 + pb*FR::BR + lcol, the vocabulary rows
-//   row(vb, i) = wv*VB*32 + vb*FR::BR + 4*lgrp + FR::roff(i).
+//   row(vb, i) = wv*WROWS + vb*FR::BR + 4*lgrp + FR::roff(i).
 // Contains one workgroup barrier; `red` must not be reused before the next one.
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool M16 = false, int PH = 0>
-__device__ __forceinline__ void tile_lse(const typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB],
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool M16 = false, int PH = 0, int VH = 0>
+__device__ __forceinline__ void tile_lse(const typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB - VH / 2],
                                          int v, float2* red, float (&mx)[PB * Frag<M16>::SUB + PH],
                                          float (&lse)[PB * Frag<M16>::SUB + PH]) {
-  using TL = Tile<WV, WB, VB, PB, SB, NS, PH>;
+  using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
   using FR = Frag<M16>;
-  constexpr int NPB = PB * FR::SUB + PH, NVB = VB * FR::SUB;
+  constexpr int NPB = PB * FR::SUB + PH, NVB = VB * FR::SUB - VH / 2;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wv = wave % WV, wb = wave / WV;
+  const int wv = TL::wv(wave), wb = TL::wb(wave);
   const int lcol = FR::lcol(lane), lgrp = FR::lgrp(lane);
-  const int rbase = wv * VB * 32 + 4 * lgrp;
+  const int rbase = wv * TL::WROWS + 4 * lgrp;
   // exp(l - m) = 2^(l * log2(e) - m * log2(e)): one fused multiply-add and one v_exp per logit.
   // A tile whose v fills all TV rows (v = 320 on the 320-row tiles) needs no row masks.
   constexpr float LOG2E = 1.4426950408889634f;
-  const bool full = v == TL::TV;
+  const bool full = v == TL::TV && VH % 2 == 0;
 #pragma unroll
   for (int pb = 0; pb < NPB; ++pb) {
     float m = neg_inf();

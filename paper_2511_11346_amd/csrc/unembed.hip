@@ -128,24 +128,23 @@ __device__ __forceinline__ void tile_draws(const typename Frag<M16>::blk_t (&acc
 // Draws for every position column of a tile at once, from the accumulators (16x16 blocks): one token per
 // column p with need(p), by inverse CDF (Alg. 1: the smallest token k with u Z < cdf[k]; the last token with
 // positive mass if rounding leaves u Z >= Z) or, greedy, the most likely token (ties: the smallest id).
-// A column's v values lie in 4 lane groups x VB*2 blocks x WV waves; each lane forms the prefix of its own
+// A column's v values lie in 4 lane groups x NVB blocks x WV waves; each lane forms the prefix of its own
 // rows (sums over the lane groups by lane permutes, over the blocks in registers, over the waves through
 // LDS) and looks for the crossing among its rows; the smallest crossing row of a column wins (LDS minimum).
 // Three workgroup barriers per call, all waves busy, nothing dumped to LDS but one sum per column and wave.
 // Wide wave tiles (more than three blocks of columns) form the terms of a block a second time after the
 // barrier instead of keeping those of all blocks in registers.
 // The stage buffers must be free.  uni(p) gives the uniform of column p, out(p, token) takes the result.
-template <class TL, int WV, int VB, int NPB, class Need, class Uni, class Out>
-__device__ __forceinline__ void tile_draws_cols(const f32x4_t (&acc)[NPB][VB * 2], const float (&mx)[NPB], int v,
+template <class TL, int WV, int NVB, int NPB, class Need, class Uni, class Out>
+__device__ __forceinline__ void tile_draws_cols(const f32x4_t (&acc)[NPB][NVB], const float (&mx)[NPB], int v,
                                                 char* smem, bool greedy, Need need, Uni uni, Out out) {
-  constexpr int NVB = VB * 2;
   constexpr bool KEEP = NPB <= 3;
   constexpr int NK = KEEP ? NPB : 1;
   static_assert(NPB * 16 == TL::WP, "the wave's blocks of 16 position columns");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wv = wave % WV, wb = wave / WV;
+  const int wv = TL::wv(wave), wb = TL::wb(wave);
   const int lcol = lane & 15, lgrp = lane >> 4;
-  const int rbase = wv * VB * 32 + 4 * lgrp;
+  const int rbase = wv * TL::WROWS + 4 * lgrp;
   float* wsum = (float*)smem;                                        // [WV][TP] sum of a wave's rows of a column
   int* cand = (int*)(wsum + WV * TL::TP);                            // [TP] smallest crossing row
   int* lastp = cand + TL::TP;                                        // [TP] last row with positive mass
@@ -248,19 +247,19 @@ constexpr bool unembed_walks_tiles() { return !SAMPLE && WB != 1; }
 
 // SPLIT: fp32 operands as planes of three bf16 terms (tile_gemm_run_split); everything but the product is
 // the bf16 kernel's.
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false>
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false, int VH = 0>
 __global__ __launch_bounds__(WV * WB * 64)
 void k_unembed(const UnembedArgs a) {
   // of the two launches over the same fp32 operands one does the work (see launch_split)
   if constexpr (SPLIT || !BF16)
     if (a.wild != nullptr && (*a.wild != 0) == SPLIT) return;
-  using TL = Tile<WV, WB, VB, PB, SB, NS>;
+  using TL = Tile<WV, WB, VB, PB, SB, NS, 0, VH>;
   constexpr bool M16 = use_m16<WV, WB, SB, NS, BF16>();
   using FR = Frag<M16>;
-  constexpr int NPB = PB * FR::SUB, NVB = VB * FR::SUB;
+  constexpr int NPB = PB * FR::SUB, NVB = VB * FR::SUB - VH / 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wv = wave % WV, wb = wave / WV;
+  const int wv = TL::wv(wave), wb = TL::wb(wave);
   const int lcol = FR::lcol(lane), lgrp = FR::lgrp(lane);
   const int nslab = a.n * a.r;
   const int nbt = (a.B + TL::TP - 1) / TL::TP;
@@ -271,7 +270,7 @@ void k_unembed(const UnembedArgs a) {
   // softmax statistics are taken, instead of after a workgroup launch with the matrix pipe idle.
   // Every other instantiation has one tile per workgroup and leaves the loop after it.
   constexpr bool WALK = unembed_walks_tiles<WB, SAMPLE>();
-  using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, WB == 1, 0, SPLIT>;
+  using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, WB == 1, 0, SPLIT, VH>;
   const void* const hstaged = SPLIT ? a.hq : (WB != 1 && SB == H_STAGE_BYTES) ? a.hs : nullptr;
   const void* const Wfeed = SPLIT ? a.Wq : WPACK ? a.Wp : a.W;
   const int dfeed = SPLIT ? 3 * a.d : a.d;            // bf16 columns of the planes
@@ -324,9 +323,9 @@ void k_unembed(const UnembedArgs a) {
     }
   }
   // this lane holds, of position column wb*PB*32 + pb*BR + lcol, rows rbase + vb*BR + roff(i)
-  const int rbase = wv * VB * 32 + 4 * lgrp;
+  const int rbase = wv * TL::WROWS + 4 * lgrp;
   float mx[NPB], lse[NPB];
-  tile_lse<WV, WB, VB, PB, SB, NS, M16>(acc, a.v, (float2*)(smem + TL::RED_OFF), mx, lse);   // (one barrier: s_x is visible)
+  tile_lse<WV, WB, VB, PB, SB, NS, M16, 0, VH>(acc, a.v, (float2*)(smem + TL::RED_OFF), mx, lse);   // (one barrier: s_x is visible)
 
   // evidence at the target tokens (the sampling instantiation never has targets)
   if constexpr (!SAMPLE) if (a.targets != nullptr) {
@@ -349,7 +348,7 @@ void k_unembed(const UnembedArgs a) {
             const int xr = x - rbase;
             if constexpr (M16) {
               // rows rbase + 16 vb + t (t in 0..3)
-              if (xr >= 0 && xr < VB * 32 && (xr & 12) == 0) {
+              if (xr >= 0 && xr < TL::WROWS && (xr & 12) == 0) {
                 const int xvb = xr >> 4;
                 f32x4_t blk = acc[pb][0];
 #pragma unroll
@@ -442,7 +441,7 @@ void k_unembed(const UnembedArgs a) {
       bool any = false;
       for (int p = tid; p < TL::TP; p += TL::NT) any |= need(p);
       if (!__syncthreads_or(any)) continue;
-      tile_draws_cols<TL, WV, VB, NPB>(
+      tile_draws_cols<TL, WV, NVB, NPB>(
           acc, mx, a.v, smem, a.greedy != 0, need,
           [&](int p) { return philox_uniform(a.seed_lo, a.seed_hi, a.offset, (uint32_t)(b0 + p), (uint32_t)s, (uint32_t)wi); },
           [&](int p, int tok) { a.drafts[((long long)(b0 + p) * a.S + s) * a.n + wi] = tok; });
@@ -498,10 +497,10 @@ constexpr int GATHER_SB = GATHER_STAGE_BYTES, GATHER_NS = 4, GATHER_NSL = 16;
 // unit); a workgroup takes up to TP rows of one bucket, gathers their h rows, multiplies
 // them with the one slab W[i][z] and draws every row's token - 1/r of the products a
 // pass over all slabs needs.
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool WPACK, int PH>
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool WPACK, int PH, int VH>
 __global__ __launch_bounds__(WV * WB * 64)
 void k_draw_gather(const DrawGatherArgs a) {
-  using TL = Tile<WV, WB, VB, PB, SB, NS, PH>;
+  using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   // each XCD owns a contiguous range of logical tiles, so that the tiles of a bucket
@@ -521,16 +520,16 @@ void k_draw_gather(const DrawGatherArgs a) {
   const int wi = g / a.r;
 
   constexpr bool M16 = use_m16<WV, WB, SB, NS, BF16>();
-  constexpr int NPB = PB * Frag<M16>::SUB + PH;
-  typename Frag<M16>::blk_t acc[NPB][VB * Frag<M16>::SUB];
-  tile_gemm<WV, WB, VB, PB, SB, NS, BF16, true, M16, WPACK, false, PH>(WPACK ? a.Wp : a.W, a.d, a.h, a.ld_h, a.B, a.d, a.v, g, 0, smem,
+  constexpr int NPB = PB * Frag<M16>::SUB + PH, NVB = VB * Frag<M16>::SUB - VH / 2;
+  typename Frag<M16>::blk_t acc[NPB][NVB];
+  tile_gemm<WV, WB, VB, PB, SB, NS, BF16, true, M16, WPACK, false, PH, VH>(WPACK ? a.Wp : a.W, a.d, a.h, a.ld_h, a.B, a.d, a.v, g, 0, smem,
                                                                        acc, rows, nrows, a.S);
   float mx[NPB], lse[NPB];
-  tile_lse<WV, WB, VB, PB, SB, NS, M16, PH>(acc, a.v, (float2*)(smem + TL::RED_OFF), mx, lse);
+  tile_lse<WV, WB, VB, PB, SB, NS, M16, PH, VH>(acc, a.v, (float2*)(smem + TL::RED_OFF), mx, lse);
 
   if constexpr (M16) {
     const int S = a.S;
-    tile_draws_cols<TL, WV, VB, NPB>(
+    tile_draws_cols<TL, WV, NVB, NPB>(
         acc, mx, a.v, smem, a.greedy != 0, [&](int p) { return p < nrows; },
         [&](int p) {
           const int rid = rows[min(p, nrows - 1)];       // b * S + s
@@ -560,13 +559,13 @@ void k_draw_gather(const DrawGatherArgs a) {
   }
 }
 
-template <int WV, int WB, int VB, int PB, int PH, bool BF16, bool WPACK = false>
+template <int WV, int WB, int VB, int PB, int PH, bool BF16, int VH = 0, bool WPACK = false>
 static hipError_t launch_draw_gather_cfg(const DrawGatherArgs& a, hipStream_t st) {
-  using TL = Tile<WV, WB, VB, PB, GATHER_SB, GATHER_NS, PH>;
+  using TL = Tile<WV, WB, VB, PB, GATHER_SB, GATHER_NS, PH, VH>;
   static_assert(TL::TP == DRAW_GATHER_TILE || TL::TP == DRAW_GATHER_TILE_WIDE, "the tile heights the bucketing is run with");
   if constexpr (!WPACK)
-    if (a.Wp != nullptr) return launch_draw_gather_cfg<WV, WB, VB, PB, PH, BF16, true>(a, st);
-  constexpr auto kern = k_draw_gather<WV, WB, VB, PB, GATHER_SB, GATHER_NS, BF16, WPACK, PH>;
+    if (a.Wp != nullptr) return launch_draw_gather_cfg<WV, WB, VB, PB, PH, BF16, VH, true>(a, st);
+  constexpr auto kern = k_draw_gather<WV, WB, VB, PB, GATHER_SB, GATHER_NS, BF16, WPACK, PH, VH>;
   if (hipError_t e = allow_lds<kern>(TL::SMEM); e != hipSuccess) return e;
   const long long rows = (long long)a.B * a.S * a.n;
   const int grid = (int)(rows / TL::TP) + a.n * a.r;             // >= sum over buckets of ceil(rows_g / TP)
@@ -578,12 +577,14 @@ template <bool BF16>
 static hipError_t launch_draw_gather_dt(const DrawGatherArgs& a, hipStream_t st) {
   if constexpr (BF16)                                // (the wide tile counts its columns in blocks of 16)
     if (a.tile == DRAW_GATHER_TILE_WIDE) {
-      if (a.v > 256) return launch_draw_gather_cfg<2, 4, 5, 1, 1, BF16>(a, st);
+      if (a.v > 272) return launch_draw_gather_cfg<2, 4, 5, 1, 1, BF16>(a, st);
+      if (a.v > 256) return launch_draw_gather_cfg<2, 4, 5, 1, 1, BF16, 3>(a, st);
       if (a.v > 128) return launch_draw_gather_cfg<2, 4, 4, 1, 1, BF16>(a, st);
       return launch_draw_gather_cfg<2, 4, 2, 1, 1, BF16>(a, st);
     }
   if (a.tile != DRAW_GATHER_TILE) return hipErrorInvalidValue;
-  if (a.v > 256) return launch_draw_gather_cfg<2, 4, 5, 1, 0, BF16>(a, st);
+  if (a.v > 272) return launch_draw_gather_cfg<2, 4, 5, 1, 0, BF16>(a, st);
+  if (a.v > 256) return launch_draw_gather_cfg<2, 4, 5, 1, 0, BF16, BF16 ? 3 : 0>(a, st);
   if (a.v > 128) return launch_draw_gather_cfg<2, 4, 4, 1, 0, BF16>(a, st);
   return launch_draw_gather_cfg<2, 4, 2, 1, 0, BF16>(a, st);
 }
@@ -929,10 +930,10 @@ hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t st)
   return dtype == MTPC_BF16 ? launch_uni_dt<true>(a, st) : launch_uni_dt<false>(a, st);
 }
 
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false>
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false, int VH = 0>
 static hipError_t launch_cfg(const UnembedArgs& a, hipStream_t st) {
-  using TL = Tile<WV, WB, VB, PB, SB, NS>;
-  constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK, SPLIT>;
+  using TL = Tile<WV, WB, VB, PB, SB, NS, 0, VH>;
+  constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK, SPLIT, VH>;
   if (hipError_t e = allow_lds<kern>(TL::SMEM); e != hipSuccess) return e;
   const int nbt = (a.B + TL::TP - 1) / TL::TP;
   int grid = nbt * a.n * a.r;
@@ -960,21 +961,27 @@ static hipError_t launch_dec(const UnembedArgs& a, int row_bytes, hipStream_t st
   return launch_cfg<WV, 1, 2, PB, 64, 4, BF16, SAMPLE>(a, st);
 }
 
+// 256-position tiles of the fewest rows that hold the vocabulary (a K stage costs what its rows cost: products,
+// loads and fragment reads alike).  The 272-row one exists for 16x16 blocks only: fp32 instructions fill 32.
+template <bool BF16, bool SAMPLE, bool WPACK, bool SPLIT = false>
+static hipError_t launch_train(const UnembedArgs& a, hipStream_t st) {
+  if (a.v > 272) return launch_cfg<2, 4, 5, 2, 64, 4, BF16, SAMPLE, WPACK, SPLIT>(a, st);
+  if (a.v > 256) return launch_cfg<2, 4, 5, 2, 64, 4, BF16, SAMPLE, WPACK, SPLIT, BF16 ? 3 : 0>(a, st);
+  if (a.v > 192) return launch_cfg<2, 4, 4, 2, 64, 4, BF16, SAMPLE, WPACK, SPLIT>(a, st);
+  if (a.v > 128) return launch_cfg<2, 4, 3, 2, 64, 4, BF16, SAMPLE, WPACK, SPLIT>(a, st);
+  return launch_cfg<2, 4, 2, 2, 64, 4, BF16, SAMPLE, WPACK, SPLIT>(a, st);
+}
+
 template <bool BF16, bool SAMPLE>
 static hipError_t launch_dt(const UnembedArgs& a, hipStream_t st) {
-  // Vocabulary tile: 5 blocks of 32 per wave pair covers v <= 320; v <= 256 and
-  // v <= 128 take narrower tiles.  Positions: 256-wide tiles for training-sized
+  // Vocabulary tile: 5 blocks of 32 per wave pair covers v <= 320; smaller v take
+  // narrower tiles.  Positions: 256-wide tiles for training-sized
   // batches, 64- or 32-wide tiles (W streamed once) for decode-sized ones.
   const int row_bytes = a.d * (BF16 ? 2 : 4);
   if (a.B > 64) {
-    if (a.Wp != nullptr && a.Wp_stage == 64) {      // the copy of W in the 64-byte stages of these tiles
-      if (a.v > 256) return launch_cfg<2, 4, 5, 2, 64, 4, BF16, SAMPLE, true>(a, st);
-      if (a.v > 128) return launch_cfg<2, 4, 4, 2, 64, 4, BF16, SAMPLE, true>(a, st);
-      return launch_cfg<2, 4, 2, 2, 64, 4, BF16, SAMPLE, true>(a, st);
-    }
-    if (a.v > 256) return launch_cfg<2, 4, 5, 2, 64, 4, BF16, SAMPLE>(a, st);
-    if (a.v > 128) return launch_cfg<2, 4, 4, 2, 64, 4, BF16, SAMPLE>(a, st);
-    return launch_cfg<2, 4, 2, 2, 64, 4, BF16, SAMPLE>(a, st);
+    if (a.Wp != nullptr && a.Wp_stage == 64)        // the copy of W in the 64-byte stages of these tiles
+      return launch_train<BF16, SAMPLE, true>(a, st);
+    return launch_train<BF16, SAMPLE, false>(a, st);
   }
   if (a.B > 32) {
     if (a.v > 256) return launch_dec<5, 2, BF16, SAMPLE>(a, row_bytes, st);
@@ -1054,9 +1061,7 @@ static hipError_t launch_split(const UnembedArgs& a, hipStream_t st) {
   };
   split(a.h, a.hq, 1, a.B, a.ld_h);
   split(a.W, a.Wq, (long long)a.n * a.r, a.v, a.d);
-  hipError_t e = a.v > 256   ? launch_cfg<2, 4, 5, 2, 64, 4, true, SAMPLE, true, true>(a, st)
-                 : a.v > 128 ? launch_cfg<2, 4, 4, 2, 64, 4, true, SAMPLE, true, true>(a, st)
-                             : launch_cfg<2, 4, 2, 2, 64, 4, true, SAMPLE, true, true>(a, st);
+  const hipError_t e = launch_train<true, SAMPLE, true, true>(a, st);
   return e != hipSuccess ? e : launch_dt<false, SAMPLE>(a, st);
 }
 

@@ -13,7 +13,8 @@ import torch
 import mtpc_inputs as mi
 from oracle import backward as bw
 from oracle import mtpc_oracle as oc
-from gpu_util import make_head
+from oracle import philox
+from gpu_util import compare_drafts, make_head
 from test_gpu_backward import check_grad
 
 pytestmark = pytest.mark.gpu
@@ -21,7 +22,8 @@ pytestmark = pytest.mark.gpu
 
 # edges of the vocabulary and position tiles, one column block, an odd and an even number of them, rows of h apart
 SIZES = [(65, 512, 2, 3, 33), (70, 544, 3, 2, 128), (256, 512, 2, 2, 129), (257, 512, 2, 3, 256),
-         (300, 1056, 2, 2, 268), (129, 1024, 1, 4, 320)]
+         (300, 1056, 2, 2, 268), (129, 1024, 1, 4, 320),
+         (65, 512, 2, 2, 192), (66, 512, 2, 2, 193), (80, 544, 2, 2, 272), (80, 544, 2, 2, 273), (260, 512, 2, 2, 265)]
 
 
 @pytest.mark.parametrize("B,d,n,r,v", SIZES)
@@ -80,3 +82,23 @@ def test_training_step(family, B, d, n, r, v):
             check_grad(k, out[k], ref[k], "f32")
     again = head.loss_backward(tg, torch.from_numpy(coef.astype(np.float32)).cuda())
     assert all(torch.equal(again[k], out[k]) for k in out if out[k] is not None)
+
+
+@pytest.mark.parametrize("v", [129, 192, 193, 257, 264, 265, 272, 273])
+@pytest.mark.parametrize("B,S", [(70, 1), (300, 3)])
+def test_bf16_vocabulary_tiles(v, B, S):
+    """The row counts at which the 256-position tiles and the gathered draws change their tile (192, 272 with
+    one wave a block short, 320): evidence, table, draws through buckets and in the kernel."""
+    inp = mi.make_inputs("hmm", B=B, d=96, n=3, r=4, v=v, dtype="bf16", seed=v + B, h_scale=1.0)
+    logphi, logw, lay = oc._params("hmm", inp.h, inp.W, inp.Wsum, inp.layers)
+    head = make_head(inp)
+    want = oc.prefix_marginals_from("hmm", logphi, logw, lay, inp.targets)
+    assert np.abs(head.prefix_marginals(torch.from_numpy(inp.targets).cuda()).cpu().numpy() - want).max() < 2e-5
+    table = torch.full((B, 3, 4, v), float("nan"), device="cuda")
+    head.sample(S, seed=3, logphi=table)
+    assert np.abs(table.cpu().numpy() - logphi).max() < 2e-5
+    u = philox.uniforms(B, S, 6, seed=3)
+    od, ol, margin = oc.sample_from("hmm", logphi, logw, lay, u, with_margin=True)
+    for prefix in (False, True):                     # through buckets; in the fused kernel where those do not pay
+        gd, gl, _ = head.sample(S, seed=3, want_prefix=prefix)
+        compare_drafts(gd, gl, od, ol, margin)
