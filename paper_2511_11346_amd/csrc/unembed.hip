@@ -593,61 +593,122 @@ hipError_t launch_draw_gather(const DrawGatherArgs& a, int dtype, hipStream_t st
   return dtype == MTPC_BF16 ? launch_draw_gather_dt<true>(a, st) : launch_draw_gather_dt<false>(a, st);
 }
 
-// Sum-unit parameters for many positions (Sec. 3.3): log omega[b,:] =
-// log_softmax(Wsum h[b]).  Same tile machinery with Wsum as the only "slab" (r rows)
-// and narrow position tiles, so that B/32 workgroups share the work.
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16>
-__global__ __launch_bounds__(WV * WB * 64)
+// Sum-unit parameters for many positions (Sec. 3.3): log omega[b,:] = log_softmax(Wsum h[b]), r <= 16 RB units,
+// 16 PB positions per workgroup.  The product is small and its chain over d long, so the waves (sixteen, or eight
+// where their partial sums would not fit in LDS) deal its 64-byte steps among themselves (together a contiguous
+// piece of every row), straight from memory into registers with U
+// steps in flight, and their partial sums are added through LDS in a fixed order.  (As one wave that walks all
+// of d through an LDS ring, 32 positions to a workgroup: 22 us for any B up to 4096 at d = 4096 bf16, r = 32, 57 us
+// in fp32 - 0.35 us per 128 bytes of a row, a barrier and a chain of LDS read and product each.)
+constexpr int sumunit_waves(int RB, int PB) { return RB * PB <= 2 ? 16 : 8; }
+template <int RB, int PB, bool BF16>
+__global__ __launch_bounds__(sumunit_waves(RB, PB) * 64)
 void k_sumunit_mfma(const void* h, long long ld_h, const void* Wsum, int B, int d, int r, float* logw) {
-  using TL = Tile<WV, WB, VB, PB, SB, NS>;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wv = wave % WV, wb = wave / WV;
-  const int l31 = lane & 31, lhalf = lane >> 5;
-  const int b0 = blockIdx.x * TL::TP;
-  f32x16_t acc[PB][VB];
-  tile_gemm<WV, WB, VB, PB, SB, NS, BF16>(Wsum, d, h, ld_h, B, d, r, 0, b0, smem, acc);
-  float mx[PB], lse[PB];
-  tile_lse<WV, WB, VB, PB, SB, NS>(acc, r, (float2*)(smem + TL::RED_OFF), mx, lse);
-  const int rbase = wv * VB * 32 + 4 * lhalf;
+  constexpr int ESZ = BF16 ? 2 : 4, NW = sumunit_waves(RB, PB), U = RB + PB <= 3 ? 8 : RB + PB <= 5 ? 6 : 3;
+  constexpr int PS = PB * 16 + 1;                    // (odd stride: the lanes of a reduction read different banks)
+  __shared__ float part[NW][RB * 16 * PS];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l15 = lane & 15, lq = lane >> 4;
+  const int b0 = blockIdx.x * PB * 16;
+  const int steps = d * ESZ / 64;
+  const char* pw[RB];
+  const char* ph[PB];
 #pragma unroll
-  for (int pb = 0; pb < PB; ++pb) {
-    const int b = b0 + wb * PB * 32 + pb * 32 + l31;
-    if (b >= B) continue;
+  for (int i = 0; i < RB; ++i) pw[i] = (const char*)Wsum + (long long)min(i * 16 + l15, r - 1) * d * ESZ + lq * 16;
 #pragma unroll
-    for (int vb = 0; vb < VB; ++vb)
+  for (int i = 0; i < PB; ++i) ph[i] = (const char*)h + (long long)min(b0 + i * 16 + l15, B - 1) * ld_h * ESZ + lq * 16;
+  f32x4_t acc[PB][RB];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int row = rbase + vb * 32 + 8 * (i >> 2) + (i & 3);
-        if (row < r) logw[(long long)b * r + row] = acc[pb][vb][i] - lse[pb];
+  for (int p = 0; p < PB; ++p)
+#pragma unroll
+    for (int i = 0; i < RB; ++i) acc[p][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = wave; s0 < steps; s0 += NW * U) {
+    i32x4_t fw[U][RB], fh[U][PB];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      // (clamped, so that all loads are in flight together; steps beyond d become zeros)
+      const long long o = (long long)min(s0 + u * NW, steps - 1) * 64;
+#pragma unroll
+      for (int i = 0; i < PB; ++i) fh[u][i] = *(const i32x4_t*)(ph[i] + o);
+#pragma unroll
+      for (int i = 0; i < RB; ++i) fw[u][i] = *(const i32x4_t*)(pw[i] + o);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u * NW >= steps) continue;            // wave-uniform
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+          if constexpr (BF16) mma_step<true>(acc[p][i], fw[u][i], fh[u][p]);
+          else {
+            // lane group lq holds columns 4 lq .. 4 lq + 3 of both operands: product t takes one of each
+            const f32x4_t x = __builtin_bit_cast(f32x4_t, fw[u][i]), y = __builtin_bit_cast(f32x4_t, fh[u][p]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[p][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t], y[t], acc[p][i], 0, 0, 0);
+          }
+        }
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < PB; ++p)
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) part[wave][(i * 16 + 4 * lq + t) * PS + p * 16 + l15] = acc[p][i][t];
+  __syncthreads();
+  // 32 lanes per position, units j, j + 32, ...
+  const int j = threadIdx.x & 31;
+  constexpr int Q = (RB + 1) / 2;
+  for (int p = threadIdx.x >> 5; p < PB * 16 && b0 + p < B; p += NW * 2) {
+    float x[Q], m = neg_inf();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int u = j + 32 * q;
+      x[q] = neg_inf();
+      if (u < r) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) sum += part[w][u * PS + p];
+        x[q] = sum;
       }
+      m = fmaxf(m, x[q]);
+    }
+    m = group_max(m, 32);
+    const float ms = m == neg_inf() ? 0.f : m;
+    float e = 0.f;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (j + 32 * q < r) e += __expf(x[q] - ms);
+    const float lse = m + __logf(group_sum(e, 32));
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (j + 32 * q < r) logw[(long long)(b0 + p) * r + j + 32 * q] = x[q] - lse;
   }
 }
 
-template <int WV, int VB, int SB, int NS, bool BF16>
+template <int RB, int PB, bool BF16>
 static hipError_t launch_sumunit_mfma_cfg(const void* h, long long ld_h, const void* Wsum, int B, int d,
                                           int r, float* logw, hipStream_t st) {
-  using TL = Tile<WV, 1, VB, 1, SB, NS>;   // WV * VB * 32 rows (>= r) x 32 positions, WV waves
-  constexpr auto kern = k_sumunit_mfma<WV, 1, VB, 1, SB, NS, BF16>;
-  if (hipError_t e = allow_lds<kern>(TL::SMEM); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((B + TL::TP - 1) / TL::TP), dim3(TL::NT), TL::SMEM, st, h, ld_h, Wsum, B,
-                     d, r, logw);
+  hipLaunchKernelGGL((k_sumunit_mfma<RB, PB, BF16>), dim3((B + PB * 16 - 1) / (PB * 16)),
+                     dim3(sumunit_waves(RB, PB) * 64), 0, st, h, ld_h,
+                     Wsum, B, d, r, logw);
   return hipGetLastError();
 }
 
-// The kernel streams h once with one small workgroup per 32 positions, so what limits it is
-// the number of bytes of h it keeps in flight: 128-byte stages when the rows allow it, no more
-// rows of Wsum in a stage than r needs (they are loaded beside h), and the LDS that saves spent
-// on a deeper ring.
+// 16 positions per workgroup as long as those fill the 256 CUs at most once, else 32: Wsum is then read from the
+// L2s half as often.
 template <bool BF16>
 static hipError_t launch_sumunit_mfma_dt(const void* h, long long ld_h, const void* Wsum, int B, int d,
                                          int r, float* logw, hipStream_t st) {
-  if ((d * (BF16 ? 2 : 4)) % 128 == 0) {
-    if (r <= 32) return launch_sumunit_mfma_cfg<1, 1, 128, 8, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
-    if (r <= 64) return launch_sumunit_mfma_cfg<2, 1, 128, 6, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
-    return launch_sumunit_mfma_cfg<2, 2, 128, 4, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
-  }
-  return launch_sumunit_mfma_cfg<2, 2, 64, 4, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
+  const bool wide = B > 4096;
+  if (r <= 16) return wide ? launch_sumunit_mfma_cfg<1, 2, BF16>(h, ld_h, Wsum, B, d, r, logw, st)
+                           : launch_sumunit_mfma_cfg<1, 1, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
+  if (r <= 32) return wide ? launch_sumunit_mfma_cfg<2, 2, BF16>(h, ld_h, Wsum, B, d, r, logw, st)
+                           : launch_sumunit_mfma_cfg<2, 1, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
+  if (r <= 64) return wide ? launch_sumunit_mfma_cfg<4, 2, BF16>(h, ld_h, Wsum, B, d, r, logw, st)
+                           : launch_sumunit_mfma_cfg<4, 1, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
+  return launch_sumunit_mfma_cfg<8, 1, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
 }
 
 hipError_t launch_sumunit_mfma(const void* h, long long ld_h, const void* Wsum, int B, int d, int r,
