@@ -613,6 +613,267 @@ __global__ __launch_bounds__(256) void k_btree_bwd(const CircuitBwdArgs a, int n
   if (lane == 0) a.loss[row] = loss;
 }
 
+constexpr int BTREE_BWD_LDS = 156 * 1024;
+// The same for shared layers of R = 16, 32 or 64 units, 16 evidence rows per workgroup and one wave per block of
+// 16 units: a layer applied to 16 rows is a matrix product, A xi on the way up and A^T delta on the way back
+// (v_mfma_f32_16x16x4_f32, the operand layout of k_btree_mfma: lane (row = l mod 16, g = l div 16) holds units
+// 16 b + 4 g + i).  A path of the program (one prefix) is walked back as soon as its P_j is known, so that path
+// values, node values and node adjoints all stay in LDS; node values are walked back at the end.  Every wave
+// forms whole vectors where a product needs them and owns the 16 units it computed everywhere else: adjoints
+// and gradients are added by their owner alone, in program order.
+// Bound by its chain of dependent steps (the forward kernel's 1,700 cycles each, twice), not by the products or by
+// memory; a lane per unit and a wave per row took 1.02 ms for 4,096 rows at R = 64, n = 16, this takes 0.24 ms.
+struct BwdOp { short t, q; };   // program step; q: its place on a path (0 first), -1 - q: walked back
+
+template <int R>
+constexpr size_t btree_bwd_lds(int n, int T) {
+  int lg = 0;
+  while ((1 << lg) < n) ++lg;
+  const size_t slots = 2 * (size_t)(n > 2 ? n - 2 : 0) + lg + 2;
+  return slots * 16 * (R + 4) * 4 + (size_t)(n + lg) * 16 * 4 + (size_t)T * sizeof(TreeStep) + 2 * (size_t)T * sizeof(BwdOp);
+}
+
+template <int R>
+__global__ __launch_bounds__(4 * R) void k_btree_bwd_mfma(const CircuitBwdArgs a, int nsteps_max) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+  constexpr int NB = R / 16, RS = R + 4;
+  extern __shared__ __align__(16) float wsm[];
+  __shared__ int s_nops;
+  const int n = a.n, n2 = max(n - 2, 0);
+  int lg = 0;
+  while ((1 << lg) < n) ++lg;
+  const int lane = threadIdx.x & 63, rl = lane & 15, g = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int own = 16 * wv + 4 * g;                   // first of this lane's four units
+  float* val = wsm;                                  // [n-2] values of nodes 1 ..
+  float* adj = val + (size_t)n2 * 16 * RS;           // [n-2] their adjoints
+  float* path = adj + (size_t)n2 * 16 * RS;          // [lg] values of the current path
+  float* padj = path + (size_t)lg * 16 * RS;         // [2] adjoint of the path value, alternating
+  float* mxs = padj + (size_t)2 * 16 * RS;           // [n-2 + lg][16] row maxima of the steps' operands
+  TreeStep* prog = (TreeStep*)(mxs + (size_t)(n + lg) * 16);
+  BwdOp* ops = (BwdOp*)(prog + nsteps_max);
+  if (threadIdx.x == 0) {
+    const int T = build_tree_program(prog, n, 1);
+    int k = 0;
+    for (int t = 0; t < n2; ++t) ops[k++] = BwdOp{(short)t, 0};
+    for (int t = n2; t < T;) {                       // a path: up to and with its root step, then back
+      int e = t;
+      while (prog[e].m != 0) ++e;
+      for (int s = t; s <= e; ++s) ops[k++] = BwdOp{(short)s, (short)(s - t)};
+      for (int s = e - 1; s >= t; --s) ops[k++] = BwdOp{(short)s, (short)(-1 - (s - t))};
+      t = e + 1;
+    }
+    for (int t = n2 - 1; t >= 0; --t) ops[k++] = BwdOp{(short)t, -1};
+    s_nops = k;
+  }
+  const long long row = (long long)blockIdx.x * 16 + rl;
+  const bool live = row < a.rows;
+  const long long rc = live ? row : (long long)a.rows - 1;       // clamped: loads stay in bounds
+  const float* e = a.e + rc * n * R + 4 * g;
+  const float* coef = a.coef + rc * n;
+  float* Ge = a.Ge + rc * n * R + own;
+  const size_t lstep = a.L > 1 ? (size_t)R * R : 0;
+  const float* lay_n = a.lay_nat + (size_t)(16 * wv + rl) * R + 4 * g;
+  const float* lay_t = a.lay_tr + (size_t)(16 * wv + rl) * R + 4 * g;
+  const size_t at = (size_t)rl * RS;                 // this row inside a slot
+  const float ninf = neg_inf();
+  const f32x4_t zero = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  f32x4_t lw[NB], gw[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    lw[b] = *(const f32x4_t*)(a.logw + rc * R + 16 * b + 4 * g);
+    gw[b] = zero;
+  }
+  for (int s = 0; s < n2; ++s) *(f32x4_t*)(adj + (size_t)s * 16 * RS + at + own) = zero;
+  if (live)
+    for (int i = 0; i < n; ++i) *(f32x4_t*)(Ge + (size_t)i * R) = zero;
+  __syncthreads();
+  const int nops = __builtin_amdgcn_readfirstlane(s_nops);
+
+  // lanes l, l ^ 16, l ^ 32, l ^ 48 share a row
+  auto across = [](float x, auto f) { x = f(x, __shfl_xor(x, 16)); return f(x, __shfl_xor(x, 32)); };
+  auto fadd = [](float x, float y) { return x + y; };
+  auto fmx = [](float x, float y) { return fmaxf(x, y); };
+  // a step of the walk, the same for every lane: in scalar registers
+  struct Op { int t, q, m, lsrc, rsrc, out; };
+  auto read_op = [&](int k) {
+    const int w = __builtin_amdgcn_readfirstlane(*(const int*)(ops + min(k, nops - 1)));
+    Op o;
+    o.t = (short)(w & 0xffff); o.q = w >> 16;
+    const int2 raw = *(const int2*)(prog + o.t);
+    const int w0 = __builtin_amdgcn_readfirstlane(raw.x), w1 = __builtin_amdgcn_readfirstlane(raw.y);
+    o.m = (short)(w0 & 0xffff); o.lsrc = w0 >> 16; o.rsrc = (short)(w1 & 0xffff); o.out = w1 >> 16;
+    return o;
+  };
+  // where the value an operand names sits (path values: the step before on the path)
+  auto slot = [&](int src, int q) { return src == -1 ? path + (size_t)(q - 1) * 16 * RS : val + (size_t)(src - 1) * 16 * RS; };
+  // layer rows and leaf evidence of the next step are fetched a step ahead
+  f32x4_t An[NB], nl[NB], nr[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) An[b] = nl[b] = nr[b] = zero;
+  auto prefetch = [&](int k, const Op& o) {
+    if (k >= nops) return;
+    if (o.lsrc >= n - 1) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) nl[b] = *(const f32x4_t*)(e + (size_t)(o.lsrc - (n - 1)) * R + 16 * b);
+    }
+    if (o.rsrc >= n - 1) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) nr[b] = *(const f32x4_t*)(e + (size_t)(o.rsrc - (n - 1)) * R + 16 * b);
+    }
+    if (o.m > 0) {
+      const float* A = (o.q < 0 ? lay_t : lay_n) + (size_t)(o.m - 1) * lstep;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) An[b] = *(const f32x4_t*)(A + 16 * b);
+    }
+  };
+  float loss = 0.f;
+  Op cur = read_op(0);
+  prefetch(0, cur);
+  for (int k = 0; k < nops; ++k) {
+    const Op st = cur;
+    const bool back = st.q < 0;
+    const int q = back ? -1 - st.q : st.q;
+    const bool up = st.t < n2;                       // a stored node (else: on a path, or its root)
+    // the operands' sum
+    f32x4_t x[NB], Ac[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      f32x4_t l = zero, r = zero;
+      if (st.lsrc >= n - 1) l = nl[b];
+      else if (st.lsrc != -2) l = *(const f32x4_t*)(slot(st.lsrc, q) + at + 16 * b + 4 * g);
+      if (st.rsrc >= n - 1) r = nr[b];
+      else if (st.rsrc != -2) r = *(const f32x4_t*)(slot(st.rsrc, q) + at + 16 * b + 4 * g);
+      x[b] = l + r;
+      Ac[b] = An[b];
+    }
+    cur = read_op(k + 1);
+    prefetch(k + 1, cur);
+    // adds the adjoint of x (this lane's four units) to an operand
+    auto scatter = [&](int src, const f32x4_t& v) {
+      if (src == -2) return;
+      if (src == -1) *(f32x4_t*)(padj + (size_t)((q - 1) & 1) * 16 * RS + at + own) = v;
+      else if (src >= n - 1) {
+        if (live) *(f32x4_t*)(Ge + (size_t)(src - (n - 1)) * R) += v;
+      } else *(f32x4_t*)(adj + (size_t)(src - 1) * 16 * RS + at + own) += v;
+    };
+    float* mslot = mxs + (size_t)(up ? st.m - 1 : n2 + q) * 16 + rl;
+    if (!back) {
+      if (st.m == 0) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) x[b] += lw[b];
+      }
+      float m = ninf;
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m = fmaxf(m, x[b][i]);
+      m = across(m, fmx);
+      const float ms = (m == ninf) ? 0.f : m;
+      if (st.m == 0) {
+        // P_j = LSE(x), adjoint of x: g_j softmax(x); the root's weights take the same
+        float sum = 0.f;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sum += __expf(x[b][i] - m);
+        const float P = m + __logf(across(sum, fadd));
+        const int j = -2 - st.out;
+        const float gj = (j + 1 < n ? coef[j + 1] : 0.f) - coef[j];
+        loss += gj * P;
+        f32x4_t mine = zero;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          f32x4_t v;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[i] = gj * __expf(x[b][i] - P);
+          gw[b] += v;
+          if (b == wv) mine = v;
+        }
+        scatter(st.lsrc, mine);
+        scatter(st.rsrc, mine);
+      } else {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x[b][i] = __expf(x[b][i] - ms);
+        f32x4_t S = zero;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) S = __builtin_amdgcn_mfma_f32_16x16x4f32(Ac[b][i], x[b][i], S, 0, 0, 0);
+        f32x4_t res;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) res[i] = ms + __logf(S[i]);
+        *(f32x4_t*)((up ? val + (size_t)(st.m - 1) * 16 * RS : path + (size_t)q * 16 * RS) + at + own) = res;
+        if (wv == 0 && g == 0) *mslot = ms;
+      }
+    } else {
+      // delta = adj(c) exp(max - c), whole; xi = exp(x - max), this wave's units
+      const float ms = *mslot;
+      const float* cs = (up ? val + (size_t)(st.m - 1) * 16 * RS : path + (size_t)q * 16 * RS) + at;
+      const float* bs = (up ? adj + (size_t)(st.m - 1) * 16 * RS : padj + (size_t)(q & 1) * 16 * RS) + at;
+      f32x4_t S = zero, xi = zero, dmine = zero;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const f32x4_t c = *(const f32x4_t*)(cs + 16 * b + 4 * g), cb = *(const f32x4_t*)(bs + 16 * b + 4 * g);
+        f32x4_t d;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d[i] = cb[i] != 0.f ? cb[i] * __expf(ms - c[i]) : 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) S = __builtin_amdgcn_mfma_f32_16x16x4f32(Ac[b][i], d[i], S, 0, 0, 0);
+        if (b == wv) {
+          dmine = d;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) xi[i] = __expf(x[b][i] - ms);
+        }
+      }
+      if (a.pi != nullptr && live) {
+        *(f32x4_t*)(a.pi + (row * nsteps_max + st.t) * R + own) = dmine;
+        *(f32x4_t*)(a.gam + (row * nsteps_max + st.t) * R + own) = xi;
+      }
+      const f32x4_t xb = xi * S;
+      scatter(st.lsrc, xb);
+      scatter(st.rsrc, xb);
+    }
+    __syncthreads();
+  }
+  // the sum units' logits: G_z - omega_z sum G
+  float tot = 0.f;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) tot += (gw[b][0] + gw[b][1]) + (gw[b][2] + gw[b][3]);
+  tot = across(tot, fadd);
+  if (a.dslT != nullptr && row < a.ldb) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if (b != wv) continue;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float v = live ? gw[b][i] - __expf(lw[b][i]) * tot : 0.f;
+        const long long o = (long long)(own + i) * a.ldb + row;
+        if (a.bf16) ((unsigned short*)a.dslT)[o] = to_bf16_rne(v); else ((float*)a.dslT)[o] = v;
+      }
+    }
+  }
+  if (live && wv == 0 && g == 0) a.loss[row] = loss;
+}
+
+template <int R>
+static hipError_t launch_btree_bwd_mfma(const CircuitBwdArgs& a, int T, hipStream_t st) {
+  const size_t lds = btree_bwd_lds<R>(a.n, T);
+  if (hipError_t e = allow_lds<k_btree_bwd_mfma<R>>(BTREE_BWD_LDS); e != hipSuccess) return e;
+  const long long rows = a.dslT ? a.ldb : a.rows;
+  hipLaunchKernelGGL(k_btree_bwd_mfma<R>, dim3((unsigned)((rows + 15) / 16)), dim3(4 * R), lds, st, a, T);
+  return hipGetLastError();
+}
+
+// 16 rows of a window fit in LDS up to n = 16 (32 at R = 16).
+static bool btree_bwd_mfma_takes(const CircuitBwdArgs& a, int T) {
+  if (a.contextual || a.lay_tr == nullptr || a.n > 64) return false;
+  const size_t lds = a.r == 64 ? btree_bwd_lds<64>(a.n, T) : a.r == 32 ? btree_bwd_lds<32>(a.n, T) : a.r == 16 ? btree_bwd_lds<16>(a.n, T) : ~(size_t)0;
+  return lds <= (size_t)BTREE_BWD_LDS;
+}
+
 // part[by][j][z][z'] = sum over the rows of block by of pi[b][j][z] * gam[b][j][z'] for step j.
 // Thread t owns outputs t, t + 256, ...: NO of them.  Nothing is accumulated across workgroups
 // here: k_layer_reduce adds the partial tiles in a fixed order, so that the layer gradients are
@@ -786,7 +1047,11 @@ hipError_t launch_circuit_bwd(const CircuitBwdArgs& a, hipStream_t st) {
     const long long cnt = (long long)a.rows * a.L * r * r;
     hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, a.dlog32, cnt);
   }
-  if (tree) hipLaunchKernelGGL(k_btree_bwd, dim3((unsigned)((rows + 3) / 4)), dim3(256), prog_bytes, st, a, T);
+  if (tree && btree_bwd_mfma_takes(a, T)) {
+    const hipError_t e = r == 64 ? launch_btree_bwd_mfma<64>(a, T, st) : r == 32 ? launch_btree_bwd_mfma<32>(a, T, st)
+                                                                                 : launch_btree_bwd_mfma<16>(a, T, st);
+    if (e != hipSuccess) return e;
+  } else if (tree) hipLaunchKernelGGL(k_btree_bwd, dim3((unsigned)((rows + 3) / 4)), dim3(256), prog_bytes, st, a, T);
   else hipLaunchKernelGGL(k_circuit_bwd, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, a);
   if (layers) {
     const int steps = T, rpb = LAYER_GRAD_ROWS;
