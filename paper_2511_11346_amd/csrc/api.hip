@@ -78,7 +78,7 @@ bool table_in_workspace(const mtpc_head* hd, int S) {      // for a sampling cal
 // 64-byte stages per row, and all of it behind one 32-bit buffer resource.
 bool stage_major_h_pays(const mtpc_head* hd) {
   const unsigned long long row = (unsigned long long)hd->d * (hd->dtype == MTPC_BF16 ? 2 : 4);
-  return hd->B > 64 && row % H_STAGE_BYTES == 0 && row * (unsigned long long)hd->B < (1ull << 32);
+  return unembed_positions(hd->B, hd->n, hd->r) == 256 && row % H_STAGE_BYTES == 0 && row * (unsigned long long)hd->B < (1ull << 32);
 }
 
 // fp32 operands of the 256-position tiles as planes of three bf16 terms (launch_unembed), where a pass over all
@@ -87,11 +87,11 @@ bool stage_major_h_pays(const mtpc_head* hd) {
 // and 6 written per element: 0.43 ms there, 4.9 TB/s) and four short launches.
 constexpr double SPLIT_TILE_US = 148, F32_TILE_US = 304;
 bool split_pays(const mtpc_head* hd) {
-  if (hd->dtype != MTPC_F32 || hd->B <= 64) return false;
+  if (hd->dtype != MTPC_F32 || unembed_positions(hd->B, hd->n, hd->r) != 256) return false;
   if ((unsigned long long)hd->B * hd->d * 6 >= (1ull << 32)) return false;      // one 32-bit buffer resource
   const double frows = hd->v > 256 ? 320 : hd->v > 192 ? 256 : hd->v > 128 ? 192 : 128;
   const double srows = (hd->v > 256 && hd->v <= 272) ? 272 : frows;            // (launch_train)
-  const double rounds = std::ceil((double)((hd->B + 255) / 256) * hd->n * hd->r / 256.0);
+  const double rounds = std::ceil((double)((hd->B + 255LL) / 256) * hd->n * hd->r / 256.0);
   const double tile = rounds / 320.0 * hd->d / 1024.0;
   const double split = (double)hd->n * hd->r * hd->v * hd->d * 10.0 / 4.9e6 + 15.0;
   return tile * srows * SPLIT_TILE_US + split < tile * frows * F32_TILE_US;

@@ -81,6 +81,17 @@ struct CtxLayerArgs {
 hipError_t launch_ctx_layers(const CtxLayerArgs& a, int dtype, hipStream_t st);
 
 hipError_t launch_unembed(const UnembedArgs& a, int dtype, hipStream_t st);
+// Positions per tile of the fused kernel.  A decode-sized batch is one tile (W is then read once).  Larger ones
+// take 256, unless the tiles of 64 or 32 positions all run at once on the 256 CUs: a K stage of those is shorter,
+// and that many CUs would stand idle (FF, n = 8, d = 4096: B = 512 92 us with 256 positions, 41 with 32;
+// CP n = 4, r = 16, d = 2048, B = 250: 66 against 42 us; fp32 CP n = 4, r = 8, d = 2048, B = 200: 660 against 148 us).
+inline int unembed_positions(int B, int n, int r) {
+  constexpr long long CUS = 256;
+  const long long slabs = (long long)n * r;
+  if (B <= 32 || slabs * ((B + 31LL) / 32) <= CUS) return 32;
+  if (B <= 64 || slabs * ((B + 63LL) / 64) <= CUS) return 64;
+  return 256;
+}
 // dst[slab][stage][row][stage_bytes] = the stage_bytes of row `row` of slab `slab` of W that K stage `stage` covers
 // Stage-major copy of `slabs` matrices of v rows (row_bytes used bytes, row_stride bytes apart): per matrix
 // [row_bytes / stage_bytes][v][stage_bytes].  W for the decode tiles (128-byte stages), h for the

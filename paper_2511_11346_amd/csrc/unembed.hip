@@ -247,7 +247,9 @@ constexpr bool unembed_walks_tiles() { return !SAMPLE && WB != 1; }
 
 // SPLIT: fp32 operands as planes of three bf16 terms (tile_gemm_run_split); everything but the product is
 // the bf16 kernel's.
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false, int VH = 0>
+// STREAM: one tile of positions, so that every byte of W is read once (loaded with the non-temporal hint).
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false, int VH = 0,
+          bool STREAM = false>
 __global__ __launch_bounds__(WV * WB * 64)
 void k_unembed(const UnembedArgs a) {
   // of the two launches over the same fp32 operands one does the work (see launch_split)
@@ -270,7 +272,7 @@ void k_unembed(const UnembedArgs a) {
   // softmax statistics are taken, instead of after a workgroup launch with the matrix pipe idle.
   // Every other instantiation has one tile per workgroup and leaves the loop after it.
   constexpr bool WALK = unembed_walks_tiles<WB, SAMPLE>();
-  using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, WB == 1, 0, SPLIT, VH>;
+  using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, STREAM, 0, SPLIT, VH>;
   const void* const hstaged = SPLIT ? a.hq : (WB != 1 && SB == H_STAGE_BYTES) ? a.hs : nullptr;
   const void* const Wfeed = SPLIT ? a.Wq : WPACK ? a.Wp : a.W;
   const int dfeed = SPLIT ? 3 * a.d : a.d;            // bf16 columns of the planes
@@ -278,7 +280,6 @@ void k_unembed(const UnembedArgs a) {
   int slab, bt;
   tile_of_block(blockIdx.x, nbt, nslab, slab, bt);
   Feed feed;
-  // the decode-sized tiles (one wave column) are launched with one tile of positions: W is a stream
   feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab, bt * TL::TP, smem, nullptr, 0, 1, hstaged);
   for (int w = blockIdx.x;;) {
   const int b0 = bt * TL::TP;
@@ -991,10 +992,11 @@ hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t st)
   return dtype == MTPC_BF16 ? launch_uni_dt<true>(a, st) : launch_uni_dt<false>(a, st);
 }
 
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false, int VH = 0>
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false, int VH = 0,
+          bool STREAM = false>
 static hipError_t launch_cfg(const UnembedArgs& a, hipStream_t st) {
   using TL = Tile<WV, WB, VB, PB, SB, NS, 0, VH>;
-  constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK, SPLIT, VH>;
+  constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK, SPLIT, VH, STREAM>;
   if (hipError_t e = allow_lds<kern>(TL::SMEM); e != hipSuccess) return e;
   const int nbt = (a.B + TL::TP - 1) / TL::TP;
   int grid = nbt * a.n * a.r;
@@ -1009,17 +1011,21 @@ static hipError_t launch_cfg(const UnembedArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Decode-shaped tiles (B <= 64: WV waves over the vocabulary, W streamed once) are bound by HBM:
-// 128-byte stages in a 3-stage ring when the rows allow it (whole cache lines per row and stage,
-// 90 KB in flight per CU; 1.5-2.5 % faster than 64-byte stages in a 4-stage ring).
+// Tiles of 32 or 64 positions (WV waves over the vocabulary): decode-sized batches, whose one tile of positions
+// makes W a stream bound by HBM, and products of few tiles (unembed_positions).  128-byte stages in a 3-stage ring
+// when the rows allow it (whole cache lines per row and stage, 90 KB in flight per CU; 1.5-2.5 % faster than
+// 64-byte stages in a 4-stage ring).
 template <int WV, int PB, bool BF16, bool SAMPLE>
 static hipError_t launch_dec(const UnembedArgs& a, int row_bytes, hipStream_t st) {
   static_assert(PACK_STAGE_BYTES == 128, "the stage-major copy of W is cut for the 128-byte stages");
+  if (a.B > PB * 32)
+    return row_bytes % 128 == 0 ? launch_cfg<WV, 1, 2, PB, 128, 3, BF16, SAMPLE>(a, st)
+                                : launch_cfg<WV, 1, 2, PB, 64, 4, BF16, SAMPLE>(a, st);
   if (row_bytes % 128 == 0) {
-    if (a.Wp != nullptr && a.Wp_stage == 128) return launch_cfg<WV, 1, 2, PB, 128, 3, BF16, SAMPLE, true>(a, st);
-    return launch_cfg<WV, 1, 2, PB, 128, 3, BF16, SAMPLE>(a, st);
+    if (a.Wp != nullptr && a.Wp_stage == 128) return launch_cfg<WV, 1, 2, PB, 128, 3, BF16, SAMPLE, true, false, 0, true>(a, st);
+    return launch_cfg<WV, 1, 2, PB, 128, 3, BF16, SAMPLE, false, false, 0, true>(a, st);
   }
-  return launch_cfg<WV, 1, 2, PB, 64, 4, BF16, SAMPLE>(a, st);
+  return launch_cfg<WV, 1, 2, PB, 64, 4, BF16, SAMPLE, false, false, 0, true>(a, st);
 }
 
 // 256-position tiles of the fewest rows that hold the vocabulary (a K stage costs what its rows cost: products,
@@ -1036,15 +1042,15 @@ static hipError_t launch_train(const UnembedArgs& a, hipStream_t st) {
 template <bool BF16, bool SAMPLE>
 static hipError_t launch_dt(const UnembedArgs& a, hipStream_t st) {
   // Vocabulary tile: 5 blocks of 32 per wave pair covers v <= 320; smaller v take
-  // narrower tiles.  Positions: 256-wide tiles for training-sized
-  // batches, 64- or 32-wide tiles (W streamed once) for decode-sized ones.
+  // narrower tiles.  Positions: see unembed_positions.
   const int row_bytes = a.d * (BF16 ? 2 : 4);
-  if (a.B > 64) {
+  const int positions = unembed_positions(a.B, a.n, a.r);
+  if (positions == 256) {
     if (a.Wp != nullptr && a.Wp_stage == 64)        // the copy of W in the 64-byte stages of these tiles
       return launch_train<BF16, SAMPLE, true>(a, st);
     return launch_train<BF16, SAMPLE, false>(a, st);
   }
-  if (a.B > 32) {
+  if (positions == 64) {
     if (a.v > 256) return launch_dec<5, 2, BF16, SAMPLE>(a, row_bytes, st);
     if (a.v > 128) return launch_dec<4, 2, BF16, SAMPLE>(a, row_bytes, st);
     return launch_dec<2, 2, BF16, SAMPLE>(a, row_bytes, st);
