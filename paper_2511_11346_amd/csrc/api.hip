@@ -74,13 +74,6 @@ bool table_in_workspace(const mtpc_head* hd, int S) {      // for a sampling cal
   return table_fits(hd);                                   // else a second pass
 }
 
-// The 256-position tiles of the fused kernel read h from a stage-major copy when one can be made: whole
-// 64-byte stages per row, and all of it behind one 32-bit buffer resource.
-bool stage_major_h_pays(const mtpc_head* hd) {
-  const unsigned long long row = (unsigned long long)hd->d * (hd->dtype == MTPC_BF16 ? 2 : 4);
-  return unembed_positions(hd->B, hd->n, hd->r) == 256 && row % H_STAGE_BYTES == 0 && row * (unsigned long long)hd->B < (1ull << 32);
-}
-
 // fp32 operands of the 256-position tiles as planes of three bf16 terms (launch_unembed), where a pass over all
 // of W is then faster: per round of tiles over the CUs SPLIT_TILE_US against F32_TILE_US (a 320 x 256 tile, 1024
 // columns; B = 2048, n r = 256, d = 3072: 3.56 against 7.29 ms), against that stand the split of W (4 bytes read
@@ -95,6 +88,16 @@ bool split_pays(const mtpc_head* hd) {
   const double tile = rounds / 320.0 * hd->d / 1024.0;
   const double split = (double)hd->n * hd->r * hd->v * hd->d * 10.0 / 4.9e6 + 15.0;
   return tile * srows * SPLIT_TILE_US + split < tile * frows * F32_TILE_US;
+}
+
+// The 256-position tiles of the fused kernel read h from a stage-major copy when one can be made: whole
+// 64-byte stages per row, and all of it behind one 32-bit buffer resource.  The copy costs the same however many
+// slabs read it: in bf16 it takes more than 64 of them (d = 4096, with and without it: FF n = 8, B = 8192 152 / 134 us,
+// n = 16 268 / 252, 64 slabs 495 / 495, 128 slabs 500 / 533).  fp32 operands that are split into terms have their own.
+bool stage_major_h_pays(const mtpc_head* hd) {
+  const unsigned long long row = (unsigned long long)hd->d * (hd->dtype == MTPC_BF16 ? 2 : 4);
+  if (hd->dtype == MTPC_BF16 && (long long)hd->n * hd->r <= 64) return false;
+  return unembed_positions(hd->B, hd->n, hd->r) == 256 && row % H_STAGE_BYTES == 0 && row * (unsigned long long)hd->B < (1ull << 32);
 }
 
 // most windows per position whose rows B*T*n still index with an int
@@ -175,7 +178,8 @@ Plan make_plan(int family, int op, const mtpc_head* hd, const mtpc_sumlayers* ly
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += up(bytes); return o; };
   p.logw = take(B * r * 4);
-  p.has_hs = (op == MTPC_OP_LOGLIK || op == MTPC_OP_MARGINALS || op == MTPC_OP_WINDOWS) && stage_major_h_pays(hd);
+  const bool terms = split && split_pays(hd);
+  p.has_hs = (op == MTPC_OP_LOGLIK || op == MTPC_OP_MARGINALS || op == MTPC_OP_WINDOWS) && !terms && stage_major_h_pays(hd);
   p.hs = p.has_hs ? take(B * (size_t)hd->d * (hd->dtype == MTPC_BF16 ? 2 : 4)) : 0;
   const bool sample = op == MTPC_OP_SAMPLE;
   const bool uni = op == MTPC_OP_MARGINALS && mode == MTPC_MARG_UNIVARIATE;
@@ -207,7 +211,7 @@ Plan make_plan(int family, int op, const mtpc_head* hd, const mtpc_sumlayers* ly
   // the calls that run the fused kernel over all of W (below: not those that draw through buckets or rows)
   const bool full_pass = op == MTPC_OP_LOGLIK || op == MTPC_OP_WINDOWS || (uni ? r == 1 || table_fits(hd) : op == MTPC_OP_MARGINALS) ||
                          (sample && (want_prefix || caller_table || !buckets_pay(hd, S, want_prefix)));
-  if (split && full_pass && split_pays(hd)) {
+  if (terms && full_pass) {
     p.has_split = true;
     p.wild = take(4);
     p.hq = take(B * (size_t)hd->d * 6);
@@ -220,7 +224,7 @@ Plan make_plan(int family, int op, const mtpc_head* hd, const mtpc_sumlayers* ly
   }
   // a sampling call whose fused kernel runs on the 256-position tiles: the stage-major copy of h, last, so
   // that a caller with a workspace of the older size still runs (see prepare)
-  if (sample && stage_major_h_pays(hd) && (want_prefix || caller_table || !buckets_pay(hd, S, want_prefix))) {
+  if (sample && !terms && stage_major_h_pays(hd) && (want_prefix || caller_table || !buckets_pay(hd, S, want_prefix))) {
     p.has_hs = true;
     p.hs = take(B * (size_t)hd->d * (hd->dtype == MTPC_BF16 ? 2 : 4));
   }
@@ -691,7 +695,7 @@ BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly,
     q.hq = take(B * (size_t)hd->d * 6);
     q.Wq = take((size_t)q.M * hd->d * 6);
   }
-  q.has_hs = stage_major_h_pays(hd);
+  q.has_hs = !q.split_fwd && stage_major_h_pays(hd);
   q.hs = q.has_hs ? take(B * (size_t)hd->d * esz) : 0;
   q.has_hTs = (unsigned long long)hd->d * q.ldb * osz < (1ull << 32);
   q.hTs = q.has_hTs ? take((size_t)hd->d * q.ldb * osz) : 0;
