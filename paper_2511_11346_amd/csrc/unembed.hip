@@ -602,10 +602,10 @@ hipError_t launch_draw_gather(const DrawGatherArgs& a, int dtype, hipStream_t st
 // of d through an LDS ring, 32 positions to a workgroup: 22 us for any B up to 4096 at d = 4096 bf16, r = 32, 57 us
 // in fp32 - 0.35 us per 128 bytes of a row, a barrier and a chain of LDS read and product each.)
 constexpr int sumunit_waves(int RB, int PB) { return RB * PB <= 2 ? 16 : 8; }
-template <int RB, int PB, bool BF16>
-__global__ __launch_bounds__(sumunit_waves(RB, PB) * 64)
+template <int RB, int PB, bool BF16, int NW>
+__global__ __launch_bounds__(NW * 64)
 void k_sumunit_mfma(const void* h, long long ld_h, const void* Wsum, int B, int d, int r, float* logw) {
-  constexpr int ESZ = BF16 ? 2 : 4, NW = sumunit_waves(RB, PB), U = RB + PB <= 3 ? 8 : RB + PB <= 5 ? 6 : 3;
+  constexpr int ESZ = BF16 ? 2 : 4, U = RB + PB <= 3 ? 8 : RB + PB <= 5 ? 6 : 3;
   constexpr int PS = PB * 16 + 1;                    // (odd stride: the lanes of a reduction read different banks)
   __shared__ float part[NW][RB * 16 * PS];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -688,12 +688,16 @@ void k_sumunit_mfma(const void* h, long long ld_h, const void* Wsum, int B, int 
   }
 }
 
+// (rows of at most 32 steps: four waves have all of them in flight, more would only add partial sums)
 template <int RB, int PB, bool BF16>
 static hipError_t launch_sumunit_mfma_cfg(const void* h, long long ld_h, const void* Wsum, int B, int d,
                                           int r, float* logw, hipStream_t st) {
-  hipLaunchKernelGGL((k_sumunit_mfma<RB, PB, BF16>), dim3((B + PB * 16 - 1) / (PB * 16)),
-                     dim3(sumunit_waves(RB, PB) * 64), 0, st, h, ld_h,
-                     Wsum, B, d, r, logw);
+  constexpr int NW = sumunit_waves(RB, PB);
+  const dim3 grid((B + PB * 16 - 1) / (PB * 16));
+  if (d * (BF16 ? 2 : 4) / 64 <= 32)
+    hipLaunchKernelGGL((k_sumunit_mfma<RB, PB, BF16, 4>), grid, dim3(256), 0, st, h, ld_h, Wsum, B, d, r, logw);
+  else
+    hipLaunchKernelGGL((k_sumunit_mfma<RB, PB, BF16, NW>), grid, dim3(NW * 64), 0, st, h, ld_h, Wsum, B, d, r, logw);
   return hipGetLastError();
 }
 
