@@ -82,14 +82,17 @@ hipError_t launch_ctx_layers(const CtxLayerArgs& a, int dtype, hipStream_t st);
 
 hipError_t launch_unembed(const UnembedArgs& a, int dtype, hipStream_t st);
 // Positions per tile of the fused kernel.  A decode-sized batch is one tile (W is then read once).  Larger ones
-// take 256, unless the tiles of 64 or 32 positions all run at once on the 256 CUs: a K stage of those is shorter,
-// and that many CUs would stand idle (FF, n = 8, d = 4096: B = 512 92 us with 256 positions, 41 with 32;
-// CP n = 4, r = 16, d = 2048, B = 250: 66 against 42 us; fp32 CP n = 4, r = 8, d = 2048, B = 200: 660 against 148 us).
+// take 256, unless fewer are enough or the narrower tiles all run at once on the 256 CUs: a K stage of those is
+// shorter, and that many CUs would stand idle.  Measured with 256 positions and with the width chosen here: FF, n = 8,
+// d = 4096, B = 512 92 / 41 us, B = 4096 101 / 83 us; CP n = 4, r = 16, d = 2048, B = 250 66 / 42 us; fp32 CP n = 4, r = 8,
+// d = 2048, B = 200 660 / 148 us; CP n = 16, r = 32, d = 4096, B = 100 309 / 264 us (fp32,
+// d = 2048: 1249 / 678 us).
 inline int unembed_positions(int B, int n, int r) {
   constexpr long long CUS = 256;
   const long long slabs = (long long)n * r;
   if (B <= 32 || slabs * ((B + 31LL) / 32) <= CUS) return 32;
   if (B <= 64 || slabs * ((B + 63LL) / 64) <= CUS) return 64;
+  if (B <= 128 || slabs * ((B + 127LL) / 128) <= CUS) return 128;
   return 256;
 }
 // dst[slab][stage][row][stage_bytes] = the stage_bytes of row `row` of slab `slab` of W that K stage `stage` covers

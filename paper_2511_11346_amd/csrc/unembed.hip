@@ -1032,15 +1032,17 @@ static hipError_t launch_dec(const UnembedArgs& a, int row_bytes, hipStream_t st
   return launch_cfg<WV, 1, 2, PB, 64, 4, BF16, SAMPLE, false, false, 0, true>(a, st);
 }
 
-// 256-position tiles of the fewest rows that hold the vocabulary (a K stage costs what its rows cost: products,
-// loads and fragment reads alike).  The 272-row one exists for 16x16 blocks only: fp32 instructions fill 32.
-template <bool BF16, bool SAMPLE, bool WPACK, bool SPLIT = false>
+// Tiles of 256 (PB = 2) or 128 positions of the fewest rows that hold the vocabulary (a K stage costs what its rows
+// cost: products, loads and fragment reads alike).  The 272-row one exists for 16x16 blocks only: fp32 instructions
+// fill 32.  What a narrower tile leaves of LDS goes to a fifth ring buffer.
+template <bool BF16, bool SAMPLE, bool WPACK, bool SPLIT = false, int PB = 2>
 static hipError_t launch_train(const UnembedArgs& a, hipStream_t st) {
-  if (a.v > 272) return launch_cfg<2, 4, 5, 2, 64, 4, BF16, SAMPLE, WPACK, SPLIT>(a, st);
-  if (a.v > 256) return launch_cfg<2, 4, 5, 2, 64, 4, BF16, SAMPLE, WPACK, SPLIT, BF16 ? 3 : 0>(a, st);
-  if (a.v > 192) return launch_cfg<2, 4, 4, 2, 64, 4, BF16, SAMPLE, WPACK, SPLIT>(a, st);
-  if (a.v > 128) return launch_cfg<2, 4, 3, 2, 64, 4, BF16, SAMPLE, WPACK, SPLIT>(a, st);
-  return launch_cfg<2, 4, 2, 2, 64, 4, BF16, SAMPLE, WPACK, SPLIT>(a, st);
+  constexpr int NS = PB == 1 ? 5 : 4;
+  if (a.v > 272) return launch_cfg<2, 4, 5, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT>(a, st);
+  if (a.v > 256) return launch_cfg<2, 4, 5, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT, BF16 ? 3 : 0>(a, st);
+  if (a.v > 192) return launch_cfg<2, 4, 4, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT>(a, st);
+  if (a.v > 128) return launch_cfg<2, 4, 3, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT>(a, st);
+  return launch_cfg<2, 4, 2, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT>(a, st);
 }
 
 template <bool BF16, bool SAMPLE>
@@ -1049,10 +1051,10 @@ static hipError_t launch_dt(const UnembedArgs& a, hipStream_t st) {
   // narrower tiles.  Positions: see unembed_positions.
   const int row_bytes = a.d * (BF16 ? 2 : 4);
   const int positions = unembed_positions(a.B, a.n, a.r);
-  if (positions == 256) {
-    if (a.Wp != nullptr && a.Wp_stage == 64)        // the copy of W in the 64-byte stages of these tiles
-      return launch_train<BF16, SAMPLE, true>(a, st);
-    return launch_train<BF16, SAMPLE, false>(a, st);
+  if (positions >= 128) {
+    const bool packed = a.Wp != nullptr && a.Wp_stage == 64;        // the copy of W in the 64-byte stages of these tiles
+    if (positions == 256) return packed ? launch_train<BF16, SAMPLE, true>(a, st) : launch_train<BF16, SAMPLE, false>(a, st);
+    return packed ? launch_train<BF16, SAMPLE, true, false, 1>(a, st) : launch_train<BF16, SAMPLE, false, false, 1>(a, st);
   }
   if (positions == 64) {
     if (a.v > 256) return launch_dec<5, 2, BF16, SAMPLE>(a, row_bytes, st);

@@ -107,9 +107,11 @@ def test_bf16_vocabulary_tiles(v, B, S, r):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("B,d,n,r,v", [(33, 64, 2, 64, 33), (64, 96, 2, 65, 320), (65, 64, 2, 3, 130), (97, 96, 3, 1, 320),
-                                       (250, 64, 4, 16, 256), (257, 128, 2, 25, 40), (257, 64, 2, 26, 40)])
+                                       (250, 64, 4, 16, 256), (257, 128, 2, 25, 40), (257, 64, 2, 26, 40),
+                                       (65, 96, 3, 65, 265), (128, 64, 3, 43, 130), (129, 64, 3, 43, 320), (300, 64, 2, 40, 272)])
 def test_few_tiles(B, d, n, r, v, dtype):
-    """Batches that leave CUs idle with 256 positions to a tile: several tiles of 32 or 64 (and the first sizes beyond)."""
+    """Batches that need fewer than 256 positions to a tile, or leave CUs idle with them: several tiles of 32, 64 or
+    128 (and the first sizes beyond)."""
     inp = mi.make_inputs("ff" if r == 1 else "cp", B=B, d=d, n=n, r=r, v=v, dtype=dtype, seed=B + v, h_scale=1.0)
     logphi, logw, _ = oc._params(inp.family, inp.h, inp.W, inp.Wsum, None)
     head = make_head(inp)
