@@ -79,8 +79,10 @@ typedef struct {
                           /* bytes for B <= 64, 64 bytes for larger batches (same results, bit  */
                           /* for bit; 3-5 % less time), and so do the token draws of a larger   */
                           /* batch (each from its one slab; 64-byte stages, 6-8 % less time).   */
-                          /* A copy with the other stage size is ignored.  W must be valid as   */
-                          /* well: every other path reads W.                                    */
+                          /* A copy with the other stage size is ignored, and so is any by a    */
+                          /* product of few tiles (n r ceil(B / 64) <= 256, B > 64) or one in    */
+                          /* fp32 that is multiplied as bf16 terms.  W must be valid as well:    */
+                          /* every other path reads W.                                          */
   int32_t W_stage_bytes;  /* stage size of that copy: 128 (also meant by 0) or 64               */
 } mtpc_head;
 
@@ -113,6 +115,9 @@ const char* mtpc_status_string(mtpc_status s);
  * of drafts per position (sample) or of windows per position (MTPC_OP_TABLE,
  * MTPC_OP_WINDOWS: T + T2) and is ignored otherwise; `mode` is the
  * mtpc_marg_mode for MTPC_OP_MARGINALS and the mtpc_bwd_mode for MTPC_OP_BACKWARD.
+ * fp32 calls whose pass over W is multiplied as three bf16 terms per value (large
+ * batches, where that is faster) need 6 bytes more per element of W and h; sampling
+ * and the training step also run without that room, on the fp32 instructions.
  * Returns 0 for invalid arguments. */
 size_t mtpc_workspace_bytes(int32_t family, int32_t op, const mtpc_head* head,
                             const mtpc_sumlayers* layers, int32_t S, int32_t mode);

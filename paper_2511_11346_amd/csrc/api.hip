@@ -80,7 +80,7 @@ bool table_in_workspace(const mtpc_head* hd, int S) {      // for a sampling cal
 // and 6 written per element: 0.43 ms there, 4.9 TB/s) and four short launches.
 constexpr double SPLIT_TILE_US = 148, F32_TILE_US = 304;
 bool split_pays(const mtpc_head* hd) {
-  if (hd->dtype != MTPC_F32 || unembed_positions(hd->B, hd->n, hd->r) != 256) return false;
+  if (hd->dtype != MTPC_F32 || unembed_positions(hd->B, hd->n, hd->r, hd->dtype) != 256) return false;
   if ((unsigned long long)hd->B * hd->d * 6 >= (1ull << 32)) return false;      // one 32-bit buffer resource
   const double frows = hd->v > 256 ? 320 : hd->v > 192 ? 256 : hd->v > 128 ? 192 : 128;
   const double srows = (hd->v > 256 && hd->v <= 272) ? 272 : frows;            // (launch_train)
@@ -97,7 +97,7 @@ bool split_pays(const mtpc_head* hd) {
 bool stage_major_h_pays(const mtpc_head* hd) {
   const unsigned long long row = (unsigned long long)hd->d * (hd->dtype == MTPC_BF16 ? 2 : 4);
   if (hd->dtype == MTPC_BF16 && (long long)hd->n * hd->r <= 64) return false;
-  return unembed_positions(hd->B, hd->n, hd->r) == 256 && row % H_STAGE_BYTES == 0 && row * (unsigned long long)hd->B < (1ull << 32);
+  return unembed_positions(hd->B, hd->n, hd->r, hd->dtype) == 256 && row % H_STAGE_BYTES == 0 && row * (unsigned long long)hd->B < (1ull << 32);
 }
 
 // most windows per position whose rows B*T*n still index with an int

@@ -87,10 +87,13 @@ hipError_t launch_unembed(const UnembedArgs& a, int dtype, hipStream_t st);
 // d = 4096, B = 512 92 / 41 us, B = 4096 101 / 83 us; CP n = 4, r = 16, d = 2048, B = 250 66 / 42 us; fp32 CP n = 4, r = 8,
 // d = 2048, B = 200 660 / 148 us; CP n = 16, r = 32, d = 4096, B = 100 309 / 264 us (fp32,
 // d = 2048: 1249 / 678 us).
-inline int unembed_positions(int B, int n, int r) {
+// (bf16 batches of 33 to 64 positions keep their one tile from 33 slabs on: they are bound by reading W, which two
+// tiles read twice and not from its 128-byte stage-major copy - 128 slabs 107 / 114 us.)
+inline int unembed_positions(int B, int n, int r, int dtype) {
   constexpr long long CUS = 256;
   const long long slabs = (long long)n * r;
-  if (B <= 32 || slabs * ((B + 31LL) / 32) <= CUS) return 32;
+  if (B <= 32) return 32;
+  if (slabs * ((B + 31LL) / 32) <= CUS && (B > 64 || dtype == MTPC_F32 || slabs <= 32)) return 32;
   if (B <= 64 || slabs * ((B + 63LL) / 64) <= CUS) return 64;
   if (B <= 128 || slabs * ((B + 127LL) / 128) <= CUS) return 128;
   return 256;

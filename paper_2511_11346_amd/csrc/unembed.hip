@@ -1050,7 +1050,7 @@ static hipError_t launch_dt(const UnembedArgs& a, hipStream_t st) {
   // Vocabulary tile: 5 blocks of 32 per wave pair covers v <= 320; smaller v take
   // narrower tiles.  Positions: see unembed_positions.
   const int row_bytes = a.d * (BF16 ? 2 : 4);
-  const int positions = unembed_positions(a.B, a.n, a.r);
+  const int positions = unembed_positions(a.B, a.n, a.r, BF16 ? MTPC_BF16 : MTPC_F32);
   if (positions >= 128) {
     const bool packed = a.Wp != nullptr && a.Wp_stage == 64;        // the copy of W in the 64-byte stages of these tiles
     if (positions == 256) return packed ? launch_train<BF16, SAMPLE, true>(a, st) : launch_train<BF16, SAMPLE, false>(a, st);
