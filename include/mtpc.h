@@ -82,7 +82,7 @@ typedef struct {
                           /* A copy with the other stage size is ignored, and so is any by a    */
                           /* batch of 33 to 64 positions of few tiles (n r <= 128 in fp32,      */
                           /* <= 32 in bf16), and by the scoring calls and the training step     */
-                          /* where fp32 is multiplied as bf16 terms (mtpc_workspace_bytes;      */
+                          /* where fp32 is multiplied as fp16 terms (mtpc_workspace_bytes;      */
                           /* draws read it all the same).  W must be valid as well: every       */
                           /* other path reads W.                                                */
   int32_t W_stage_bytes;  /* stage size of that copy: 128 (also meant by 0) or 64               */
@@ -117,10 +117,11 @@ const char* mtpc_status_string(mtpc_status s);
  * of drafts per position (sample) or of windows per position (MTPC_OP_TABLE,
  * MTPC_OP_WINDOWS: T + T2) and is ignored otherwise; `mode` is the
  * mtpc_marg_mode for MTPC_OP_MARGINALS and the mtpc_bwd_mode for MTPC_OP_BACKWARD.
- * fp32 calls whose pass over W is multiplied as three bf16 terms per value (large
+ * fp32 calls whose pass over W is multiplied as two fp16 terms per value (large
  * batches, where that is faster; sampling never is) ask for 6 bytes more per element of W
  * and h; they also run without that room, on the fp32 instructions (results differ within
- * fp32 rounding of the sums).
+ * fp32 rounding of the sums), and take those by themselves for operands the terms would not do
+ * justice: infinite or NaN values, rows most of which is below 2^-16 of their largest value.
  * Returns 0 for invalid arguments. */
 size_t mtpc_workspace_bytes(int32_t family, int32_t op, const mtpc_head* head,
                             const mtpc_sumlayers* layers, int32_t S, int32_t mode);
@@ -142,7 +143,7 @@ mtpc_status mtpc_btree_loglik(const mtpc_head* head, const mtpc_sumlayers* A,
  *   targets is ignored and may be NULL.  The size mtpc_workspace_bytes returns has room for
  *   the input units of all positions (B n r v floats, when that is at most 8 GiB and r > 1):
  *   one pass writes them, a second kernel mixes them.  A workspace smaller by that many bytes
- *   (or, in fp32, by that and the room of the bf16 terms) is accepted too; the r units of a token
+ *   (or, in fp32, by that and the room of the fp16 terms) is accepted too; the r units of a token
  *   are then mixed in registers (slower, above all for a few positions). */
 mtpc_status mtpc_ff_marginals(const mtpc_head* head, const int32_t* targets, int32_t mode, float* out);
 mtpc_status mtpc_cp_marginals(const mtpc_head* head, const int32_t* targets, int32_t mode, float* out);
@@ -315,9 +316,10 @@ mtpc_status mtpc_btree_verify(const mtpc_head* head, const mtpc_sumlayers* A, co
  * (n*r*v*B fp32) and the logit gradient is one elementwise pass; with the
  * smaller MTPC_BWD_RECOMPUTE size nothing of size n*r*v*B is kept in fp32 and the
  * logits are recomputed (one more pass of the unembedding product).
- * fp32 contractions of more than 64 positions (layers not computed from h) multiply each value as three
- * bf16 terms: exact but for values below 2^-110, whose last bits are lost; results that are
- * not finite are those of fp32 sums.
+ * fp32 contractions of more than 64 positions (layers not computed from h) multiply each value as two
+ * fp16 terms: 23 bits of it, or 2^-40 of the largest value it is summed beside (the logit gradient of
+ * a token over all positions, that of a position over all tokens, a feature of h, a row of W); results
+ * that are not finite are those of fp32 sums.
  * targets: ids in [0, v), or -1 (that variable is summed out and receives no
  * gradient).
  * dlayers has the shape of the stored layer logits ([n-1][r][r], or [1][r][r] for a

@@ -74,11 +74,11 @@ bool table_in_workspace(const mtpc_head* hd, int S) {      // for a sampling cal
   return table_fits(hd);                                   // else a second pass
 }
 
-// fp32 operands of the 256-position tiles as planes of three bf16 terms (launch_unembed), where a pass over all
+// fp32 operands of the 256-position tiles as planes of two fp16 terms (launch_unembed), where a pass over all
 // of W is then faster: per round of tiles over the CUs SPLIT_TILE_US against F32_TILE_US (a 320 x 256 tile, 1024
-// columns; B = 2048, n r = 256, d = 3072: 3.56 against 7.29 ms), against that stand the split of W (4 bytes read
-// and 6 written per element: 0.43 ms there, 4.9 TB/s) and four short launches.
-constexpr double SPLIT_TILE_US = 148, F32_TILE_US = 304;
+// columns; B = 2048, n r = 256, d = 3072: 1.83 against 7.29 ms, 3.19 ms through three bf16 terms and six products), against
+// that stand the split of W (4 bytes read and written per element: 0.31 ms there, 5.4 TB/s) and four short launches.
+constexpr double SPLIT_TILE_US = 90, F32_TILE_US = 304;
 bool split_pays(const mtpc_head* hd) {
   if (hd->dtype != MTPC_F32 || unembed_positions(hd->B, hd->n, hd->r, hd->dtype) != 256) return false;
   if ((unsigned long long)hd->B * hd->d * 6 >= (1ull << 32)) return false;      // one 32-bit buffer resource
@@ -86,7 +86,7 @@ bool split_pays(const mtpc_head* hd) {
   const double srows = (hd->v > 256 && hd->v <= 272) ? 272 : frows;            // (launch_train)
   const double rounds = std::ceil((double)((hd->B + 255LL) / 256) * hd->n * hd->r / 256.0);
   const double tile = rounds / 320.0 * hd->d / 1024.0;
-  const double split = (double)hd->n * hd->r * hd->v * hd->d * 10.0 / 4.9e6 + 15.0;
+  const double split = (double)hd->n * hd->r * hd->v * hd->d * 8.0 / 5.4e6 + 20.0;
   return tile * srows * SPLIT_TILE_US + split < tile * frows * F32_TILE_US;
 }
 
@@ -110,7 +110,7 @@ struct Plan {           // byte offsets into the workspace
   size_t logw, lay_nat, lay_circ, e, zleaf, lat, logm, table, total;
   size_t hs;            // stage-major copy of h for the 256-position tiles of the fused kernel
   bool has_hs;
-  size_t Wq, hq, wild;  // fp32 as three bf16 terms: planes of W and h, flag (launch_unembed)
+  size_t Wq, hq, wild;  // fp32 as two fp16 terms: planes of W and h, flag (launch_unembed)
   bool has_split;
   size_t lean_total;    // univariate marginals: the plan without the table (and the planes its one pass reads)
   size_t bk_count, bk_slot, bk_rowoff, bk_tileoff, bk_tilebucket, bk_list;
@@ -264,7 +264,7 @@ mtpc_status prepare(int family, int op, const mtpc_head* hd, const mtpc_sumlayer
   if ((uintptr_t)hd->workspace & 15) return MTPC_ERR_WORKSPACE;
   if (hd->workspace_bytes < plan.total) {
     // Univariate marginals run without the table in a workspace smaller by the table or more - also where the planes of
-    // bf16 terms would leave room for one: that is how a caller asks for it - and need no planes then.
+    // fp16 terms would leave room for one: that is how a caller asks for it - and need no planes then.
     const bool uni = op == MTPC_OP_MARGINALS && mode == MTPC_MARG_UNIVARIATE;
     const bool lean = uni && plan.has_table && plan.total - hd->workspace_bytes >= (size_t)hd->B * hd->n * hd->r * hd->v * 4;
     // every other call runs without the planes, on the fp32 instructions
@@ -291,7 +291,7 @@ UnembedArgs unembed_args(const mtpc_head* hd) {
   return u;
 }
 
-// the scratch of the bf16 terms (when the plan has room for it) into the arguments
+// the scratch of the fp16 terms (when the plan has room for it) into the arguments
 void split_scratch(const mtpc_head* hd, const Plan& p, UnembedArgs& u) {
   if (!p.has_split) return;
   char* ws = (char*)hd->workspace;
@@ -652,7 +652,7 @@ struct BwdPlan {
   int Lst;                  // stored layers (1: one matrix shared by all steps)
   int steps;                // reverse-pass steps with a layer (HMM: n-1; tree: program length)
   long long M, Mx, Mlay, Mtot, ldM, ldb;
-  // fp32 as three bf16 terms: in the forward pass (split_pays) and in the two contractions
+  // fp32 as two fp16 terms: in the forward pass (split_pays) and in the two contractions
   bool split_fwd, split;
   size_t Wq, hq, wild, dslT, big;
 };
@@ -800,7 +800,9 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   UnembedArgs u = unembed_args(hd);
   u.targets = targets; u.T = 1; u.e = (float*)(ws + q.e);
   if (q.keep_phi) { u.phiT = (float*)(ws + q.phi); u.ld_phi = q.ldb; }
-  if (q.split_fwd) { u.Wq = ws + q.Wq; u.hq = ws + q.hq; u.wild = (int*)(ws + q.wild); }
+  // (exponents of the rows of W and Wsum, for the forward pass and the contraction over them: behind the planes of WT)
+  int* const wexp = q.split ? plane_exps(ws + q.WT, hd->d * q.ldM) : nullptr;
+  if (q.split_fwd) { u.Wq = ws + q.Wq; u.hq = ws + q.hq; u.wild = (int*)(ws + q.wild); u.Wexp = wexp; }
   HIP_TRY(stage_major_h(hd, q.has_hs, q.hs, u, st));
   HIP_TRY(launch_unembed(u, hd->dtype, st));
 
@@ -852,6 +854,11 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
     g.dLT = ws + q.dLT; g.dL = ws + q.dL;
     g.staged = grads_staged;
     g.planes = q.split; g.big = big; g.dslT = ws + q.dslT;
+    if (q.split) {
+      g.Wexp = wexp; g.d = hd->d;
+      g.W = q.split_fwd ? nullptr : hd->W;
+      g.Wsum = family == MTPC_FF ? nullptr : hd->Wsum;
+    }
     HIP_TRY(launch_grad_from_phi(g, hd->dtype, st));
   } else {
     GradLogitsArgs g{};
@@ -878,9 +885,13 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   t.stage_rows = wt_staged ? hd->d : 0;
   t.planes = q.split; t.big = big;
   t.src = hd->W; t.ld_src = hd->d; t.R = (int)q.M; t.C = hd->d;
-  t.dst = ws + q.WT; t.ld_dst = q.ldM; t.col0 = 0; t.Rpad = (int)(family == MTPC_FF ? q.ldM : q.M);
+  t.dst = ws + q.WT; t.ld_dst = q.ldM; t.col0 = 0; t.Rpad = (int)(family == MTPC_FF || q.split ? q.ldM : q.M);
+  if (q.split) {                              // (W and Wsum at once)
+    t.exps = wexp;
+    t.src2 = hd->Wsum; t.R2 = (int)(q.Mx - q.M);
+  }
   HIP_TRY(launch_transpose(t, hd->dtype, st));
-  if (family != MTPC_FF) {
+  if (family != MTPC_FF && !q.split) {
     t.src = hd->Wsum; t.ld_src = hd->d; t.R = hd->r; t.C = hd->d;
     t.col0 = q.M; t.Rpad = (int)((ctx ? q.Mlay : q.ldM) - q.M);
     HIP_TRY(launch_transpose(t, hd->dtype, st));
@@ -896,6 +907,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   HIP_TRY(launch_transpose(t, hd->dtype, st));
   if (q.split) {
     t.dst = ws + q.hTs; t.stage_rows = hd->d; t.planes = 1;
+    t.exps = nullptr; t.plain = ws + q.hT; t.ld_plain = q.ldb;
     HIP_TRY(launch_transpose(t, hd->dtype, st));
   } else if (q.has_hTs)
     HIP_TRY(launch_pack_rows(ws + q.hT, ws + q.hTs, 1, hd->d, (int)(q.ldb * esz), q.ldb * (long long)esz, H_STAGE_BYTES, st));
@@ -907,6 +919,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   m.Bs = wt_staged ? ws + q.WT : nullptr;
   m.As = grads_staged ? ws + q.dL : nullptr; m.As_rows = hd->B;
   m.planes = q.split;
+  m.Ae = q.split ? plane_exps(ws + q.dL, hd->B * q.ldM) : nullptr;
   m.C = dh; m.ldc = hd->d; m.split = hd->B; m.n2 = 0; m.C2 = nullptr; m.split3 = 0x7fffffff; m.C3 = nullptr;
   m.ksplit = q.ksplit; m.kchunk = q.kchunk; m.partial = q.ksplit > 1 ? (float*)(ws + q.partial) : nullptr;
   HIP_TRY(launch_gemm_tn(m, hd->dtype, st));
@@ -921,6 +934,10 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   m.Bm = ws + q.hT; m.ldb = q.ldb; m.N = hd->d; m.K = (int)q.ldb;
   m.Bs = q.has_hTs ? ws + q.hTs : nullptr;
   m.As = grads_staged ? ws + q.dLT : nullptr; m.As_rows = (int)q.M;
+  if (q.split) {
+    m.Ae = plane_exps(ws + q.dLT, q.M * q.ldb);
+    m.Be = plane_exps(ws + q.hTs, hd->d * q.ldb);
+  }
   m.C = dW; m.ldc = hd->d;
   m.split = (int)q.M; m.n2 = (family == MTPC_FF || own_dwsum) ? 0 : hd->r; m.C2 = dWsum;
   m.split3 = ctx ? (int)q.Mlay : 0x7fffffff; m.C3 = dR;

@@ -87,74 +87,145 @@ __global__ __launch_bounds__(256) void k_transpose_vec(const TransposeArgs a) {
   }
 }
 
-// fp32 matrices into planes of three bf16 terms (split3) of the transpose, stage-major with a.stage_rows rows:
-// [3 columns/32][stage_rows][64 bytes].  64 x 64 tiles through LDS; a thread splits eight neighbours along the
-// contraction, 16 bytes of each plane (element by element where a column block starts or ends inside them).
+// Planes of two fp16 terms (split2) of [src; src2]^T, whose rows give up the scales that a.exps holds, stage-major with
+// a.stage_rows rows: [2 columns/32][stage_rows][64 bytes].  64 x 64 tiles through LDS; a thread splits eight neighbours along
+// the contraction, 16 bytes of each plane.
 __global__ __launch_bounds__(256) void k_transpose_planes(const TransposeArgs a) {
   __shared__ float tile[64][64 + 1];
   const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
-  const float* src = (const float*)a.src;
   unsigned short* dst = (unsigned short*)a.dst;
+  bool bad = false;
   {
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    const int c = c0 + tx;
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-      const int r = r0 + ty + 4 * k, c = c0 + tx;
-      tile[ty + 4 * k][tx] = (r < a.R && c < a.C) ? src[(long long)r * a.ld_src + c] : 0.f;
+      const int r = r0 + ty + 4 * k;
+      float x = 0.f;
+      if (c < a.C && r < a.R + a.R2) {
+        const float* row = r < a.R ? (const float*)a.src + (long long)r * a.ld_src : (const float*)a.src2 + (long long)(r - a.R) * a.ld_src;
+        x = __builtin_amdgcn_ldexpf(row[c], -a.exps[r]);
+        bad |= !(fabsf(x) <= 65504.f);
+      }
+      tile[ty + 4 * k][tx] = x;
     }
   }
+  if (bad) *a.big = 1;
   __syncthreads();
   // four threads write the 64 bytes of a row of one plane
   const int ch = threadIdx.x & 3, cc = threadIdx.x >> 2;
   const int c = c0 + cc;
   if (c >= a.C) return;
-  bool large = false;
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     const int rl = half * 32 + ch * 8, r = r0 + rl;
     if (r >= a.Rpad) continue;
-    struct alignas(16) Oct { unsigned short v[8]; } o[3];
+    struct alignas(16) Oct { unsigned short v[8]; } o[2];
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-      unsigned short q[3];
-      split3(tile[rl + t][cc], q);
-      large |= fabsf(tile[rl + t][cc]) > SPLIT_LARGE;
-#pragma unroll
-      for (int p = 0; p < 3; ++p) o[p].v[t] = q[p];
+      unsigned short q[2];
+      split2(tile[rl + t][cc], q);
+      o[0].v[t] = q[0]; o[1].v[t] = q[1];
     }
-    const long long k = a.col0 + r;
 #pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      if ((k & 7) == 0 && r + 8 <= a.Rpad) {
-        *(Oct*)(dst + ((k / 32 * 3 + p) * a.stage_rows + c) * 32 + k % 32) = o[p];
-      } else {
-        for (int t = 0; t < 8; ++t)
-          if (r + t < a.Rpad) dst[(((k + t) / 32 * 3 + p) * a.stage_rows + c) * 32 + (k + t) % 32] = o[p].v[t];
+    for (int p = 0; p < 2; ++p) *(Oct*)(dst + (((long long)(r / 32) * 2 + p) * a.stage_rows + c) * 32 + r % 32) = o[p];
+  }
+}
+
+// Exponents of the rows of the two planes that k_grad_from_phi writes (see split2).  The first workgroups take up to 64 rows of
+// one slab of dLT each: the largest magnitude of a row over all positions, one more read of the probabilities; the gradients
+// and targets of the slab, apart in memory, go through LDS once per workgroup (fetched by every wave for its rows of any slabs,
+// this took 330 us for 562 MB of probabilities).  The others take 16 rows of dL: no value of row b is larger
+// than |Ge[b][i][j]| 2^(largest exponent of the rows of W[i][j]), which is off by what the softmax leaves of it only (a row
+// whose every token is certain), well within the 16 bits that the terms have to spare.
+__global__ __launch_bounds__(256) void k_grad_exps(const GradPhiArgs a, int* __restrict__ rexp, int* __restrict__ bexp, int row_blocks) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+  typedef __attribute__((ext_vector_type(4))) int i32x4_t;
+  extern __shared__ int s_slab[];                    // [n*r] largest exponent of a slab's rows
+  constexpr int CH = 1024;                           // positions per step
+  __shared__ __align__(16) float s_g[CH];
+  __shared__ __align__(16) int s_x[CH];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nr = a.n * a.r;
+  if ((int)blockIdx.x < row_blocks) {
+    constexpr int RW = 16;                           // rows of a wave (those of the four waves alternate)
+    const int parts = (a.v + 63) / 64;
+    const int slab = blockIdx.x / parts, r0 = (blockIdx.x - slab * parts) * 64 + wave;
+    const float* phi = a.phiT + (long long)slab * a.v * a.ld_phi;
+    float big[RW];
+#pragma unroll
+    for (int k = 0; k < RW; ++k) big[k] = 0.f;
+    for (int c0 = 0; c0 < a.B; c0 += CH) {
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < CH / 256; ++q) {
+        const int i = tid + q * 256, b = c0 + i;
+        const int x = b < a.B ? a.targets[(long long)b * a.n + slab / a.r] : -1;
+        s_x[i] = x;
+        s_g[i] = x != -1 ? a.Ge[(long long)b * nr + slab] : 0.f;
+      }
+      __syncthreads();
+      for (int i = 4 * lane; i < CH && c0 + i < a.B; i += 256) {
+        const f32x4_t g = *(const f32x4_t*)(s_g + i);
+        const i32x4_t x = *(const i32x4_t*)(s_x + i);
+        f32x4_t ph[RW];
+#pragma unroll
+        for (int k = 0; k < RW; ++k) ph[k] = *(const f32x4_t*)(phi + (long long)min(r0 + 4 * k, a.v - 1) * a.ld_phi + c0 + i);
+#pragma unroll
+        for (int k = 0; k < RW; ++k)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const float y = c0 + i + c < a.B ? fabsf(g[c] * ((r0 + 4 * k == x[c] ? 1.f : 0.f) - ph[k][c])) : 0.f;
+            big[k] = y <= 3.402823466e38f ? fmaxf(big[k], y) : big[k];
+          }
       }
     }
+#pragma unroll
+    for (int k = 0; k < RW; ++k) {
+      const float y = group_max(big[k], 64);
+      if (lane == 0 && r0 + 4 * k < a.v) rexp[(long long)slab * a.v + r0 + 4 * k] = split_exp(y);
+    }
+    return;
   }
-  if (large) *a.big = 1;
+  for (int i = tid; i < nr; i += 256) s_slab[i] = -1000;
+  __syncthreads();
+  for (long long m = tid; m < a.M; m += 256) atomicMax(&s_slab[(int)(m / a.v)], a.Wexp[m]);
+  __syncthreads();
+  const int b = ((int)blockIdx.x - row_blocks) * 16 + (tid >> 4), t = tid & 15;
+  const int r2 = (int)(a.Mx - a.M);
+  int e = -100000;
+  auto see = [&](float y, int scale) {
+    y = fabsf(y);
+    if (y > 0.f && y <= 3.402823466e38f) e = max(e, __builtin_amdgcn_frexp_expf(y) + scale);
+  };
+  if (b < a.B) {
+    for (int i = t; i < nr; i += 16) see(a.Ge[(long long)b * nr + i], s_slab[i]);
+    for (int j = t; j < r2; j += 16) see(((const float*)a.dslT)[j * a.ldb + b], a.Wexp[a.M + j]);
+  }
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) e = max(e, __shfl_xor(e, o));
+  if (b < a.B && t == 0) bexp[b] = e > -100000 ? e - 15 : 0;
 }
 
 // 64 (m) x 128 (b) tiles: logit gradient from the stored probabilities, written in both
 // layouts (dLT along b straight away, dL along m after a transpose through LDS).  A thread
 // moves four neighbouring elements at a time (16-byte loads, 8- or 16-byte stores).
-// PLANES (fp32): both layouts as planes of three bf16 terms, as tile_gemm_run_split reads them.
+// PLANES (fp32): both layouts as planes of two fp16 terms, as tile_gemm_run_split reads them; rexp and bexp hold the
+// exponents of their rows.
 template <typename T, bool PLANES = false>
-__global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a) {
+__global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a, const int* __restrict__ rexp, const int* __restrict__ bexp) {
   struct alignas(4 * sizeof(T)) Quad { T v[4]; };
-  // four neighbours along K, to row `row` of a staged matrix of `rows` rows
-  auto put_planes = [](void* dst, long long k, long long rows, long long row, const Quad& x) {
-    struct alignas(8) Half { unsigned short v[4]; } o[3];
+  // four neighbours along K, to row `row` of a staged matrix of `rows` rows; e[c]: the power of two x[c] is multiplied with
+  auto put_planes = [](void* dst, long long k, long long rows, long long row, const Quad& x, const int (&e)[4]) {
+    struct alignas(8) Half { unsigned short v[4]; } o[2];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      unsigned short q[3];
-      split3((float)x.v[c], q);
-#pragma unroll
-      for (int p = 0; p < 3; ++p) o[p].v[c] = q[p];
+      unsigned short q[2];
+      split2(__builtin_amdgcn_ldexpf((float)x.v[c], e[c]), q);
+      o[0].v[c] = q[0]; o[1].v[c] = q[1];
     }
 #pragma unroll
-    for (int p = 0; p < 3; ++p) *(Half*)((unsigned short*)dst + ((k / 32 * 3 + p) * rows + row) * 32 + k % 32) = o[p];
+    for (int p = 0; p < 2; ++p) *(Half*)((unsigned short*)dst + ((k / 32 * 2 + p) * rows + row) * 32 + k % 32) = o[p];
   };
   __shared__ T tile[64][128 + 4];
   const long long m0 = (long long)blockIdx.y * 64;
@@ -169,7 +240,7 @@ __global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a) {
   const bool col_ok = b < a.ldb;                                // ldb is a multiple of 4: all four or none
   int cur_slab = -1, x[4] = {-1, -1, -1, -1};
   float g[4] = {0.f, 0.f, 0.f, 0.f};
-  bool large = false;
+  bool bad = false;
 #pragma unroll 2
   for (int k = 0; k < 8; ++k) {
     const int ml = ty + 8 * k;
@@ -198,8 +269,10 @@ __global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a) {
       for (int c = 0; c < 4; ++c)
         if (b + c < a.B && x[c] != -1) out.v[c] = conv(g[c] * ((av == x[c] ? 1.f : 0.f) - pv[c]));
       constexpr int EPS = 64 / (int)sizeof(T);     // elements of a row per stage (b is a multiple of 4)
-      if constexpr (PLANES) put_planes(a.dLT, b, a.M, m, out);
-      else if (a.staged) *(Quad*)(dLT + ((long long)(b / EPS) * a.M + m) * EPS + b % EPS) = out;
+      if constexpr (PLANES) {
+        const int e = -rexp[m];
+        put_planes(a.dLT, b, a.M, m, out, {e, e, e, e});
+      } else if (a.staged) *(Quad*)(dLT + ((long long)(b / EPS) * a.M + m) * EPS + b % EPS) = out;
       else *(Quad*)(dLT + m * a.ldb + b) = out;
     } else if (m < a.Mx && col_ok) {
       out = *(const Quad*)((const T*)a.dslT + (m - a.M) * a.ldb + b);   // sum-unit rows, written by the reverse pass
@@ -207,13 +280,17 @@ __global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       tile[ml][4 * tx + c] = out.v[c];
-      if constexpr (PLANES) large |= fabsf(out.v[c]) > SPLIT_LARGE;
+      if constexpr (PLANES) bad |= !(fabsf(out.v[c]) <= 3.402823466e38f);
     }
   }
   if constexpr (PLANES)
-    if (large) *a.big = 1;
+    if (bad) *a.big = 1;
   __syncthreads();
   const int mq = threadIdx.x & 15, br = threadIdx.x >> 4;        // 16 row quads x 16 positions per pass
+  int we[4] = {0, 0, 0, 0};
+  if constexpr (PLANES)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) we[c] = a.Wexp[min(m0 + 4 * mq + c, a.Mx - 1)];
 #pragma unroll 2
   for (int k = 0; k < 8; ++k) {
     const int bl = br + 16 * k;
@@ -223,8 +300,10 @@ __global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) out.v[c] = tile[4 * mq + c][bl];
       constexpr int EPS = 64 / (int)sizeof(T);
-      if constexpr (PLANES) put_planes(a.dL, m, a.B, b0 + bl, out);
-      else if (a.staged) *(Quad*)(dL + ((m / EPS) * a.B + (b0 + bl)) * EPS + m % EPS) = out;
+      if constexpr (PLANES) {
+        const int e = bexp[b0 + bl];
+        put_planes(a.dL, m, a.B, b0 + bl, out, {we[0] - e, we[1] - e, we[2] - e, we[3] - e});
+      } else if (a.staged) *(Quad*)(dL + ((m / EPS) * a.B + (b0 + bl)) * EPS + m % EPS) = out;
       else *(Quad*)(dL + (long long)(b0 + bl) * a.ldM + m) = out;
     }
   }
@@ -1022,7 +1101,9 @@ hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t st) {
   if (a.C < 1 || a.Rpad < 1) return hipSuccess;
   const dim3 grid((a.C + 63) / 64, (a.Rpad + 63) / 64);
   if (a.planes) {
-    if (dtype != MTPC_F32 || a.stage_rows <= 0) return hipErrorInvalidValue;
+    if (dtype != MTPC_F32 || a.stage_rows != a.C || a.col0 != 0 || a.Rpad % 32 != 0) return hipErrorInvalidValue;
+    if (a.exps == nullptr)
+      return launch_split_rows(a.plain, a.dst, 1, a.C, a.Rpad, a.ld_plain * 4, plane_exps(a.dst, (long long)a.C * a.Rpad), a.big, 0, st);
     hipLaunchKernelGGL(k_transpose_planes, grid, dim3(256), 0, st, a);
     return hipGetLastError();
   }
@@ -1041,9 +1122,19 @@ hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t st) {
 
 hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st) {
   const dim3 grid((unsigned)((a.ldb + 127) / 128), (unsigned)((a.ldM + 63) / 64));
-  if (dtype == MTPC_BF16) hipLaunchKernelGGL(k_grad_from_phi<unsigned short>, grid, dim3(256), 0, st, a);
-  else if (a.planes) hipLaunchKernelGGL((k_grad_from_phi<float, true>), grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL(k_grad_from_phi<float>, grid, dim3(256), 0, st, a);
+  if (dtype == MTPC_BF16) hipLaunchKernelGGL(k_grad_from_phi<unsigned short>, grid, dim3(256), 0, st, a, nullptr, nullptr);
+  else if (a.planes) {
+    hipError_t e = hipSuccess;
+    if (a.W != nullptr) e = launch_split_rows(a.W, nullptr, 1, (int)a.M, a.d, a.d * 4LL, a.Wexp, a.big, 0, st);
+    if (e == hipSuccess && a.Wsum != nullptr)
+      e = launch_split_rows(a.Wsum, nullptr, 1, (int)(a.Mx - a.M), a.d, a.d * 4LL, a.Wexp + a.M, a.big, 0, st);
+    if (e != hipSuccess) return e;
+    int* const rexp = plane_exps(a.dLT, a.M * a.ldb);
+    int* const bexp = plane_exps(a.dL, a.B * a.ldM);
+    const int rb = a.n * a.r * ((a.v + 63) / 64), bb = (a.B + 15) / 16;
+    hipLaunchKernelGGL(k_grad_exps, dim3(rb + bb), dim3(256), (size_t)a.n * a.r * 4, st, a, rexp, bexp, rb);
+    hipLaunchKernelGGL((k_grad_from_phi<float, true>), grid, dim3(256), 0, st, a, rexp, bexp);
+  } else hipLaunchKernelGGL(k_grad_from_phi<float>, grid, dim3(256), 0, st, a, nullptr, nullptr);
   return hipGetLastError();
 }
 

@@ -107,7 +107,7 @@ hipError_t launch_unembed_grad(const GradLogitsArgs& a, int dtype, hipStream_t s
 }
 
 // ---------------------------------------------------------------------------
-// SPLIT: fp32 operands as planes of three bf16 terms (tile_gemm_run_split), both stage-major.
+// SPLIT: fp32 operands as planes of two fp16 terms (tile_gemm_run_split), both stage-major.
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool ASTAGED, bool SPLIT = false>
 __global__ __launch_bounds__(WV * WB * 64)
 void k_gemm_tn(const GemmArgs a) {
@@ -142,8 +142,8 @@ void k_gemm_tn(const GemmArgs a) {
   TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, ASTAGED, false, 0, SPLIT> feed;
   auto open = [&](const Where& t) {
     if constexpr (SPLIT) {
-      const long long s0 = (long long)(t.k0 / 32) * 3;             // (chunks are multiples of 64 columns)
-      feed.open((const char*)a.As + s0 * a.As_rows * 64, 0, a.Bm, 0, a.N, 3 * t.klen, t.rows, 0, t.b0, smem, nullptr, 0, 1,
+      const long long s0 = (long long)(t.k0 / 32) * 2;             // (chunks are multiples of 64 columns)
+      feed.open((const char*)a.As + s0 * a.As_rows * 64, 0, a.Bm, 0, a.N, 2 * t.klen, t.rows, 0, t.b0, smem, nullptr, 0, 1,
                 (const char*)a.Bs + s0 * a.N * 64, a.As_rows, t.slab * TL::TV);
       return;
     }
@@ -159,6 +159,18 @@ void k_gemm_tn(const GemmArgs a) {
   Where cur = where(blockIdx.x);
   open(cur);
   for (int w = blockIdx.x;;) {
+    // exponents of the tile's operand rows: fetched now, parked in LDS behind the product
+    constexpr int XE = (TL::ROWS + TL::NT - 1) / TL::NT;
+    int epre[XE];
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int q = 0; q < XE; ++q) {
+        const int idx = min((int)threadIdx.x + q * TL::NT, TL::ROWS - 1);
+        epre[q] = 0;
+        if (idx < TL::TV) { if (a.Ae != nullptr) epre[q] = a.Ae[min(cur.slab * TL::TV + idx, a.M - 1)]; }
+        else if (a.Be != nullptr) epre[q] = a.Be[min(cur.b0 + idx - TL::TV, a.N - 1)];
+      }
+    }
     typename FR::blk_t acc[NPB][NVB];
     if constexpr (SPLIT) tile_gemm_run_split(feed, cur.klen, smem, acc);
     else tile_gemm_run(feed, cur.klen, smem, acc);
@@ -170,6 +182,15 @@ void k_gemm_tn(const GemmArgs a) {
     }
     const int slab = cur.slab, b0 = cur.b0, rows = cur.rows, ks = cur.ks;
     const int rbase = wv * VB * 32 + 4 * lgrp;
+    if constexpr (SPLIT) {
+      int* s_e = (int*)(smem + TL::SMEM);
+      // (the product's last barrier is behind the reads of the tile before)
+#pragma unroll
+      for (int q = 0; q < XE; ++q)
+        if ((int)threadIdx.x + q * TL::NT < TL::ROWS) s_e[threadIdx.x + q * TL::NT] = epre[q];
+      __syncthreads();
+      tile_unscale<TL>(acc, s_e, rbase, wb * TL::WP + lcol);
+    }
     // A full tile that lies inside one destination (the common case): one base pointer per
     // column, rows at constant multiples of ldc.
     bool stored = false;
@@ -231,14 +252,16 @@ static hipError_t launch_gemm_cfg(const GemmArgs& a, hipStream_t st) {
   if constexpr (!ASTAGED)
     if (a.As != nullptr) return launch_gemm_cfg<WV, WB, VB, PB, BF16, true>(a, st);
   constexpr auto kern = k_gemm_tn<WV, WB, VB, PB, 64, 4, BF16, ASTAGED, SPLIT>;
-  if (hipError_t e = allow_lds<kern>(TL::SMEM); e != hipSuccess) return e;
+  constexpr int smem = TL::SMEM + (SPLIT ? TL::ROWS * 4 : 0);
+  static_assert(smem <= 160 * 1024, "LDS budget of one CU");
+  if (hipError_t e = allow_lds<kern>(smem); e != hipSuccess) return e;
   const int nslab = (a.M + TL::TV - 1) / TL::TV, nbt = (a.N + TL::TP - 1) / TL::TP;
   int grid = nslab * nbt * max(a.ksplit, 1);
   // one workgroup per CU (the ring takes most of a CU's LDS), a multiple of the 8 XCDs the ids are dealt over
   int cus = 0;
   if (hipError_t e = cu_count(&cus); e != hipSuccess) return e;
   if (cus >= 8) grid = std::min(grid, cus / 8 * 8);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(TL::NT), TL::SMEM, st, a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(TL::NT), smem, st, a);
   return hipGetLastError();
 }
 
@@ -280,8 +303,8 @@ hipError_t launch_gemm_tn(const GemmArgs& a0, int dtype, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Results of products of planes that are not finite, formed anew from whole fp32 values (x1 + x2 + x3 is exact).  A no-op
-// unless *big is set, which takes an operand beyond SPLIT_LARGE: a product of single terms of such a value may be NaN
+// Results of products of planes that are not finite, formed anew from whole fp32 values (x1 + x2).  A no-op
+// unless *big is set, which takes an infinite or NaN operand: a product of single terms of such a value may be NaN
 // where the sum is an infinity.  Anything but fast: 64 x 64 results per workgroup and step of the walk, left as soon as
 // the tile has nothing to mend - and given up where every sum to mend has become NaN (NaN operands, say).
 __global__ __launch_bounds__(256) void k_gemm_nonfinite(const GemmArgs a0, const GemmArgs a1, const int* big) {
@@ -312,11 +335,11 @@ __global__ __launch_bounds__(256) void k_gemm_nonfinite(const GemmArgs a0, const
         for (int e = 0; e < 8; ++e) s[e] = 0.f;
         if (row < end)
 #pragma unroll
-          for (int p = 0; p < 3; ++p) {
+          for (int p = 0; p < 2; ++p) {
             struct alignas(16) Oct { unsigned short v[8]; };
-            const Oct o = *(const Oct*)((const char*)planes + ((3LL * k + p) * rows + row) * 64 + ch * 16);
+            const Oct o = *(const Oct*)((const char*)planes + ((2LL * k + p) * rows + row) * 64 + ch * 16);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) s[e] += __uint_as_float((unsigned)o.v[e] << 16);
+            for (int e = 0; e < 8; ++e) s[e] += (float)__builtin_bit_cast(_Float16, o.v[e]);
           }
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[ch * 8 + e][lr] = s[e];
@@ -346,7 +369,11 @@ __global__ __launch_bounds__(256) void k_gemm_nonfinite(const GemmArgs a0, const
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          if (mend >> (4 * i + j) & 1) a.C[(long long)(row0 + 4 * ty + i) * a.ldc + col0 + tx + 16 * j] = acc[i][j];
+          if (mend >> (4 * i + j) & 1) {
+            const int r = row0 + 4 * ty + i, c = col0 + tx + 16 * j;
+            a.C[(long long)r * a.ldc + c] =
+                __builtin_amdgcn_ldexpf(acc[i][j], (a.Ae != nullptr ? a.Ae[r] : 0) + (a.Be != nullptr ? a.Be[c] : 0));
+          }
     }
   }
 }

@@ -40,12 +40,14 @@ struct UnembedArgs {
   float* logphi;        // [B][n][r][v] normalised logits of every slab, or nullptr
   float* phiT;          // [n*r*v][ld_phi] softmax probabilities, transposed, or nullptr (evidence kernel only)
   long long ld_phi;
-  // fp32 operands of 256-position tiles, multiplied as three bf16 terms each (split_pays): scratch that
-  // launch_unembed fills with the planes of W, [n*r][3 d/32][v][64 bytes], and of h, [3 d/32][B][64 bytes], and
-  // a flag it sets when an operand is infinite, NaN or huge (the fp32 instruction takes over then).  Or nullptr
+  // fp32 operands of 256-position tiles, multiplied as two fp16 terms each (split_pays): scratch that
+  // launch_unembed fills with the planes of W, [n*r][2 d/32][v][64 bytes], and of h, [2 d/32][B][64 bytes], the exponents of
+  // their rows behind them (plane_exps), and a flag it sets when the terms do not do an operand justice (see
+  // k_split_rows; the fp32 instruction takes over then).  Or nullptr
   void* Wq;
   void* hq;
   int* wild;
+  int* Wexp;            // where the exponents of W's rows go, [n*r*v], or nullptr: behind its planes
 };
 
 // Univariate marginals: M[b][i][a] = log sum_j m[b][i][j] phi[b][i][j][a].
@@ -108,6 +110,14 @@ hipError_t launch_pack_rows(const void* src, void* dst, long long slabs, int v, 
 constexpr int H_STAGE_BYTES = 64;
 constexpr int PACK_STAGE_BYTES = 128;
 hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t st);
+
+// Exponents of the rows of a matrix stored as planes of two fp16 terms of `elements` values: right behind them.  (Planes
+// have room for six bytes per value in every workspace: four are the terms.)
+inline int* plane_exps(void* planes, long long elements) { return (int*)((char*)planes + 4 * elements); }
+// fp32 rows as planes of two fp16 terms (unembed.hip, k_split_rows): `slabs` matrices of v rows, each [2 d/32][v][64 bytes], and
+// the exponents of all rows; dst nullptr: the exponents only
+hipError_t launch_split_rows(const void* src, void* dst, long long slabs, int v, int d, long long row_stride, int* exps,
+                             int* flag, int guard, hipStream_t st);
 
 // ---- small kernels (circuits.hip) -----------------------------------------
 // log omega[b][:] = log_softmax(Wsum h[b])
@@ -290,11 +300,16 @@ struct GradPhiArgs {
   // rows m < M of dLT as [ldb * esz / 64][M][64 bytes] (the sum-unit rows M..Mx-1 stay where they are, behind
   // it), dL as [ldM * esz / 64][B][64 bytes] (then dl_end = ldM: every column is written here)
   int staged;
-  // 1 (fp32, staged): both as planes of three bf16 terms, stages of 32 columns per term (tile_gemm_run_split):
-  // dLT [3 ldb/32][M][64 bytes], dL [3 ldM/32][B][64 bytes]
+  // 1 (fp32, staged): both as planes of two fp16 terms, stages of 32 columns per term (tile_gemm_run_split):
+  // dLT [2 ldb/32][M][64 bytes], dL [2 ldM/32][B][64 bytes], the exponents of their rows behind them (plane_exps).
+  // The rows of dL are those of dL[b][m] 2^Wexp[m]: they meet rows of W without their scale
   int planes;
   const void* dslT;     // the sum-unit rows M..Mx-1 of dLT, [Mx - M][ldb] in the dtype of h
-  int* big;             // planes: set to 1 when an element is beyond SPLIT_LARGE
+  int* big;             // planes: set to 1 when an element is infinite or NaN
+  int* Wexp;            // planes: exponents of the rows of W and, behind them, of Wsum [Mx]; those of the matrices given
+  const void* W;        // here, [M][d] and [Mx - M][d], are formed first (W nullptr: the forward pass has left them)
+  const void* Wsum;
+  int d;
 };
 hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st);
 
@@ -316,11 +331,13 @@ struct GemmArgs {
   // columns and write their partial tile to partial[ks][M][ldc]; a second kernel adds the
   // partials in a fixed order into C (single output buffer only)
   int ksplit; int kchunk; float* partial;
-  int planes;           // fp32 only: As and Bs hold three bf16 terms per value, [3 K/32][rows][64 bytes]
+  int planes;           // fp32 only: As and Bs hold two fp16 terms per value, [2 K/32][rows][64 bytes]
+  const int* Ae;        // ... and these the exponents of their rows (nullptr: 0)
+  const int* Be;
 };
 hipError_t launch_gemm_tn(const GemmArgs& a, int dtype, hipStream_t st);
 // After two products of planes: where *big is set, forms every result that is not finite anew as an fp32 sum of the
-// whole values (see SPLIT_LARGE).  Single output buffer C only.
+// whole values (see split2).  Single output buffer C only.
 hipError_t launch_gemm_nonfinite(const GemmArgs& a, const GemmArgs& b, const int* big, hipStream_t st);
 // number of K splits that fills the 256 CUs best for an M x N output (1: none)
 inline int gemm_ksplit(int M, int N, int K) {
@@ -345,9 +362,15 @@ struct TransposeArgs {
   // 0: dst[c][col0 + r].  Else the destination is stage-major in 64-byte stages with this many rows,
   // [columns * esz / 64][stage_rows][64 bytes] (the form the contraction kernels read an operand in)
   int stage_rows;
-  // 1 (fp32, stage_rows set): three bf16 terms per value, [3 columns/32][stage_rows][64 bytes]
+  // 1 (fp32, stage_rows set, col0 = 0, Rpad a multiple of 32): two fp16 terms per value, [2 columns/32][stage_rows][64 bytes]
   int planes;
-  int* big;             // planes: set to 1 when an element is beyond SPLIT_LARGE
+  int* big;             // planes: set to 1 when an element is infinite or NaN
+  // planes of [src; src2]^T without the scales of the rows of src (exps[R]) and src2 (behind them; R2 rows of the same stride) ...
+  const int* exps;
+  const void* src2; int R2;
+  // ... or (exps nullptr) of src^T, whose rows get scales of their own, left behind the planes (plane_exps): from its
+  // transpose in fp32, [C][ld_plain], columns up to Rpad
+  const void* plain; long long ld_plain;
 };
 hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t st);
 
@@ -451,26 +474,20 @@ __device__ __forceinline__ float philox_uniform(uint32_t seed_lo, uint32_t seed_
   return (float)(word >> 8) * 5.9604644775390625e-8f;
 }
 
-// x as the exact sum of three bf16 terms (8 significant bits each: 24 in all), the next one the nearest bf16 of
-// what is left.  A finite x keeps finite terms (next to the largest value the nearest bf16 would be infinite:
-// the one below is taken); an infinite or NaN x is its own first term, the others are 0.
-// Terms below 2^-126 lose low bits, which matters to values below 2^-110 only.
-// Where an operand is infinite, or so large that products overflow, the products of single terms can be infinities of
-// both signs or infinity times zero: NaN where the product of the values is an infinity.  Operands beyond SPLIT_LARGE are
-// therefore noted, and what they take part in is left to fp32 multiply-adds.
-constexpr float SPLIT_LARGE = 0x1p60f;     // two values up to it: products below 2^120
-__device__ __forceinline__ void split3(float x, unsigned short (&t)[3]) {
-  auto bits = [](float y) { return (unsigned)__builtin_bit_cast(unsigned short, (__bf16)y) << 16; };
-  const unsigned ux = __float_as_uint(x);
-  const bool finite = (ux & 0x7f800000u) != 0x7f800000u;
-  unsigned u1 = bits(x);
-  if ((u1 & 0x7f800000u) == 0x7f800000u && finite) u1 = ux & 0xffff0000u;
-  const float r1 = finite ? x - __uint_as_float(u1) : 0.f;
-  const unsigned u2 = bits(r1);
-  const float r2 = r1 - __uint_as_float(u2);
-  t[0] = (unsigned short)(u1 >> 16);
-  t[1] = (unsigned short)(u2 >> 16);
-  t[2] = (unsigned short)(bits(r2) >> 16);
+// A scaled x (|x| < 2^15) as two fp16 terms of 11 significant bits, the second one the nearest of what the first leaves: their
+// sum is off by at most half a unit of x's 23rd bit, or 2^-25.  An infinite or NaN x is its own first term and the second is 0:
+// products of single terms may then be NaN (infinity times a second term of 0) where the product of the values is an
+// infinity, so such operands are noted, and what they take part in is left to fp32 multiply-adds.
+__device__ __forceinline__ void split2(float x, unsigned short (&t)[2]) {
+  const _Float16 hi = (_Float16)x;
+  const bool finite = (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u;
+  const _Float16 lo = (_Float16)(finite ? x - (float)hi : 0.f);
+  t[0] = __builtin_bit_cast(unsigned short, hi);
+  t[1] = __builtin_bit_cast(unsigned short, lo);
+}
+// exponent E with x 2^-E in [2^14, 2^15), for the largest |x| of a row (0: 0)
+__device__ __forceinline__ int split_exp(float largest) {
+  return largest > 0.f ? __builtin_amdgcn_frexp_expf(largest) - 15 : 0;
 }
 
 __device__ __forceinline__ float neg_inf() { return -__builtin_inff(); }

@@ -10,6 +10,7 @@
 namespace mtpc {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) int i32x4_t;
@@ -89,6 +90,11 @@ __device__ __forceinline__ void mma_step(f32x4_t& acc, const i32x4_t& a, const i
   static_assert(BF16, "the 16x16 blocks are used by the bf16 kernels only");
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
                                                 acc, 0, 0, 0);
+}
+
+// the same product of fp16 terms (tile_gemm_run_split)
+__device__ __forceinline__ void mma_step_f16(f32x4_t& acc, const i32x4_t& a, const i32x4_t& b) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), acc, 0, 0, 0);
 }
 
 template <bool BF16>
@@ -189,15 +195,14 @@ __device__ __forceinline__ int swz(int row) {
 // 1^f(8+k) must differ: f = (0, 3, 2, 1).
 __device__ __forceinline__ int swz16(int row) { return (0 - (row >> 2)) & 3; }
 
-// Ring buffers of the plane stages of tile_gemm_run_split: first terms alternate between two.
-constexpr int SPLIT_SLOT_A0 = 0, SPLIT_SLOT_C = 2, SPLIT_SLOT_B = 3;
+// Ring buffers of the plane stages of tile_gemm_run_split: both terms of the columns alternate between two.
+constexpr int SPLIT_SLOT_HI = 0, SPLIT_SLOT_LO = 2;
 
 // Where the operands of one tile come from, and the direct-to-LDS loads that bring them in: open()
 // describes the tile and issues the first NS-1 stages of its ring, tile_gemm_run() multiplies.  Apart,
 // so that a workgroup that walks several tiles can open the next one (the ring is free once the run
 // has returned) before it turns to the epilogue of the one it has just multiplied.
-// SPLIT: the operands are fp32 matrices as planes of three bf16 terms (see tile_gemm_run_split); only the
-// first two planes are issued here.
+// SPLIT: the operands are fp32 matrices as planes of two fp16 terms (see tile_gemm_run_split).
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER = false, bool M16 = false,
           bool WPACK = false, bool STREAMW = false, int PH = 0, bool SPLIT = false, int VH = 0>
 struct TileFeed {
@@ -291,8 +296,9 @@ struct TileFeed {
     hstep = (unsigned)__builtin_amdgcn_readfirstlane((int)(hpk ? (unsigned)B * SB : (unsigned)SB));
     wstep = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(wall ? wrows_total : v) * SB));
     if constexpr (SPLIT) {
-      issue(SPLIT_SLOT_A0);
-      issue(SPLIT_SLOT_B);
+      issue(SPLIT_SLOT_HI);
+      issue(SPLIT_SLOT_LO);
+      if (d > 64) issue(SPLIT_SLOT_HI + 1);
     } else {
       const int KI = d * ESZ / SB;
       for (int s = 0; s < NS - 1; ++s)
@@ -529,19 +535,22 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
   __syncthreads();     // all waves are done reading the ring
 }
 
-// The product of two fp32 operands on the bf16 matrix pipes.  An fp32 value is the exact sum of three bf16
-// terms x1 + x2 + x3, each the nearest bf16 of what the ones before leave (see split3), and
-//   x y = x1 y1 + x1 y2 + x2 y2 + x2 y1 + x3 y1 + x1 y3 + (x2 y3 + x3 y2 + x3 y3),
-// where what is left out is at most about 2^-24 |x y| (|x2| <= 2^-8, |x3| <= 2^-17 of the leading power of two: two cross
-// terms of 2^-25), what one fp32 multiply-add may round off.  The six
-// products cost 6 / 16 of the fp32 instruction's time; products and sums are fp32 as there, with one rounding
-// per 32 terms of K instead of one per 1 or 2.
+// The product of two fp32 operands on the fp16 matrix pipes.  A row of either operand, scaled by a power of two that
+// takes its largest value into [2^14, 2^15), is the sum of two fp16 terms x1 + x2 (see split2), 11 bits each, up to half a
+// unit of bit 23 or, where that is more, 2^-40 of the row's largest value; and
+//   x y = x1 y2 + x1 y1 + x2 y1 + (x2 y2),
+// where what is left out is at most 2^-22 |x y| and 2^-25 of it on average, without a sign of its own.  The three products
+// cost 3 / 16 of the fp32 instruction's time; products are exact and sums fp32 as there, with one rounding per 32 terms of K
+// instead of one per 1 or 2: in a sum of a few hundred terms those roundings, not the terms, are the error that is left.
+// The row scales are powers of two that the epilogue takes out again.
 // Both operands are stage-major (TileFeed with WPACK and hs) in 64-byte stages that hold 32 columns of ONE
-// term: stages 3k, 3k+1, 3k+2 are terms 1, 2, 3 of columns 32k .. 32k+31.  d: fp32 columns.
-// Schedule: the ping-pong clusters of tile_gemm_run, six per 32 columns; a cluster re-reads only the operand
-// that changes (56 fragment reads per 240 products instead of 84).  Of the four ring buffers two alternate
-// for the first terms, which are needed to the end of their columns; loads are issued four or five clusters
-// before their first use.  One stage of loads feeds two clusters, where the bf16 kernel loads one for each.
+// term: stages 2k and 2k+1 are terms 1 and 2 of columns 32k .. 32k+31.  d: fp32 columns.
+// Schedule: the ping-pong clusters of tile_gemm_run, three per 32 columns; a cluster reads only what it does not have
+// (28 fragment reads per 120 products where the bf16 kernel needs 42), and the ring takes two stages for three clusters.
+// Of its four buffers two alternate for each term; loads are issued three or four clusters before their first use.
+// Bound by the power of the products and of the two operand stages behind every three of them: 1.45 PFLOP/s of issued products
+// (B = 2048, n r = 256, d = 3072, v = 268: 1.83 ms; three bf16 terms and six products 3.19 ms, the fp32 instruction 7.29 ms;
+// registers only, the fp16 product runs at 1.88 PFLOP/s and the bf16 one at 2.02).
 template <int WV, int WB, int VB, int PB, int SB, int NS, int VH>
 __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB, NS, true, false, true, true, false, 0, true, VH>& feed,
                                                     int d, char* smem, f32x4_t (&acc)[2 * PB][2 * VB - VH / 2]) {
@@ -581,22 +590,22 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
     for (int pb = 0; pb < 2 * PB; ++pb)
 #pragma unroll
       for (int vb = 0; vb < decltype(nvb)::value; ++vb) {
-        mma_step<true>(acc[pb][vb], ga[vb], gb[pb]);
+        mma_step_f16(acc[pb][vb], ga[vb], gb[pb]);
         __builtin_amdgcn_sched_barrier(0);
       }
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
   };
   const int KI = d / 32;
-  MTPC_WAIT_VMCNT(TL::PER);                 // the first terms of the first columns have landed
+  if (KI > 1) MTPC_WAIT_VMCNT(TL::PER); else MTPC_WAIT_VMCNT(0);     // both terms of the first columns have landed
   __syncthreads();
-  // ALLOW: loads of this wave that may still be on their way when the next cluster reads (negative: that
-  // cluster reads no new buffer).  Group 1 waits at the end of its memory cluster, group 0 after its products:
-  // either way before the barrier that lets the other group read.
   auto run = [&](auto grp) {
     constexpr int G = decltype(grp)::value;
     constexpr std::integral_constant<int, NVB16 - (G == 1 ? VH % 2 : 0)> nvb{};
-    auto rest = [&](auto allow) {           // what follows the reads and loads of a memory cluster
+    // What follows the reads and loads of a memory cluster.  ALLOW: loads of this wave that may still be on their way when
+    // the next cluster reads (negative: that cluster reads no new buffer).  Group 1 waits at the end of its memory
+    // cluster, group 0 after its products: either way before the barrier that lets the other group read.
+    auto rest = [&](auto allow) {
       constexpr int ALLOW = decltype(allow)::value;
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (G == 1 && ALLOW >= 0) MTPC_WAIT_VMCNT(ALLOW >= 0 ? ALLOW : 0);
@@ -605,27 +614,25 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
       if constexpr (G == 0 && ALLOW >= 0) MTPC_WAIT_VMCNT(ALLOW >= 0 ? ALLOW : 0);
       barrier();
     };
-    auto columns = [&](int k, auto lastk) { // the six products of 32 columns; the last ones issue no more
-      constexpr bool LAST = decltype(lastk)::value;
-      const int a = k & 1;
-      read_a(a, nvb); read_b(a);                 // x1 y1.  Third terms and the next first terms go where nobody reads
-      feed.issue(SPLIT_SLOT_C);             // any more since the last barrier
-      rest(std::integral_constant<int, TL::PER>{});            // second terms landed
-      read_b(SPLIT_SLOT_B);                 // x1 y2
-      if constexpr (!LAST) feed.issue(a ^ 1);
+    // The three products of 32 columns, LEFT of them still to come (2: or more).  Loads go where nobody reads any more since
+    // the last barrier: the second terms of the columns after these over those of the ones before, the first terms
+    // of the columns after next over this pair's, once both operands' are in registers.
+    auto columns = [&](int k, auto left) {
+      constexpr int LEFT = decltype(left)::value;
+      const int hi = SPLIT_SLOT_HI + (k & 1), lo = SPLIT_SLOT_LO + (k & 1);
+      read_b(lo); read_a(hi, nvb);          // x1 y2
+      if constexpr (LEFT >= 1) feed.issue(lo ^ 1);
       rest(std::integral_constant<int, -1>{});
-      read_a(SPLIT_SLOT_B, nvb);                 // x2 y2
+      read_b(hi);                           // x1 y1
       rest(std::integral_constant<int, -1>{});
-      read_b(a);                            // x2 y1: the buffer of the second terms is free
-      if constexpr (!LAST) feed.issue(SPLIT_SLOT_B);
-      rest(std::integral_constant<int, LAST ? 0 : 2 * TL::PER>{});   // third terms landed
-      read_a(SPLIT_SLOT_C, nvb);                 // x3 y1
-      rest(std::integral_constant<int, -1>{});
-      read_a(a, nvb); read_b(SPLIT_SLOT_C);      // x1 y3
-      rest(std::integral_constant<int, LAST ? -1 : TL::PER>{});      // the next first terms landed
+      read_a(lo, nvb);                      // x2 y1
+      if constexpr (LEFT >= 2) feed.issue(hi);
+      rest(std::integral_constant<int, LEFT >= 2 ? TL::PER : LEFT == 1 ? 0 : -1>{});     // the next pair landed
     };
-    for (int k = 0; k < KI - 1; ++k) columns(k, std::false_type{});
-    columns(KI - 1, std::true_type{});
+    int k = 0;
+    for (; k < KI - 2; ++k) columns(k, std::integral_constant<int, 2>{});
+    if (k < KI - 1) columns(k++, std::integral_constant<int, 1>{});
+    columns(k, std::integral_constant<int, 0>{});
   };
   if (wave >> 2) {
     __syncthreads();                        // start one cluster late
@@ -635,6 +642,23 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
     __syncthreads();                        // pairs with the late start of the other group
   }
   __syncthreads();                          // all waves are done reading the ring
+}
+
+// The scales of the rows of both operands out of the finished accumulators: acc *= 2^(rows + cols).  s_e holds the exponents
+// of the tile's TV rows and TP columns (LDS; the caller's barrier lies behind its stores).
+template <class TL, int NPB, int NVB>
+__device__ __forceinline__ void tile_unscale(f32x4_t (&acc)[NPB][NVB], const int* s_e, int rbase, int cbase) {
+  int ec[NPB];
+#pragma unroll
+  for (int pb = 0; pb < NPB; ++pb) ec[pb] = s_e[TL::TV + cbase + pb * 16];
+#pragma unroll
+  for (int vb = 0; vb < NVB; ++vb) {
+    const int* er = s_e + min(rbase + vb * 16, TL::TV - 4);          // (a block that is not there: any)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int pb = 0; pb < NPB; ++pb) acc[pb][vb][i] = __builtin_amdgcn_ldexpf(acc[pb][vb][i], er[i] + ec[pb]);
+  }
 }
 
 // D = W_slab x h_tile^T for one workgroup; on return every wave holds its VB x PB

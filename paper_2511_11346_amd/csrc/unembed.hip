@@ -245,8 +245,8 @@ __device__ __forceinline__ void tile_draws_cols(const f32x4_t (&acc)[NPB][NVB], 
 template <int WB, bool SAMPLE>
 constexpr bool unembed_walks_tiles() { return !SAMPLE && WB != 1; }
 
-// SPLIT: fp32 operands as planes of three bf16 terms (tile_gemm_run_split); everything but the product is
-// the bf16 kernel's.
+// SPLIT: fp32 operands as planes of two fp16 terms (tile_gemm_run_split); everything but the product, and the scales of
+// its rows that come out of the result behind it, is the bf16 kernel's.
 // STREAM: one tile of positions, so that every byte of W is read once (loaded with the non-temporal hint).
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false, int VH = 0,
           bool STREAM = false>
@@ -275,7 +275,9 @@ void k_unembed(const UnembedArgs a) {
   using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, STREAM, 0, SPLIT, VH>;
   const void* const hstaged = SPLIT ? a.hq : (WB != 1 && SB == H_STAGE_BYTES) ? a.hs : nullptr;
   const void* const Wfeed = SPLIT ? a.Wq : WPACK ? a.Wp : a.W;
-  const int dfeed = SPLIT ? 3 * a.d : a.d;            // bf16 columns of the planes
+  const int dfeed = SPLIT ? 2 * a.d : a.d;            // 16-bit columns of the planes
+  const int* const hexp = SPLIT ? (const int*)((const char*)a.hq + 4LL * a.B * a.d) : nullptr;      // (plane_exps)
+  int* const s_e = (int*)(smem + TL::SMEM);           // SPLIT: exponents of the tile's rows and columns [TV + TP]
   const int ntiles = nbt * nslab;
   int slab, bt;
   tile_of_block(blockIdx.x, nbt, nslab, slab, bt);
@@ -305,6 +307,17 @@ void k_unembed(const UnembedArgs a) {
     }
   }
 
+  // exponents of the tile's operand rows, the same way
+  constexpr int XE = (TL::ROWS + TL::NT - 1) / TL::NT;
+  int epre[XE];
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int q = 0; q < XE; ++q) {
+      const int idx = min(tid + q * TL::NT, TL::ROWS - 1);
+      epre[q] = idx < TL::TV ? a.Wexp[(long long)slab * a.v + min(idx, a.v - 1)] : hexp[min(b0 + idx - TL::TV, a.B - 1)];
+    }
+  }
+
   typename FR::blk_t acc[NPB][NVB];
   if constexpr (SPLIT) tile_gemm_run_split(feed, a.d, smem, acc);
   else tile_gemm_run(feed, a.d, smem, acc);
@@ -325,6 +338,13 @@ void k_unembed(const UnembedArgs a) {
   }
   // this lane holds, of position column wb*PB*32 + pb*BR + lcol, rows rbase + vb*BR + roff(i)
   const int rbase = wv * TL::WROWS + 4 * lgrp;
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int q = 0; q < XE; ++q)
+      if (tid + q * TL::NT < TL::ROWS) s_e[tid + q * TL::NT] = epre[q];
+    __syncthreads();
+    tile_unscale<TL>(acc, s_e, rbase, wb * TL::WP + lcol);
+  }
   float mx[NPB], lse[NPB];
   tile_lse<WV, WB, VB, PB, SB, NS, M16, 0, VH>(acc, a.v, (float2*)(smem + TL::RED_OFF), mx, lse);   // (one barrier: s_x is visible)
 
@@ -1043,7 +1063,9 @@ template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE
 static hipError_t launch_cfg(const UnembedArgs& a, hipStream_t st) {
   using TL = Tile<WV, WB, VB, PB, SB, NS, 0, VH>;
   constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK, SPLIT, VH, STREAM>;
-  if (hipError_t e = allow_lds<kern>(TL::SMEM); e != hipSuccess) return e;
+  constexpr int smem = TL::SMEM + (SPLIT ? TL::ROWS * 4 : 0);
+  static_assert(smem <= 160 * 1024, "LDS budget of one CU");
+  if (hipError_t e = allow_lds<kern>(smem); e != hipSuccess) return e;
   const int nbt = (a.B + TL::TP - 1) / TL::TP;
   int grid = nbt * a.n * a.r;
   if constexpr (unembed_walks_tiles<WB, SAMPLE>()) {
@@ -1053,7 +1075,7 @@ static hipError_t launch_cfg(const UnembedArgs& a, hipStream_t st) {
     if (hipError_t e = cu_count(&cus); e != hipSuccess) return e;
     if (cus >= 8) grid = std::min(grid, cus / 8 * 8);
   }
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(TL::NT), TL::SMEM, st, a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(TL::NT), smem, st, a);
   return hipGetLastError();
 }
 
@@ -1144,52 +1166,116 @@ hipError_t launch_pack_rows(const void* src, void* dst, long long slabs, int v, 
   return hipGetLastError();
 }
 
-// fp32 rows as planes of three bf16 terms (split3), stage-major: per matrix [3 d/32][v][64 bytes], stage 3k+p
-// holding term p of columns 32k..32k+31.  One thread splits 8 columns: four threads read one 128-byte line and
-// write 64 contiguous bytes of each plane, neighbouring rows follow.  Sets *wild when a value is infinite, NaN or
-// beyond SPLIT_LARGE.
-__global__ __launch_bounds__(256) void k_split_rows(const char* __restrict__ src, char* __restrict__ dst, long long slabs, int v,
-                                                    int d, long long row_stride, int* wild) {
-  const long long per_slab = (long long)v * (d / 8);
-  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (t >= slabs * per_slab) return;
-  const long long slab = t / per_slab;
-  const int u = (int)(t - slab * per_slab);
-  const int k = u / (v * 4), w = u - k * v * 4, row = w >> 2, ch = w & 3;
-  const char* s = src + (slab * v + row) * row_stride + (long long)k * 128 + ch * 32;
-  const f32x4_t x0 = __builtin_nontemporal_load((const f32x4_t*)s), x1 = __builtin_nontemporal_load((const f32x4_t*)(s + 16));
-  struct alignas(16) Oct { unsigned short v[8]; } o[3];
-  bool bad = false;
+// fp32 rows as planes of two fp16 terms (split2), stage-major: per matrix [2 d/32][v][64 bytes], stage 2k+p holding term p of
+// columns 32k..32k+31 times 2^-E, E the exponent of the row (split_exp of its largest finite value), left in exps.
+// A workgroup takes eight rows, a thread eight neighbouring columns at a time: four threads read one 128-byte line and write
+// 64 contiguous bytes of each plane, eight rows of a stage follow each other.  Rows of up to 4096 columns stay in registers
+// between the search for their largest value and the split, so the matrix is read once: 843 MB to as many of planes in 0.34 ms
+// (4.9 TB/s); a row at a time per thread quad and three planes took 0.43 ms.
+// Sets *flag when a value is infinite or NaN.  guard: also when the terms may do a row less than justice: a value below 2^-16
+// of the row's largest has fewer than 23 bits left (2^-40 of the largest), which matters where most of the row is that
+// small - one outlier - and not where a few values of a row happen to be near 0 (one in 16).
+constexpr int SPLIT_ROWS = 8, SPLIT_KEEP = 8;        // rows of a workgroup, steps of 512 columns kept in registers
+__global__ __launch_bounds__(512) void k_split_rows(const char* __restrict__ src, char* __restrict__ dst, int v, int d,
+                                                    long long row_stride, int* __restrict__ exps, int* flag, int guard) {
+  __shared__ unsigned s_max[8][SPLIT_ROWS];
+  __shared__ int s_small[8][SPLIT_ROWS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int rblocks = (v + SPLIT_ROWS - 1) / SPLIT_ROWS;
+  const int slab = blockIdx.x / rblocks, rl = (tid >> 2) & (SPLIT_ROWS - 1);
+  const int row = (blockIdx.x - slab * rblocks) * SPLIT_ROWS + rl, ch = tid & 3, sub = tid >> 5;
+  const bool live = row < v;
+  const char* s = src + ((long long)slab * v + min(row, v - 1)) * row_stride + ch * 32;
+  const int stages = d / 32;
+  f32x4_t x[SPLIT_KEEP][2];
 #pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const float x = c < 4 ? x0[c & 3] : x1[c & 3];
-    bad |= !(fabsf(x) <= SPLIT_LARGE);
-    unsigned short q[3];
-    split3(x, q);
-#pragma unroll
-    for (int p = 0; p < 3; ++p) o[p].v[c] = q[p];
+  for (int it = 0; it < SPLIT_KEEP; ++it) {
+    const int k = it * 16 + sub;
+    x[it][0] = x[it][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (live && k < stages) {
+      x[it][0] = __builtin_nontemporal_load((const f32x4_t*)(s + (long long)k * 128));
+      x[it][1] = __builtin_nontemporal_load((const f32x4_t*)(s + (long long)k * 128 + 16));
+    }
   }
+  unsigned m = 0;                                    // largest finite magnitude, as bits
+  bool bad = false;
+  auto look = [&](const f32x4_t& y) {
 #pragma unroll
-  for (int p = 0; p < 3; ++p)
-    *(Oct*)(dst + ((slab * (3LL * (d / 32)) + 3LL * k + p) * v + row) * 64 + ch * 16) = o[p];
-  if (bad) *wild = 1;
+    for (int c = 0; c < 4; ++c) {
+      const unsigned u = __float_as_uint(y[c]) & 0x7fffffffu;
+      bad |= u >= 0x7f800000u;
+      m = max(m, u < 0x7f800000u ? u : 0u);
+    }
+  };
+#pragma unroll
+  for (int it = 0; it < SPLIT_KEEP; ++it) { look(x[it][0]); look(x[it][1]); }
+  for (int k = SPLIT_KEEP * 16 + sub; live && k < stages; k += 16) {
+    look(*(const f32x4_t*)(s + (long long)k * 128));
+    look(*(const f32x4_t*)(s + (long long)k * 128 + 16));
+  }
+  // the threads of a row: lanes that differ in bits 0, 1 and 5, all eight waves
+  auto over = [&](unsigned y, int bit) { return (unsigned)__shfl_xor((int)y, bit); };
+  m = max(m, over(m, 1)); m = max(m, over(m, 2)); m = max(m, over(m, 32));
+  if ((lane & 35) == 0) s_max[wave][rl] = m;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 8; ++w) m = max(m, s_max[w][rl]);
+  const int E = split_exp(__uint_as_float(m));
+  int small = 0;
+  auto put = [&](const f32x4_t& y0, const f32x4_t& y1, int k) {
+    struct alignas(16) Oct { unsigned short v[8]; } o[2];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const float y = __builtin_amdgcn_ldexpf(c < 4 ? y0[c & 3] : y1[c & 3], -E);
+      small += y != 0.f && fabsf(y) < 0.5f;
+      unsigned short q[2];
+      split2(y, q);
+      o[0].v[c] = q[0]; o[1].v[c] = q[1];
+    }
+    if (dst == nullptr || !live || k >= stages) return;
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+      *(Oct*)(dst + (((long long)slab * 2 * stages + 2LL * k + p) * v + row) * 64 + ch * 16) = o[p];
+  };
+  if (dst != nullptr || guard) {
+#pragma unroll
+    for (int it = 0; it < SPLIT_KEEP; ++it) put(x[it][0], x[it][1], it * 16 + sub);
+    for (int k = SPLIT_KEEP * 16 + sub; live && k < stages; k += 16)
+      put(*(const f32x4_t*)(s + (long long)k * 128), *(const f32x4_t*)(s + (long long)k * 128 + 16), k);
+  }
+  if (guard) {
+    small += __shfl_xor(small, 1); small += __shfl_xor(small, 2); small += __shfl_xor(small, 32);
+    if ((lane & 35) == 0) s_small[wave][rl] = small;
+    __syncthreads();
+    small = 0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) small += s_small[w][rl];
+    bad |= small > d / 16;
+  }
+  if (live && ch == 0 && sub == 0) exps[(long long)slab * v + row] = E;
+  if (live && bad) *flag = 1;
+}
+
+hipError_t launch_split_rows(const void* src, void* dst, long long slabs, int v, int d, long long row_stride, int* exps,
+                             int* flag, int guard, hipStream_t st) {
+  const long long blocks = slabs * ((v + SPLIT_ROWS - 1) / SPLIT_ROWS);
+  hipLaunchKernelGGL(k_split_rows, dim3((unsigned)blocks), dim3(512), 0, st, (const char*)src, (char*)dst, v, d, row_stride, exps,
+                     flag, guard);
+  return hipGetLastError();
 }
 
 __global__ void k_clear_flag(int* flag) { *flag = 0; }
 
-// fp32 operands through their bf16 terms.  Infinite, NaN and huge operands stay with the fp32 instruction, whose sums
-// such values enter once instead of term by term: which of the two launches does the work is known on the
-// device only, the other one's workgroups leave at once (about 5 us).
-static hipError_t launch_split(const UnembedArgs& a, hipStream_t st) {
+// fp32 operands through their fp16 terms.  Operands that those would not do justice stay with the fp32 instruction: which of
+// the two launches does the work is known on the device only, the other one's workgroups leave at once (about 5 us).
+static hipError_t launch_split(const UnembedArgs& a0, hipStream_t st) {
+  UnembedArgs a = a0;
+  const long long slabs = (long long)a.n * a.r;
+  if (a.Wexp == nullptr) a.Wexp = plane_exps(a.Wq, slabs * a.v * a.d);
   hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, st, a.wild);
-  auto split = [&](const void* src, void* dst, long long slabs, int v, long long ld) {
-    const long long chunks = slabs * v * (a.d / 8);
-    hipLaunchKernelGGL(k_split_rows, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, st, (const char*)src, (char*)dst,
-                       slabs, v, a.d, ld * 4, a.wild);
-  };
-  split(a.h, a.hq, 1, a.B, a.ld_h);
-  split(a.W, a.Wq, (long long)a.n * a.r, a.v, a.d);
-  const hipError_t e = launch_train<true, false, true, true>(a, st);
+  hipError_t e = launch_split_rows(a.h, a.hq, 1, a.B, a.d, a.ld_h * 4, plane_exps(a.hq, (long long)a.B * a.d), a.wild, 1, st);
+  if (e == hipSuccess) e = launch_split_rows(a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wexp, a.wild, 1, st);
+  if (e == hipSuccess) e = launch_train<true, false, true, true>(a, st);
   return e != hipSuccess ? e : launch_dt<false, false>(a, st);
 }
 
