@@ -654,7 +654,9 @@ struct BwdPlan {
   long long M, Mx, Mlay, Mtot, ldM, ldb;
   // fp32 as two fp16 terms: in the forward pass (split_pays) and in the two contractions
   bool split_fwd, split;
-  size_t Wq, hq, wild, dslT, big;
+  size_t hq, wild, dslT, big;
+  bool staged;              // the logit gradient stage-major, as the contractions read it
+  bool along_rows;          // bf16: the dh contraction reads W and the logit gradient along their rows
 };
 
 BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly, bool keep_phi, bool split = true) {
@@ -690,12 +692,36 @@ BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly,
   if (q.split) q.big = take(4);
   q.dslT = q.split ? take((size_t)(q.Mx - q.M) * q.ldb * esz) : q.dLT + (size_t)q.M * q.ldb * esz;
   q.dL = take(B * q.ldM * osz);
+  // (stage-major when one kernel writes every element of both layouts - no layer-logit columns from elsewhere - and one
+  // 32-bit buffer resource spans each)
+  q.staged = q.split || (keep_phi && !q.ctx && (unsigned long long)q.M * q.ldb * esz < lim && (unsigned long long)B * q.ldM * esz < lim);
+  q.ksplit = gemm_ksplit(hd->B, hd->d, (int)q.ldM);
+  q.kchunk = (int)q.ldM;
+  if (q.ksplit > 1) {
+    q.kchunk = (int)(((q.ldM + q.ksplit - 1) / q.ksplit + 63) / 64 * 64);
+    q.ksplit = (int)((q.ldM + q.kchunk - 1) / q.kchunk);
+  }
+  // Operands along their rows: dLT with the sum-unit rows and zeros up to ldM behind the others, which - like the sum-unit rows
+  // in a layout of their own - take the room of the dL that is then not needed.
+  if (q.staged && !q.split && hd->dtype == MTPC_BF16 && (unsigned long long)q.ldM * q.ldb * 2 < lim && (unsigned long long)q.ldM * hd->d * 2 < lim) {
+    const size_t own = up(q.dLT + (size_t)q.ldM * q.ldb * 2);
+    // What it saves: the transpose of W, the other layout of the gradient (4.2 TB/s) and a launch.  What it costs: a stage of 32 rows
+    // takes 0.05 us longer where all CUs are busy (n r v = 327,680, d = 3072, B = 4096: 22.3 ms without, 21.0 ms with it), up to
+    // 0.28 us where they wait for their loads (n r v = 2880, d = 1408, B = 2548: 169, 177 us; 804, 1664, 4726: 166, 172 us;
+    // 47,168, 320, 350: 308, 303 us).
+    const double tiles = (double)((hd->B + 255) / 256) * ((hd->d + 255) / 256) * q.ksplit;
+    const double stages = std::ceil(tiles / 256) * (q.kchunk / 32);
+    const double saved = ((double)q.M * hd->d * 4 + (double)q.M * hd->B * 2) / 4.2e6 + 4;
+    if (own + (size_t)(q.Mx - q.M) * q.ldb * 2 <= q.dL + B * q.ldM * 2 && saved > stages * (tiles >= 256 ? 0.05 : 0.28)) {
+      q.along_rows = true;
+      q.dslT = own;
+    }
+  }
   q.WT = take((size_t)hd->d * q.ldM * osz);
   q.hT = take((size_t)hd->d * q.ldb * esz);
-  if (q.split_fwd) {
+  if (q.split_fwd) {                          // (the planes of W are those the dh contraction reads: in WT)
     q.wild = take(4);
     q.hq = take(B * (size_t)hd->d * 6);
-    q.Wq = take((size_t)q.M * hd->d * 6);
   }
   q.has_hs = !q.split_fwd && stage_major_h_pays(hd);
   q.hs = q.has_hs ? take(B * (size_t)hd->d * esz) : 0;
@@ -722,13 +748,7 @@ BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly,
   // fp32 accumulation of per-position layer-logit gradients: the tree, or one R for all steps
   if (q.ctx && (family == MTPC_BTREE || (q.Lst == 1 && L > 1))) q.dlog32 = take(B * (size_t)q.Lst * r * r * 4);
   if (keep_phi) q.phi = take((size_t)q.M * q.ldb * 4);
-  q.ksplit = gemm_ksplit(hd->B, hd->d, (int)q.ldM);
-  q.kchunk = (int)q.ldM;
-  if (q.ksplit > 1) {
-    q.kchunk = (int)(((q.ldM + q.ksplit - 1) / q.ksplit + 63) / 64 * 64);
-    q.ksplit = (int)((q.ldM + q.kchunk - 1) / q.kchunk);
-    q.partial = take((size_t)q.ksplit * B * hd->d * 4);
-  }
+  if (q.ksplit > 1) q.partial = take((size_t)q.ksplit * B * hd->d * 4);
   q.total = off;
   return q;
 }
@@ -800,9 +820,12 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   UnembedArgs u = unembed_args(hd);
   u.targets = targets; u.T = 1; u.e = (float*)(ws + q.e);
   if (q.keep_phi) { u.phiT = (float*)(ws + q.phi); u.ld_phi = q.ldb; }
-  // (exponents of the rows of W and Wsum, for the forward pass and the contraction over them: behind the planes of WT)
+  // (planes of W and, behind them, Wsum, one matrix of ldM rows for the forward pass and the contraction over them: in WT)
   int* const wexp = q.split ? plane_exps(ws + q.WT, hd->d * q.ldM) : nullptr;
-  if (q.split_fwd) { u.Wq = ws + q.Wq; u.hq = ws + q.hq; u.wild = (int*)(ws + q.wild); u.Wexp = wexp; }
+  if (q.split_fwd) {
+    u.Wq = ws + q.WT; u.Wq_rows = (int)q.ldM; u.Wexp = wexp;
+    u.hq = ws + q.hq; u.wild = (int*)(ws + q.wild);
+  }
   HIP_TRY(stage_major_h(hd, q.has_hs, q.hs, u, st));
   HIP_TRY(launch_unembed(u, hd->dtype, st));
 
@@ -839,11 +862,19 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   }
   HIP_TRY(launch_circuit_bwd(c, st));
 
-  // ---- logit gradient in both layouts: dLT [.][ldb] and dL = dLT^T [B][ldM]
-  // (stage-major, as the contractions read their 320-row operands, when this kernel writes every element of
-  // both - no layer-logit columns from elsewhere - and one 32-bit buffer resource spans each)
-  const bool grads_staged = q.split || (q.keep_phi && !ctx && (unsigned long long)q.M * q.ldb * esz < (1ull << 32) &&
-                                        (unsigned long long)hd->B * q.ldM * esz < (1ull << 32));
+  // ---- [W; Wsum] as an operand read along its rows: in fp32 as planes (all rows the forward pass has not split), in bf16 W
+  // itself and, in WT, a copy of the rows beyond its whole stages
+  const int kmain = (int)(q.M / 32 * 32);
+  if (q.split) {
+    TransposeArgs w{};
+    w.along_rows = 1; w.planes = 1; w.big = big; w.exps = wexp;
+    w.src = hd->W; w.ld_src = hd->d; w.R = (int)q.M; w.C = hd->d; w.Rpad = (int)q.ldM;
+    w.src2 = hd->Wsum; w.R2 = (int)(q.Mx - q.M);
+    w.row0 = q.split_fwd ? (int)q.M : 0;
+    w.dst = ws + q.WT;
+    HIP_TRY(launch_transpose(w, hd->dtype, st));
+  }
+  // ---- logit gradient in both layouts: dLT [.][ldb] and dL = dLT^T [B][ldM] (the first one only where that is read along its rows)
   TransposeArgs t{};
   if (q.keep_phi) {
     GradPhiArgs g{};
@@ -852,13 +883,11 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
     g.M = q.M; g.Mx = q.Mx; g.ldM = q.ldM; g.ldb = q.ldb;
     g.dl_end = ctx ? q.Mlay : q.ldM;           // the layer-logit columns are written by the reverse pass
     g.dLT = ws + q.dLT; g.dL = ws + q.dL;
-    g.staged = grads_staged;
+    g.staged = q.staged;
     g.planes = q.split; g.big = big; g.dslT = ws + q.dslT;
-    if (q.split) {
-      g.Wexp = wexp; g.d = hd->d;
-      g.W = q.split_fwd ? nullptr : hd->W;
-      g.Wsum = family == MTPC_FF ? nullptr : hd->Wsum;
-    }
+    g.Wexp = wexp; g.wild = q.split_fwd ? (const int*)(ws + q.wild) : nullptr;
+    g.rows_only = q.along_rows;
+    if (q.along_rows) { g.W = hd->W; g.Wsum = hd->Wsum; g.d = hd->d; g.tail_row = kmain; g.tail = ws + q.WT; }
     HIP_TRY(launch_grad_from_phi(g, hd->dtype, st));
   } else {
     GradLogitsArgs g{};
@@ -878,23 +907,21 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
     t.dst = ws + q.dLT + (size_t)q.Mlay * q.ldb * esz; t.ld_dst = q.ldb; t.col0 = 0; t.Rpad = (int)q.ldb;
     HIP_TRY(launch_transpose(t, hd->dtype, st));
   }
-  // ---- WT = [W; Wsum; (gap); R]^T [d][ldM], hT = h^T [d][ldb]
+  // ---- WT = [W; Wsum; (gap); R]^T [d][ldM] (where W is not read along its rows), hT = h^T [d][ldb]
   // WT is read by the dh contraction only, as its 256-row operand: written stage-major straight away
   // (64-byte stages, [ldM * esz / 64][d][64 bytes]) when one 32-bit buffer resource spans it
-  const bool wt_staged = (unsigned long long)hd->d * q.ldM * esz < (1ull << 32);
+  const bool w_rows = q.split || q.along_rows;
+  const bool wt_staged = !w_rows && (unsigned long long)hd->d * q.ldM * esz < (1ull << 32);
   t.stage_rows = wt_staged ? hd->d : 0;
-  t.planes = q.split; t.big = big;
-  t.src = hd->W; t.ld_src = hd->d; t.R = (int)q.M; t.C = hd->d;
-  t.dst = ws + q.WT; t.ld_dst = q.ldM; t.col0 = 0; t.Rpad = (int)(family == MTPC_FF || q.split ? q.ldM : q.M);
-  if (q.split) {                              // (W and Wsum at once)
-    t.exps = wexp;
-    t.src2 = hd->Wsum; t.R2 = (int)(q.Mx - q.M);
-  }
-  HIP_TRY(launch_transpose(t, hd->dtype, st));
-  if (family != MTPC_FF && !q.split) {
-    t.src = hd->Wsum; t.ld_src = hd->d; t.R = hd->r; t.C = hd->d;
-    t.col0 = q.M; t.Rpad = (int)((ctx ? q.Mlay : q.ldM) - q.M);
+  if (!w_rows) {
+    t.src = hd->W; t.ld_src = hd->d; t.R = (int)q.M; t.C = hd->d;
+    t.dst = ws + q.WT; t.ld_dst = q.ldM; t.col0 = 0; t.Rpad = (int)(family == MTPC_FF ? q.ldM : q.M);
     HIP_TRY(launch_transpose(t, hd->dtype, st));
+    if (family != MTPC_FF) {
+      t.src = hd->Wsum; t.ld_src = hd->d; t.R = hd->r; t.C = hd->d;
+      t.col0 = q.M; t.Rpad = (int)((ctx ? q.Mlay : q.ldM) - q.M);
+      HIP_TRY(launch_transpose(t, hd->dtype, st));
+    }
   }
   if (ctx) {
     t.src = ly->R; t.ld_src = hd->d; t.R = (int)(q.Lst * rr); t.C = hd->d;
@@ -904,12 +931,12 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   t.stage_rows = t.planes = 0;                // hT also feeds the small dWsum kernel: plain, plus a stage-major copy
   t.src = hd->h; t.ld_src = hd->ld_h; t.R = hd->B; t.C = hd->d;
   t.dst = ws + q.hT; t.ld_dst = q.ldb; t.col0 = 0; t.Rpad = (int)q.ldb;
-  HIP_TRY(launch_transpose(t, hd->dtype, st));
   if (q.split) {
-    t.dst = ws + q.hTs; t.stage_rows = hd->d; t.planes = 1;
-    t.exps = nullptr; t.plain = ws + q.hT; t.ld_plain = q.ldb;
-    HIP_TRY(launch_transpose(t, hd->dtype, st));
-  } else if (q.has_hTs)
+    t.plain = t.dst; t.ld_plain = q.ldb;
+    t.dst = ws + q.hTs; t.stage_rows = hd->d; t.planes = 1; t.big = big;
+  }
+  HIP_TRY(launch_transpose(t, hd->dtype, st));
+  if (!q.split && q.has_hTs)
     HIP_TRY(launch_pack_rows(ws + q.hT, ws + q.hTs, 1, hd->d, (int)(q.ldb * esz), q.ldb * (long long)esz, H_STAGE_BYTES, st));
 
   // ---- the two contractions
@@ -917,9 +944,20 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   m.A = ws + q.dL; m.lda = q.ldM; m.M = hd->B;                   // dh[b][k] = sum_m dL[b][m] WT[k][m]
   m.Bm = ws + q.WT; m.ldb = q.ldM; m.N = hd->d; m.K = (int)q.ldM;
   m.Bs = wt_staged ? ws + q.WT : nullptr;
-  m.As = grads_staged ? ws + q.dL : nullptr; m.As_rows = hd->B;
+  m.As = q.staged ? ws + q.dL : nullptr; m.As_rows = hd->B;
   m.planes = q.split;
-  m.Ae = q.split ? plane_exps(ws + q.dL, hd->B * q.ldM) : nullptr;
+  if (q.split) {                                                 // planes of dL; W along its rows
+    m.Ae = plane_exps(ws + q.dL, hd->B * q.ldM);
+    m.Bs = ws + q.WT;
+    m.Bk.base = ws + q.WT; m.Bk.row = 64; m.Bk.term = (unsigned)(q.ldM * 64); m.Bk.chunk = 2 * m.Bk.term;
+    m.Bk.bytes = (unsigned)(hd->d * q.ldM * 4); m.Bk.kmain = (int)q.ldM;
+  } else if (q.along_rows) {
+    m.Ak.base = ws + q.dLT; m.Ak.row = 64; m.Ak.chunk = (unsigned)(q.ldM * 64); m.Ak.bytes = (unsigned)(q.ldM * q.ldb * 2);
+    m.Ak.kmain = (int)q.ldM;
+    m.Bk.base = hd->W; m.Bk.row = (unsigned)hd->d * 2; m.Bk.chunk = 64; m.Bk.bytes = (unsigned)((long long)kmain * hd->d * 2);
+    m.Bk.kmain = kmain;
+    m.Bk.tail = ws + q.WT; m.Bk.tail_bytes = (unsigned)((q.ldM - kmain) * hd->d * 2);
+  }
   m.C = dh; m.ldc = hd->d; m.split = hd->B; m.n2 = 0; m.C2 = nullptr; m.split3 = 0x7fffffff; m.C3 = nullptr;
   m.ksplit = q.ksplit; m.kchunk = q.kchunk; m.partial = q.ksplit > 1 ? (float*)(ws + q.partial) : nullptr;
   HIP_TRY(launch_gemm_tn(m, hd->dtype, st));
@@ -933,7 +971,8 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   m.A = ws + q.dLT; m.lda = q.ldb; m.M = (int)(own_dwsum ? q.M : q.Mtot);
   m.Bm = ws + q.hT; m.ldb = q.ldb; m.N = hd->d; m.K = (int)q.ldb;
   m.Bs = q.has_hTs ? ws + q.hTs : nullptr;
-  m.As = grads_staged ? ws + q.dLT : nullptr; m.As_rows = (int)q.M;
+  m.As = q.staged ? ws + q.dLT : nullptr; m.As_rows = (int)(q.along_rows ? q.ldM : q.M);
+  m.Ak = m.Bk = KRows{};
   if (q.split) {
     m.Ae = plane_exps(ws + q.dLT, q.M * q.ldb);
     m.Be = plane_exps(ws + q.hTs, hd->d * q.ldb);

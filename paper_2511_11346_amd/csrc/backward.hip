@@ -87,48 +87,127 @@ __global__ __launch_bounds__(256) void k_transpose_vec(const TransposeArgs a) {
   }
 }
 
-// Planes of two fp16 terms (split2) of [src; src2]^T, whose rows give up the scales that a.exps holds, stage-major with
-// a.stage_rows rows: [2 columns/32][stage_rows][64 bytes].  64 x 64 tiles through LDS; a thread splits eight neighbours along
-// the contraction, 16 bytes of each plane.
-__global__ __launch_bounds__(256) void k_transpose_planes(const TransposeArgs a) {
-  __shared__ float tile[64][64 + 1];
-  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
-  unsigned short* dst = (unsigned short*)a.dst;
+// src^T in fp32 (a.plain) and, as planes of two fp16 terms with scales of its rows (split2), in a.dst.  A workgroup takes 16
+// columns of src, all R rows, once: 64 bytes of each of 16 rows at a time through LDS; the largest value of a column is known
+// when its last row has passed, and the columns, read back, are split.
+__global__ __launch_bounds__(256) void k_transpose_split(const TransposeArgs a, int* __restrict__ exps) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+  constexpr int U = 4;                               // steps of 64 rows in flight
+  __shared__ float tile[16][64 * U + 1];
+  __shared__ unsigned s_max[16];
+  const int tid = threadIdx.x, c0 = blockIdx.x * 16;
+  const float* const src = (const float*)a.src;
+  float* const plain = (float*)a.plain;
+  if (tid < 16) s_max[tid] = 0;
   bool bad = false;
-  {
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    const int c = c0 + tx;
+  for (int r0 = 0; r0 < a.Rpad; r0 += 64 * U) {
+    // four threads to the 64 bytes of a row
+    f32x4_t x[U];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const int r = r0 + ty + 4 * k;
-      float x = 0.f;
-      if (c < a.C && r < a.R + a.R2) {
-        const float* row = r < a.R ? (const float*)a.src + (long long)r * a.ld_src : (const float*)a.src2 + (long long)(r - a.R) * a.ld_src;
-        x = __builtin_amdgcn_ldexpf(row[c], -a.exps[r]);
-        bad |= !(fabsf(x) <= 65504.f);
-      }
-      tile[ty + 4 * k][tx] = x;
+    for (int u = 0; u < U; ++u) {
+      const int r = r0 + 64 * u + (tid >> 2);
+      x[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      if (r < a.R) x[u] = *(const f32x4_t*)(src + (long long)r * a.ld_src + c0 + 4 * (tid & 3));
     }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) tile[4 * (tid & 3) + c][64 * u + (tid >> 2)] = x[u][c];
+    __syncthreads();
+    // 16 threads to a column, four neighbouring rows each
+    const int c = tid >> 4;
+    unsigned m = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int rl = 64 * u + 4 * (tid & 15), r = r0 + rl;
+      f32x4_t y;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        y[t] = tile[c][rl + t];
+        const unsigned v = __float_as_uint(y[t]) & 0x7fffffffu;
+        bad |= v >= 0x7f800000u;
+        m = max(m, v < 0x7f800000u ? v : 0u);
+      }
+      if (r < a.Rpad) *(f32x4_t*)(plain + (long long)(c0 + c) * a.ld_plain + r) = y;
+    }
+    if (m != 0) atomicMax(&s_max[c], m);
   }
   if (bad) *a.big = 1;
-  __syncthreads();
-  // four threads write the 64 bytes of a row of one plane
-  const int ch = threadIdx.x & 3, cc = threadIdx.x >> 2;
-  const int c = c0 + cc;
-  if (c >= a.C) return;
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int rl = half * 32 + ch * 8, r = r0 + rl;
-    if (r >= a.Rpad) continue;
+  __syncthreads();                                   // (and the workgroup's stores are visible to it)
+  // four threads to the 64 bytes of a column's stage, 16 columns behind each other
+  const int c = (tid >> 2) & 15, ch = tid & 3;
+  const int E = split_exp(__uint_as_float(s_max[c]));
+  if (tid < 64 && ch == 0) exps[c0 + c] = E;
+  const float* const col = plain + (long long)(c0 + c) * a.ld_plain + ch * 8;
+  unsigned short* const dst = (unsigned short*)a.dst + (long long)(c0 + c) * 32 + ch * 8;
+  for (int k = tid >> 6; k < a.Rpad / 32; k += 4) {
+    const f32x4_t y0 = *(const f32x4_t*)(col + k * 32), y1 = *(const f32x4_t*)(col + k * 32 + 4);
     struct alignas(16) Oct { unsigned short v[8]; } o[2];
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       unsigned short q[2];
-      split2(tile[rl + t][cc], q);
+      split2(__builtin_amdgcn_ldexpf(t < 4 ? y0[t & 3] : y1[t & 3], -E), q);
       o[0].v[t] = q[0]; o[1].v[t] = q[1];
     }
 #pragma unroll
-    for (int p = 0; p < 2; ++p) *(Oct*)(dst + (((long long)(r / 32) * 2 + p) * a.stage_rows + c) * 32 + r % 32) = o[p];
+    for (int p = 0; p < 2; ++p) *(Oct*)(dst + (2LL * k + p) * a.stage_rows * 32) = o[p];
+  }
+}
+
+// The logit gradient from the stored probabilities where only dLT is wanted: no transpose, so no LDS.  A thread takes eight
+// neighbouring positions of a row, 16 threads 512 bytes of probabilities, a wave four rows: 256 bytes of each of four chunks of
+// dLT.  A workgroup takes 128 positions of `rows` rows, 16 at a time.  Bound by memory: 8.1 GB in 1.73 ms (4.7 TB/s) where both layouts
+// take 10.7 GB and 2.30 ms (n r v = 327,680, B = 4096); with 32 positions of 16 rows to a wave - lines of probabilities 16 KB apart -
+// it took 2.07 ms.
+// The workgroups behind those write the rows of [W; Wsum; 0] from tail_row on, which the contraction along W's rows reads
+// beside W's whole stages of 32 rows.
+__global__ __launch_bounds__(256) void k_grad_rows(const GradPhiArgs a, int rows, int row_blocks) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+  struct alignas(16) Oct { unsigned short v[8]; };
+  if ((int)blockIdx.y >= row_blocks) {
+    const long long t = ((long long)(blockIdx.y - row_blocks) * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
+    const int per = a.d / 8;
+    const long long m = a.tail_row + t / per, c = t % per * 8;
+    if (m >= a.ldM) return;
+    Oct o{};
+    if (m < a.M) o = *(const Oct*)((const unsigned short*)a.W + m * a.d + c);
+    else if (m < a.Mx) o = *(const Oct*)((const unsigned short*)a.Wsum + (m - a.M) * a.d + c);
+    *(Oct*)((unsigned short*)a.tail + (m - a.tail_row) * a.d + c) = o;
+    return;
+  }
+  const int b = blockIdx.x * 128 + (threadIdx.x & 15) * 8;
+  if (b >= a.ldb) return;
+  unsigned short* const out = (unsigned short*)a.dLT + (long long)(b / 32) * a.ldM * 32 + b % 32;
+  int cur_slab = -1, x[8];
+  float g[8];
+#pragma unroll 4
+  for (int k = 0; k < rows / 16; ++k) {
+    const long long m = (long long)blockIdx.y * rows + k * 16 + (threadIdx.x >> 4);
+    if (m >= a.ldM) return;
+    Oct o{};
+    if (m < a.M) {
+      const f32x4_t* p = (const f32x4_t*)(a.phiT + m * a.ld_phi + b);
+      const f32x4_t p0 = __builtin_nontemporal_load(p), p1 = __builtin_nontemporal_load(p + 1);
+      const int slab = (int)(m / a.v), av = (int)(m - (long long)slab * a.v);
+      if (slab != cur_slab) {
+        cur_slab = slab;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          x[c] = -1; g[c] = 0.f;
+          if (b + c < a.B) {
+            x[c] = a.targets[(long long)(b + c) * a.n + slab / a.r];
+            g[c] = a.Ge[(long long)(b + c) * a.n * a.r + slab];
+          }
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        if (x[c] != -1) o.v[c] = to_bf16_rne(g[c] * ((av == x[c] ? 1.f : 0.f) - (c < 4 ? p0[c & 3] : p1[c & 3])));
+    } else if (m < a.Mx) {
+      o = *(const Oct*)((const unsigned short*)a.dslT + (m - a.M) * a.ldb + b);        // sum-unit rows, written by the reverse pass
+    }
+    *(Oct*)(out + m * 32) = o;
   }
 }
 
@@ -147,30 +226,37 @@ __global__ __launch_bounds__(256) void k_grad_exps(const GradPhiArgs a, int* __r
   __shared__ __align__(16) int s_x[CH];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nr = a.n * a.r;
+  if (blockIdx.x == 0 && tid == 0 && a.wild != nullptr && *a.wild != 0) *a.big = 1;
   if ((int)blockIdx.x < row_blocks) {
     constexpr int RW = 16;                           // rows of a wave (those of the four waves alternate)
     const int parts = (a.v + 63) / 64;
     const int slab = blockIdx.x / parts, r0 = (blockIdx.x - slab * parts) * 64 + wave;
+    if (r0 - wave >= a.v) return;
     const float* phi = a.phiT + (long long)slab * a.v * a.ld_phi;
     float big[RW];
 #pragma unroll
     for (int k = 0; k < RW; ++k) big[k] = 0.f;
+    f32x4_t ph[RW];
+    auto fetch = [&](int b) {                        // (b beyond the last position: any)
+#pragma unroll
+      for (int k = 0; k < RW; ++k) ph[k] = *(const f32x4_t*)(phi + (long long)min(r0 + 4 * k, a.v - 1) * a.ld_phi + min((long long)b, a.ldb - 4));
+    };
     for (int c0 = 0; c0 < a.B; c0 += CH) {
+      fetch(c0 + 4 * lane);                          // (on their way while the gradients are fetched)
       __syncthreads();
 #pragma unroll
       for (int q = 0; q < CH / 256; ++q) {
         const int i = tid + q * 256, b = c0 + i;
-        const int x = b < a.B ? a.targets[(long long)b * a.n + slab / a.r] : -1;
+        const int bc = min(b, a.B - 1);
+        const int x = a.targets[(long long)bc * a.n + slab / a.r];
+        const float g = a.Ge[(long long)bc * nr + slab];
         s_x[i] = x;
-        s_g[i] = x != -1 ? a.Ge[(long long)b * nr + slab] : 0.f;
+        s_g[i] = b < a.B && x != -1 ? g : 0.f;
       }
       __syncthreads();
       for (int i = 4 * lane; i < CH && c0 + i < a.B; i += 256) {
         const f32x4_t g = *(const f32x4_t*)(s_g + i);
         const i32x4_t x = *(const i32x4_t*)(s_x + i);
-        f32x4_t ph[RW];
-#pragma unroll
-        for (int k = 0; k < RW; ++k) ph[k] = *(const f32x4_t*)(phi + (long long)min(r0 + 4 * k, a.v - 1) * a.ld_phi + c0 + i);
 #pragma unroll
         for (int k = 0; k < RW; ++k)
 #pragma unroll
@@ -178,18 +264,46 @@ __global__ __launch_bounds__(256) void k_grad_exps(const GradPhiArgs a, int* __r
             const float y = c0 + i + c < a.B ? fabsf(g[c] * ((r0 + 4 * k == x[c] ? 1.f : 0.f) - ph[k][c])) : 0.f;
             big[k] = y <= 3.402823466e38f ? fmaxf(big[k], y) : big[k];
           }
+        fetch(c0 + i + 256);
       }
     }
+    // the largest of each row over the lanes, rows halved at every exchange: lane l ends up with row l / 4
 #pragma unroll
-    for (int k = 0; k < RW; ++k) {
-      const float y = group_max(big[k], 64);
-      if (lane == 0 && r0 + 4 * k < a.v) rexp[(long long)slab * a.v + r0 + 4 * k] = split_exp(y);
-    }
+    for (int o = 32, R = RW / 2; o >= 4; o >>= 1, R >>= 1)
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const bool up = lane & o;
+        const float mine = up ? big[k + R] : big[k], other = up ? big[k] : big[k + R];
+        big[k] = fmaxf(mine, __shfl_xor(other, o));
+      }
+    const float y = group_max(big[0], 4);
+    const int row = r0 + 4 * (lane >> 2);
+    if ((lane & 3) == 0 && row < a.v) rexp[(long long)slab * a.v + row] = split_exp(y);
     return;
   }
   for (int i = tid; i < nr; i += 256) s_slab[i] = -1000;
   __syncthreads();
-  for (long long m = tid; m < a.M; m += 256) atomicMax(&s_slab[(int)(m / a.v)], a.Wexp[m]);
+  for (int m0 = 8 * tid; m0 < (int)a.M; m0 += 4 * 8 * 256) {
+    int e8[4][8];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) e8[u][c] = a.Wexp[min(m0 + u * 2048 + c, (int)a.M - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      int slab = min(m0 + u * 2048, (int)a.M - 1) / a.v, e = -1000;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int at = min(m0 + u * 2048 + c, (int)a.M - 1) / a.v;
+        if (at != slab) {
+          atomicMax(&s_slab[slab], e);
+          slab = at; e = -1000;
+        }
+        e = max(e, e8[u][c]);
+      }
+      atomicMax(&s_slab[slab], e);
+    }
+  }
   __syncthreads();
   const int b = ((int)blockIdx.x - row_blocks) * 16 + (tid >> 4), t = tid & 15;
   const int r2 = (int)(a.Mx - a.M);
@@ -1100,11 +1214,16 @@ __global__ __launch_bounds__(256) void k_fill_zero(float* p, long long n) {
 hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t st) {
   if (a.C < 1 || a.Rpad < 1) return hipSuccess;
   const dim3 grid((a.C + 63) / 64, (a.Rpad + 63) / 64);
+  if (a.along_rows) {
+    if (dtype != MTPC_F32 || !a.planes || a.ld_src != a.C) return hipErrorInvalidValue;
+    if (a.row0 >= a.Rpad) return hipSuccess;
+    const char* src = (const char*)a.src + (long long)a.row0 * a.C * 4;
+    return launch_split_rows(src, (char*)a.dst + a.row0 * 64LL, 1, a.Rpad - a.row0, a.C, a.C * 4LL, a.exps + a.row0, a.big, 0, st, a.Rpad,
+                             a.R - a.row0, a.src2, a.R2);
+  }
   if (a.planes) {
-    if (dtype != MTPC_F32 || a.stage_rows != a.C || a.col0 != 0 || a.Rpad % 32 != 0) return hipErrorInvalidValue;
-    if (a.exps == nullptr)
-      return launch_split_rows(a.plain, a.dst, 1, a.C, a.Rpad, a.ld_plain * 4, plane_exps(a.dst, (long long)a.C * a.Rpad), a.big, 0, st);
-    hipLaunchKernelGGL(k_transpose_planes, grid, dim3(256), 0, st, a);
+    if (dtype != MTPC_F32 || a.stage_rows != a.C || a.C % 16 != 0 || a.col0 != 0 || a.Rpad % 32 != 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_transpose_split, dim3(a.C / 16), dim3(256), 0, st, a, plane_exps(a.dst, (long long)a.C * a.Rpad));
     return hipGetLastError();
   }
   const int esz = dtype == MTPC_BF16 ? 2 : 4, ve = 16 / esz;
@@ -1122,13 +1241,16 @@ hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t st) {
 
 hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st) {
   const dim3 grid((unsigned)((a.ldb + 127) / 128), (unsigned)((a.ldM + 63) / 64));
-  if (dtype == MTPC_BF16) hipLaunchKernelGGL(k_grad_from_phi<unsigned short>, grid, dim3(256), 0, st, a, nullptr, nullptr);
+  if (a.rows_only) {
+    if (dtype != MTPC_BF16 || !a.staged) return hipErrorInvalidValue;
+    const long long cols = (a.ldb + 127) / 128;
+    int rows = 256;                                  // fewer where that leaves CUs without a workgroup
+    while (rows > 16 && cols * ((a.ldM + rows - 1) / rows) < 1024) rows /= 2;
+    const long long row_blocks = (a.ldM + rows - 1) / rows;
+    const long long tail_blocks = ((a.ldM - a.tail_row) * (a.d / 8) + 256 * cols - 1) / (256 * cols);
+    hipLaunchKernelGGL(k_grad_rows, dim3((unsigned)cols, (unsigned)(row_blocks + tail_blocks)), dim3(256), 0, st, a, rows, (int)row_blocks);
+  } else if (dtype == MTPC_BF16) hipLaunchKernelGGL(k_grad_from_phi<unsigned short>, grid, dim3(256), 0, st, a, nullptr, nullptr);
   else if (a.planes) {
-    hipError_t e = hipSuccess;
-    if (a.W != nullptr) e = launch_split_rows(a.W, nullptr, 1, (int)a.M, a.d, a.d * 4LL, a.Wexp, a.big, 0, st);
-    if (e == hipSuccess && a.Wsum != nullptr)
-      e = launch_split_rows(a.Wsum, nullptr, 1, (int)(a.Mx - a.M), a.d, a.d * 4LL, a.Wexp + a.M, a.big, 0, st);
-    if (e != hipSuccess) return e;
     int* const rexp = plane_exps(a.dLT, a.M * a.ldb);
     int* const bexp = plane_exps(a.dL, a.B * a.ldM);
     const int rb = a.n * a.r * ((a.v + 63) / 64), bb = (a.B + 15) / 16;

@@ -108,7 +108,10 @@ hipError_t launch_unembed_grad(const GradLogitsArgs& a, int dtype, hipStream_t s
 
 // ---------------------------------------------------------------------------
 // SPLIT: fp32 operands as planes of two fp16 terms (tile_gemm_run_split), both stage-major.
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool ASTAGED, bool SPLIT = false>
+// KR: operands given along their rows (TileFeed::open_rows): transposed on the way from LDS into registers, where a
+// transposed copy of W (2.0 GB in, 2.0 GB out, 1.04 ms for n r = 1024, d = 3072) and a second layout of the logit gradient would
+// only serve this product.
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool ASTAGED, bool SPLIT = false, int KR = 0>
 __global__ __launch_bounds__(WV * WB * 64)
 void k_gemm_tn(const GemmArgs a) {
   using TL = Tile<WV, WB, VB, PB, SB, NS>;
@@ -139,8 +142,12 @@ void k_gemm_tn(const GemmArgs a) {
     t.klen = min(a.kchunk, a.K - t.k0);
     return t;
   };
-  TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, ASTAGED, false, 0, SPLIT> feed;
+  TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, ASTAGED, false, 0, SPLIT, 0, KR> feed;
   auto open = [&](const Where& t) {
+    if constexpr (KR != 0) {
+      feed.open_rows(a.As, a.As_rows, a.Ak, a.M, t.slab * TL::TV, a.Bk, a.N, t.b0, t.k0, t.klen, smem);
+      return;
+    }
     if constexpr (SPLIT) {
       const long long s0 = (long long)(t.k0 / 32) * 2;             // (chunks are multiples of 64 columns)
       feed.open((const char*)a.As + s0 * a.As_rows * 64, 0, a.Bm, 0, a.N, 2 * t.klen, t.rows, 0, t.b0, smem, nullptr, 0, 1,
@@ -244,14 +251,14 @@ void k_gemm_tn(const GemmArgs a) {
   }
 }
 
-template <int WV, int WB, int VB, int PB, bool BF16, bool ASTAGED = false, bool SPLIT = false>
+template <int WV, int WB, int VB, int PB, bool BF16, bool ASTAGED = false, bool SPLIT = false, int KR = 0>
 static hipError_t launch_gemm_cfg(const GemmArgs& a, hipStream_t st) {
   using TL = Tile<WV, WB, VB, PB, 64, 4>;
   if constexpr (!BF16 && !ASTAGED)
     if (a.planes) return launch_gemm_cfg<WV, WB, VB, PB, true, true, true>(a, st);
-  if constexpr (!ASTAGED)
+  if constexpr (!ASTAGED && KR == 0)
     if (a.As != nullptr) return launch_gemm_cfg<WV, WB, VB, PB, BF16, true>(a, st);
-  constexpr auto kern = k_gemm_tn<WV, WB, VB, PB, 64, 4, BF16, ASTAGED, SPLIT>;
+  constexpr auto kern = k_gemm_tn<WV, WB, VB, PB, 64, 4, BF16, ASTAGED, SPLIT, KR>;
   constexpr int smem = TL::SMEM + (SPLIT ? TL::ROWS * 4 : 0);
   static_assert(smem <= 160 * 1024, "LDS budget of one CU");
   if (hipError_t e = allow_lds<kern>(smem); e != hipSuccess) return e;
@@ -287,6 +294,10 @@ static hipError_t launch_gemm_dt(const GemmArgs& a, hipStream_t st) {
     const double rounds = wgs >= 1024 ? wgs / 256.0 : (double)(long long)((wgs + 255) / 256);
     return rounds * rows * gain;
   };
+  if (a.Bk.base != nullptr) {
+    if constexpr (BF16) return a.Ak.base != nullptr ? launch_gemm_cfg<2, 4, 4, 2, true, false, false, 3>(a, st) : hipErrorInvalidValue;
+    else return a.planes ? launch_gemm_cfg<2, 4, 4, 2, true, true, true, 2>(a, st) : hipErrorInvalidValue;
+  }
   if (a.ksplit == 1 && cost(320, 0.93) < cost(256, 1.0)) return launch_gemm_cfg<2, 4, 5, 2, BF16>(a, st);
   return launch_gemm_cfg<2, 4, 4, 2, BF16>(a, st);
 }
@@ -344,9 +355,27 @@ __global__ __launch_bounds__(256) void k_gemm_nonfinite(const GemmArgs a0, const
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[ch * 8 + e][lr] = s[e];
       };
+      // the second operand along its rows: 32 rows of 64 columns, eight neighbouring columns of one row to a thread
+      auto load_rows = [&](float (&x)[32][64 + 1], const KRows& m, int k) {
+        const int row = threadIdx.x >> 3, col = col0 + (threadIdx.x & 7) * 8;
+        float s[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[e] = 0.f;
+        if (col < a.N)
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            struct alignas(16) Oct { unsigned short v[8]; };
+            const Oct o = *(const Oct*)((const char*)m.base + (size_t)p * m.term + (size_t)(col / 32) * m.chunk + (size_t)(32 * k + row) * m.row + col % 32 * 2);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s[e] += (float)__builtin_bit_cast(_Float16, o.v[e]);
+          }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[row][(threadIdx.x & 7) * 8 + e] = s[e];
+      };
       for (int k = 0; k < a.K / 32; ++k) {
         load(xa, a.As, a.As_rows, row0 + lr, a.M, k);
-        load(xb, a.Bs, a.N, col0 + lr, a.N, k);
+        if (a.Bk.base != nullptr) load_rows(xb, a.Bk, k);
+        else load(xb, a.Bs, a.N, col0 + lr, a.N, k);
         __syncthreads();
 #pragma unroll 4
         for (int q = 0; q < 32; ++q) {

@@ -48,6 +48,7 @@ struct UnembedArgs {
   void* hq;
   int* wild;
   int* Wexp;            // where the exponents of W's rows go, [n*r*v], or nullptr: behind its planes
+  int Wq_rows;          // > 0: the planes of W are ONE matrix of so many rows, [2 d/32][Wq_rows][64 bytes], slab after slab
 };
 
 // Univariate marginals: M[b][i][a] = log sum_j m[b][i][j] phi[b][i][j][a].
@@ -114,10 +115,12 @@ hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t st)
 // Exponents of the rows of a matrix stored as planes of two fp16 terms of `elements` values: right behind them.  (Planes
 // have room for six bytes per value in every workspace: four are the terms.)
 inline int* plane_exps(void* planes, long long elements) { return (int*)((char*)planes + 4 * elements); }
-// fp32 rows as planes of two fp16 terms (unembed.hip, k_split_rows): `slabs` matrices of v rows, each [2 d/32][v][64 bytes], and
-// the exponents of all rows; dst nullptr: the exponents only
+// fp32 rows as planes of two fp16 terms (unembed.hip, k_split_rows): `slabs` matrices of v rows, each [2 d/32][v][64 bytes] or,
+// with dst_rows > 0, all rows of one matrix of so many, and the exponents of all rows.  Rows from `rows1` on (one slab) are
+// the `rows2` of src2 and then zeros
 hipError_t launch_split_rows(const void* src, void* dst, long long slabs, int v, int d, long long row_stride, int* exps,
-                             int* flag, int guard, hipStream_t st);
+                             int* flag, int guard, hipStream_t st, long long dst_rows = 0, int rows1 = 0x7fffffff,
+                             const void* src2 = nullptr, int rows2 = 0);
 
 // ---- small kernels (circuits.hip) -----------------------------------------
 // log omega[b][:] = log_softmax(Wsum h[b])
@@ -306,12 +309,28 @@ struct GradPhiArgs {
   int planes;
   const void* dslT;     // the sum-unit rows M..Mx-1 of dLT, [Mx - M][ldb] in the dtype of h
   int* big;             // planes: set to 1 when an element is infinite or NaN
-  int* Wexp;            // planes: exponents of the rows of W and, behind them, of Wsum [Mx]; those of the matrices given
-  const void* W;        // here, [M][d] and [Mx - M][d], are formed first (W nullptr: the forward pass has left them)
+  int* Wexp;            // planes: exponents of the rows of W and, behind them, of Wsum [Mx] (launch_transpose, along_rows)
+  const int* wild;      // planes: the flag of the forward pass that has split W; set, it sets *big; or nullptr
+  // 1 (staged, bf16): no dL; dLT [ldb/32][ldM][64 bytes], the sum-unit rows and zeros behind the others; and rows tail_row ..
+  // ldM - 1 of [W; Wsum; 0], [ldM][d], are copied to `tail`
+  int rows_only;
+  const void* W;
   const void* Wsum;
-  int d;
+  int d, tail_row;
+  void* tail;
 };
 hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st);
+
+// An operand of a contraction given along its rows: K runs down the rows, columns lie in chunks of 32 (64 bytes).  Element
+// (k, 32 c + x) is at base + c * chunk + k * row + 2 x; rows from kmain (a multiple of 32) on come from `tail` instead,
+// rows and chunks the same distances apart.  term (planes of fp16 terms): how far the second term lies behind the first.
+struct KRows {
+  const void* base;
+  const void* tail;
+  unsigned chunk, row, term;
+  unsigned bytes, tail_bytes;
+  int kmain;
+};
 
 // C[M][N] (fp32, row stride ldc; optionally split by rows over two buffers) = A[M][K] * B[N][K]^T, both operands K-contiguous
 // with row strides lda / ldb (elements); K a multiple of 32 (bf16) or 16 (fp32).
@@ -334,6 +353,9 @@ struct GemmArgs {
   int planes;           // fp32 only: As and Bs hold two fp16 terms per value, [2 K/32][rows][64 bytes]
   const int* Ae;        // ... and these the exponents of their rows (nullptr: 0)
   const int* Be;
+  // operands given along their rows instead, their K rows of M and N columns: both (bf16), or the second one beside A's planes.
+  // base nullptr: as above
+  KRows Ak, Bk;
 };
 hipError_t launch_gemm_tn(const GemmArgs& a, int dtype, hipStream_t st);
 // After two products of planes: where *big is set, forms every result that is not finite anew as an fp32 sum of the
@@ -365,12 +387,15 @@ struct TransposeArgs {
   // 1 (fp32, stage_rows set, col0 = 0, Rpad a multiple of 32): two fp16 terms per value, [2 columns/32][stage_rows][64 bytes]
   int planes;
   int* big;             // planes: set to 1 when an element is infinite or NaN
-  // planes of [src; src2]^T without the scales of the rows of src (exps[R]) and src2 (behind them; R2 rows of the same stride) ...
-  const int* exps;
-  const void* src2; int R2;
-  // ... or (exps nullptr) of src^T, whose rows get scales of their own, left behind the planes (plane_exps): from its
-  // transpose in fp32, [C][ld_plain], columns up to Rpad
-  const void* plain; long long ld_plain;
+  // planes: rows of dst get scales of their own, left behind the planes (plane_exps); src^T in fp32 goes to plain, [C][ld_plain],
+  // columns up to Rpad
+  void* plain; long long ld_plain;
+  // no transpose, but [src; src2] (R and R2 rows of C values, dense) and zeros behind them as an operand that is read along its
+  // rows (KRows): planes [2 C/32][Rpad][64 bytes] with the scales of the rows in `exps`, of which the first row0 have been
+  // written (0 or R)
+  int along_rows;
+  const void* src2; int R2; int row0;
+  int* exps;
 };
 hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t st);
 

@@ -195,6 +195,21 @@ __device__ __forceinline__ int swz(int row) {
 // 1^f(8+k) must differ: f = (0, 3, 2, 1).
 __device__ __forceinline__ int swz16(int row) { return (0 - (row >> 2)) & 3; }
 
+// LDS image of an operand given along its rows (KRows): per 64 columns a block of 32 rows of 128 bytes, whose 32-byte pieces (16 columns) are XOR-swizzled so
+// that the eight pieces that half a wave reads at once - four neighbouring rows, and the four eight rows on - lie in
+// different banks.
+__device__ __forceinline__ int swz_krow(int row) { return ((row >> 1) & 1) | (((row >> 3) & 1) << 1); }
+// Fragment of 16 columns and 32 rows from there, transposed on the way into registers: the 16 lanes of a group hand in four
+// rows of 32 bytes, eight bytes each, and every lane gets its column's four.  p: this lane's eight bytes of rows 8 (l / 16) ...
+__device__ __forceinline__ i32x4_t read_krows(const char* p) {
+  typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+  typedef __attribute__((ext_vector_type(2))) int i32x2_t;
+  typedef __attribute__((address_space(3))) s16x4_t* lds_t;
+  const i32x2_t lo = __builtin_bit_cast(i32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)p));
+  const i32x2_t hi = __builtin_bit_cast(i32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)(p + 512)));
+  return i32x4_t{lo[0], lo[1], hi[0], hi[1]};
+}
+
 // Ring buffers of the plane stages of tile_gemm_run_split: both terms of the columns alternate between two.
 constexpr int SPLIT_SLOT_HI = 0, SPLIT_SLOT_LO = 2;
 
@@ -203,8 +218,9 @@ constexpr int SPLIT_SLOT_HI = 0, SPLIT_SLOT_LO = 2;
 // so that a workgroup that walks several tiles can open the next one (the ring is free once the run
 // has returned) before it turns to the epilogue of the one it has just multiplied.
 // SPLIT: the operands are fp32 matrices as planes of two fp16 terms (see tile_gemm_run_split).
+// KR: operands given along their rows (KRows, open_rows): 2 the one of the tile's columns, 3 both; tiles of 256 x 256.
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER = false, bool M16 = false,
-          bool WPACK = false, bool STREAMW = false, int PH = 0, bool SPLIT = false, int VH = 0>
+          bool WPACK = false, bool STREAMW = false, int PH = 0, bool SPLIT = false, int VH = 0, int KR = 0>
 struct TileFeed {
   using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
   static constexpr int ESZ = BF16 ? 2 : 4;
@@ -217,6 +233,9 @@ struct TileFeed {
   unsigned kofsH;                                    // ... and for h, stage-major or not
   unsigned hstep, wstep;
   int wave, hrows;
+  // KR: the rows of srdH that are left, in stages, and where it goes on from there
+  i32x4_t srdT;
+  int hleft;
 
   __device__ __forceinline__ void issue_one(int q, int buf) {   // q-th wave-load of this wave for one stage
     __builtin_assume(wave >= 0 && wave < TL::NW);    // (which loads are W's and which exist is then known per q, mostly)
@@ -237,18 +256,77 @@ struct TileFeed {
       if (STREAMW && isW)
         load_to_lds<true>(voff[q], srdW, WPACK ? kofsW : kofs, lds0 + buf * TL::STAGE + wl * 1024);
       else
-        load_to_lds(voff[q], isW ? srdW : srdH, isW ? (WPACK ? kofsW : kofs) : kofsH, lds0 + buf * TL::STAGE + wl * 1024);
+        load_to_lds(voff[q], isW ? srdW : srdH, isW ? (WPACK || KR == 3 ? kofsW : kofs) : kofsH, lds0 + buf * TL::STAGE + wl * 1024);
     }
   }
   __device__ __forceinline__ void advance() {
-    kofs += SB;
-    if constexpr (WPACK) kofsW += wstep;
+    if constexpr (KR == 0) kofs += SB;
+    if constexpr (WPACK || KR == 3) kofsW += wstep;
     kofsH += hstep;
+    if constexpr (KR != 0 && SPLIT) hstep = kofs - hstep;       // (kofs: the distance of two terms and back, constant here)
+    if constexpr (KR != 0 && !SPLIT) {
+      const bool over = --hleft == 0;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) srdH[i] = over ? srdT[i] : srdH[i];
+      kofsH = over ? 0u : kofsH;
+    }
   }
   __device__ __forceinline__ void issue(int buf) {
 #pragma unroll
     for (int q = 0; q < TL::LPW; ++q) issue_one(q, buf);
     advance();
+  }
+
+  // lane offset of the q-th load of an operand given along its rows: eight rows of 64 columns from column 32 * chunk0 on
+  __device__ __forceinline__ unsigned row_offset(int wl, const KRows& m, int chunk0, int chunks) {
+    const int lane = threadIdx.x & 63;
+    const int row = (wl & 3) * 8 + (lane >> 3), c = (lane & 7) ^ (swz_krow(row) << 1);
+    const int chunk = min(chunk0 + 2 * (wl >> 2) + (c >> 2), chunks - 1);       // (columns that are not there: any)
+    return (unsigned)chunk * m.chunk + (unsigned)row * m.row + (c & 3) * 16;
+  }
+  // KR: columns a0 .. of `ak` (of acols; KR = 3) or rows of the stage-major planes at Ap [2 K/32][arows][64] (KR = 2), columns
+  // b0 .. of `bk` (of bcols), rows k0 .. k0 + klen - 1.  a0, b0, k0 and klen are multiples of 32.
+  __device__ __forceinline__ void open_rows(const void* Ap, int arows, const KRows& ak, int acols, int a0, const KRows& bk, int bcols, int b0,
+                                            int k0, int klen, char* smem) {
+    static_assert(KR == 2 || KR == 3, "");
+    static_assert(TL::TV == 256 && TL::TP == 256 && SB == 64 && TL::LPW == 4, "16 loads of each operand per stage, two and two per wave");
+    const int lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if constexpr (KR == 3) {
+      srdW = make_srd(ak.base, ak.bytes);
+      kofsW = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)k0 * ak.row));
+      wstep = (unsigned)__builtin_amdgcn_readfirstlane((int)(32u * ak.row));
+    } else {
+      srdW = make_srd((const char*)Ap + (long long)(k0 / 32) * 2 * arows * 64, (unsigned)((long long)klen * 4 * arows));
+      kofsW = 0;
+      wstep = (unsigned)__builtin_amdgcn_readfirstlane(arows * 64);
+    }
+    const bool main = k0 < bk.kmain;                   // workgroup-uniform
+    srdT = make_srd(bk.tail, bk.tail_bytes);
+    srdH = main ? make_srd(bk.base, bk.bytes) : srdT;
+    hleft = main ? (bk.kmain - k0) / 32 : 0;
+    kofsH = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(main ? k0 : k0 - bk.kmain) * bk.row));
+    hstep = (unsigned)__builtin_amdgcn_readfirstlane((int)(SPLIT ? bk.term : 32u * bk.row));
+    kofs = (unsigned)__builtin_amdgcn_readfirstlane((int)(32u * bk.row));
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int wl = wave + q * TL::NW;                // loads 0-15 of a stage: the tile's rows, 16-31: its columns
+      if constexpr (KR == 3) voff[q] = row_offset(wl, ak, a0 / 32, (acols + 31) / 32);
+      else {
+        const int row = wl * TL::RPL + lane / CPR, ch = (lane % CPR) ^ swz16(row);
+        voff[q] = (unsigned)min(a0 + row, arows - 1) * SB + ch * 16;
+      }
+      voff[q + 2] = row_offset(wl, bk, b0 / 32, (bcols + 31) / 32);
+    }
+    lds0 = (unsigned)(size_t)smem;
+    if constexpr (SPLIT) {
+      issue(SPLIT_SLOT_HI);
+      issue(SPLIT_SLOT_LO);
+      if (klen > 32) issue(SPLIT_SLOT_HI + 1);
+    } else {
+      for (int s = 0; s < NS - 1; ++s)
+        if (s < klen / 32) issue(s);
+    }
   }
 
   // Arguments as for tile_gemm.  The ring must be free (no wave still reads it).
@@ -309,8 +387,8 @@ struct TileFeed {
 
 // The product of a tile whose feed is open: on return every wave holds its VB x PB accumulator blocks and
 // all waves have passed a barrier (the ring is free).
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER, bool M16, bool WPACK, bool STREAMW, int PH, int VH>
-__device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, false, VH>& feed,
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER, bool M16, bool WPACK, bool STREAMW, int PH, int VH, int KR>
+__device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, false, VH, KR>& feed,
                                               int d, char* smem,
                                               typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB - VH / 2]) {
   using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
@@ -409,15 +487,28 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
     constexpr int NVB16 = 2 * VB - VH / 2;     // 16-row blocks of a wave (group 1: one fewer when VH is odd)
     constexpr int NPB16 = 2 * PB + PH;
     const int b16 = (TL::TV + wb * TL::WP + l15) * SB + ((lq ^ sw16) << 4);
+    // operands along their rows: this lane's row and eight bytes of the first piece; piece p of a 64-column block is at ^ (32 p)
+    static_assert(KR == 0 || (M16 && KR == 3 && TL::WP == 64 && TL::WROWS == 128), "64 columns of one block per wave, 128 rows of two");
+    const int krow = 8 * lq + (l15 >> 2), k16 = krow * 128 + (swz_krow(krow) << 5) + (l15 & 3) * 8;
     i32x4_t ga[NVB16], gb[NPB16];
     bool act16[NPB16];
 #pragma unroll
     for (int pb = 0; pb < NPB16; ++pb) act16[pb] = !GATHER || wb * TL::WP + pb * 16 < hrows;
+    // Operands along their rows take two fragment reads where others take one: the memory cluster is then the longer one, and
+    // the loads, too, leave behind every eighth product instead (dh of n r = 1024, d = 3072, B = 4096: 6.29 / 5.79 ms; with
+    // one read per fragment, 40 products a cluster, 5.7 / 6.3 ms for the evidence pass).
+    constexpr bool LATE = KR == 3;
+    static_assert(!LATE || (TL::LPW == NPB16 && NVB16 == 8), "one load per row of eight products");
     // memory cluster of stage `it`: its fragments, and (LOAD) the loads of stage it+NS-1 into the
     // buffer of stage it-1 (last read before the previous barrier)
     auto mem_cluster = [&](int it, auto load, auto nvb) {
       const char* cur = smem + (it % NS) * TL::STAGE;
-      if constexpr (M16) {
+      if constexpr (KR == 3) {
+#pragma unroll
+        for (int pb = 0; pb < NPB16; ++pb) gb[pb] = read_krows(cur + (TL::TV * SB + wb * 4096) + (k16 ^ ((pb & 3) << 5)));
+#pragma unroll
+        for (int vb = 0; vb < NVB16; ++vb) ga[vb] = read_krows(cur + (wv * 2 + (vb >> 2)) * 4096 + (k16 ^ ((vb & 3) << 5)));
+      } else if constexpr (M16) {
 #pragma unroll
         for (int pb = 0; pb < NPB16; ++pb) gb[pb] = *(const i32x4_t*)(cur + b16 + pb * 16 * SB);
 #pragma unroll
@@ -426,12 +517,12 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
         load_frags(cur, 0, 0);
         load_frags(cur, 1, 1);
       }
-      if constexpr (decltype(load)::value) issue((it + NS - 1) % NS);
+      if constexpr (!LATE && decltype(load)::value) issue((it + NS - 1) % NS);
       __builtin_amdgcn_sched_barrier(0);
     };
     // (a branch between two MFMAs costs about as much as an MFMA: empty position blocks are
     // skipped a whole row of products at a time)
-    auto compute_cluster = [&](auto nvb) {
+    auto compute_cluster = [&](int it, auto load, auto nvb) {
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_setprio(1);
       if constexpr (M16) {
@@ -442,6 +533,12 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
             for (int vb = 0; vb < decltype(nvb)::value; ++vb) {
               mma_step<BF16>(acc[pb][vb], ga[vb], gb[pb]);
               __builtin_amdgcn_sched_barrier(0);
+              if constexpr (LATE && decltype(load)::value)
+                if (vb == 3) {
+                  issue_one(pb, (it + NS - 1) % NS);
+                  if (pb == NPB16 - 1) advance();
+                  __builtin_amdgcn_sched_barrier(0);
+                }
             }
           }
       } else {
@@ -470,9 +567,9 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
       int it = 0;
       for (; it < KM; ++it) {
         mem_cluster(it, std::true_type{}, nvb);
-        if constexpr (G == 1) MTPC_WAIT_VMCNT((NS - 2) * TL::PER);
+        if constexpr (G == 1) MTPC_WAIT_VMCNT((NS - (LATE ? 3 : 2)) * TL::PER);
         barrier();
-        compute_cluster(nvb);
+        compute_cluster(it, std::true_type{}, nvb);
         if constexpr (G == 0) MTPC_WAIT_VMCNT((NS - 2) * TL::PER);
         barrier();
       }
@@ -480,7 +577,7 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
         mem_cluster(it, std::false_type{}, nvb);
         if constexpr (G == 1) MTPC_WAIT_VMCNT(0);
         barrier();
-        compute_cluster(nvb);
+        compute_cluster(it, std::false_type{}, nvb);
         if constexpr (G == 0) MTPC_WAIT_VMCNT(0);
         barrier();
       }
@@ -551,8 +648,8 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
 // Bound by the power of the products and of the two operand stages behind every three of them: 1.45 PFLOP/s of issued products
 // (B = 2048, n r = 256, d = 3072, v = 268: 1.83 ms; three bf16 terms and six products 3.19 ms, the fp32 instruction 7.29 ms;
 // registers only, the fp16 product runs at 1.88 PFLOP/s and the bf16 one at 2.02).
-template <int WV, int WB, int VB, int PB, int SB, int NS, int VH>
-__device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB, NS, true, false, true, true, false, 0, true, VH>& feed,
+template <int WV, int WB, int VB, int PB, int SB, int NS, int VH, int KR>
+__device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB, NS, true, false, true, true, false, 0, true, VH, KR>& feed,
                                                     int d, char* smem, f32x4_t (&acc)[2 * PB][2 * VB - VH / 2]) {
   using TL = Tile<WV, WB, VB, PB, SB, NS, 0, VH>;
   constexpr int NVB16 = 2 * VB - VH / 2;
@@ -573,10 +670,15 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
 #pragma unroll
     for (int vb = 0; vb < decltype(nvb)::value; ++vb) ga[vb] = *(const i32x4_t*)(cur + a16 + vb * 16 * SB);
   };
+  static_assert(KR == 0 || (KR == 2 && TL::WP == 64), "64 columns of one block per wave");
+  const int krow = 8 * lq + (l15 >> 2), k16 = krow * 128 + (swz_krow(krow) << 5) + (l15 & 3) * 8;    // (as in tile_gemm_run)
   auto read_b = [&](int slot) {
     const char* cur = smem + slot * TL::STAGE;
 #pragma unroll
-    for (int pb = 0; pb < 2 * PB; ++pb) gb[pb] = *(const i32x4_t*)(cur + b16 + pb * 16 * SB);
+    for (int pb = 0; pb < 2 * PB; ++pb) {
+      if constexpr (KR == 2) gb[pb] = read_krows(cur + (TL::TV * SB + wb * 4096) + (k16 ^ ((pb & 3) << 5)));
+      else gb[pb] = *(const i32x4_t*)(cur + b16 + pb * 16 * SB);
+    }
   };
   auto barrier = [&]() {
     __builtin_amdgcn_sched_barrier(0);

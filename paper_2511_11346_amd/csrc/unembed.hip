@@ -282,7 +282,8 @@ void k_unembed(const UnembedArgs a) {
   int slab, bt;
   tile_of_block(blockIdx.x, nbt, nslab, slab, bt);
   Feed feed;
-  feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab, bt * TL::TP, smem, nullptr, 0, 1, hstaged);
+  const int wrows = SPLIT ? a.Wq_rows : 0;
+  feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab, bt * TL::TP, smem, nullptr, 0, 1, hstaged, wrows, slab * a.v);
   for (int w = blockIdx.x;;) {
   const int b0 = bt * TL::TP;
   const int wi = slab / a.r, wj = slab - wi * a.r;
@@ -326,7 +327,7 @@ void k_unembed(const UnembedArgs a) {
   if constexpr (WALK)
     if (wnext < ntiles) {
       tile_of_block(wnext, nbt, nslab, slab_next, bt_next);
-      feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab_next, bt_next * TL::TP, smem, nullptr, 0, 1, hstaged);
+      feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab_next, bt_next * TL::TP, smem, nullptr, 0, 1, hstaged, wrows, slab_next * a.v);
     }
 
   if constexpr (!SAMPLE) if (a.targets != nullptr) {
@@ -1177,22 +1178,26 @@ hipError_t launch_pack_rows(const void* src, void* dst, long long slabs, int v, 
 // small - one outlier - and not where a few values of a row happen to be near 0 (one in 16).
 constexpr int SPLIT_ROWS = 8, SPLIT_KEEP = 8;        // rows of a workgroup, steps of 512 columns kept in registers
 __global__ __launch_bounds__(512) void k_split_rows(const char* __restrict__ src, char* __restrict__ dst, int v, int d,
-                                                    long long row_stride, int* __restrict__ exps, int* flag, int guard) {
+                                                    long long row_stride, int* __restrict__ exps, int* flag, int guard,
+                                                    long long dst_rows, int rows1, const char* __restrict__ src2, int rows2) {
   __shared__ unsigned s_max[8][SPLIT_ROWS];
   __shared__ int s_small[8][SPLIT_ROWS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rblocks = (v + SPLIT_ROWS - 1) / SPLIT_ROWS;
   const int slab = blockIdx.x / rblocks, rl = (tid >> 2) & (SPLIT_ROWS - 1);
   const int row = (blockIdx.x - slab * rblocks) * SPLIT_ROWS + rl, ch = tid & 3, sub = tid >> 5;
-  const bool live = row < v;
-  const char* s = src + ((long long)slab * v + min(row, v - 1)) * row_stride + ch * 32;
+  const bool live = row < v, second = row >= rows1, read = live && (!second || row - rows1 < rows2);
+  const char* s = (second ? src2 : src) + ((long long)slab * v + (!read ? 0 : second ? row - rows1 : row)) * row_stride + ch * 32;
+  // stages 2k and 2k + 1 of this thread's 16 bytes
+  const long long srow = dst_rows > 0 ? dst_rows : v;
+  char* const out = dst + ((dst_rows > 0 ? (long long)slab * v : (long long)slab * 2 * (d / 32) * v) + row) * 64 + ch * 16;
   const int stages = d / 32;
   f32x4_t x[SPLIT_KEEP][2];
 #pragma unroll
   for (int it = 0; it < SPLIT_KEEP; ++it) {
     const int k = it * 16 + sub;
     x[it][0] = x[it][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    if (live && k < stages) {
+    if (read && k < stages) {
       x[it][0] = __builtin_nontemporal_load((const f32x4_t*)(s + (long long)k * 128));
       x[it][1] = __builtin_nontemporal_load((const f32x4_t*)(s + (long long)k * 128 + 16));
     }
@@ -1209,7 +1214,7 @@ __global__ __launch_bounds__(512) void k_split_rows(const char* __restrict__ src
   };
 #pragma unroll
   for (int it = 0; it < SPLIT_KEEP; ++it) { look(x[it][0]); look(x[it][1]); }
-  for (int k = SPLIT_KEEP * 16 + sub; live && k < stages; k += 16) {
+  for (int k = SPLIT_KEEP * 16 + sub; read && k < stages; k += 16) {
     look(*(const f32x4_t*)(s + (long long)k * 128));
     look(*(const f32x4_t*)(s + (long long)k * 128 + 16));
   }
@@ -1232,17 +1237,16 @@ __global__ __launch_bounds__(512) void k_split_rows(const char* __restrict__ src
       split2(y, q);
       o[0].v[c] = q[0]; o[1].v[c] = q[1];
     }
-    if (dst == nullptr || !live || k >= stages) return;
+    if (!live || k >= stages) return;
 #pragma unroll
     for (int p = 0; p < 2; ++p)
-      *(Oct*)(dst + (((long long)slab * 2 * stages + 2LL * k + p) * v + row) * 64 + ch * 16) = o[p];
+      *(Oct*)(out + (2LL * k + p) * srow * 64) = o[p];
   };
-  if (dst != nullptr || guard) {
 #pragma unroll
-    for (int it = 0; it < SPLIT_KEEP; ++it) put(x[it][0], x[it][1], it * 16 + sub);
-    for (int k = SPLIT_KEEP * 16 + sub; live && k < stages; k += 16)
-      put(*(const f32x4_t*)(s + (long long)k * 128), *(const f32x4_t*)(s + (long long)k * 128 + 16), k);
-  }
+  for (int it = 0; it < SPLIT_KEEP; ++it) put(x[it][0], x[it][1], it * 16 + sub);
+  const f32x4_t zero = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int k = SPLIT_KEEP * 16 + sub; live && k < stages; k += 16)
+    put(read ? *(const f32x4_t*)(s + (long long)k * 128) : zero, read ? *(const f32x4_t*)(s + (long long)k * 128 + 16) : zero, k);
   if (guard) {
     small += __shfl_xor(small, 1); small += __shfl_xor(small, 2); small += __shfl_xor(small, 32);
     if ((lane & 35) == 0) s_small[wave][rl] = small;
@@ -1257,10 +1261,10 @@ __global__ __launch_bounds__(512) void k_split_rows(const char* __restrict__ src
 }
 
 hipError_t launch_split_rows(const void* src, void* dst, long long slabs, int v, int d, long long row_stride, int* exps,
-                             int* flag, int guard, hipStream_t st) {
+                             int* flag, int guard, hipStream_t st, long long dst_rows, int rows1, const void* src2, int rows2) {
   const long long blocks = slabs * ((v + SPLIT_ROWS - 1) / SPLIT_ROWS);
   hipLaunchKernelGGL(k_split_rows, dim3((unsigned)blocks), dim3(512), 0, st, (const char*)src, (char*)dst, v, d, row_stride, exps,
-                     flag, guard);
+                     flag, guard, dst_rows, rows1, (const char*)src2, rows2);
   return hipGetLastError();
 }
 
@@ -1274,7 +1278,7 @@ static hipError_t launch_split(const UnembedArgs& a0, hipStream_t st) {
   if (a.Wexp == nullptr) a.Wexp = plane_exps(a.Wq, slabs * a.v * a.d);
   hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, st, a.wild);
   hipError_t e = launch_split_rows(a.h, a.hq, 1, a.B, a.d, a.ld_h * 4, plane_exps(a.hq, (long long)a.B * a.d), a.wild, 1, st);
-  if (e == hipSuccess) e = launch_split_rows(a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wexp, a.wild, 1, st);
+  if (e == hipSuccess) e = launch_split_rows(a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wexp, a.wild, 1, st, a.Wq_rows);
   if (e == hipSuccess) e = launch_train<true, false, true, true>(a, st);
   return e != hipSuccess ? e : launch_dt<false, false>(a, st);
 }
