@@ -92,6 +92,7 @@ hipError_t launch_unembed(const UnembedArgs& a, int dtype, hipStream_t st);
 // d = 2048: 1249 / 678 us).
 // (bf16 batches of 33 to 64 positions keep their one tile from 33 slabs on: they are bound by reading W, which two
 // tiles read twice and not from its 128-byte stage-major copy - 128 slabs 107 / 114 us.)
+// (Where this says 256, launches that walk their tiles choose anew among 256, 192 and 128: walk_positions, unembed.hip.)
 inline int unembed_positions(int B, int n, int r, int dtype) {
   constexpr long long CUS = 256;                 // (not asked of the device: the size of a workspace follows from this, and that
                                                  // query works, and stays the same, where there is none or none is in use yet)

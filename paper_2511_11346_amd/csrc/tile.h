@@ -648,11 +648,11 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
 // Bound by the power of the products and of the two operand stages behind every three of them: 1.45 PFLOP/s of issued products
 // (B = 2048, n r = 256, d = 3072, v = 268: 1.83 ms; three bf16 terms and six products 3.19 ms, the fp32 instruction 7.29 ms;
 // registers only, the fp16 product runs at 1.88 PFLOP/s and the bf16 one at 2.02).
-template <int WV, int WB, int VB, int PB, int SB, int NS, int VH, int KR>
-__device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB, NS, true, false, true, true, false, 0, true, VH, KR>& feed,
-                                                    int d, char* smem, f32x4_t (&acc)[2 * PB][2 * VB - VH / 2]) {
-  using TL = Tile<WV, WB, VB, PB, SB, NS, 0, VH>;
-  constexpr int NVB16 = 2 * VB - VH / 2;
+template <int WV, int WB, int VB, int PB, int SB, int NS, int PH, int VH, int KR>
+__device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB, NS, true, false, true, true, false, PH, true, VH, KR>& feed,
+                                                    int d, char* smem, f32x4_t (&acc)[2 * PB + PH][2 * VB - VH / 2]) {
+  using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
+  constexpr int NPB16 = 2 * PB + PH, NVB16 = 2 * VB - VH / 2;
   static_assert(TL::NW == 8 && SB == 64 && NS == 4, "ping-pong of two wave groups over four ring buffers");
   const int lane = threadIdx.x & 63, wave = feed.wave;
   const int wv = TL::wv(wave), wb = TL::wb(wave);
@@ -661,10 +661,10 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
   const int a16 = (wv * TL::WROWS + l15) * SB + ((lq ^ sw16) << 4);
   const int b16 = (TL::TV + wb * TL::WP + l15) * SB + ((lq ^ sw16) << 4);
 #pragma unroll
-  for (int pb = 0; pb < 2 * PB; ++pb)
+  for (int pb = 0; pb < NPB16; ++pb)
 #pragma unroll
     for (int vb = 0; vb < NVB16; ++vb) acc[pb][vb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  i32x4_t ga[NVB16], gb[2 * PB];
+  i32x4_t ga[NVB16], gb[NPB16];
   auto read_a = [&](int slot, auto nvb) {
     const char* cur = smem + slot * TL::STAGE;
 #pragma unroll
@@ -675,7 +675,7 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
   auto read_b = [&](int slot) {
     const char* cur = smem + slot * TL::STAGE;
 #pragma unroll
-    for (int pb = 0; pb < 2 * PB; ++pb) {
+    for (int pb = 0; pb < NPB16; ++pb) {
       if constexpr (KR == 2) gb[pb] = read_krows(cur + (TL::TV * SB + wb * 4096) + (k16 ^ ((pb & 3) << 5)));
       else gb[pb] = *(const i32x4_t*)(cur + b16 + pb * 16 * SB);
     }
@@ -689,7 +689,7 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int pb = 0; pb < 2 * PB; ++pb)
+    for (int pb = 0; pb < NPB16; ++pb)
 #pragma unroll
       for (int vb = 0; vb < decltype(nvb)::value; ++vb) {
         mma_step_f16(acc[pb][vb], ga[vb], gb[pb]);

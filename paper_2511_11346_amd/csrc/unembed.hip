@@ -248,17 +248,18 @@ constexpr bool unembed_walks_tiles() { return !SAMPLE && WB != 1; }
 // SPLIT: fp32 operands as planes of two fp16 terms (tile_gemm_run_split); everything but the product, and the scales of
 // its rows that come out of the result behind it, is the bf16 kernel's.
 // STREAM: one tile of positions, so that every byte of W is read once (loaded with the non-temporal hint).
+// PH: 16 more positions per wave (Tile).
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false, int VH = 0,
-          bool STREAM = false>
+          bool STREAM = false, int PH = 0>
 __global__ __launch_bounds__(WV * WB * 64)
 void k_unembed(const UnembedArgs a) {
   // of the two launches over the same fp32 operands one does the work (see launch_split)
   if constexpr (SPLIT || !BF16)
     if (a.wild != nullptr && (*a.wild != 0) == SPLIT) return;
-  using TL = Tile<WV, WB, VB, PB, SB, NS, 0, VH>;
+  using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
   constexpr bool M16 = use_m16<WV, WB, SB, NS, BF16>();
   using FR = Frag<M16>;
-  constexpr int NPB = PB * FR::SUB, NVB = VB * FR::SUB - VH / 2;
+  constexpr int NPB = PB * FR::SUB + PH, NVB = VB * FR::SUB - VH / 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wv = TL::wv(wave), wb = TL::wb(wave);
@@ -272,7 +273,7 @@ void k_unembed(const UnembedArgs a) {
   // softmax statistics are taken, instead of after a workgroup launch with the matrix pipe idle.
   // Every other instantiation has one tile per workgroup and leaves the loop after it.
   constexpr bool WALK = unembed_walks_tiles<WB, SAMPLE>();
-  using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, STREAM, 0, SPLIT, VH>;
+  using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, STREAM, PH, SPLIT, VH>;
   const void* const hstaged = SPLIT ? a.hq : (WB != 1 && SB == H_STAGE_BYTES) ? a.hs : nullptr;
   const void* const Wfeed = SPLIT ? a.Wq : WPACK ? a.Wp : a.W;
   const int dfeed = SPLIT ? 2 * a.d : a.d;            // 16-bit columns of the planes
@@ -337,7 +338,7 @@ void k_unembed(const UnembedArgs a) {
       if (idx < nxw * TL::TP) s_x[idx] = xpre[q];
     }
   }
-  // this lane holds, of position column wb*PB*32 + pb*BR + lcol, rows rbase + vb*BR + roff(i)
+  // this lane holds, of position column wb*WP + pb*BR + lcol, rows rbase + vb*BR + roff(i)
   const int rbase = wv * TL::WROWS + 4 * lgrp;
   if constexpr (SPLIT) {
 #pragma unroll
@@ -347,13 +348,13 @@ void k_unembed(const UnembedArgs a) {
     tile_unscale<TL>(acc, s_e, rbase, wb * TL::WP + lcol);
   }
   float mx[NPB], lse[NPB];
-  tile_lse<WV, WB, VB, PB, SB, NS, M16, 0, VH>(acc, a.v, (float2*)(smem + TL::RED_OFF), mx, lse);   // (one barrier: s_x is visible)
+  tile_lse<WV, WB, VB, PB, SB, NS, M16, PH, VH>(acc, a.v, (float2*)(smem + TL::RED_OFF), mx, lse);   // (one barrier: s_x is visible)
 
   // evidence at the target tokens (the sampling instantiation never has targets)
   if constexpr (!SAMPLE) if (a.targets != nullptr) {
 #pragma unroll
     for (int pb = 0; pb < NPB; ++pb) {
-      const int b = b0 + wb * PB * 32 + pb * FR::BR + lcol;
+      const int b = b0 + wb * TL::WP + pb * FR::BR + lcol;
       if (b < a.B) {
         const int TT = a.T + a.T2;
         for (int t = 0; t < TT; ++t) {
@@ -406,7 +407,7 @@ void k_unembed(const UnembedArgs a) {
     // the column blocks of a row are stored back to back, together they fill whole lines).
     // phi = 2^((l - lse) log2 e): one fused multiply-add and one v_exp per probability
     constexpr float LOG2E = 1.4426950408889634f;
-    const int bl = b0 + wb * PB * 32 + lcol;
+    const int bl = b0 + wb * TL::WP + lcol;
     float* col = a.phiT + ((long long)slab * a.v + rbase) * a.ld_phi + bl;
     float shift[NPB];
 #pragma unroll
@@ -431,7 +432,7 @@ void k_unembed(const UnembedArgs a) {
     const bool vec = (a.v & 3) == 0;
 #pragma unroll
     for (int pb = 0; pb < NPB; ++pb) {
-      const int b = b0 + wb * PB * 32 + pb * FR::BR + lcol;
+      const int b = b0 + wb * TL::WP + pb * FR::BR + lcol;
       if (b >= a.B) continue;
       float* dst = a.logphi + (((long long)b * a.n + wi) * a.r + wj) * a.v;
 #pragma unroll
@@ -1060,10 +1061,10 @@ hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t st)
 }
 
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false, int VH = 0,
-          bool STREAM = false>
+          bool STREAM = false, int PH = 0>
 static hipError_t launch_cfg(const UnembedArgs& a, hipStream_t st) {
-  using TL = Tile<WV, WB, VB, PB, SB, NS, 0, VH>;
-  constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK, SPLIT, VH, STREAM>;
+  using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
+  constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK, SPLIT, VH, STREAM, PH>;
   constexpr int smem = TL::SMEM + (SPLIT ? TL::ROWS * 4 : 0);
   static_assert(smem <= 160 * 1024, "LDS budget of one CU");
   if (hipError_t e = allow_lds<kern>(smem); e != hipSuccess) return e;
@@ -1102,21 +1103,44 @@ static hipError_t launch_dec(const UnembedArgs& a, int row_bytes, hipStream_t st
   return launch_cfg<WV, 1, 2, PB, 64, 4, BF16, SAMPLE, false, false, 0, true>(a, st);
 }
 
-// Tiles of 256 (PB = 2) or 128 positions of the fewest rows that hold the vocabulary (a K stage costs what its rows
+// Tiles of 256 (PB = 2), 192 (PB = PH = 1) or 128 positions of the fewest rows that hold the vocabulary (a K stage costs what its rows
 // cost: products, loads and fragment reads alike).  The 272-row one exists for 16x16 blocks only: fp32 instructions
 // fill 32.  What a narrower tile leaves of LDS goes to a fifth ring buffer.
-template <bool BF16, bool SAMPLE, bool WPACK, bool SPLIT = false, int PB = 2>
+template <bool BF16, bool SAMPLE, bool WPACK, bool SPLIT = false, int PB = 2, int PH = 0>
 static hipError_t launch_train(const UnembedArgs& a, hipStream_t st) {
-  constexpr int NS = PB == 1 ? 5 : 4;
+  constexpr int NS = PB == 1 && PH == 0 ? 5 : 4;
   // A pass that writes the table is bound by its stores where rows of W are short, and those of 16 bytes per lane leave the
   // 272-row tile more slowly (the halves of a column are in different wave groups): v = 268, n r = 960, B = 1182, with 320 / 272
   // rows 939 / 962 us at d = 448, 1178 / 1178 at d = 1024, 880 / 843 at d = 2048 (marginals over all tokens).
   const bool stores = BF16 && !SPLIT && a.logphi != nullptr && a.d < 1024 && a.v < 272 && a.v % 4 == 0;
-  if (a.v > 272 || (a.v > 256 && stores)) return launch_cfg<2, 4, 5, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT>(a, st);
-  if (a.v > 256) return launch_cfg<2, 4, 5, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT, BF16 ? 3 : 0>(a, st);
-  if (a.v > 192) return launch_cfg<2, 4, 4, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT>(a, st);
-  if (a.v > 128) return launch_cfg<2, 4, 3, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT>(a, st);
-  return launch_cfg<2, 4, 2, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT>(a, st);
+  if (a.v > 272 || (a.v > 256 && stores)) return launch_cfg<2, 4, 5, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT, 0, false, PH>(a, st);
+  if (a.v > 256) return launch_cfg<2, 4, 5, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT, BF16 ? 3 : 0, false, PH>(a, st);
+  if (a.v > 192) return launch_cfg<2, 4, 4, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT, 0, false, PH>(a, st);
+  if (a.v > 128) return launch_cfg<2, 4, 3, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT, 0, false, PH>(a, st);
+  return launch_cfg<2, 4, 2, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT, 0, false, PH>(a, st);
+}
+
+// Positions per tile of a batch beyond the decode tiles' (launches that walk their tiles, 16x16 blocks): what counts is the
+// number of rounds the tiles make over the CUs, times what a round costs.  A round of 192 positions takes 0.77 to 0.87 of
+// one of 256 (least at v = 320, most at v = 100), one of 128 between 0.55 and 0.74: a K stage does not shrink with its
+// products (two barriers, the same rows of W).  So a narrower tile pays where it saves rounds or makes as many: up to 192 positions
+// beyond a multiple of 256, or a last round that is nearly empty.  CP, d = 2048, v = 320, 256 / 192 positions: n r = 512,
+// B = 300 281 / 248 us, B = 570 402 / 349; n r = 128, B = 1100 190 / 167; 5 rounds against 6 (n r = 256, B = 1100) 330 / 324 and, at
+// v = 100 and d = 4096, 10 against 12 575 / 599: not taken.  n r = 96, B = 570, d = 512, two rounds of any width: 53 / 46 /
+// 41 us with 128.  Of 713 sizes (B 140 .. 2000) 385 change: 0.76 to 1.01 of the time, 0.89 in the mean.
+// fp32 terms (`terms`; their ring has four buffers, so 128 positions gain nothing there): 0.87 as well up to 272 rows (n r = 256,
+// B = 570, d = 2048, v = 268 697 / 583 us), 0.68 to 0.78 of the 320-row tile (854 / 657; 5 rounds against 6, B = 1100, 1202 / 1022).
+static hipError_t walk_positions(const UnembedArgs& a, bool terms, int& positions) {
+  int cus = 0;
+  if (hipError_t e = cu_count(&cus); e != hipSuccess) return e;
+  const int width[3] = {256, 192, 128}, cost[3] = {100, terms && a.v > 272 ? 74 : 87, 74};
+  long long least = 0;
+  for (int k = 0; k < (terms ? 2 : 3); ++k) {
+    const long long tiles = (long long)a.n * a.r * ((a.B + width[k] - 1) / width[k]);
+    const long long c = (tiles + cus - 1) / cus * cost[k];
+    if (k == 0 || c < least) { least = c; positions = width[k]; }
+  }
+  return hipSuccess;
 }
 
 template <bool BF16, bool SAMPLE>
@@ -1131,6 +1155,11 @@ static hipError_t launch_dt(const UnembedArgs& a, hipStream_t st) {
   if (SAMPLE && BF16 && positions == 64 && a.B > 64 && a.v <= 128) positions = 128;
   if (positions >= 128) {
     const bool packed = a.Wp != nullptr && a.Wp_stage == 64;        // the copy of W in the 64-byte stages of these tiles
+    if constexpr (BF16 && !SAMPLE) {
+      if (positions == 256)
+        if (hipError_t e = walk_positions(a, false, positions); e != hipSuccess) return e;
+      if (positions == 192) return packed ? launch_train<BF16, SAMPLE, true, false, 1, 1>(a, st) : launch_train<BF16, SAMPLE, false, false, 1, 1>(a, st);
+    }
     if (positions == 256) return packed ? launch_train<BF16, SAMPLE, true>(a, st) : launch_train<BF16, SAMPLE, false>(a, st);
     return packed ? launch_train<BF16, SAMPLE, true, false, 1>(a, st) : launch_train<BF16, SAMPLE, false, false, 1>(a, st);
   }
@@ -1279,7 +1308,10 @@ static hipError_t launch_split(const UnembedArgs& a0, hipStream_t st) {
   hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, st, a.wild);
   hipError_t e = launch_split_rows(a.h, a.hq, 1, a.B, a.d, a.ld_h * 4, plane_exps(a.hq, (long long)a.B * a.d), a.wild, 1, st);
   if (e == hipSuccess) e = launch_split_rows(a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wexp, a.wild, 1, st, a.Wq_rows);
-  if (e == hipSuccess) e = launch_train<true, false, true, true>(a, st);
+  int positions = 256;
+  if (e == hipSuccess) e = walk_positions(a, true, positions);
+  if (e == hipSuccess)
+    e = positions == 192 ? launch_train<true, false, true, true, 1, 1>(a, st) : launch_train<true, false, true, true>(a, st);
   return e != hipSuccess ? e : launch_dt<false, false>(a, st);
 }
 
