@@ -689,7 +689,7 @@ BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly,
   q.split_fwd = q.split && split_pays(hd);
   const size_t osz = q.split ? 6 : esz;       // bytes per element of the contractions' operands
   q.dLT = take((size_t)(q.ctx ? q.ldM : q.split ? q.M : q.Mx) * q.ldb * osz);
-  if (q.split) q.big = take(4);
+  if (q.split) q.big = take(16 + (size_t)q.ldb * 4);        // flag and, 16 bytes on, the largest exponent of each position
   q.dslT = q.split ? take((size_t)(q.Mx - q.M) * q.ldb * esz) : q.dLT + (size_t)q.M * q.ldb * esz;
   q.dL = take(B * q.ldM * osz);
   // (stage-major when one kernel writes every element of both layouts - no layer-logit columns from elsewhere - and one
@@ -838,7 +838,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   c.dslT = family == MTPC_FF ? nullptr : (void*)(ws + q.dslT);
   c.ldb = q.ldb; c.bf16 = hd->dtype == MTPC_BF16; c.loss = loss;
   int* const big = q.split ? (int*)(ws + q.big) : nullptr;
-  c.clear = big;
+  if (big) HIP_TRY(launch_clear(big, 4 + q.ldb, st));
   if (L > 0) {
     c.lay_nat = (const float*)(ws + q.lay_nat);
     c.lay_tr = (ctx || q.perpos) ? nullptr : (const float*)(ws + q.lay_tr);
@@ -884,7 +884,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
     g.dl_end = ctx ? q.Mlay : q.ldM;           // the layer-logit columns are written by the reverse pass
     g.dLT = ws + q.dLT; g.dL = ws + q.dL;
     g.staged = q.staged;
-    g.planes = q.split; g.big = big; g.dslT = ws + q.dslT;
+    g.planes = q.split; g.big = big; g.top = big ? big + 4 : nullptr; g.dslT = ws + q.dslT;
     g.Wexp = wexp; g.wild = q.split_fwd ? (const int*)(ws + q.wild) : nullptr;
     g.rows_only = q.along_rows;
     if (q.along_rows) { g.W = hd->W; g.Wsum = hd->Wsum; g.d = hd->d; g.tail_row = kmain; g.tail = ws + q.WT; }

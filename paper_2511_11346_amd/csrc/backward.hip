@@ -211,19 +211,23 @@ __global__ __launch_bounds__(256) void k_grad_rows(const GradPhiArgs a, int rows
   }
 }
 
-// Exponents of the rows of the two planes that k_grad_from_phi writes (see split2).  The first workgroups take up to 64 rows of
-// one slab of dLT each: the largest magnitude of a row over all positions, one more read of the probabilities; the gradients
-// and targets of the slab, apart in memory, go through LDS once per workgroup (fetched by every wave for its rows of any slabs,
-// this took 330 us for 562 MB of probabilities).  The others take 16 rows of dL: no value of row b is larger
-// than |Ge[b][i][j]| 2^(largest exponent of the rows of W[i][j]), which is off by what the softmax leaves of it only (a row
-// whose every token is certain), well within the 16 bits that the terms have to spare.
-__global__ __launch_bounds__(256) void k_grad_exps(const GradPhiArgs a, int* __restrict__ rexp, int* __restrict__ bexp, int row_blocks) {
+// Exponents of the rows of the two planes that k_grad_from_phi writes (see split2): the largest magnitude of a row of dLT over all
+// positions, and of a row of dL, whose elements carry the scales of W's rows, over all tokens.  One more read of the
+// probabilities.  The first workgroups take up to 64 rows of one slab each; the gradients and targets of the slab, apart in memory,
+// go through LDS once per workgroup (fetched by every wave for its rows of any slabs, this took 330 us for 562 MB of
+// probabilities), and so do the maxima of the positions on their way to a.top: 1 + TOP_BIAS + the exponent, 0 for a position without a
+// gradient.  (A bound on a position's maximum from its gradients and the largest exponent of each slab is not enough: a row
+// of W far above the others may belong to a token without probability.)  The other workgroups add the sum-unit rows
+// of 16 positions each to a.top.
+constexpr int TOP_BIAS = 4096;
+__device__ __forceinline__ int top_exp(int top) { return top > 0 ? top - 1 - TOP_BIAS - 15 : 0; }
+__global__ __launch_bounds__(256) void k_grad_exps(const GradPhiArgs a, int* __restrict__ rexp, int row_blocks) {
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;
   typedef __attribute__((ext_vector_type(4))) int i32x4_t;
-  extern __shared__ int s_slab[];                    // [n*r] largest exponent of a slab's rows
   constexpr int CH = 1024;                           // positions per step
   __shared__ __align__(16) float s_g[CH];
   __shared__ __align__(16) int s_x[CH];
+  __shared__ int s_top[CH];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nr = a.n * a.r;
   if (blockIdx.x == 0 && tid == 0 && a.wild != nullptr && *a.wild != 0) *a.big = 1;
@@ -234,8 +238,13 @@ __global__ __launch_bounds__(256) void k_grad_exps(const GradPhiArgs a, int* __r
     if (r0 - wave >= a.v) return;
     const float* phi = a.phiT + (long long)slab * a.v * a.ld_phi;
     float big[RW];
+    int we[RW];                                      // (of a row that is not there: of a row of zeros)
 #pragma unroll
-    for (int k = 0; k < RW; ++k) big[k] = 0.f;
+    for (int k = 0; k < RW; ++k) {
+      big[k] = 0.f;
+      const int row = r0 + 4 * k;
+      we[k] = 1 + TOP_BIAS + (row < a.v ? a.Wexp[(long long)slab * a.v + row] : SPLIT_ZERO_ROW);
+    }
     f32x4_t ph[RW];
     auto fetch = [&](int b) {                        // (b beyond the last position: any)
 #pragma unroll
@@ -243,7 +252,6 @@ __global__ __launch_bounds__(256) void k_grad_exps(const GradPhiArgs a, int* __r
     };
     for (int c0 = 0; c0 < a.B; c0 += CH) {
       fetch(c0 + 4 * lane);                          // (on their way while the gradients are fetched)
-      __syncthreads();
 #pragma unroll
       for (int q = 0; q < CH / 256; ++q) {
         const int i = tid + q * 256, b = c0 + i;
@@ -252,19 +260,32 @@ __global__ __launch_bounds__(256) void k_grad_exps(const GradPhiArgs a, int* __r
         const float g = a.Ge[(long long)bc * nr + slab];
         s_x[i] = x;
         s_g[i] = b < a.B && x != -1 ? g : 0.f;
+        s_top[i] = 0;
       }
       __syncthreads();
       for (int i = 4 * lane; i < CH && c0 + i < a.B; i += 256) {
         const f32x4_t g = *(const f32x4_t*)(s_g + i);
         const i32x4_t x = *(const i32x4_t*)(s_x + i);
+        int top[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int k = 0; k < RW; ++k)
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             const float y = c0 + i + c < a.B ? fabsf(g[c] * ((r0 + 4 * k == x[c] ? 1.f : 0.f) - ph[k][c])) : 0.f;
-            big[k] = y <= 3.402823466e38f ? fmaxf(big[k], y) : big[k];
+            const bool counts = y <= 3.402823466e38f && y > 0.f;
+            big[k] = counts ? fmaxf(big[k], y) : big[k];
+            top[c] = counts ? max(top[c], __builtin_amdgcn_frexp_expf(y) + we[k]) : top[c];
           }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (top[c] > 0) atomicMax(&s_top[i + c], top[c]);
         fetch(c0 + i + 256);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < CH / 256; ++q) {           // (few of a position's maxima are above those of the workgroups before)
+        const int top = s_top[tid + q * 256], b = c0 + tid + q * 256;
+        if (top > 0 && b < a.B && top > __hip_atomic_load(a.top + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(a.top + b, top);
       }
     }
     // the largest of each row over the lanes, rows halved at every exchange: lane l ends up with row l / 4
@@ -281,53 +302,26 @@ __global__ __launch_bounds__(256) void k_grad_exps(const GradPhiArgs a, int* __r
     if ((lane & 3) == 0 && row < a.v) rexp[(long long)slab * a.v + row] = split_exp(y);
     return;
   }
-  for (int i = tid; i < nr; i += 256) s_slab[i] = -1000;
-  __syncthreads();
-  for (int m0 = 8 * tid; m0 < (int)a.M; m0 += 4 * 8 * 256) {
-    int e8[4][8];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) e8[u][c] = a.Wexp[min(m0 + u * 2048 + c, (int)a.M - 1)];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      int slab = min(m0 + u * 2048, (int)a.M - 1) / a.v, e = -1000;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const int at = min(m0 + u * 2048 + c, (int)a.M - 1) / a.v;
-        if (at != slab) {
-          atomicMax(&s_slab[slab], e);
-          slab = at; e = -1000;
-        }
-        e = max(e, e8[u][c]);
-      }
-      atomicMax(&s_slab[slab], e);
-    }
-  }
-  __syncthreads();
   const int b = ((int)blockIdx.x - row_blocks) * 16 + (tid >> 4), t = tid & 15;
   const int r2 = (int)(a.Mx - a.M);
-  int e = -100000;
-  auto see = [&](float y, int scale) {
-    y = fabsf(y);
-    if (y > 0.f && y <= 3.402823466e38f) e = max(e, __builtin_amdgcn_frexp_expf(y) + scale);
-  };
-  if (b < a.B) {
-    for (int i = t; i < nr; i += 16) see(a.Ge[(long long)b * nr + i], s_slab[i]);
-    for (int j = t; j < r2; j += 16) see(((const float*)a.dslT)[j * a.ldb + b], a.Wexp[a.M + j]);
-  }
+  int top = 0;
+  if (b < a.B)
+    for (int j = t; j < r2; j += 16) {
+      const float y = fabsf(((const float*)a.dslT)[j * a.ldb + b]);
+      if (y > 0.f && y <= 3.402823466e38f) top = max(top, __builtin_amdgcn_frexp_expf(y) + 1 + TOP_BIAS + a.Wexp[a.M + j]);
+    }
 #pragma unroll
-  for (int o = 1; o < 16; o <<= 1) e = max(e, __shfl_xor(e, o));
-  if (b < a.B && t == 0) bexp[b] = e > -100000 ? e - 15 : 0;
+  for (int o = 1; o < 16; o <<= 1) top = max(top, __shfl_xor(top, o));
+  if (b < a.B && t == 0 && top > 0) atomicMax(a.top + b, top);
 }
 
 // 64 (m) x 128 (b) tiles: logit gradient from the stored probabilities, written in both
 // layouts (dLT along b straight away, dL along m after a transpose through LDS).  A thread
 // moves four neighbouring elements at a time (16-byte loads, 8- or 16-byte stores).
-// PLANES (fp32): both layouts as planes of two fp16 terms, as tile_gemm_run_split reads them; rexp and bexp hold the
-// exponents of their rows.
+// PLANES (fp32): both layouts as planes of two fp16 terms, as tile_gemm_run_split reads them; rexp and a.top hold the
+// exponents of their rows, and those of dL are left in bexp.
 template <typename T, bool PLANES = false>
-__global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a, const int* __restrict__ rexp, const int* __restrict__ bexp) {
+__global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a, const int* __restrict__ rexp, int* __restrict__ bexp) {
   struct alignas(4 * sizeof(T)) Quad { T v[4]; };
   // four neighbours along K, to row `row` of a staged matrix of `rows` rows; e[c]: the power of two x[c] is multiplied with
   auto put_planes = [](void* dst, long long k, long long rows, long long row, const Quad& x, const int (&e)[4]) {
@@ -415,7 +409,8 @@ __global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a, cons
       for (int c = 0; c < 4; ++c) out.v[c] = tile[4 * mq + c][bl];
       constexpr int EPS = 64 / (int)sizeof(T);
       if constexpr (PLANES) {
-        const int e = bexp[b0 + bl];
+        const int e = top_exp(a.top[b0 + bl]);
+        if (m == 0) bexp[b0 + bl] = e;
         put_planes(a.dL, m, a.B, b0 + bl, out, {we[0] - e, we[1] - e, we[2] - e, we[3] - e});
       } else if (a.staged) *(Quad*)(dL + ((m / EPS) * a.B + (b0 + bl)) * EPS + m % EPS) = out;
       else *(Quad*)(dL + (long long)(b0 + bl) * a.ldM + m) = out;
@@ -450,7 +445,6 @@ __device__ __forceinline__ void wave_matvec(const float* __restrict__ M, const f
 
 // One wave per evidence row; lane l holds units l and l + 64.
 __global__ __launch_bounds__(256) void k_circuit_bwd(const CircuitBwdArgs a) {
-  if (a.clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *a.clear = 0;
   __shared__ float sP[4][64];
   __shared__ float sX[4][128];
   __shared__ float sPi[4][128], sC[4][128];
@@ -639,7 +633,6 @@ __global__ __launch_bounds__(256) void k_circuit_bwd(const CircuitBwdArgs a) {
 // and adj(x) goes to both operands (leaf: evidence gradient; stored node: its
 // adjoint; path value: the adjoint consumed by the previous step of the path).
 __global__ __launch_bounds__(256) void k_btree_bwd(const CircuitBwdArgs a, int nsteps_max) {
-  if (a.clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *a.clear = 0;
   extern __shared__ TreeStep bprog[];
   __shared__ float sX[4][128];
   __shared__ float sPi[4][128];
@@ -839,7 +832,6 @@ constexpr size_t btree_bwd_lds(int n, int T) {
 
 template <int R>
 __global__ __launch_bounds__(4 * R) void k_btree_bwd_mfma(const CircuitBwdArgs a, int nsteps_max) {
-  if (a.clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *a.clear = 0;
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;
   constexpr int NB = R / 16, RS = R + 4;
   extern __shared__ __align__(16) float wsm[];
@@ -1253,10 +1245,15 @@ hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st)
   else if (a.planes) {
     int* const rexp = plane_exps(a.dLT, a.M * a.ldb);
     int* const bexp = plane_exps(a.dL, a.B * a.ldM);
-    const int rb = a.n * a.r * ((a.v + 63) / 64), bb = (a.B + 15) / 16;
-    hipLaunchKernelGGL(k_grad_exps, dim3(rb + bb), dim3(256), (size_t)a.n * a.r * 4, st, a, rexp, bexp, rb);
+    const int rb = a.n * a.r * ((a.v + 63) / 64), bb = a.Mx > a.M ? (a.B + 15) / 16 : 0;
+    hipLaunchKernelGGL(k_grad_exps, dim3(rb + bb), dim3(256), 0, st, a, rexp, rb);
     hipLaunchKernelGGL((k_grad_from_phi<float, true>), grid, dim3(256), 0, st, a, rexp, bexp);
   } else hipLaunchKernelGGL(k_grad_from_phi<float>, grid, dim3(256), 0, st, a, nullptr, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_clear(int* p, long long n, hipStream_t st) {
+  hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (float*)p, n);
   return hipGetLastError();
 }
 

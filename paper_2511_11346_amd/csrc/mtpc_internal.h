@@ -310,6 +310,7 @@ struct GradPhiArgs {
   int planes;
   const void* dslT;     // the sum-unit rows M..Mx-1 of dLT, [Mx - M][ldb] in the dtype of h
   int* big;             // planes: set to 1 when an element is infinite or NaN
+  int* top;             // planes: scratch [ldb], cleared (k_grad_exps)
   int* Wexp;            // planes: exponents of the rows of W and, behind them, of Wsum [Mx] (launch_transpose, along_rows)
   const int* wild;      // planes: the flag of the forward pass that has split W; set, it sets *big; or nullptr
   // 1 (staged, bf16): no dL; dLT [ldb/32][ldM][64 bytes], the sum-unit rows and zeros behind the others; and rows tail_row ..
@@ -321,6 +322,8 @@ struct GradPhiArgs {
   void* tail;
 };
 hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st);
+// n ints set to 0 by a kernel
+hipError_t launch_clear(int* p, long long n, hipStream_t st);
 
 // An operand of a contraction given along its rows: K runs down the rows, columns lie in chunks of 32 (64 bytes).  Element
 // (k, 32 c + x) is at base + c * chunk + k * row + 2 x; rows from kmain (a multiple of 32) on come from `tail` instead,
@@ -431,7 +434,6 @@ struct CircuitBwdArgs {
   int bf16;
   float* loss;           // [rows]
   float* dlayers;        // [L][r][r] gradient w.r.t. the layer logits (accumulated), or nullptr
-  int* clear;            // set to 0 (the flag of the launches that follow, which saves that a launch of its own), or nullptr
 };
 hipError_t launch_circuit_bwd(const CircuitBwdArgs& a, hipStream_t st);
 constexpr int LAYER_GRAD_ROWS = 256;   // rows whose contribution to a layer gradient one workgroup sums
@@ -511,9 +513,11 @@ __device__ __forceinline__ void split2(float x, unsigned short (&t)[2]) {
   t[0] = __builtin_bit_cast(unsigned short, hi);
   t[1] = __builtin_bit_cast(unsigned short, lo);
 }
-// exponent E with x 2^-E in [2^14, 2^15), for the largest |x| of a row (0: 0)
+// exponent E with x 2^-E in [2^14, 2^15), for the largest |x| of a row.  A row of zeros has one below every other: where
+// exponents of rows meet in a maximum (k_grad_exps) it must not win
+constexpr int SPLIT_ZERO_ROW = -100000;
 __device__ __forceinline__ int split_exp(float largest) {
-  return largest > 0.f ? __builtin_amdgcn_frexp_expf(largest) - 15 : 0;
+  return largest > 0.f ? __builtin_amdgcn_frexp_expf(largest) - 15 : SPLIT_ZERO_ROW;
 }
 
 __device__ __forceinline__ float neg_inf() { return -__builtin_inff(); }

@@ -1,0 +1,70 @@
+"""GPU parity of fp32 training where one row is far larger or smaller than the others: the products through two fp16 terms per
+value take out one scale per row.
+
+Every row and every column of a gradient is compared by itself, relative to its own norm: an error that hides behind a larger
+neighbour counts.  Tolerance, as for gradients far below the others (test_gpu_fp16_terms.py): ROW = 3e-5 of the norm, and half
+as much again as the step that recomputes its logits, on the fp32 instruction, is off on the same inputs."""
+import numpy as np
+import pytest
+import torch
+
+import mtpc_inputs as mi
+from oracle import backward as bw
+from gpu_util import make_head, takes_terms
+
+pytestmark = pytest.mark.gpu
+
+ROW = 3e-5
+
+
+def zero_token(inp, coef, gain):
+    inp.W *= gain
+    inp.W[:, :, 3] = 0.0
+
+
+def zero_sum_units(inp, coef, gain):
+    inp.W *= gain
+    if inp.Wsum is not None:
+        inp.Wsum[:] = 0.0
+
+
+def impossible_token(inp, coef, power):
+    """A token whose weights are 2^power and whose probability is 0."""
+    inp.h[:, 0] = 1.0
+    inp.W[:, :, -1] = 0.0
+    inp.W[:, :, -1, 0] = -2.0 ** power
+    inp.targets[:] %= inp.v - 1
+
+
+CASES = {
+    "zero token": (zero_token, 1.0), "zero token, small W": (zero_token, 2.0 ** -8), "zero token, confident": (zero_token, 3.0),
+    "zero sum units": (zero_sum_units, 1.0), "zero sum units, confident": (zero_sum_units, 3.0),
+    "zero sum units, small W": (zero_sum_units, 2.0 ** -8), "impossible token 2^12": (impossible_token, 12),
+    "impossible token 2^24": (impossible_token, 24),
+}
+
+
+@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("family,B,d,n,r,v", [("cp", 257, 512, 8, 11, 33), ("ff", 300, 544, 3, 1, 33)])
+def test_every_row_and_column_of_a_gradient(family, B, d, n, r, v, case):
+    """(Forward pass with and without terms.)"""
+    inp = mi.make_inputs(family, B=B, d=d, n=n, r=r, v=v, dtype="f32", seed=B, h_scale=1.0)
+    coef = bw.loss_coefficients(0.8, np.random.default_rng(B).random((B, n)) > 0.15).astype(np.float32)
+    CASES[case][0](inp, coef, *CASES[case][1:])
+    assert takes_terms(make_head(inp)) == (family == "cp")
+    ref = bw.loss_and_gradients(family, inp.h, inp.W, inp.Wsum, inp.layers, inp.targets, coef)
+    tg, cf = torch.from_numpy(inp.targets.astype(np.int32)).cuda(), torch.from_numpy(coef).cuda()
+    out, plain = make_head(inp).loss_backward(tg, cf), make_head(inp).loss_backward(tg, cf, recompute=True)
+    bad = []
+    for k in ("dW", "dh"):
+        want = ref[k].reshape(-1, d)
+        for axis, what in ((1, "row"), (0, "column")):
+            size = np.linalg.norm(want, axis=axis)
+            off = [np.linalg.norm(o[k].cpu().numpy().astype(np.float64).reshape(-1, d) - want, axis=axis) for o in (out, plain)]
+            seen = size > 2.0 ** -100 * size.max()
+            assert all(np.isfinite(o).all() and (o[~seen] <= size.max() * 2.0 ** -24).all() for o in off), (k, what)
+            worst = [(o[seen] / size[seen]).max() for o in off]
+            print(case, k, what, "worst %.2g, on the fp32 instruction %.2g" % tuple(worst))
+            if not worst[0] < ROW + 1.5 * worst[1]:
+                bad.append((k, what, worst))
+    assert not bad
