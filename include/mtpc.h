@@ -121,7 +121,8 @@ const char* mtpc_status_string(mtpc_status s);
  * batches, where that is faster; sampling never is) ask for 6 bytes more per element of W
  * and h; they also run without that room, on the fp32 instructions (results differ within
  * fp32 rounding of the sums), and take those by themselves for operands the terms would not do
- * justice: infinite or NaN values, rows most of which is below 2^-16 of their largest value.
+ * justice: infinite or NaN values, rows with more than one value in 16, of those other than 0,
+ * below 2^-18 of the largest.
  * Returns 0 for invalid arguments. */
 size_t mtpc_workspace_bytes(int32_t family, int32_t op, const mtpc_head* head,
                             const mtpc_sumlayers* layers, int32_t S, int32_t mode);

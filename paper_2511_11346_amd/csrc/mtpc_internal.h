@@ -513,6 +513,8 @@ __device__ __forceinline__ void split2(float x, unsigned short (&t)[2]) {
   t[0] = __builtin_bit_cast(unsigned short, hi);
   t[1] = __builtin_bit_cast(unsigned short, lo);
 }
+// scaled values below this (about 2^-18 of their row's largest) have fewer than 22 bits left
+constexpr float SPLIT_SMALL = 0.125f;
 // exponent E with x 2^-E in [2^14, 2^15), for the largest |x| of a row.  A row of zeros has one below every other: where
 // exponents of rows meet in a maximum (k_grad_exps) it must not win
 constexpr int SPLIT_ZERO_ROW = -100000;

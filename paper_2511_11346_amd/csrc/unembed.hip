@@ -1202,15 +1202,15 @@ hipError_t launch_pack_rows(const void* src, void* dst, long long slabs, int v, 
 // 64 contiguous bytes of each plane, eight rows of a stage follow each other.  Rows of up to 4096 columns stay in registers
 // between the search for their largest value and the split, so the matrix is read once: 843 MB to as many of planes in 0.34 ms
 // (4.9 TB/s); a row at a time per thread quad and three planes took 0.43 ms.
-// Sets *flag when a value is infinite or NaN.  guard: also when the terms may do a row less than justice: a value below 2^-16
-// of the row's largest has fewer than 23 bits left (2^-40 of the largest), which matters where most of the row is that
-// small - one outlier - and not where a few values of a row happen to be near 0 (one in 16).
+// Sets *flag when a value is infinite or NaN.  guard: also when the terms may do a row less than justice: a value below
+// SPLIT_SMALL is small beside its row's largest, which matters where much of the row is - one outlier - and not where a
+// few values happen to be near 0: more than one in 16 of those that are not 0 (of a row with few of them, any).
 constexpr int SPLIT_ROWS = 8, SPLIT_KEEP = 8;        // rows of a workgroup, steps of 512 columns kept in registers
 __global__ __launch_bounds__(512) void k_split_rows(const char* __restrict__ src, char* __restrict__ dst, int v, int d,
                                                     long long row_stride, int* __restrict__ exps, int* flag, int guard,
                                                     long long dst_rows, int rows1, const char* __restrict__ src2, int rows2) {
   __shared__ unsigned s_max[8][SPLIT_ROWS];
-  __shared__ int s_small[8][SPLIT_ROWS];
+  __shared__ int s_small[8][SPLIT_ROWS], s_zero[8][SPLIT_ROWS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rblocks = (v + SPLIT_ROWS - 1) / SPLIT_ROWS;
   const int slab = blockIdx.x / rblocks, rl = (tid >> 2) & (SPLIT_ROWS - 1);
@@ -1255,35 +1255,50 @@ __global__ __launch_bounds__(512) void k_split_rows(const char* __restrict__ src
 #pragma unroll
   for (int w = 0; w < 8; ++w) m = max(m, s_max[w][rl]);
   const int E = split_exp(__uint_as_float(m));
-  int small = 0;
+  int small = 0;                                     // (with those that are 0)
   auto put = [&](const f32x4_t& y0, const f32x4_t& y1, int k) {
+    if (!live || k >= stages) return;
     struct alignas(16) Oct { unsigned short v[8]; } o[2];
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       const float y = __builtin_amdgcn_ldexpf(c < 4 ? y0[c & 3] : y1[c & 3], -E);
-      small += y != 0.f && fabsf(y) < 0.5f;
+      small += fabsf(y) < SPLIT_SMALL;
       unsigned short q[2];
       split2(y, q);
       o[0].v[c] = q[0]; o[1].v[c] = q[1];
     }
-    if (!live || k >= stages) return;
 #pragma unroll
     for (int p = 0; p < 2; ++p)
       *(Oct*)(out + (2LL * k + p) * srow * 64) = o[p];
   };
 #pragma unroll
   for (int it = 0; it < SPLIT_KEEP; ++it) put(x[it][0], x[it][1], it * 16 + sub);
-  const f32x4_t zero = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const f32x4_t zeros = f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int k = SPLIT_KEEP * 16 + sub; live && k < stages; k += 16)
-    put(read ? *(const f32x4_t*)(s + (long long)k * 128) : zero, read ? *(const f32x4_t*)(s + (long long)k * 128 + 16) : zero, k);
+    put(read ? *(const f32x4_t*)(s + (long long)k * 128) : zeros, read ? *(const f32x4_t*)(s + (long long)k * 128 + 16) : zeros, k);
   if (guard) {
-    small += __shfl_xor(small, 1); small += __shfl_xor(small, 2); small += __shfl_xor(small, 32);
-    if ((lane & 35) == 0) s_small[wave][rl] = small;
-    __syncthreads();
-    small = 0;
+    if (__syncthreads_or(small > 0)) {               // (only then the zeros, which do not count, matter)
+      int zero = 0;
+      auto count = [&](const f32x4_t& y) {
 #pragma unroll
-    for (int w = 0; w < 8; ++w) small += s_small[w][rl];
-    bad |= small > d / 16;
+        for (int c = 0; c < 4; ++c) zero += y[c] == 0.f;
+      };
+#pragma unroll
+      for (int it = 0; it < SPLIT_KEEP; ++it)
+        if (live && it * 16 + sub < stages) { count(x[it][0]); count(x[it][1]); }
+      for (int k = SPLIT_KEEP * 16 + sub; live && k < stages; k += 16) {
+        count(read ? *(const f32x4_t*)(s + (long long)k * 128) : zeros);
+        count(read ? *(const f32x4_t*)(s + (long long)k * 128 + 16) : zeros);
+      }
+      auto sum = [&](int y) { y += __shfl_xor(y, 1); y += __shfl_xor(y, 2); return y + __shfl_xor(y, 32); };
+      small = sum(small); zero = sum(zero);
+      if ((lane & 35) == 0) { s_small[wave][rl] = small; s_zero[wave][rl] = zero; }
+      __syncthreads();
+      small = zero = 0;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) { small += s_small[w][rl]; zero += s_zero[w][rl]; }
+      bad |= small - zero > (d - zero) / 16;
+    }
   }
   if (live && ch == 0 && sub == 0) exps[(long long)slab * v + row] = E;
   if (live && bad) *flag = 1;

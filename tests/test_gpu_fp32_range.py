@@ -1,4 +1,4 @@
-"""GPU parity of fp32 training where one row is far larger or smaller than the others: the products through two fp16 terms per
+"""GPU parity of fp32 scoring and training where one row or value is far larger or smaller than the others: the products through two fp16 terms per
 value take out one scale per row.
 
 Every row and every column of a gradient is compared by itself, relative to its own norm: an error that hides behind a larger
@@ -10,11 +10,12 @@ import torch
 
 import mtpc_inputs as mi
 from oracle import backward as bw
+from oracle import mtpc_oracle as oc
 from gpu_util import make_head, takes_terms
 
 pytestmark = pytest.mark.gpu
 
-ROW = 3e-5
+LOG, ROW = 2e-5, 3e-5
 
 
 def zero_token(inp, coef, gain):
@@ -68,3 +69,24 @@ def test_every_row_and_column_of_a_gradient(family, B, d, n, r, v, case):
             if not worst[0] < ROW + 1.5 * worst[1]:
                 bad.append((k, what, worst))
     assert not bad
+
+
+@pytest.mark.parametrize("kept", [4, 20, 31])
+@pytest.mark.parametrize("power", [20, 30])
+def test_sparse_rows_with_an_outlier(kept, power):
+    """Rows of h with a few values other than 0 (fewer than one in 16) and one far above them, which W does not see."""
+    inp = mi.make_inputs("cp", B=257, d=512, n=8, r=11, v=33, dtype="f32", seed=power, h_scale=1.0)
+    rng = np.random.default_rng(kept)
+    for b in range(0, inp.B, 3):
+        off = rng.permutation(np.arange(1, inp.d))[kept:]
+        inp.h[b, off] = 0.0
+        inp.h[b, 0] = 2.0 ** power
+    inp.W[..., 0] = 0.0
+    inp.Wsum[:, 0] = 0.0
+    head = make_head(inp)
+    assert takes_terms(head)
+    logphi, logw, _ = oc._params("cp", inp.h, inp.W, inp.Wsum, None)
+    want = oc.prefix_marginals_from("cp", logphi, logw, None, inp.targets)
+    err = np.abs(head.prefix_marginals(torch.from_numpy(inp.targets).cuda()).cpu().numpy() - want).max()
+    print(kept, power, err)
+    assert err < LOG * 8 ** 0.5
