@@ -295,7 +295,7 @@ UnembedArgs unembed_args(const mtpc_head* hd) {
 void split_scratch(const mtpc_head* hd, const Plan& p, UnembedArgs& u) {
   if (!p.has_split) return;
   char* ws = (char*)hd->workspace;
-  u.Wq = ws + p.Wq; u.hq = ws + p.hq; u.wild = (int*)(ws + p.wild);
+  u.Wq = ws + p.Wq; u.hq = ws + p.hq; u.wild = (int*)(ws + p.wild); u.three = 1;
 }
 
 // the stage-major copy of h into the workspace (when the plan has room for it) and into the arguments

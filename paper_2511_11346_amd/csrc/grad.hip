@@ -111,7 +111,7 @@ hipError_t launch_unembed_grad(const GradLogitsArgs& a, int dtype, hipStream_t s
 // KR: operands given along their rows (TileFeed::open_rows): transposed on the way from LDS into registers, where a
 // transposed copy of W (2.0 GB in, 2.0 GB out, 1.04 ms for n r = 1024, d = 3072) and a second layout of the logit gradient would
 // only serve this product.
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool ASTAGED, bool SPLIT = false, int KR = 0>
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool ASTAGED, int SPLIT = 0, int KR = 0>
 __global__ __launch_bounds__(WV * WB * 64)
 void k_gemm_tn(const GemmArgs a) {
   using TL = Tile<WV, WB, VB, PB, SB, NS>;
@@ -148,7 +148,7 @@ void k_gemm_tn(const GemmArgs a) {
       feed.open_rows(a.As, a.As_rows, a.Ak, a.M, t.slab * TL::TV, a.Bk, a.N, t.b0, t.k0, t.klen, smem);
       return;
     }
-    if constexpr (SPLIT) {
+    if constexpr (SPLIT != 0) {
       const long long s0 = (long long)(t.k0 / 32) * 2;             // (chunks are multiples of 64 columns)
       feed.open((const char*)a.As + s0 * a.As_rows * 64, 0, a.Bm, 0, a.N, 2 * t.klen, t.rows, 0, t.b0, smem, nullptr, 0, 1,
                 (const char*)a.Bs + s0 * a.N * 64, a.As_rows, t.slab * TL::TV);
@@ -169,7 +169,7 @@ void k_gemm_tn(const GemmArgs a) {
     // exponents of the tile's operand rows: fetched now, parked in LDS behind the product
     constexpr int XE = (TL::ROWS + TL::NT - 1) / TL::NT;
     int epre[XE];
-    if constexpr (SPLIT) {
+    if constexpr (SPLIT != 0) {
 #pragma unroll
       for (int q = 0; q < XE; ++q) {
         const int idx = min((int)threadIdx.x + q * TL::NT, TL::ROWS - 1);
@@ -179,7 +179,7 @@ void k_gemm_tn(const GemmArgs a) {
       }
     }
     typename FR::blk_t acc[NPB][NVB];
-    if constexpr (SPLIT) tile_gemm_run_split(feed, cur.klen, smem, acc);
+    if constexpr (SPLIT != 0) tile_gemm_run_split(feed, cur.klen, smem, acc);
     else tile_gemm_run(feed, cur.klen, smem, acc);
     const int wnext = w + (int)gridDim.x;
     Where nxt = cur;
@@ -189,7 +189,7 @@ void k_gemm_tn(const GemmArgs a) {
     }
     const int slab = cur.slab, b0 = cur.b0, rows = cur.rows, ks = cur.ks;
     const int rbase = wv * VB * 32 + 4 * lgrp;
-    if constexpr (SPLIT) {
+    if constexpr (SPLIT != 0) {
       int* s_e = (int*)(smem + TL::SMEM);
       // (the product's last barrier is behind the reads of the tile before)
 #pragma unroll
@@ -251,15 +251,15 @@ void k_gemm_tn(const GemmArgs a) {
   }
 }
 
-template <int WV, int WB, int VB, int PB, bool BF16, bool ASTAGED = false, bool SPLIT = false, int KR = 0>
+template <int WV, int WB, int VB, int PB, bool BF16, bool ASTAGED = false, int SPLIT = 0, int KR = 0>
 static hipError_t launch_gemm_cfg(const GemmArgs& a, hipStream_t st) {
   using TL = Tile<WV, WB, VB, PB, 64, 4>;
   if constexpr (!BF16 && !ASTAGED)
-    if (a.planes) return launch_gemm_cfg<WV, WB, VB, PB, true, true, true>(a, st);
+    if (a.planes) return launch_gemm_cfg<WV, WB, VB, PB, true, true, 2>(a, st);
   if constexpr (!ASTAGED && KR == 0)
     if (a.As != nullptr) return launch_gemm_cfg<WV, WB, VB, PB, BF16, true>(a, st);
   constexpr auto kern = k_gemm_tn<WV, WB, VB, PB, 64, 4, BF16, ASTAGED, SPLIT, KR>;
-  constexpr int smem = TL::SMEM + (SPLIT ? TL::ROWS * 4 : 0);
+  constexpr int smem = TL::SMEM + (SPLIT != 0 ? TL::ROWS * 4 : 0);
   static_assert(smem <= 160 * 1024, "LDS budget of one CU");
   if (hipError_t e = allow_lds<kern>(smem); e != hipSuccess) return e;
   const int nslab = (a.M + TL::TV - 1) / TL::TV, nbt = (a.N + TL::TP - 1) / TL::TP;
@@ -295,8 +295,8 @@ static hipError_t launch_gemm_dt(const GemmArgs& a, hipStream_t st) {
     return rounds * rows * gain;
   };
   if (a.Bk.base != nullptr) {
-    if constexpr (BF16) return a.Ak.base != nullptr ? launch_gemm_cfg<2, 4, 4, 2, true, false, false, 3>(a, st) : hipErrorInvalidValue;
-    else return a.planes ? launch_gemm_cfg<2, 4, 4, 2, true, true, true, 2>(a, st) : hipErrorInvalidValue;
+    if constexpr (BF16) return a.Ak.base != nullptr ? launch_gemm_cfg<2, 4, 4, 2, true, false, 0, 3>(a, st) : hipErrorInvalidValue;
+    else return a.planes ? launch_gemm_cfg<2, 4, 4, 2, true, true, 2, 2>(a, st) : hipErrorInvalidValue;
   }
   if (a.ksplit == 1 && cost(320, 0.93) < cost(256, 1.0)) return launch_gemm_cfg<2, 4, 5, 2, BF16>(a, st);
   return launch_gemm_cfg<2, 4, 4, 2, BF16>(a, st);

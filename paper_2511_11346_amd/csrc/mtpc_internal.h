@@ -42,12 +42,12 @@ struct UnembedArgs {
   long long ld_phi;
   // fp32 operands of 256-position tiles, multiplied as two fp16 terms each (split_pays): scratch that
   // launch_unembed fills with the planes of W, [n*r][2 d/32][v][64 bytes], and of h, [2 d/32][B][64 bytes], the exponents of
-  // their rows behind them (plane_exps), and a flag it sets when the terms do not do an operand justice (see
-  // k_split_rows; the fp32 instruction takes over then).  Or nullptr
+  // their rows behind them (plane_exps), and a flag (SPLIT_*) of what the terms do not do justice (k_split_rows).  Or nullptr
   void* Wq;
   void* hq;
   int* wild;
   int* Wexp;            // where the exponents of W's rows go, [n*r*v], or nullptr: behind its planes
+  int three;            // operands without SPLIT_WHOLE that are SPLIT_WIDE go through three bf16 terms, in the same scratch
   int Wq_rows;          // > 0: the planes of W are ONE matrix of so many rows, [2 d/32][Wq_rows][64 bytes], slab after slab
 };
 
@@ -113,15 +113,27 @@ constexpr int H_STAGE_BYTES = 64;
 constexpr int PACK_STAGE_BYTES = 128;
 hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t st);
 
+// Flag bits of operands that are multiplied as terms.  WIDE: a row holds values too far apart for two fp16 terms.  WHOLE: a
+// value is beyond SPLIT_LARGE, where sums of products of bf16 terms may overflow.  Infinite and NaN values are both.
+// STOP: beside WIDE, where only launches after the one that raises it look at it.
+constexpr int SPLIT_WIDE = 1, SPLIT_WHOLE = 2, SPLIT_STOP = 4;
 // Exponents of the rows of a matrix stored as planes of two fp16 terms of `elements` values: right behind them.  (Planes
-// have room for six bytes per value in every workspace: four are the terms.)
+// have room for six bytes per value in every workspace: four are those terms, six are three bf16 terms.)
 inline int* plane_exps(void* planes, long long elements) { return (int*)((char*)planes + 4 * elements); }
 // fp32 rows as planes of two fp16 terms (unembed.hip, k_split_rows): `slabs` matrices of v rows, each [2 d/32][v][64 bytes] or,
 // with dst_rows > 0, all rows of one matrix of so many, and the exponents of all rows.  Rows from `rows1` on (one slab) are
 // the `rows2` of src2 and then zeros
 hipError_t launch_split_rows(const void* src, void* dst, long long slabs, int v, int d, long long row_stride, int* exps,
                              int* flag, int guard, hipStream_t st, long long dst_rows = 0, int rows1 = 0x7fffffff,
-                             const void* src2 = nullptr, int rows2 = 0);
+                             const void* src2 = nullptr, int rows2 = 0, int first = 0, int skip = 0);
+// Up to two matrices as planes of three bf16 terms (split3), the layouts as above with 3 for 2; nothing is done unless the bits
+// `mask` of *flag are `want`
+struct Split3Job {
+  const void* src; void* dst;
+  long long slabs; int v, d; long long row_stride, dst_rows;
+  int rows1; const void* src2; int rows2;
+};
+hipError_t launch_split3(const Split3Job& j0, const Split3Job& j1, int* flag, int mask, int want, hipStream_t st);
 
 // ---- small kernels (circuits.hip) -----------------------------------------
 // log omega[b][:] = log_softmax(Wsum h[b])
@@ -512,6 +524,31 @@ __device__ __forceinline__ void split2(float x, unsigned short (&t)[2]) {
   const _Float16 lo = (_Float16)(finite ? x - (float)hi : 0.f);
   t[0] = __builtin_bit_cast(unsigned short, hi);
   t[1] = __builtin_bit_cast(unsigned short, lo);
+}
+// x as the exact sum of three bf16 terms (8 significant bits each: 24 in all), the next one the nearest bf16 of
+// what is left.  A finite x keeps finite terms (next to the largest value the nearest bf16 would be infinite:
+// the one below is taken); an infinite or NaN x is its own first term, the others are 0.
+// Terms below 2^-126 lose low bits, which matters to values below 2^-110 only.
+// Where an operand is infinite, or so large that products overflow, the products of single terms can be infinities of
+// both signs or infinity times zero: NaN where the product of the values is an infinity.  Operands beyond SPLIT_LARGE are
+// therefore noted (SPLIT_WHOLE), and what they take part in is left to fp32 multiply-adds.
+constexpr float SPLIT_LARGE = 0x1p60f;     // two values up to it: products below 2^120
+__device__ __forceinline__ void split3(float x, unsigned short (&t)[3]) {
+  auto bits = [](float y) { return (unsigned)__builtin_bit_cast(unsigned short, (__bf16)y) << 16; };
+  const unsigned ux = __float_as_uint(x);
+  const bool finite = (ux & 0x7f800000u) != 0x7f800000u;
+  unsigned u1 = bits(x);
+  if ((u1 & 0x7f800000u) == 0x7f800000u && finite) u1 = ux & 0xffff0000u;
+  const float r1 = finite ? x - __uint_as_float(u1) : 0.f;
+  const unsigned u2 = bits(r1);
+  const float r2 = r1 - __uint_as_float(u2);
+  t[0] = (unsigned short)(u1 >> 16);
+  t[1] = (unsigned short)(u2 >> 16);
+  t[2] = (unsigned short)(bits(r2) >> 16);
+}
+// Flag bits, set by one atomic where they are not set yet
+__device__ __forceinline__ void raise_flag(int* flag, int bits) {
+  if (bits != 0 && (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bits) != bits) atomicOr(flag, bits);
 }
 // scaled values below this (about 2^-18 of their row's largest) have fewer than 22 bits left
 constexpr float SPLIT_SMALL = 0.125f;

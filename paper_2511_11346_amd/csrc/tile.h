@@ -210,17 +210,19 @@ __device__ __forceinline__ i32x4_t read_krows(const char* p) {
   return i32x4_t{lo[0], lo[1], hi[0], hi[1]};
 }
 
-// Ring buffers of the plane stages of tile_gemm_run_split: both terms of the columns alternate between two.
+// Ring buffers of the plane stages of tile_gemm_run_split.  Two terms: both of them alternate between two.  Three: the first
+// ones do, the others have one each.
 constexpr int SPLIT_SLOT_HI = 0, SPLIT_SLOT_LO = 2;
+constexpr int SPLIT3_SLOT_A0 = 0, SPLIT3_SLOT_C = 2, SPLIT3_SLOT_B = 3;
 
 // Where the operands of one tile come from, and the direct-to-LDS loads that bring them in: open()
 // describes the tile and issues the first NS-1 stages of its ring, tile_gemm_run() multiplies.  Apart,
 // so that a workgroup that walks several tiles can open the next one (the ring is free once the run
 // has returned) before it turns to the epilogue of the one it has just multiplied.
-// SPLIT: the operands are fp32 matrices as planes of two fp16 terms (see tile_gemm_run_split).
+// SPLIT: the operands are fp32 matrices as planes of two fp16 (2) or three bf16 (3) terms (see tile_gemm_run_split).
 // KR: operands given along their rows (KRows, open_rows): 2 the one of the tile's columns, 3 both; tiles of 256 x 256.
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER = false, bool M16 = false,
-          bool WPACK = false, bool STREAMW = false, int PH = 0, bool SPLIT = false, int VH = 0, int KR = 0>
+          bool WPACK = false, bool STREAMW = false, int PH = 0, int SPLIT = 0, int VH = 0, int KR = 0>
 struct TileFeed {
   using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
   static constexpr int ESZ = BF16 ? 2 : 4;
@@ -263,8 +265,8 @@ struct TileFeed {
     if constexpr (KR == 0) kofs += SB;
     if constexpr (WPACK || KR == 3) kofsW += wstep;
     kofsH += hstep;
-    if constexpr (KR != 0 && SPLIT) hstep = kofs - hstep;       // (kofs: the distance of two terms and back, constant here)
-    if constexpr (KR != 0 && !SPLIT) {
+    if constexpr (KR != 0 && SPLIT != 0) hstep = kofs - hstep;       // (kofs: the distance of two terms and back, constant here)
+    if constexpr (KR != 0 && SPLIT == 0) {
       const bool over = --hleft == 0;
 #pragma unroll
       for (int i = 0; i < 3; ++i) srdH[i] = over ? srdT[i] : srdH[i];
@@ -306,7 +308,7 @@ struct TileFeed {
     srdH = main ? make_srd(bk.base, bk.bytes) : srdT;
     hleft = main ? (bk.kmain - k0) / 32 : 0;
     kofsH = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(main ? k0 : k0 - bk.kmain) * bk.row));
-    hstep = (unsigned)__builtin_amdgcn_readfirstlane((int)(SPLIT ? bk.term : 32u * bk.row));
+    hstep = (unsigned)__builtin_amdgcn_readfirstlane((int)(SPLIT != 0 ? bk.term : 32u * bk.row));
     kofs = (unsigned)__builtin_amdgcn_readfirstlane((int)(32u * bk.row));
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -319,7 +321,8 @@ struct TileFeed {
       voff[q + 2] = row_offset(wl, bk, b0 / 32, (bcols + 31) / 32);
     }
     lds0 = (unsigned)(size_t)smem;
-    if constexpr (SPLIT) {
+    static_assert(SPLIT != 3, "two terms");
+    if constexpr (SPLIT == 2) {
       issue(SPLIT_SLOT_HI);
       issue(SPLIT_SLOT_LO);
       if (klen > 32) issue(SPLIT_SLOT_HI + 1);
@@ -373,7 +376,10 @@ struct TileFeed {
     // has to be told where they come out of a select)
     hstep = (unsigned)__builtin_amdgcn_readfirstlane((int)(hpk ? (unsigned)B * SB : (unsigned)SB));
     wstep = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(wall ? wrows_total : v) * SB));
-    if constexpr (SPLIT) {
+    if constexpr (SPLIT == 3) {
+      issue(SPLIT3_SLOT_A0);
+      issue(SPLIT3_SLOT_B);
+    } else if constexpr (SPLIT == 2) {
       issue(SPLIT_SLOT_HI);
       issue(SPLIT_SLOT_LO);
       if (d > 64) issue(SPLIT_SLOT_HI + 1);
@@ -388,7 +394,7 @@ struct TileFeed {
 // The product of a tile whose feed is open: on return every wave holds its VB x PB accumulator blocks and
 // all waves have passed a barrier (the ring is free).
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER, bool M16, bool WPACK, bool STREAMW, int PH, int VH, int KR>
-__device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, false, VH, KR>& feed,
+__device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, 0, VH, KR>& feed,
                                               int d, char* smem,
                                               typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB - VH / 2]) {
   using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
@@ -648,8 +654,14 @@ __device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, B
 // Bound by the power of the products and of the two operand stages behind every three of them: 1.45 PFLOP/s of issued products
 // (B = 2048, n r = 256, d = 3072, v = 268: 1.83 ms; three bf16 terms and six products 3.19 ms, the fp32 instruction 7.29 ms;
 // registers only, the fp16 product runs at 1.88 PFLOP/s and the bf16 one at 2.02).
-template <int WV, int WB, int VB, int PB, int SB, int NS, int PH, int VH, int KR>
-__device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB, NS, true, false, true, true, false, PH, true, VH, KR>& feed,
+// SPLIT = 3, for operands that those terms do not do justice (k_split_rows): three bf16 terms, each the nearest bf16 of what the
+// ones before leave (split3), whose sum is the value, whatever its row holds.
+//   x y = x1 y1 + x1 y2 + x2 y2 + x2 y1 + x3 y1 + x1 y3 + (x2 y3 + x3 y2 + x3 y3)
+// leaves out at most about 2^-24 |x y| (|x2| <= 2^-8, |x3| <= 2^-17 of the leading power of two), what one fp32 multiply-add may
+// round off.  Stages 3k .. 3k+2 are the terms of columns 32k .. 32k+31; six clusters per 32 columns, each of which reads
+// the operand that changes; loads are issued four or five clusters before their first use.
+template <int WV, int WB, int VB, int PB, int SB, int NS, int PH, int SPLIT, int VH, int KR>
+__device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB, NS, true, false, true, true, false, PH, SPLIT, VH, KR>& feed,
                                                     int d, char* smem, f32x4_t (&acc)[2 * PB + PH][2 * VB - VH / 2]) {
   using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
   constexpr int NPB16 = 2 * PB + PH, NVB16 = 2 * VB - VH / 2;
@@ -692,14 +704,16 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
     for (int pb = 0; pb < NPB16; ++pb)
 #pragma unroll
       for (int vb = 0; vb < decltype(nvb)::value; ++vb) {
-        mma_step_f16(acc[pb][vb], ga[vb], gb[pb]);
+        if constexpr (SPLIT == 3) mma_step<true>(acc[pb][vb], ga[vb], gb[pb]);
+        else mma_step_f16(acc[pb][vb], ga[vb], gb[pb]);
         __builtin_amdgcn_sched_barrier(0);
       }
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
   };
   const int KI = d / 32;
-  if (KI > 1) MTPC_WAIT_VMCNT(TL::PER); else MTPC_WAIT_VMCNT(0);     // both terms of the first columns have landed
+  // both terms of the first columns have landed (of three: the first)
+  if (SPLIT == 3 || KI > 1) MTPC_WAIT_VMCNT(TL::PER); else MTPC_WAIT_VMCNT(0);
   __syncthreads();
   auto run = [&](auto grp) {
     constexpr int G = decltype(grp)::value;
@@ -731,10 +745,35 @@ __device__ __forceinline__ void tile_gemm_run_split(TileFeed<WV, WB, VB, PB, SB,
       if constexpr (LEFT >= 2) feed.issue(hi);
       rest(std::integral_constant<int, LEFT >= 2 ? TL::PER : LEFT == 1 ? 0 : -1>{});     // the next pair landed
     };
+    // The six products of the three-term form; the last ones issue no more.
+    auto columns3 = [&](int k, auto lastk) {
+      constexpr bool LAST = decltype(lastk)::value;
+      const int a = SPLIT3_SLOT_A0 + (k & 1);
+      read_a(a, nvb); read_b(a);            // x1 y1.  Third terms and the next first terms go where nobody reads
+      feed.issue(SPLIT3_SLOT_C);            // any more since the last barrier
+      rest(std::integral_constant<int, TL::PER>{});            // second terms landed
+      read_b(SPLIT3_SLOT_B);                // x1 y2
+      if constexpr (!LAST) feed.issue(a ^ 1);
+      rest(std::integral_constant<int, -1>{});
+      read_a(SPLIT3_SLOT_B, nvb);           // x2 y2
+      rest(std::integral_constant<int, -1>{});
+      read_b(a);                            // x2 y1: the buffer of the second terms is free
+      if constexpr (!LAST) feed.issue(SPLIT3_SLOT_B);
+      rest(std::integral_constant<int, LAST ? 0 : 2 * TL::PER>{});   // third terms landed
+      read_a(SPLIT3_SLOT_C, nvb);           // x3 y1
+      rest(std::integral_constant<int, -1>{});
+      read_a(a, nvb); read_b(SPLIT3_SLOT_C);      // x1 y3
+      rest(std::integral_constant<int, LAST ? -1 : TL::PER>{});      // the next first terms landed
+    };
     int k = 0;
-    for (; k < KI - 2; ++k) columns(k, std::integral_constant<int, 2>{});
-    if (k < KI - 1) columns(k++, std::integral_constant<int, 1>{});
-    columns(k, std::integral_constant<int, 0>{});
+    if constexpr (SPLIT == 3) {
+      for (; k < KI - 1; ++k) columns3(k, std::false_type{});
+      columns3(k, std::true_type{});
+    } else {
+      for (; k < KI - 2; ++k) columns(k, std::integral_constant<int, 2>{});
+      if (k < KI - 1) columns(k++, std::integral_constant<int, 1>{});
+      columns(k, std::integral_constant<int, 0>{});
+    }
   };
   if (wave >> 2) {
     __syncthreads();                        // start one cluster late

@@ -245,17 +245,21 @@ __device__ __forceinline__ void tile_draws_cols(const f32x4_t (&acc)[NPB][NVB], 
 template <int WB, bool SAMPLE>
 constexpr bool unembed_walks_tiles() { return !SAMPLE && WB != 1; }
 
-// SPLIT: fp32 operands as planes of two fp16 terms (tile_gemm_run_split); everything but the product, and the scales of
-// its rows that come out of the result behind it, is the bf16 kernel's.
+// SPLIT: fp32 operands as planes of two fp16 terms or three bf16 terms (tile_gemm_run_split); everything but the product, and the
+// scales of fp16 terms' rows that come out of the result behind it, is the bf16 kernel's.
 // STREAM: one tile of positions, so that every byte of W is read once (loaded with the non-temporal hint).
 // PH: 16 more positions per wave (Tile).
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false, int VH = 0,
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, int SPLIT = 0, int VH = 0,
           bool STREAM = false, int PH = 0>
 __global__ __launch_bounds__(WV * WB * 64)
 void k_unembed(const UnembedArgs a) {
-  // of the two launches over the same fp32 operands one does the work (see launch_split)
-  if constexpr (SPLIT || !BF16)
-    if (a.wild != nullptr && (*a.wild != 0) == SPLIT) return;
+  // of the launches over the same fp32 operands one does the work (see launch_split)
+  if constexpr (SPLIT != 0 || !BF16)
+    if (a.wild != nullptr) {
+      const int flag = *a.wild;
+      const bool three = a.three != 0 && (flag & SPLIT_WHOLE) == 0;
+      if (SPLIT != ((flag & SPLIT_WIDE) == 0 ? 2 : three ? 3 : 0)) return;
+    }
   using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
   constexpr bool M16 = use_m16<WV, WB, SB, NS, BF16>();
   using FR = Frag<M16>;
@@ -276,9 +280,9 @@ void k_unembed(const UnembedArgs a) {
   using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, STREAM, PH, SPLIT, VH>;
   const void* const hstaged = SPLIT ? a.hq : (WB != 1 && SB == H_STAGE_BYTES) ? a.hs : nullptr;
   const void* const Wfeed = SPLIT ? a.Wq : WPACK ? a.Wp : a.W;
-  const int dfeed = SPLIT ? 2 * a.d : a.d;            // 16-bit columns of the planes
-  const int* const hexp = SPLIT ? (const int*)((const char*)a.hq + 4LL * a.B * a.d) : nullptr;      // (plane_exps)
-  int* const s_e = (int*)(smem + TL::SMEM);           // SPLIT: exponents of the tile's rows and columns [TV + TP]
+  const int dfeed = SPLIT != 0 ? SPLIT * a.d : a.d;   // 16-bit columns of the planes
+  const int* const hexp = SPLIT == 2 ? (const int*)((const char*)a.hq + 4LL * a.B * a.d) : nullptr;      // (plane_exps)
+  int* const s_e = (int*)(smem + TL::SMEM);           // SPLIT = 2: exponents of the tile's rows and columns [TV + TP]
   const int ntiles = nbt * nslab;
   int slab, bt;
   tile_of_block(blockIdx.x, nbt, nslab, slab, bt);
@@ -312,7 +316,7 @@ void k_unembed(const UnembedArgs a) {
   // exponents of the tile's operand rows, the same way
   constexpr int XE = (TL::ROWS + TL::NT - 1) / TL::NT;
   int epre[XE];
-  if constexpr (SPLIT) {
+  if constexpr (SPLIT == 2) {
 #pragma unroll
     for (int q = 0; q < XE; ++q) {
       const int idx = min(tid + q * TL::NT, TL::ROWS - 1);
@@ -321,7 +325,7 @@ void k_unembed(const UnembedArgs a) {
   }
 
   typename FR::blk_t acc[NPB][NVB];
-  if constexpr (SPLIT) tile_gemm_run_split(feed, a.d, smem, acc);
+  if constexpr (SPLIT != 0) tile_gemm_run_split(feed, a.d, smem, acc);
   else tile_gemm_run(feed, a.d, smem, acc);
   const int wnext = w + (int)gridDim.x;
   int slab_next = 0, bt_next = 0;
@@ -340,7 +344,7 @@ void k_unembed(const UnembedArgs a) {
   }
   // this lane holds, of position column wb*WP + pb*BR + lcol, rows rbase + vb*BR + roff(i)
   const int rbase = wv * TL::WROWS + 4 * lgrp;
-  if constexpr (SPLIT) {
+  if constexpr (SPLIT == 2) {
 #pragma unroll
     for (int q = 0; q < XE; ++q)
       if (tid + q * TL::NT < TL::ROWS) s_e[tid + q * TL::NT] = epre[q];
@@ -1060,12 +1064,12 @@ hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t st)
   return dtype == MTPC_BF16 ? launch_uni_dt<true>(a, st) : launch_uni_dt<false>(a, st);
 }
 
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, bool SPLIT = false, int VH = 0,
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, int SPLIT = 0, int VH = 0,
           bool STREAM = false, int PH = 0>
 static hipError_t launch_cfg(const UnembedArgs& a, hipStream_t st) {
   using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
   constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK, SPLIT, VH, STREAM, PH>;
-  constexpr int smem = TL::SMEM + (SPLIT ? TL::ROWS * 4 : 0);
+  constexpr int smem = TL::SMEM + (SPLIT == 2 ? TL::ROWS * 4 : 0);
   static_assert(smem <= 160 * 1024, "LDS budget of one CU");
   if (hipError_t e = allow_lds<kern>(smem); e != hipSuccess) return e;
   const int nbt = (a.B + TL::TP - 1) / TL::TP;
@@ -1106,13 +1110,13 @@ static hipError_t launch_dec(const UnembedArgs& a, int row_bytes, hipStream_t st
 // Tiles of 256 (PB = 2), 192 (PB = PH = 1) or 128 positions of the fewest rows that hold the vocabulary (a K stage costs what its rows
 // cost: products, loads and fragment reads alike).  The 272-row one exists for 16x16 blocks only: fp32 instructions
 // fill 32.  What a narrower tile leaves of LDS goes to a fifth ring buffer.
-template <bool BF16, bool SAMPLE, bool WPACK, bool SPLIT = false, int PB = 2, int PH = 0>
+template <bool BF16, bool SAMPLE, bool WPACK, int SPLIT = 0, int PB = 2, int PH = 0>
 static hipError_t launch_train(const UnembedArgs& a, hipStream_t st) {
   constexpr int NS = PB == 1 && PH == 0 ? 5 : 4;
   // A pass that writes the table is bound by its stores where rows of W are short, and those of 16 bytes per lane leave the
   // 272-row tile more slowly (the halves of a column are in different wave groups): v = 268, n r = 960, B = 1182, with 320 / 272
   // rows 939 / 962 us at d = 448, 1178 / 1178 at d = 1024, 880 / 843 at d = 2048 (marginals over all tokens).
-  const bool stores = BF16 && !SPLIT && a.logphi != nullptr && a.d < 1024 && a.v < 272 && a.v % 4 == 0;
+  const bool stores = BF16 && SPLIT == 0 && a.logphi != nullptr && a.d < 1024 && a.v < 272 && a.v % 4 == 0;
   if (a.v > 272 || (a.v > 256 && stores)) return launch_cfg<2, 4, 5, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT, 0, false, PH>(a, st);
   if (a.v > 256) return launch_cfg<2, 4, 5, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT, BF16 ? 3 : 0, false, PH>(a, st);
   if (a.v > 192) return launch_cfg<2, 4, 4, PB, 64, NS, BF16, SAMPLE, WPACK, SPLIT, 0, false, PH>(a, st);
@@ -1158,10 +1162,10 @@ static hipError_t launch_dt(const UnembedArgs& a, hipStream_t st) {
     if constexpr (BF16 && !SAMPLE) {
       if (positions == 256)
         if (hipError_t e = walk_positions(a, false, positions); e != hipSuccess) return e;
-      if (positions == 192) return packed ? launch_train<BF16, SAMPLE, true, false, 1, 1>(a, st) : launch_train<BF16, SAMPLE, false, false, 1, 1>(a, st);
+      if (positions == 192) return packed ? launch_train<BF16, SAMPLE, true, 0, 1, 1>(a, st) : launch_train<BF16, SAMPLE, false, 0, 1, 1>(a, st);
     }
     if (positions == 256) return packed ? launch_train<BF16, SAMPLE, true>(a, st) : launch_train<BF16, SAMPLE, false>(a, st);
-    return packed ? launch_train<BF16, SAMPLE, true, false, 1>(a, st) : launch_train<BF16, SAMPLE, false, false, 1>(a, st);
+    return packed ? launch_train<BF16, SAMPLE, true, 0, 1>(a, st) : launch_train<BF16, SAMPLE, false, 0, 1>(a, st);
   }
   if (positions == 64) {
     if (a.v > 256) return launch_dec<5, 2, BF16, SAMPLE>(a, row_bytes, st);
@@ -1202,15 +1206,19 @@ hipError_t launch_pack_rows(const void* src, void* dst, long long slabs, int v, 
 // 64 contiguous bytes of each plane, eight rows of a stage follow each other.  Rows of up to 4096 columns stay in registers
 // between the search for their largest value and the split, so the matrix is read once: 843 MB to as many of planes in 0.34 ms
 // (4.9 TB/s); a row at a time per thread quad and three planes took 0.43 ms.
-// Sets *flag when a value is infinite or NaN.  guard: also when the terms may do a row less than justice: a value below
-// SPLIT_SMALL is small beside its row's largest, which matters where much of the row is - one outlier - and not where a
+// Raises SPLIT_WHOLE for values beyond SPLIT_LARGE, and SPLIT_WIDE for infinite and NaN ones.  guard: SPLIT_WIDE also when the
+// terms may do a row less than justice: a value below SPLIT_SMALL is small beside its row's largest, which matters where much of the row is - one outlier - and not where a
 // few values happen to be near 0: more than one in 16 of those that are not 0 (of a row with few of them, any).
+// first: raises SPLIT_STOP beside SPLIT_WIDE.  skip: a caller that has no use for the planes of one matrix where another is
+// SPLIT_WIDE; nothing is done where the launch before has found that, and little more than the reads where this one does.
 constexpr int SPLIT_ROWS = 8, SPLIT_KEEP = 8;        // rows of a workgroup, steps of 512 columns kept in registers
-__global__ __launch_bounds__(512) void k_split_rows(const char* __restrict__ src, char* __restrict__ dst, int v, int d,
+// (four waves to a SIMD, so that two workgroups share a CU: with one, the same reads take a quarter longer)
+__global__ __launch_bounds__(512, 4) void k_split_rows(const char* __restrict__ src, char* __restrict__ dst, int v, int d,
                                                     long long row_stride, int* __restrict__ exps, int* flag, int guard,
-                                                    long long dst_rows, int rows1, const char* __restrict__ src2, int rows2) {
+                                                    long long dst_rows, int rows1, const char* __restrict__ src2, int rows2, int first, int skip) {
+  if (skip && (*flag & SPLIT_STOP) != 0) return;     // (raised by launches before this one only: the same for every wave)
   __shared__ unsigned s_max[8][SPLIT_ROWS];
-  __shared__ int s_small[8][SPLIT_ROWS], s_zero[8][SPLIT_ROWS];
+  __shared__ int s_small[8][SPLIT_ROWS], s_zero[8][SPLIT_ROWS], s_stop;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rblocks = (v + SPLIT_ROWS - 1) / SPLIT_ROWS;
   const int slab = blockIdx.x / rblocks, rl = (tid >> 2) & (SPLIT_ROWS - 1);
@@ -1232,12 +1240,12 @@ __global__ __launch_bounds__(512) void k_split_rows(const char* __restrict__ src
     }
   }
   unsigned m = 0;                                    // largest finite magnitude, as bits
-  bool bad = false;
+  bool odd = false;                                  // a value that is infinite or NaN
   auto look = [&](const f32x4_t& y) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const unsigned u = __float_as_uint(y[c]) & 0x7fffffffu;
-      bad |= u >= 0x7f800000u;
+      odd |= u >= 0x7f800000u;
       m = max(m, u < 0x7f800000u ? u : 0u);
     }
   };
@@ -1251,7 +1259,9 @@ __global__ __launch_bounds__(512) void k_split_rows(const char* __restrict__ src
   auto over = [&](unsigned y, int bit) { return (unsigned)__shfl_xor((int)y, bit); };
   m = max(m, over(m, 1)); m = max(m, over(m, 2)); m = max(m, over(m, 32));
   if ((lane & 35) == 0) s_max[wave][rl] = m;
+  if (tid == 0) s_stop = skip ? __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & SPLIT_WIDE : 0;
   __syncthreads();
+  if (s_stop != 0) return;
 #pragma unroll
   for (int w = 0; w < 8; ++w) m = max(m, s_max[w][rl]);
   const int E = split_exp(__uint_as_float(m));
@@ -1276,57 +1286,115 @@ __global__ __launch_bounds__(512) void k_split_rows(const char* __restrict__ src
   const f32x4_t zeros = f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int k = SPLIT_KEEP * 16 + sub; live && k < stages; k += 16)
     put(read ? *(const f32x4_t*)(s + (long long)k * 128) : zeros, read ? *(const f32x4_t*)(s + (long long)k * 128 + 16) : zeros, k);
+  int raise = odd ? SPLIT_WIDE | SPLIT_WHOLE : 0;
   if (guard) {
-    if (__syncthreads_or(small > 0)) {               // (only then the zeros, which do not count, matter)
+    auto sum = [&](int y) { y += __shfl_xor(y, 1); y += __shfl_xor(y, 2); return y + __shfl_xor(y, 32); };
+    small = sum(small);
+    if ((lane & 35) == 0) s_small[wave][rl] = small;
+    __syncthreads();
+    small = 0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) small += s_small[w][rl];
+    // (up to one in 16 of all, zeros included: no zeros make that more than one in 16 of the others)
+    if (__syncthreads_or(live && small > d / 16)) {
       int zero = 0;
-      auto count = [&](const f32x4_t& y) {
+      for (int k = sub; live && k < stages; k += 16)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) zero += y[c] == 0.f;
-      };
-#pragma unroll
-      for (int it = 0; it < SPLIT_KEEP; ++it)
-        if (live && it * 16 + sub < stages) { count(x[it][0]); count(x[it][1]); }
-      for (int k = SPLIT_KEEP * 16 + sub; live && k < stages; k += 16) {
-        count(read ? *(const f32x4_t*)(s + (long long)k * 128) : zeros);
-        count(read ? *(const f32x4_t*)(s + (long long)k * 128 + 16) : zeros);
-      }
-      auto sum = [&](int y) { y += __shfl_xor(y, 1); y += __shfl_xor(y, 2); return y + __shfl_xor(y, 32); };
-      small = sum(small); zero = sum(zero);
-      if ((lane & 35) == 0) { s_small[wave][rl] = small; s_zero[wave][rl] = zero; }
+        for (int c = 0; c < 8; ++c) zero += !read || *(const float*)(s + (long long)k * 128 + c * 4) == 0.f;
+      zero = sum(zero);
+      if ((lane & 35) == 0) s_zero[wave][rl] = zero;
       __syncthreads();
-      small = zero = 0;
+      zero = 0;
 #pragma unroll
-      for (int w = 0; w < 8; ++w) { small += s_small[w][rl]; zero += s_zero[w][rl]; }
-      bad |= small - zero > (d - zero) / 16;
+      for (int w = 0; w < 8; ++w) zero += s_zero[w][rl];
+      if (ch == 0 && sub == 0 && small - zero > (d - zero) / 16) raise |= SPLIT_WIDE;
     }
   }
-  if (live && ch == 0 && sub == 0) exps[(long long)slab * v + row] = E;
-  if (live && bad) *flag = 1;
+  if (live && ch == 0 && sub == 0) {
+    exps[(long long)slab * v + row] = E;
+    if (__uint_as_float(m) > SPLIT_LARGE) raise |= SPLIT_WHOLE;
+  }
+  if (live) raise_flag(flag, first && (raise & SPLIT_WIDE) ? raise | SPLIT_STOP : raise);
 }
 
 hipError_t launch_split_rows(const void* src, void* dst, long long slabs, int v, int d, long long row_stride, int* exps,
-                             int* flag, int guard, hipStream_t st, long long dst_rows, int rows1, const void* src2, int rows2) {
+                             int* flag, int guard, hipStream_t st, long long dst_rows, int rows1, const void* src2, int rows2, int first, int skip) {
   const long long blocks = slabs * ((v + SPLIT_ROWS - 1) / SPLIT_ROWS);
   hipLaunchKernelGGL(k_split_rows, dim3((unsigned)blocks), dim3(512), 0, st, (const char*)src, (char*)dst, v, d, row_stride, exps,
-                     flag, guard, dst_rows, rows1, (const char*)src2, rows2);
+                     flag, guard, dst_rows, rows1, (const char*)src2, rows2, first, skip);
+  return hipGetLastError();
+}
+
+// Planes of three bf16 terms: one thread splits 8 columns; four threads read one 128-byte line and write 64 contiguous bytes of
+// each plane, neighbouring rows follow (843 MB of W in 0.43 ms, 4.9 TB/s).  Raises SPLIT_WHOLE (a matrix that k_split_rows has skipped
+// is seen here first).
+__global__ __launch_bounds__(256) void k_split3(const Split3Job j0, const Split3Job j1, int* flag, int mask, int want) {
+  if ((__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & mask) != want) return;
+  bool large = false;
+  for (int g = 0; g < 2; ++g) {
+    const Split3Job& j = g == 0 ? j0 : j1;
+    const long long per_slab = (long long)j.v * (j.d / 8), total = j.slabs * per_slab;
+    const long long srow = j.dst_rows > 0 ? j.dst_rows : j.v;
+    for (long long t = (long long)blockIdx.x * 256 + threadIdx.x; t < total; t += (long long)gridDim.x * 256) {
+      const long long slab = t / per_slab;
+      const int u = (int)(t - slab * per_slab);
+      const int k = u / (j.v * 4), w = u - k * j.v * 4, row = w >> 2, ch = w & 3;
+      const bool second = row >= j.rows1;
+      f32x4_t x[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+      if (!second || row - j.rows1 < j.rows2) {
+        const char* s = (second ? (const char*)j.src2 + (long long)(row - j.rows1) * j.row_stride : (const char*)j.src + (slab * j.v + row) * j.row_stride) +
+                        (long long)k * 128 + ch * 32;
+        x[0] = __builtin_nontemporal_load((const f32x4_t*)s);
+        x[1] = __builtin_nontemporal_load((const f32x4_t*)(s + 16));
+      }
+      struct alignas(16) Oct { unsigned short v[8]; } o[3];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        unsigned short q[3];
+        split3(x[c >> 2][c & 3], q);
+        large |= !(fabsf(x[c >> 2][c & 3]) <= SPLIT_LARGE);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) o[p].v[c] = q[p];
+      }
+      char* const out = (char*)j.dst + ((j.dst_rows > 0 ? slab * j.v : slab * 3 * (j.d / 32) * j.v) + row) * 64 + ch * 16;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *(Oct*)(out + (3LL * k + p) * srow * 64) = o[p];
+    }
+  }
+  if (large) raise_flag(flag, SPLIT_WHOLE);
+}
+
+hipError_t launch_split3(const Split3Job& j0, const Split3Job& j1, int* flag, int mask, int want, hipStream_t st) {
+  const long long chunks = std::max(j0.slabs * j0.v * (j0.d / 8), j1.slabs * j1.v * (j1.d / 8));
+  // (at most eight workgroups per CU, which walk: mostly there is nothing to do, and many would take long to say so)
+  hipLaunchKernelGGL(k_split3, dim3((unsigned)std::min((chunks + 255) / 256, 2048LL)), dim3(256), 0, st, j0, j1, flag, mask, want);
   return hipGetLastError();
 }
 
 __global__ void k_clear_flag(int* flag) { *flag = 0; }
 
-// fp32 operands through their fp16 terms.  Operands that those would not do justice stay with the fp32 instruction: which of
-// the two launches does the work is known on the device only, the other one's workgroups leave at once (about 5 us).
+// fp32 operands through their fp16 terms.  Operands that those would not do justice go through three bf16 terms, which cost
+// 1.7 times as much (see tile_gemm_run_split), and what those cannot take stays with the fp32 instruction: which of the
+// three launches does the work is known on the device only, the others' workgroups leave at once (2 to 3 us each, as the split
+// into bf16 terms that is not needed).
 static hipError_t launch_split(const UnembedArgs& a0, hipStream_t st) {
   UnembedArgs a = a0;
   const long long slabs = (long long)a.n * a.r;
   if (a.Wexp == nullptr) a.Wexp = plane_exps(a.Wq, slabs * a.v * a.d);
   hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, st, a.wild);
-  hipError_t e = launch_split_rows(a.h, a.hq, 1, a.B, a.d, a.ld_h * 4, plane_exps(a.hq, (long long)a.B * a.d), a.wild, 1, st);
-  if (e == hipSuccess) e = launch_split_rows(a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wexp, a.wild, 1, st, a.Wq_rows);
+  hipError_t e = launch_split_rows(a.h, a.hq, 1, a.B, a.d, a.ld_h * 4, plane_exps(a.hq, (long long)a.B * a.d), a.wild, 1, st, 0, 0x7fffffff,
+                                   nullptr, 0, a.three, 0);
+  if (e == hipSuccess) e = launch_split_rows(a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wexp, a.wild, 1, st, a.Wq_rows, 0x7fffffff, nullptr, 0, 0, a.three);
+  if (e == hipSuccess && a.three) {
+    const Split3Job jh{a.h, a.hq, 1, a.B, a.d, a.ld_h * 4LL, 0, 0x7fffffff, nullptr, 0};
+    const Split3Job jw{a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wq_rows, 0x7fffffff, nullptr, 0};
+    e = launch_split3(jh, jw, a.wild, SPLIT_WIDE | SPLIT_WHOLE, SPLIT_WIDE, st);
+  }
   int positions = 256;
   if (e == hipSuccess) e = walk_positions(a, true, positions);
   if (e == hipSuccess)
-    e = positions == 192 ? launch_train<true, false, true, true, 1, 1>(a, st) : launch_train<true, false, true, true>(a, st);
+    e = positions == 192 ? launch_train<true, false, true, 2, 1, 1>(a, st) : launch_train<true, false, true, 2>(a, st);
+  if (e == hipSuccess && a.three) e = launch_train<true, false, true, 3>(a, st);
   return e != hipSuccess ? e : launch_dt<false, false>(a, st);
 }
 

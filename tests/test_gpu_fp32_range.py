@@ -12,6 +12,7 @@ import mtpc_inputs as mi
 from oracle import backward as bw
 from oracle import mtpc_oracle as oc
 from gpu_util import make_head, takes_terms
+from test_gpu_split import without_planes
 
 pytestmark = pytest.mark.gpu
 
@@ -90,3 +91,33 @@ def test_sparse_rows_with_an_outlier(kept, power):
     err = np.abs(head.prefix_marginals(torch.from_numpy(inp.targets).cuda()).cpu().numpy() - want).max()
     print(kept, power, err)
     assert err < LOG * 8 ** 0.5
+
+
+@pytest.mark.parametrize("B,d,n,r,v", [(257, 512, 8, 11, 33), (513, 544, 4, 20, 320), (300, 1056, 8, 11, 268), (257, 512, 8, 11, 129), (300, 512, 8, 12, 193)])
+@pytest.mark.parametrize("where", ["h", "W", "h of infinity in W"])
+def test_an_outlier_costs_the_terms_but_not_the_matrix_pipes(where, B, d, n, r, v):
+    """Beside a row with an outlier the call goes through three bf16 terms, which hold it; with an infinite weight as well, through
+    the fp32 instruction.  Neither gives the bits of a workspace without room for planes, unless that is the same route."""
+    inp = mi.make_inputs("cp", B=B, d=d, n=n, r=r, v=v, dtype="f32", seed=v, h_scale=1.0)
+    inp.W[..., 0] = 0.0
+    inp.Wsum[:, 0] = 0.0
+    if where == "W":
+        inp.h[:, 0] = 0.0
+        inp.W[1, 2, 3, 0] = 2.0 ** 28
+    else:
+        inp.h[5, 0] = 2.0 ** 28
+    logphi, logw, _ = oc._params("cp", inp.h, inp.W, inp.Wsum, None)
+    want = oc.prefix_marginals_from("cp", logphi, logw, None, inp.targets)
+    if where == "h of infinity in W":
+        inp.W[0, 0, 0, 1] = -np.inf
+        inp.h[:, 1] = np.abs(inp.h[:, 1]) + 1e-3
+        inp.targets[:, 0] = 0                            # a token that one unit rules out
+        logphi, logw, _ = oc._params("cp", inp.h, np.where(np.isinf(inp.W), -1e30, inp.W), inp.Wsum, None)
+        want = oc.prefix_marginals_from("cp", logphi, logw, None, inp.targets)
+    head = make_head(inp)
+    assert takes_terms(head)
+    tg = torch.from_numpy(inp.targets).cuda()
+    got, plain = head.prefix_marginals(tg).cpu().numpy(), without_planes(head, tg).cpu().numpy()
+    assert np.abs(got - want).max() < LOG * n ** 0.5
+    assert np.abs(plain - want).max() < LOG * n ** 0.5
+    assert np.array_equal(got, plain) == (where == "h of infinity in W")
