@@ -120,9 +120,10 @@ const char* mtpc_status_string(mtpc_status s);
  * fp32 calls whose pass over W is multiplied as two fp16 terms per value (large
  * batches, where that is faster; sampling never is) ask for 6 bytes more per element of W
  * and h; they also run without that room, on the fp32 instructions (results differ within
- * fp32 rounding of the sums), and take those by themselves for operands the terms would not do
- * justice: infinite or NaN values, rows with more than one value in 16, of those other than 0,
- * below 2^-18 of the largest.
+ * fp32 rounding of the sums).  Operands that those terms would not do justice - a row with more than one
+ * value in 16, of those other than 0, below 2^-18 of the largest - go through three bf16 terms, which
+ * hold every value whole, in the same scratch (1.7 times the time), and those among them that are infinite
+ * or beyond 2^60 through the fp32 instructions.
  * Returns 0 for invalid arguments. */
 size_t mtpc_workspace_bytes(int32_t family, int32_t op, const mtpc_head* head,
                             const mtpc_sumlayers* layers, int32_t S, int32_t mode);
@@ -318,9 +319,11 @@ mtpc_status mtpc_btree_verify(const mtpc_head* head, const mtpc_sumlayers* A, co
  * smaller MTPC_BWD_RECOMPUTE size nothing of size n*r*v*B is kept in fp32 and the
  * logits are recomputed (one more pass of the unembedding product).
  * fp32 contractions of more than 64 positions (layers not computed from h) multiply each value as two
- * fp16 terms: 23 bits of it, or 2^-40 of the largest value it is summed beside (the logit gradient of
- * a token over all positions, that of a position over all tokens, a feature of h, a row of W); results
- * that are not finite are those of fp32 sums.
+ * fp16 terms: 22 bits of it or more, down to 2^-18 of the largest it is scaled beside (the logit gradient of
+ * a token over all positions, that of a position over all tokens, a feature of h over the positions that
+ * have a gradient, a row of W).  Where more than one in 16 of a feature of h, of a row or of a column of W is
+ * below that, or a position's features are next to nothing beside those of the others, all operands go
+ * through three bf16 terms, which hold every value whole; results that are not finite are those of fp32 sums.
  * targets: ids in [0, v), or -1 (that variable is summed out and receives no
  * gradient).
  * dlayers has the shape of the stored layer logits ([n-1][r][r], or [1][r][r] for a

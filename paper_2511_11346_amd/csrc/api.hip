@@ -654,7 +654,8 @@ struct BwdPlan {
   long long M, Mx, Mlay, Mtot, ldM, ldb;
   // fp32 as two fp16 terms: in the forward pass (split_pays) and in the two contractions
   bool split_fwd, split;
-  size_t hq, wild, dslT, big;
+  size_t hq, dslT;
+  size_t terms;             // flag of the terms; 16 bytes on, what the scales of the terms are decided by (run_backward)
   bool staged;              // the logit gradient stage-major, as the contractions read it
   bool along_rows;          // bf16: the dh contraction reads W and the logit gradient along their rows
 };
@@ -689,7 +690,7 @@ BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly,
   q.split_fwd = q.split && split_pays(hd);
   const size_t osz = q.split ? 6 : esz;       // bytes per element of the contractions' operands
   q.dLT = take((size_t)(q.ctx ? q.ldM : q.split ? q.M : q.Mx) * q.ldb * osz);
-  if (q.split) q.big = take(16 + (size_t)q.ldb * 4);        // flag and, 16 bytes on, the largest exponent of each position
+  if (q.split) q.terms = take(16 + (size_t)(q.ldb + hd->d) * 8 + (size_t)q.M * 4);
   q.dslT = q.split ? take((size_t)(q.Mx - q.M) * q.ldb * esz) : q.dLT + (size_t)q.M * q.ldb * esz;
   q.dL = take(B * q.ldM * osz);
   // (stage-major when one kernel writes every element of both layouts - no layer-logit columns from elsewhere - and one
@@ -720,7 +721,6 @@ BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly,
   q.WT = take((size_t)hd->d * q.ldM * osz);
   q.hT = take((size_t)hd->d * q.ldb * esz);
   if (q.split_fwd) {                          // (the planes of W are those the dh contraction reads: in WT)
-    q.wild = take(4);
     q.hq = take(B * (size_t)hd->d * 6);
   }
   q.has_hs = !q.split_fwd && stage_major_h_pays(hd);
@@ -822,9 +822,16 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   if (q.keep_phi) { u.phiT = (float*)(ws + q.phi); u.ld_phi = q.ldb; }
   // (planes of W and, behind them, Wsum, one matrix of ldM rows for the forward pass and the contraction over them: in WT)
   int* const wexp = q.split ? plane_exps(ws + q.WT, hd->d * q.ldM) : nullptr;
+  int* const flag = q.split ? (int*)(ws + q.terms) : nullptr;
+  int* const top = q.split ? flag + 4 : nullptr;                                   // per position: the largest element of its row of dL
+  unsigned* const weights = q.split ? (unsigned*)top + q.ldb : nullptr;            // ... and the magnitudes of its row of h
+  int* const cols = q.split ? top + 2 * q.ldb : nullptr;                           // per column of W: small values, zeros
+  int* const rows = q.split ? cols + 2 * hd->d : nullptr;                          // per row of dLT: its largest element
+  const int nflags = q.split ? (int)(4 + 2 * (q.ldb + hd->d) + q.M) : 0;
   if (q.split_fwd) {
-    u.Wq = ws + q.WT; u.Wq_rows = (int)q.ldM; u.Wexp = wexp;
-    u.hq = ws + q.hq; u.wild = (int*)(ws + q.wild);
+    HIP_TRY(launch_clear(flag, nflags, st));
+    u.Wq = ws + q.WT; u.Wq_rows = (int)q.ldM; u.Wexp = wexp; u.cols = cols;
+    u.hq = ws + q.hq; u.wild = flag; u.cleared = 1; u.three = 1;
   }
   HIP_TRY(stage_major_h(hd, q.has_hs, q.hs, u, st));
   HIP_TRY(launch_unembed(u, hd->dtype, st));
@@ -837,8 +844,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   c.coef = coef; c.Ge = (float*)(ws + q.Ge);
   c.dslT = family == MTPC_FF ? nullptr : (void*)(ws + q.dslT);
   c.ldb = q.ldb; c.bf16 = hd->dtype == MTPC_BF16; c.loss = loss;
-  int* const big = q.split ? (int*)(ws + q.big) : nullptr;
-  if (big) HIP_TRY(launch_clear(big, 4 + q.ldb, st));
+  if (!q.split_fwd) { c.clear = flag; c.nclear = nflags; }
   if (L > 0) {
     c.lay_nat = (const float*)(ws + q.lay_nat);
     c.lay_tr = (ctx || q.perpos) ? nullptr : (const float*)(ws + q.lay_tr);
@@ -867,7 +873,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   const int kmain = (int)(q.M / 32 * 32);
   if (q.split) {
     TransposeArgs w{};
-    w.along_rows = 1; w.planes = 1; w.big = big; w.exps = wexp;
+    w.along_rows = 1; w.planes = 1; w.flag = flag; w.exps = wexp; w.cols = cols;
     w.src = hd->W; w.ld_src = hd->d; w.R = (int)q.M; w.C = hd->d; w.Rpad = (int)q.ldM;
     w.src2 = hd->Wsum; w.R2 = (int)(q.Mx - q.M);
     w.row0 = q.split_fwd ? (int)q.M : 0;
@@ -876,18 +882,32 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   }
   // ---- logit gradient in both layouts: dLT [.][ldb] and dL = dLT^T [B][ldM] (the first one only where that is read along its rows)
   TransposeArgs t{};
+  GradPhiArgs g{};
   if (q.keep_phi) {
-    GradPhiArgs g{};
     g.phiT = (const float*)(ws + q.phi); g.ld_phi = q.ldb; g.targets = targets; g.Ge = c.Ge;
     g.B = hd->B; g.n = hd->n; g.r = hd->r; g.v = hd->v;
     g.M = q.M; g.Mx = q.Mx; g.ldM = q.ldM; g.ldb = q.ldb;
     g.dl_end = ctx ? q.Mlay : q.ldM;           // the layer-logit columns are written by the reverse pass
     g.dLT = ws + q.dLT; g.dL = ws + q.dL;
     g.staged = q.staged;
-    g.planes = q.split; g.big = big; g.top = big ? big + 4 : nullptr; g.dslT = ws + q.dslT;
-    g.Wexp = wexp; g.wild = q.split_fwd ? (const int*)(ws + q.wild) : nullptr;
+    g.planes = q.split; g.flag = flag; g.top = top; g.rows = rows; g.weights = weights; g.cols = cols; g.dslT = ws + q.dslT; g.Wexp = wexp;
     g.rows_only = q.along_rows;
-    if (q.along_rows) { g.W = hd->W; g.Wsum = hd->Wsum; g.d = hd->d; g.tail_row = kmain; g.tail = ws + q.WT; }
+    g.d = hd->d;
+    if (q.along_rows) { g.W = hd->W; g.Wsum = hd->Wsum; g.tail_row = kmain; g.tail = ws + q.WT; }
+    if (q.split) {
+      // which terms: the scales of h^T over the positions that have a gradient, those of the gradient, then the planes of all or,
+      // where those do not do, three terms of all
+      HIP_TRY(launch_live_positions(g, st));
+      TransposeArgs x{};
+      x.src = hd->h; x.ld_src = hd->ld_h; x.R = hd->B; x.C = hd->d; x.Rpad = (int)q.ldb;
+      x.plain = ws + q.hT; x.ld_plain = q.ldb;
+      x.dst = ws + q.hTs; x.stage_rows = hd->d; x.planes = 1; x.flag = flag; x.live = top; x.weights = weights;
+      HIP_TRY(launch_transpose(x, hd->dtype, st));
+      HIP_TRY(launch_grad_exps(g, st));
+      const Split3Job jw{hd->W, ws + q.WT, 1, (int)q.ldM, hd->d, hd->d * 4LL, q.ldM, (int)q.M, hd->Wsum, (int)(q.Mx - q.M), (int)q.M};
+      const Split3Job jh{ws + q.hT, ws + q.hTs, 1, hd->d, (int)q.ldb, q.ldb * 4, 0, 0x7fffffff, nullptr, 0, 0};
+      HIP_TRY(launch_split3(jw, jh, flag, 1, st));
+    }
     HIP_TRY(launch_grad_from_phi(g, hd->dtype, st));
   } else {
     GradLogitsArgs g{};
@@ -928,14 +948,10 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
     t.col0 = q.Mlay; t.Rpad = (int)(q.ldM - q.Mlay);
     HIP_TRY(launch_transpose(t, hd->dtype, st));
   }
-  t.stage_rows = t.planes = 0;                // hT also feeds the small dWsum kernel: plain, plus a stage-major copy
+  t.stage_rows = 0;                           // hT also feeds the small dWsum kernel: plain, plus a stage-major copy
   t.src = hd->h; t.ld_src = hd->ld_h; t.R = hd->B; t.C = hd->d;
   t.dst = ws + q.hT; t.ld_dst = q.ldb; t.col0 = 0; t.Rpad = (int)q.ldb;
-  if (q.split) {
-    t.plain = t.dst; t.ld_plain = q.ldb;
-    t.dst = ws + q.hTs; t.stage_rows = hd->d; t.planes = 1; t.big = big;
-  }
-  HIP_TRY(launch_transpose(t, hd->dtype, st));
+  if (!q.split) HIP_TRY(launch_transpose(t, hd->dtype, st));
   if (!q.split && q.has_hTs)
     HIP_TRY(launch_pack_rows(ws + q.hT, ws + q.hTs, 1, hd->d, (int)(q.ldb * esz), q.ldb * (long long)esz, H_STAGE_BYTES, st));
 
@@ -945,9 +961,9 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   m.Bm = ws + q.WT; m.ldb = q.ldM; m.N = hd->d; m.K = (int)q.ldM;
   m.Bs = wt_staged ? ws + q.WT : nullptr;
   m.As = q.staged ? ws + q.dL : nullptr; m.As_rows = hd->B;
-  m.planes = q.split;
+  m.planes = q.split; m.flag = flag;
   if (q.split) {                                                 // planes of dL; W along its rows
-    m.Ae = plane_exps(ws + q.dL, hd->B * q.ldM);
+    m.Atop = top;
     m.Bs = ws + q.WT;
     m.Bk.base = ws + q.WT; m.Bk.row = 64; m.Bk.term = (unsigned)(q.ldM * 64); m.Bk.chunk = 2 * m.Bk.term;
     m.Bk.bytes = (unsigned)(hd->d * q.ldM * 4); m.Bk.kmain = (int)q.ldM;
@@ -974,14 +990,14 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   m.As = q.staged ? ws + q.dLT : nullptr; m.As_rows = (int)(q.along_rows ? q.ldM : q.M);
   m.Ak = m.Bk = KRows{};
   if (q.split) {
-    m.Ae = plane_exps(ws + q.dLT, q.M * q.ldb);
+    m.Atop = rows;
     m.Be = plane_exps(ws + q.hTs, hd->d * q.ldb);
   }
   m.C = dW; m.ldc = hd->d;
   m.split = (int)q.M; m.n2 = (family == MTPC_FF || own_dwsum) ? 0 : hd->r; m.C2 = dWsum;
   m.split3 = ctx ? (int)q.Mlay : 0x7fffffff; m.C3 = dR;
   HIP_TRY(launch_gemm_tn(m, hd->dtype, st));
-  if (q.split) HIP_TRY(launch_gemm_nonfinite(to_h, m, big, st));
+  if (q.split) HIP_TRY(launch_gemm_nonfinite(to_h, m, flag, st));
   if (own_dwsum)
     HIP_TRY(launch_dwsum(ws + q.dslT, ws + q.hT, q.ldb, hd->r, hd->d, hd->dtype, dWsum, st));
   return MTPC_OK;

@@ -13,6 +13,10 @@ __device__ __forceinline__ unsigned short to_bf16_rne(float x) {
   u += 0x7fffu + ((u >> 16) & 1u);
   return (unsigned short)(u >> 16);
 }
+// a.nclear ints of a.clear to 0, by a whole grid
+__device__ __forceinline__ void clear_ints(const CircuitBwdArgs& a) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < a.nclear; i += gridDim.x * blockDim.x) a.clear[i] = 0;
+}
 __device__ __forceinline__ float wsum(float x) { return group_sum(x, 64); }
 __device__ __forceinline__ float wmax(float x) { return group_max(x, 64); }
 
@@ -90,22 +94,27 @@ __global__ __launch_bounds__(256) void k_transpose_vec(const TransposeArgs a) {
 // src^T in fp32 (a.plain) and, as planes of two fp16 terms with scales of its rows (split2), in a.dst.  A workgroup takes 16
 // columns of src, all R rows, once: 64 bytes of each of 16 rows at a time through LDS; the largest value of a column is known
 // when its last row has passed, and the columns, read back, are split.
-__global__ __launch_bounds__(256) void k_transpose_split(const TransposeArgs a, int* __restrict__ exps) {
+// Rows of src whose `live` is 0 (positions without a gradient, which add nothing to any sum) are left out of the planes and
+// the scales.  Raises SPLIT_WIDE for columns with more than one small value in 16 (as k_split_rows does for rows), and
+// adds to a.weights the scaled magnitudes of every row of src, for check_planes.
+__global__ __launch_bounds__(512) void k_transpose_split(const TransposeArgs a, int* __restrict__ exps) {
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-  constexpr int U = 4;                               // steps of 64 rows in flight
-  __shared__ float tile[16][64 * U + 1];
+  typedef __attribute__((ext_vector_type(4))) int i32x4_t;
+  constexpr int U = 4, RT = 128;                     // steps of RT rows in flight
+  __shared__ float tile[16][RT * U + 1];
   __shared__ unsigned s_max[16];
-  const int tid = threadIdx.x, c0 = blockIdx.x * 16;
+  __shared__ int s_small[16], s_none[16];
+  const int tid = threadIdx.x, lane = tid & 63, c0 = blockIdx.x * 16;
   const float* const src = (const float*)a.src;
   float* const plain = (float*)a.plain;
-  if (tid < 16) s_max[tid] = 0;
-  bool bad = false;
-  for (int r0 = 0; r0 < a.Rpad; r0 += 64 * U) {
+  if (tid < 16) { s_max[tid] = 0; s_small[tid] = 0; s_none[tid] = 0; }
+  unsigned largest = 0;
+  for (int r0 = 0; r0 < a.Rpad; r0 += RT * U) {
     // four threads to the 64 bytes of a row
     f32x4_t x[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int r = r0 + 64 * u + (tid >> 2);
+      const int r = r0 + RT * u + (tid >> 2);
       x[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
       if (r < a.R) x[u] = *(const f32x4_t*)(src + (long long)r * a.ld_src + c0 + 4 * (tid & 3));
     }
@@ -113,27 +122,29 @@ __global__ __launch_bounds__(256) void k_transpose_split(const TransposeArgs a, 
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) tile[4 * (tid & 3) + c][64 * u + (tid >> 2)] = x[u][c];
+      for (int c = 0; c < 4; ++c) tile[4 * (tid & 3) + c][RT * u + (tid >> 2)] = x[u][c];
     __syncthreads();
-    // 16 threads to a column, four neighbouring rows each
-    const int c = tid >> 4;
+    // 32 threads to a column, four neighbouring rows each
+    const int c = tid >> 5;
     unsigned m = 0;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int rl = 64 * u + 4 * (tid & 15), r = r0 + rl;
+      const int rl = RT * u + 4 * (tid & 31), r = r0 + rl;
+      if (r >= a.Rpad) continue;
+      const i32x4_t live = *(const i32x4_t*)(a.live + r);
       f32x4_t y;
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         y[t] = tile[c][rl + t];
         const unsigned v = __float_as_uint(y[t]) & 0x7fffffffu;
-        bad |= v >= 0x7f800000u;
-        m = max(m, v < 0x7f800000u ? v : 0u);
+        largest = max(largest, v);
+        m = max(m, v < 0x7f800000u && live[t] > 0 ? v : 0u);
       }
-      if (r < a.Rpad) *(f32x4_t*)(plain + (long long)(c0 + c) * a.ld_plain + r) = y;
+      *(f32x4_t*)(plain + (long long)(c0 + c) * a.ld_plain + r) = y;
     }
     if (m != 0) atomicMax(&s_max[c], m);
   }
-  if (bad) *a.big = 1;
+  raise_flag(a.flag, largest >= 0x7f800000u ? SPLIT_WIDE | SPLIT_WHOLE : largest > __float_as_uint(SPLIT_LARGE) ? SPLIT_WHOLE : 0);
   __syncthreads();                                   // (and the workgroup's stores are visible to it)
   // four threads to the 64 bytes of a column's stage, 16 columns behind each other
   const int c = (tid >> 2) & 15, ch = tid & 3;
@@ -141,18 +152,66 @@ __global__ __launch_bounds__(256) void k_transpose_split(const TransposeArgs a, 
   if (tid < 64 && ch == 0) exps[c0 + c] = E;
   const float* const col = plain + (long long)(c0 + c) * a.ld_plain + ch * 8;
   unsigned short* const dst = (unsigned short*)a.dst + (long long)(c0 + c) * 32 + ch * 8;
-  for (int k = tid >> 6; k < a.Rpad / 32; k += 4) {
+  int small = 0, none = 0;                           // (small: with those that are 0)
+  for (int k = tid >> 6; k < a.Rpad / 32; k += 8) {
     const f32x4_t y0 = *(const f32x4_t*)(col + k * 32), y1 = *(const f32x4_t*)(col + k * 32 + 4);
+    const i32x4_t l0 = *(const i32x4_t*)(a.live + k * 32 + ch * 8), l1 = *(const i32x4_t*)(a.live + k * 32 + ch * 8 + 4);
     struct alignas(16) Oct { unsigned short v[8]; } o[2];
+    unsigned w[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
+      const float x = (t < 4 ? l0[t & 3] : l1[t & 3]) > 0 ? (t < 4 ? y0[t & 3] : y1[t & 3]) : 0.f, y = __builtin_amdgcn_ldexpf(x, -E);
+      none += x == 0.f;
+      small += fabsf(y) < SPLIT_SMALL;
+      w[t] = (unsigned)fminf(fabsf(y), 32768.f);
       unsigned short q[2];
-      split2(__builtin_amdgcn_ldexpf(t < 4 ? y0[t & 3] : y1[t & 3], -E), q);
+      split2(y, q);
       o[0].v[t] = q[0]; o[1].v[t] = q[1];
     }
 #pragma unroll
     for (int p = 0; p < 2; ++p) *(Oct*)(dst + (2LL * k + p) * a.stage_rows * 32) = o[p];
+    // the sum over the 16 columns, rows halved at every exchange but the last: one row to a lane (of two)
+#pragma unroll
+    for (int o2 = 4, n = 4; n >= 1; o2 <<= 1, n >>= 1)
+#pragma unroll
+      for (int t = 0; t < n; ++t) {
+        const bool up = lane & o2;
+        const unsigned mine = up ? w[t + n] : w[t], other = up ? w[t] : w[t + n];
+        w[t] = mine + (unsigned)__shfl_xor((int)other, o2);
+      }
+    const unsigned sum = w[0] + (unsigned)__shfl_xor((int)w[0], 32);
+    const int r = k * 32 + ch * 8 + (lane & 4) + (lane & 8) / 4 + (lane & 16) / 16;
+    if (lane < 32 && sum > 0) atomicAdd(a.weights + r, sum);
   }
+  atomicAdd(&s_small[c], small - none);
+  atomicAdd(&s_none[c], none);
+  __syncthreads();
+  if (tid < 16 && s_small[tid] > (a.Rpad - s_none[tid]) / 16) raise_flag(a.flag, SPLIT_WIDE);
+}
+
+// What the counts of single rows and columns of an operand cannot say, by one workgroup of k_grad_exps (whether a position has a
+// gradient is known by then, and what the others add to a.top does not change that).
+// h^T has a scale per feature, so a position may be small in most of them.  The terms are off by 2^-40 of the scale in each, which
+// has to be little beside that position's values alone (what an entry of dW sums is this position's alone where its
+// gradients are the largest), and beside it all other positions' terms of the gradient are as far off as theirs
+// make them: sqrt(B) times 2^-40 of an average position, as a random walk.  Both stay below 2^-23 where the position's
+// magnitudes add up to 2^-17 of d scales (which a value has of 2^14 to 2^15 units: d / 4), and of sqrt(B) average positions.
+// [W; Wsum] has a scale per row: a column may be small in most rows, which decides about that column of dh.
+__device__ __forceinline__ void check_planes(const GradPhiArgs& a, float (&s_sum)[4], float (&s_cnt)[4]) {
+  const int tid = threadIdx.x;
+  float sum = 0.f, cnt = 0.f;
+  for (int b = tid; b < a.B; b += 256)
+    if (a.top[b] > 0) { sum += (float)a.weights[b]; cnt += 1.f; }
+  sum = wsum(sum); cnt = wsum(cnt);
+  if ((tid & 63) == 0) { s_sum[tid >> 6] = sum; s_cnt[tid >> 6] = cnt; }
+  __syncthreads();
+  sum = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+  cnt = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+  const float least = fmaxf((float)a.d * 0.25f, sum / fmaxf(cnt, 1.f) * sqrtf((float)a.B) * 0x1p-17f);
+  bool wide = false;
+  for (int b = tid; b < a.B; b += 256) wide |= a.top[b] > 0 && (float)a.weights[b] < least;
+  for (int k = tid; k < a.d; k += 256) wide |= a.cols[k] > ((int)a.ldM - a.cols[a.d + k]) / 16;
+  if (wide) raise_flag(a.flag, SPLIT_WIDE);
 }
 
 // The logit gradient from the stored probabilities where only dLT is wanted: no transpose, so no LDS.  A thread takes eight
@@ -211,131 +270,178 @@ __global__ __launch_bounds__(256) void k_grad_rows(const GradPhiArgs a, int rows
   }
 }
 
-// Exponents of the rows of the two planes that k_grad_from_phi writes (see split2): the largest magnitude of a row of dLT over all
-// positions, and of a row of dL, whose elements carry the scales of W's rows, over all tokens.  One more read of the
-// probabilities.  The first workgroups take up to 64 rows of one slab each; the gradients and targets of the slab, apart in memory,
-// go through LDS once per workgroup (fetched by every wave for its rows of any slabs, this took 330 us for 562 MB of
-// probabilities), and so do the maxima of the positions on their way to a.top: 1 + TOP_BIAS + the exponent, 0 for a position without a
-// gradient.  (A bound on a position's maximum from its gradients and the largest exponent of each slab is not enough: a row
-// of W far above the others may belong to a token without probability.)  The other workgroups add the sum-unit rows
-// of 16 positions each to a.top.
-constexpr int TOP_BIAS = 4096;
-__device__ __forceinline__ int top_exp(int top) { return top > 0 ? top - 1 - TOP_BIAS - 15 : 0; }
-__global__ __launch_bounds__(256) void k_grad_exps(const GradPhiArgs a, int* __restrict__ rexp, int row_blocks) {
+// a.top: 1, the least, for a position that has a gradient, else 0.  A wave to a position.  (Before everything that reads the
+// probabilities: the transpose of h asks for it, and between k_grad_exps and k_grad_from_phi, which finds what is left of the
+// probabilities in the last cache, that costs the latter a third where they fit.)
+__global__ __launch_bounds__(256) void k_live_positions(const GradPhiArgs a) {
+  const int b = blockIdx.x * 4 + (threadIdx.x >> 6), t = threadIdx.x & 63, nr = a.n * a.r;
+  if (b >= a.B) return;                              // (all 64)
+  bool some = false;
+  for (int i = t; i < nr; i += 64) some |= a.Ge[(long long)b * nr + i] != 0.f && a.targets[(long long)b * a.n + i / a.r] != -1;
+  for (int j = t; j < (int)(a.Mx - a.M); j += 64) some |= ((const float*)a.dslT)[j * a.ldb + b] != 0.f;
+  some = __any(some);
+  if (t == 0) a.top[b] = some;
+}
+
+// What the scales of the two planes that k_grad_from_phi writes (see split2) follow from: the largest magnitude of a row of dLT over
+// all positions (a.rows), and of a row of dL, whose elements carry the scales of W's rows, over all tokens (a.top), as bits.
+// One more read of the probabilities.  The first workgroups take CH positions of `count` blocks of up to 64 rows of one slab: the
+// gradients and targets of the slab, apart in memory, go through LDS (fetched by every wave for its rows of any slabs, this
+// took 330 us for 562 MB of probabilities), and so do the maxima of the positions, which leave with one atomic of the workgroup
+// each.  (A bound on a position's maximum from its gradients and the largest exponent of each slab is not enough: a row of W far
+// above the others may belong to a token without probability.)  The next ones add the sum-unit rows of 16 positions each to
+// a.top, and the last one looks at the other operands (check_planes).
+__global__ __launch_bounds__(256, 4) void k_grad_exps(const GradPhiArgs a, int row_blocks, int count) {
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;
   typedef __attribute__((ext_vector_type(4))) int i32x4_t;
-  constexpr int CH = 1024;                           // positions per step
+  constexpr int CH = 512;
   __shared__ __align__(16) float s_g[CH];
   __shared__ __align__(16) int s_x[CH];
   __shared__ int s_top[CH];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nr = a.n * a.r;
-  if (blockIdx.x == 0 && tid == 0 && a.wild != nullptr && *a.wild != 0) *a.big = 1;
-  if ((int)blockIdx.x < row_blocks) {
+  // what the largest magnitude of some elements, as bits (above infinity: NaN), and the largest of a position's say about them
+  auto note = [&](unsigned big, int top) {
+    raise_flag(a.flag, big >= 0x7f800000u || top >= 0x7f800000 ? SPLIT_WIDE | SPLIT_WHOLE : big > __float_as_uint(SPLIT_LARGE) ? SPLIT_WHOLE : 0);
+  };
+  const int groups = (row_blocks + count - 1) / count;
+  if ((int)blockIdx.x < groups) {
     constexpr int RW = 16;                           // rows of a wave (those of the four waves alternate)
-    const int parts = (a.v + 63) / 64;
-    const int slab = blockIdx.x / parts, r0 = (blockIdx.x - slab * parts) * 64 + wave;
-    if (r0 - wave >= a.v) return;
-    const float* phi = a.phiT + (long long)slab * a.v * a.ld_phi;
-    float big[RW];
-    int we[RW];                                      // (of a row that is not there: of a row of zeros)
+    const int parts = (a.v + 63) / 64, c0 = blockIdx.y * CH;
+    unsigned largest = 0;
+    int slab = -1;
 #pragma unroll
-    for (int k = 0; k < RW; ++k) {
-      big[k] = 0.f;
-      const int row = r0 + 4 * k;
-      we[k] = 1 + TOP_BIAS + (row < a.v ? a.Wexp[(long long)slab * a.v + row] : SPLIT_ZERO_ROW);
-    }
+    for (int q = 0; q < CH / 256; ++q) s_top[tid + q * 256] = 0;
     f32x4_t ph[RW];
-    auto fetch = [&](int b) {                        // (b beyond the last position: any)
+    auto fetch = [&](int g, int b) {                 // rows of this wave in block g, positions b ..  (b beyond the last position: any)
+      const int s = g / parts, r0 = (g - s * parts) * 64 + wave;
+      const float* phi = a.phiT + (long long)s * a.v * a.ld_phi + min((long long)b + 4 * lane, a.ldb - 4);
 #pragma unroll
-      for (int k = 0; k < RW; ++k) ph[k] = *(const f32x4_t*)(phi + (long long)min(r0 + 4 * k, a.v - 1) * a.ld_phi + min((long long)b, a.ldb - 4));
+      for (int k = 0; k < RW; ++k) ph[k] = *(const f32x4_t*)(phi + (long long)min(r0 + 4 * k, a.v - 1) * a.ld_phi);
     };
-    for (int c0 = 0; c0 < a.B; c0 += CH) {
-      fetch(c0 + 4 * lane);                          // (on their way while the gradients are fetched)
+    const int end = min(row_blocks, (int)(blockIdx.x + 1) * count);
+    fetch(blockIdx.x * count, c0);
+#pragma unroll 1
+    for (int g = blockIdx.x * count; g < end; ++g) {
+      const int s = g / parts, r0 = (g - s * parts) * 64 + wave;
+      unsigned big[RW];
+      int we[RW];                                    // (of a row that is not there: of a row of zeros)
 #pragma unroll
-      for (int q = 0; q < CH / 256; ++q) {
-        const int i = tid + q * 256, b = c0 + i;
-        const int bc = min(b, a.B - 1);
-        const int x = a.targets[(long long)bc * a.n + slab / a.r];
-        const float g = a.Ge[(long long)bc * nr + slab];
-        s_x[i] = x;
-        s_g[i] = b < a.B && x != -1 ? g : 0.f;
-        s_top[i] = 0;
+      for (int k = 0; k < RW; ++k) {
+        big[k] = 0;
+        const int row = r0 + 4 * k;
+        we[k] = __builtin_amdgcn_readfirstlane(row < a.v ? a.Wexp[(long long)s * a.v + row] : SPLIT_ZERO_ROW);
       }
-      __syncthreads();
-      for (int i = 4 * lane; i < CH && c0 + i < a.B; i += 256) {
-        const f32x4_t g = *(const f32x4_t*)(s_g + i);
+      if (s != slab) {
+        slab = s;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < CH / 256; ++q) {
+          const int i = tid + q * 256, b = c0 + i;
+          const int bc = min(b, a.B - 1);
+          const int x = a.targets[(long long)bc * a.n + slab / a.r];
+          const float ge = a.Ge[(long long)bc * nr + slab];
+          s_x[i] = x;
+          s_g[i] = b < a.B && x != -1 ? ge : 0.f;
+        }
+        __syncthreads();
+      }
+#pragma unroll 1
+      for (int o = 0; o < CH && c0 + o < a.B; o += 256) {
+        const int i = o + 4 * lane;
+        const f32x4_t ge = *(const f32x4_t*)(s_g + i);
         const i32x4_t x = *(const i32x4_t*)(s_x + i);
-        int top[4] = {0, 0, 0, 0};
+        float top[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int k = 0; k < RW; ++k)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const float y = c0 + i + c < a.B ? fabsf(g[c] * ((r0 + 4 * k == x[c] ? 1.f : 0.f) - ph[k][c])) : 0.f;
-            const bool counts = y <= 3.402823466e38f && y > 0.f;
-            big[k] = counts ? fmaxf(big[k], y) : big[k];
-            top[c] = counts ? max(top[c], __builtin_amdgcn_frexp_expf(y) + we[k]) : top[c];
+          for (int c = 0; c < 4; ++c) {              // (no gradient beyond the last position, whose probabilities may be anything)
+            const float y = ge[c] != 0.f ? fabsf(ge[c] * ((r0 + 4 * k == x[c] ? 1.f : 0.f) - ph[k][c])) : 0.f;
+            big[k] = max(big[k], __float_as_uint(y));
+            top[c] = fmaxf(top[c], __builtin_amdgcn_ldexpf(y, we[k]));
           }
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          if (top[c] > 0) atomicMax(&s_top[i + c], top[c]);
-        fetch(c0 + i + 256);
+          if (top[c] > 0.f) atomicMax(&s_top[i + c], (int)__float_as_uint(top[c]));
+        const bool more = o + 256 < CH && c0 + o + 256 < a.B;
+        fetch(more ? g : min(g + 1, end - 1), more ? c0 + o + 256 : c0);
       }
-      __syncthreads();
+      // the largest of each row over the lanes, rows halved at every exchange: lane l ends up with row l / 4
 #pragma unroll
-      for (int q = 0; q < CH / 256; ++q) {           // (few of a position's maxima are above those of the workgroups before)
-        const int top = s_top[tid + q * 256], b = c0 + tid + q * 256;
-        if (top > 0 && b < a.B && top > __hip_atomic_load(a.top + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(a.top + b, top);
-      }
+      for (int o = 32, R = RW / 2; o >= 4; o >>= 1, R >>= 1)
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          const bool up = lane & o;
+          const unsigned mine = up ? big[k + R] : big[k], other = up ? big[k] : big[k + R];
+          big[k] = max(mine, (unsigned)__shfl_xor((int)other, o));
+        }
+      unsigned y = big[0];
+      y = max(y, (unsigned)__shfl_xor((int)y, 1));
+      y = max(y, (unsigned)__shfl_xor((int)y, 2));
+      const int row = r0 + 4 * (lane >> 2);
+      if ((lane & 3) == 0 && row < a.v && y > 0) atomicMax(a.rows + (long long)s * a.v + row, y);
+      largest = max(largest, y);
     }
-    // the largest of each row over the lanes, rows halved at every exchange: lane l ends up with row l / 4
+    __syncthreads();
+    // (few of a position's maxima are above those of the workgroups before)
+    int have[CH / 256], most = 0;
 #pragma unroll
-    for (int o = 32, R = RW / 2; o >= 4; o >>= 1, R >>= 1)
+    for (int q = 0; q < CH / 256; ++q)
+      have[q] = __hip_atomic_load(a.top + min(c0 + tid + q * 256, a.B - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-      for (int k = 0; k < R; ++k) {
-        const bool up = lane & o;
-        const float mine = up ? big[k + R] : big[k], other = up ? big[k] : big[k + R];
-        big[k] = fmaxf(mine, __shfl_xor(other, o));
-      }
-    const float y = group_max(big[0], 4);
-    const int row = r0 + 4 * (lane >> 2);
-    if ((lane & 3) == 0 && row < a.v) rexp[(long long)slab * a.v + row] = split_exp(y);
+    for (int q = 0; q < CH / 256; ++q) {
+      const int top = s_top[tid + q * 256];          // (0 beyond the last position)
+      most = max(most, top);
+      if (top > have[q]) atomicMax(a.top + c0 + tid + q * 256, top);
+    }
+    note(largest, most);
     return;
   }
-  const int b = ((int)blockIdx.x - row_blocks) * 16 + (tid >> 4), t = tid & 15;
+  if (blockIdx.y > 0) return;
+  __shared__ float s_sum[4], s_cnt[4];
+  if (blockIdx.x == gridDim.x - 1) {
+    check_planes(a, s_sum, s_cnt);
+    return;
+  }
+  const int b = ((int)blockIdx.x - groups) * 16 + (tid >> 4), t = tid & 15;
   const int r2 = (int)(a.Mx - a.M);
+  unsigned big = 0;
   int top = 0;
   if (b < a.B)
     for (int j = t; j < r2; j += 16) {
       const float y = fabsf(((const float*)a.dslT)[j * a.ldb + b]);
-      if (y > 0.f && y <= 3.402823466e38f) top = max(top, __builtin_amdgcn_frexp_expf(y) + 1 + TOP_BIAS + a.Wexp[a.M + j]);
+      big = max(big, __float_as_uint(y));
+      top = max(top, (int)__float_as_uint(__builtin_amdgcn_ldexpf(y, a.Wexp[a.M + j])));
     }
 #pragma unroll
   for (int o = 1; o < 16; o <<= 1) top = max(top, __shfl_xor(top, o));
   if (b < a.B && t == 0 && top > 0) atomicMax(a.top + b, top);
+  note(big, top);
 }
 
 // 64 (m) x 128 (b) tiles: logit gradient from the stored probabilities, written in both
 // layouts (dLT along b straight away, dL along m after a transpose through LDS).  A thread
 // moves four neighbouring elements at a time (16-byte loads, 8- or 16-byte stores).
-// PLANES (fp32): both layouts as planes of two fp16 terms, as tile_gemm_run_split reads them; rexp and a.top hold the
-// exponents of their rows, and those of dL are left in bexp.
-template <typename T, bool PLANES = false>
-__global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a, const int* __restrict__ rexp, int* __restrict__ bexp) {
+// PLANES (fp32): both layouts as planes of two fp16 terms, as tile_gemm_run_split reads them, whose rows have the scales of a.rows
+// and a.top (largest_exp); or of three bf16 terms where *a.flag says so.
+template <typename T, int PLANES>
+__device__ __forceinline__ void grad_from_phi(const GradPhiArgs& a, const int* __restrict__ rows, const int* __restrict__ top, T (&tile)[64][128 + 4]) {
   struct alignas(4 * sizeof(T)) Quad { T v[4]; };
   // four neighbours along K, to row `row` of a staged matrix of `rows` rows; e[c]: the power of two x[c] is multiplied with
   auto put_planes = [](void* dst, long long k, long long rows, long long row, const Quad& x, const int (&e)[4]) {
-    struct alignas(8) Half { unsigned short v[4]; } o[2];
+    constexpr int TERMS = PLANES == 3 ? 3 : 2;
+    struct alignas(8) Half { unsigned short v[4]; } o[TERMS];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      unsigned short q[2];
-      split2(__builtin_amdgcn_ldexpf((float)x.v[c], e[c]), q);
-      o[0].v[c] = q[0]; o[1].v[c] = q[1];
+      unsigned short q[TERMS];
+      if constexpr (PLANES == 3) split3((float)x.v[c], q);
+      else split2(__builtin_amdgcn_ldexpf((float)x.v[c], e[c]), q);
+#pragma unroll
+      for (int p = 0; p < TERMS; ++p) o[p].v[c] = q[p];
     }
 #pragma unroll
-    for (int p = 0; p < 2; ++p) *(Half*)((unsigned short*)dst + ((k / 32 * 2 + p) * rows + row) * 32 + k % 32) = o[p];
+    for (int p = 0; p < TERMS; ++p) *(Half*)((unsigned short*)dst + ((k / 32 * TERMS + p) * rows + row) * 32 + k % 32) = o[p];
   };
-  __shared__ T tile[64][128 + 4];
   const long long m0 = (long long)blockIdx.y * 64;
   const int b0 = blockIdx.x * 128;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;      // 32 column quads x 8 rows per pass
@@ -377,8 +483,8 @@ __global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a, cons
       for (int c = 0; c < 4; ++c)
         if (b + c < a.B && x[c] != -1) out.v[c] = conv(g[c] * ((av == x[c] ? 1.f : 0.f) - pv[c]));
       constexpr int EPS = 64 / (int)sizeof(T);     // elements of a row per stage (b is a multiple of 4)
-      if constexpr (PLANES) {
-        const int e = -rexp[m];
+      if constexpr (PLANES != 0) {
+        const int e = PLANES == 2 ? -largest_exp(rows[m]) : 0;
         put_planes(a.dLT, b, a.M, m, out, {e, e, e, e});
       } else if (a.staged) *(Quad*)(dLT + ((long long)(b / EPS) * a.M + m) * EPS + b % EPS) = out;
       else *(Quad*)(dLT + m * a.ldb + b) = out;
@@ -388,15 +494,15 @@ __global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a, cons
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       tile[ml][4 * tx + c] = out.v[c];
-      if constexpr (PLANES) bad |= !(fabsf(out.v[c]) <= 3.402823466e38f);
+      if constexpr (PLANES == 3) bad |= !(fabsf(out.v[c]) <= SPLIT_LARGE);
     }
   }
-  if constexpr (PLANES)
-    if (bad) *a.big = 1;
+  if constexpr (PLANES == 3)
+    if (bad) raise_flag(a.flag, SPLIT_WHOLE);
   __syncthreads();
   const int mq = threadIdx.x & 15, br = threadIdx.x >> 4;        // 16 row quads x 16 positions per pass
   int we[4] = {0, 0, 0, 0};
-  if constexpr (PLANES)
+  if constexpr (PLANES == 2)
 #pragma unroll
     for (int c = 0; c < 4; ++c) we[c] = a.Wexp[min(m0 + 4 * mq + c, a.Mx - 1)];
 #pragma unroll 2
@@ -408,14 +514,20 @@ __global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a, cons
 #pragma unroll
       for (int c = 0; c < 4; ++c) out.v[c] = tile[4 * mq + c][bl];
       constexpr int EPS = 64 / (int)sizeof(T);
-      if constexpr (PLANES) {
-        const int e = top_exp(a.top[b0 + bl]);
-        if (m == 0) bexp[b0 + bl] = e;
+      if constexpr (PLANES != 0) {
+        const int e = PLANES == 2 ? largest_exp(top[b0 + bl]) : 0;
         put_planes(a.dL, m, a.B, b0 + bl, out, {we[0] - e, we[1] - e, we[2] - e, we[3] - e});
       } else if (a.staged) *(Quad*)(dL + ((m / EPS) * a.B + (b0 + bl)) * EPS + m % EPS) = out;
       else *(Quad*)(dL + (long long)(b0 + bl) * a.ldM + m) = out;
     }
   }
+}
+template <typename T, bool PLANES = false>
+__global__ __launch_bounds__(256) void k_grad_from_phi(const GradPhiArgs a, const int* __restrict__ rows, const int* __restrict__ top) {
+  __shared__ T tile[64][128 + 4];
+  if constexpr (!PLANES) grad_from_phi<T, 0>(a, rows, top, tile);
+  else if ((*a.flag & SPLIT_WIDE) == 0) grad_from_phi<T, 2>(a, rows, top, tile);
+  else grad_from_phi<T, 3>(a, rows, top, tile);       // (which raises SPLIT_WHOLE only)
 }
 
 // acc_u = sum_k sh[k] * M[k*r + unit_u] for the lane's units (lane, lane + 64); M is an
@@ -445,6 +557,7 @@ __device__ __forceinline__ void wave_matvec(const float* __restrict__ M, const f
 
 // One wave per evidence row; lane l holds units l and l + 64.
 __global__ __launch_bounds__(256) void k_circuit_bwd(const CircuitBwdArgs a) {
+  clear_ints(a);
   __shared__ float sP[4][64];
   __shared__ float sX[4][128];
   __shared__ float sPi[4][128], sC[4][128];
@@ -633,6 +746,7 @@ __global__ __launch_bounds__(256) void k_circuit_bwd(const CircuitBwdArgs a) {
 // and adj(x) goes to both operands (leaf: evidence gradient; stored node: its
 // adjoint; path value: the adjoint consumed by the previous step of the path).
 __global__ __launch_bounds__(256) void k_btree_bwd(const CircuitBwdArgs a, int nsteps_max) {
+  clear_ints(a);
   extern __shared__ TreeStep bprog[];
   __shared__ float sX[4][128];
   __shared__ float sPi[4][128];
@@ -832,6 +946,7 @@ constexpr size_t btree_bwd_lds(int n, int T) {
 
 template <int R>
 __global__ __launch_bounds__(4 * R) void k_btree_bwd_mfma(const CircuitBwdArgs a, int nsteps_max) {
+  clear_ints(a);
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;
   constexpr int NB = R / 16, RS = R + 4;
   extern __shared__ __align__(16) float wsm[];
@@ -1210,12 +1325,13 @@ hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t st) {
     if (dtype != MTPC_F32 || !a.planes || a.ld_src != a.C) return hipErrorInvalidValue;
     if (a.row0 >= a.Rpad) return hipSuccess;
     const char* src = (const char*)a.src + (long long)a.row0 * a.C * 4;
-    return launch_split_rows(src, (char*)a.dst + a.row0 * 64LL, 1, a.Rpad - a.row0, a.C, a.C * 4LL, a.exps + a.row0, a.big, 0, st, a.Rpad,
-                             a.R - a.row0, a.src2, a.R2);
+    return launch_split_rows(src, (char*)a.dst + a.row0 * 64LL, 1, a.Rpad - a.row0, a.C, a.C * 4LL, a.exps + a.row0, a.flag, 1, st, a.Rpad,
+                             a.R - a.row0, a.src2, a.R2, 0, 1, a.cols);
   }
   if (a.planes) {
+    if (a.live == nullptr || a.weights == nullptr) return hipErrorInvalidValue;
     if (dtype != MTPC_F32 || a.stage_rows != a.C || a.C % 16 != 0 || a.col0 != 0 || a.Rpad % 32 != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_transpose_split, dim3(a.C / 16), dim3(256), 0, st, a, plane_exps(a.dst, (long long)a.C * a.Rpad));
+    hipLaunchKernelGGL(k_transpose_split, dim3(a.C / 16), dim3(512), 0, st, a, plane_exps(a.dst, (long long)a.C * a.Rpad));
     return hipGetLastError();
   }
   const int esz = dtype == MTPC_BF16 ? 2 : 4, ve = 16 / esz;
@@ -1243,12 +1359,22 @@ hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st)
     hipLaunchKernelGGL(k_grad_rows, dim3((unsigned)cols, (unsigned)(row_blocks + tail_blocks)), dim3(256), 0, st, a, rows, (int)row_blocks);
   } else if (dtype == MTPC_BF16) hipLaunchKernelGGL(k_grad_from_phi<unsigned short>, grid, dim3(256), 0, st, a, nullptr, nullptr);
   else if (a.planes) {
-    int* const rexp = plane_exps(a.dLT, a.M * a.ldb);
-    int* const bexp = plane_exps(a.dL, a.B * a.ldM);
-    const int rb = a.n * a.r * ((a.v + 63) / 64), bb = a.Mx > a.M ? (a.B + 15) / 16 : 0;
-    hipLaunchKernelGGL(k_grad_exps, dim3(rb + bb), dim3(256), 0, st, a, rexp, rb);
-    hipLaunchKernelGGL((k_grad_from_phi<float, true>), grid, dim3(256), 0, st, a, rexp, bexp);
+    hipLaunchKernelGGL((k_grad_from_phi<float, true>), grid, dim3(256), 0, st, a, a.rows, a.top);
   } else hipLaunchKernelGGL(k_grad_from_phi<float>, grid, dim3(256), 0, st, a, nullptr, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_live_positions(const GradPhiArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(k_live_positions, dim3((a.B + 3) / 4), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_grad_exps(const GradPhiArgs& a, hipStream_t st) {
+  const int rb = a.n * a.r * ((a.v + 63) / 64), bb = a.Mx > a.M ? (a.B + 15) / 16 : 0, chunks = (a.B + 511) / 512;
+  // four workgroups per CU; two blocks of rows each as soon as that leaves one, since a position's atomic is what they share
+  const long long all = (long long)rb * chunks;
+  const int count = (int)std::min((long long)rb, std::max((all + 1023) / 1024, all >= 512 ? 2LL : 1LL));
+  hipLaunchKernelGGL(k_grad_exps, dim3((rb + count - 1) / count + bb + 1, chunks), dim3(256), 0, st, a, rb, count);
   return hipGetLastError();
 }
 

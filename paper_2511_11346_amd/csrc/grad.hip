@@ -107,19 +107,17 @@ hipError_t launch_unembed_grad(const GradLogitsArgs& a, int dtype, hipStream_t s
 }
 
 // ---------------------------------------------------------------------------
-// SPLIT: fp32 operands as planes of two fp16 terms (tile_gemm_run_split), both stage-major.
+// SPLIT: fp32 operands as planes of two fp16 or three bf16 terms (tile_gemm_run_split), both stage-major; a.flag says which.
 // KR: operands given along their rows (TileFeed::open_rows): transposed on the way from LDS into registers, where a
 // transposed copy of W (2.0 GB in, 2.0 GB out, 1.04 ms for n r = 1024, d = 3072) and a second layout of the logit gradient would
 // only serve this product.
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool ASTAGED, int SPLIT = 0, int KR = 0>
-__global__ __launch_bounds__(WV * WB * 64)
-void k_gemm_tn(const GemmArgs a) {
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool ASTAGED, int SPLIT, int KR>
+__device__ __forceinline__ void gemm_tn_tiles(const GemmArgs& a, char* smem) {
   using TL = Tile<WV, WB, VB, PB, SB, NS>;
   constexpr bool M16 = use_m16<WV, WB, SB, NS, BF16>();
   using FR = Frag<M16>;
   constexpr int NPB = PB * FR::SUB, NVB = VB * FR::SUB;
   constexpr int ESZ = BF16 ? 2 : 4;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wv = wave % WV, wb = wave / WV;
   const int lcol = FR::lcol(lane), lgrp = FR::lgrp(lane);
@@ -149,8 +147,8 @@ void k_gemm_tn(const GemmArgs a) {
       return;
     }
     if constexpr (SPLIT != 0) {
-      const long long s0 = (long long)(t.k0 / 32) * 2;             // (chunks are multiples of 64 columns)
-      feed.open((const char*)a.As + s0 * a.As_rows * 64, 0, a.Bm, 0, a.N, 2 * t.klen, t.rows, 0, t.b0, smem, nullptr, 0, 1,
+      const long long s0 = (long long)(t.k0 / 32) * SPLIT;         // (chunks are multiples of 64 columns)
+      feed.open((const char*)a.As + s0 * a.As_rows * 64, 0, a.Bm, 0, a.N, SPLIT * t.klen, t.rows, 0, t.b0, smem, nullptr, 0, 1,
                 (const char*)a.Bs + s0 * a.N * 64, a.As_rows, t.slab * TL::TV);
       return;
     }
@@ -169,12 +167,12 @@ void k_gemm_tn(const GemmArgs a) {
     // exponents of the tile's operand rows: fetched now, parked in LDS behind the product
     constexpr int XE = (TL::ROWS + TL::NT - 1) / TL::NT;
     int epre[XE];
-    if constexpr (SPLIT != 0) {
+    if constexpr (SPLIT == 2) {
 #pragma unroll
       for (int q = 0; q < XE; ++q) {
         const int idx = min((int)threadIdx.x + q * TL::NT, TL::ROWS - 1);
         epre[q] = 0;
-        if (idx < TL::TV) { if (a.Ae != nullptr) epre[q] = a.Ae[min(cur.slab * TL::TV + idx, a.M - 1)]; }
+        if (idx < TL::TV) epre[q] = largest_exp(a.Atop[min(cur.slab * TL::TV + idx, a.M - 1)]);
         else if (a.Be != nullptr) epre[q] = a.Be[min(cur.b0 + idx - TL::TV, a.N - 1)];
       }
     }
@@ -189,7 +187,7 @@ void k_gemm_tn(const GemmArgs a) {
     }
     const int slab = cur.slab, b0 = cur.b0, rows = cur.rows, ks = cur.ks;
     const int rbase = wv * VB * 32 + 4 * lgrp;
-    if constexpr (SPLIT != 0) {
+    if constexpr (SPLIT == 2) {
       int* s_e = (int*)(smem + TL::SMEM);
       // (the product's last barrier is behind the reads of the tile before)
 #pragma unroll
@@ -251,6 +249,20 @@ void k_gemm_tn(const GemmArgs a) {
   }
 }
 
+// SPLIT = 2: planes of two terms or, where the flag says so, of three (one launch: a second one that finds nothing to do takes
+// 2.4 us of small training steps)
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool ASTAGED, int SPLIT = 0, int KR = 0>
+__global__ __launch_bounds__(WV * WB * 64)
+void k_gemm_tn(const GemmArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  if constexpr (SPLIT == 2)
+    if ((*a.flag & SPLIT_WIDE) != 0) {
+      gemm_tn_tiles<WV, WB, VB, PB, SB, NS, BF16, ASTAGED, 3, KR>(a, smem);
+      return;
+    }
+  gemm_tn_tiles<WV, WB, VB, PB, SB, NS, BF16, ASTAGED, SPLIT, KR>(a, smem);
+}
+
 template <int WV, int WB, int VB, int PB, bool BF16, bool ASTAGED = false, int SPLIT = 0, int KR = 0>
 static hipError_t launch_gemm_cfg(const GemmArgs& a, hipStream_t st) {
   using TL = Tile<WV, WB, VB, PB, 64, 4>;
@@ -258,8 +270,9 @@ static hipError_t launch_gemm_cfg(const GemmArgs& a, hipStream_t st) {
     if (a.planes) return launch_gemm_cfg<WV, WB, VB, PB, true, true, 2>(a, st);
   if constexpr (!ASTAGED && KR == 0)
     if (a.As != nullptr) return launch_gemm_cfg<WV, WB, VB, PB, BF16, true>(a, st);
+  if (SPLIT == 2 && (a.flag == nullptr || a.Atop == nullptr)) return hipErrorInvalidValue;
   constexpr auto kern = k_gemm_tn<WV, WB, VB, PB, 64, 4, BF16, ASTAGED, SPLIT, KR>;
-  constexpr int smem = TL::SMEM + (SPLIT != 0 ? TL::ROWS * 4 : 0);
+  constexpr int smem = TL::SMEM + (SPLIT == 2 ? TL::ROWS * 4 : 0);
   static_assert(smem <= 160 * 1024, "LDS budget of one CU");
   if (hipError_t e = allow_lds<kern>(smem); e != hipSuccess) return e;
   const int nslab = (a.M + TL::TV - 1) / TL::TV, nbt = (a.N + TL::TP - 1) / TL::TP;
@@ -314,12 +327,12 @@ hipError_t launch_gemm_tn(const GemmArgs& a0, int dtype, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Results of products of planes that are not finite, formed anew from whole fp32 values (x1 + x2).  A no-op
-// unless *big is set, which takes an infinite or NaN operand: a product of single terms of such a value may be NaN
+// Results of products of planes of three terms that are not finite, formed anew from whole fp32 values (x1 + x2 + x3 is exact).  A
+// no-op unless *flag says so, which takes an operand beyond SPLIT_LARGE: a product of single terms of such a value may be NaN
 // where the sum is an infinity.  Anything but fast: 64 x 64 results per workgroup and step of the walk, left as soon as
 // the tile has nothing to mend - and given up where every sum to mend has become NaN (NaN operands, say).
-__global__ __launch_bounds__(256) void k_gemm_nonfinite(const GemmArgs a0, const GemmArgs a1, const int* big) {
-  if (*big == 0) return;
+__global__ __launch_bounds__(256) void k_gemm_nonfinite(const GemmArgs a0, const GemmArgs a1, const int* flag) {
+  if ((*flag & (SPLIT_WIDE | SPLIT_WHOLE)) != (SPLIT_WIDE | SPLIT_WHOLE)) return;
   __shared__ float xa[32][64 + 1], xb[32][64 + 1];
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;           // rows 4 ty + i, columns tx + 16 j of a tile
   const int lr = threadIdx.x >> 2, ch = threadIdx.x & 3;            // loads: eight columns of K of one row
@@ -346,11 +359,11 @@ __global__ __launch_bounds__(256) void k_gemm_nonfinite(const GemmArgs a0, const
         for (int e = 0; e < 8; ++e) s[e] = 0.f;
         if (row < end)
 #pragma unroll
-          for (int p = 0; p < 2; ++p) {
+          for (int p = 0; p < 3; ++p) {
             struct alignas(16) Oct { unsigned short v[8]; };
-            const Oct o = *(const Oct*)((const char*)planes + ((2LL * k + p) * rows + row) * 64 + ch * 16);
+            const Oct o = *(const Oct*)((const char*)planes + ((3LL * k + p) * rows + row) * 64 + ch * 16);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) s[e] += (float)__builtin_bit_cast(_Float16, o.v[e]);
+            for (int e = 0; e < 8; ++e) s[e] += __uint_as_float((unsigned)o.v[e] << 16);
           }
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[ch * 8 + e][lr] = s[e];
@@ -363,11 +376,11 @@ __global__ __launch_bounds__(256) void k_gemm_nonfinite(const GemmArgs a0, const
         for (int e = 0; e < 8; ++e) s[e] = 0.f;
         if (col < a.N)
 #pragma unroll
-          for (int p = 0; p < 2; ++p) {
+          for (int p = 0; p < 3; ++p) {
             struct alignas(16) Oct { unsigned short v[8]; };
-            const Oct o = *(const Oct*)((const char*)m.base + (size_t)p * m.term + (size_t)(col / 32) * m.chunk + (size_t)(32 * k + row) * m.row + col % 32 * 2);
+            const Oct o = *(const Oct*)((const char*)m.base + (size_t)p * m.term + (size_t)(col / 32) * 3 * m.term + (size_t)(32 * k + row) * m.row + col % 32 * 2);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) s[e] += (float)__builtin_bit_cast(_Float16, o.v[e]);
+            for (int e = 0; e < 8; ++e) s[e] += __uint_as_float((unsigned)o.v[e] << 16);
           }
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[row][(threadIdx.x & 7) * 8 + e] = s[e];
@@ -398,20 +411,16 @@ __global__ __launch_bounds__(256) void k_gemm_nonfinite(const GemmArgs a0, const
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          if (mend >> (4 * i + j) & 1) {
-            const int r = row0 + 4 * ty + i, c = col0 + tx + 16 * j;
-            a.C[(long long)r * a.ldc + c] =
-                __builtin_amdgcn_ldexpf(acc[i][j], (a.Ae != nullptr ? a.Ae[r] : 0) + (a.Be != nullptr ? a.Be[c] : 0));
-          }
+          if (mend >> (4 * i + j) & 1) a.C[(long long)(row0 + 4 * ty + i) * a.ldc + col0 + tx + 16 * j] = acc[i][j];
     }
   }
 }
 
-hipError_t launch_gemm_nonfinite(const GemmArgs& a, const GemmArgs& b, const int* big, hipStream_t st) {
+hipError_t launch_gemm_nonfinite(const GemmArgs& a, const GemmArgs& b, const int* flag, hipStream_t st) {
   if (!a.planes || !b.planes || a.n2 > 0 || b.n2 > 0) return hipErrorInvalidValue;
   int cus = 0;
   if (hipError_t e = cu_count(&cus); e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_gemm_nonfinite, dim3(4 * cus), dim3(256), 0, st, a, b, big);
+  hipLaunchKernelGGL(k_gemm_nonfinite, dim3(4 * cus), dim3(256), 0, st, a, b, flag);
   return hipGetLastError();
 }
 

@@ -48,6 +48,8 @@ struct UnembedArgs {
   int* wild;
   int* Wexp;            // where the exponents of W's rows go, [n*r*v], or nullptr: behind its planes
   int three;            // operands without SPLIT_WHOLE that are SPLIT_WIDE go through three bf16 terms, in the same scratch
+  int cleared;          // the flag is 0 already
+  int* cols;            // counts of the columns of W (launch_split_rows), or nullptr
   int Wq_rows;          // > 0: the planes of W are ONE matrix of so many rows, [2 d/32][Wq_rows][64 bytes], slab after slab
 };
 
@@ -115,25 +117,27 @@ hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t st)
 
 // Flag bits of operands that are multiplied as terms.  WIDE: a row holds values too far apart for two fp16 terms.  WHOLE: a
 // value is beyond SPLIT_LARGE, where sums of products of bf16 terms may overflow.  Infinite and NaN values are both.
-// STOP: beside WIDE, where only launches after the one that raises it look at it.
-constexpr int SPLIT_WIDE = 1, SPLIT_WHOLE = 2, SPLIT_STOP = 4;
-// Exponents of the rows of a matrix stored as planes of two fp16 terms of `elements` values: right behind them.  (Planes
+// STOP: beside WIDE, where only launches after the one that raises it look at it.  DONE: the planes of three terms have been written
+// for a forward pass; UNDONE: not all of them, since that raised WHOLE.
+constexpr int SPLIT_WIDE = 1, SPLIT_WHOLE = 2, SPLIT_STOP = 4, SPLIT_DONE = 8, SPLIT_UNDONE = 16;
+// Exponents of the rows of a matrix (W, h or its transpose) stored as planes of two fp16 terms of `elements` values: right behind them.  (Planes
 // have room for six bytes per value in every workspace: four are those terms, six are three bf16 terms.)
 inline int* plane_exps(void* planes, long long elements) { return (int*)((char*)planes + 4 * elements); }
 // fp32 rows as planes of two fp16 terms (unembed.hip, k_split_rows): `slabs` matrices of v rows, each [2 d/32][v][64 bytes] or,
 // with dst_rows > 0, all rows of one matrix of so many, and the exponents of all rows.  Rows from `rows1` on (one slab) are
-// the `rows2` of src2 and then zeros
+// the `rows2` of src2 and then zeros.  cols [2][d]: incremented by the small values (SPLIT_SMALL) and the zeros of each column
 hipError_t launch_split_rows(const void* src, void* dst, long long slabs, int v, int d, long long row_stride, int* exps,
                              int* flag, int guard, hipStream_t st, long long dst_rows = 0, int rows1 = 0x7fffffff,
-                             const void* src2 = nullptr, int rows2 = 0, int first = 0, int skip = 0);
-// Up to two matrices as planes of three bf16 terms (split3), the layouts as above with 3 for 2; nothing is done unless the bits
-// `mask` of *flag are `want`
+                             const void* src2 = nullptr, int rows2 = 0, int first = 0, int skip = 0, int* cols = nullptr);
+// Up to two matrices as planes of three bf16 terms (split3), the layouts as above with 3 for 2.  Forward pass (whole = 0): where *flag
+// is SPLIT_WIDE alone; else (1) where it is SPLIT_WIDE, without the first done_rows rows that a forward pass has done
 struct Split3Job {
   const void* src; void* dst;
   long long slabs; int v, d; long long row_stride, dst_rows;
   int rows1; const void* src2; int rows2;
+  int done_rows;
 };
-hipError_t launch_split3(const Split3Job& j0, const Split3Job& j1, int* flag, int mask, int want, hipStream_t st);
+hipError_t launch_split3(const Split3Job& j0, const Split3Job& j1, int* flag, int whole, hipStream_t st);
 
 // ---- small kernels (circuits.hip) -----------------------------------------
 // log omega[b][:] = log_softmax(Wsum h[b])
@@ -317,14 +321,17 @@ struct GradPhiArgs {
   // it), dL as [ldM * esz / 64][B][64 bytes] (then dl_end = ldM: every column is written here)
   int staged;
   // 1 (fp32, staged): both as planes of two fp16 terms, stages of 32 columns per term (tile_gemm_run_split):
-  // dLT [2 ldb/32][M][64 bytes], dL [2 ldM/32][B][64 bytes], the exponents of their rows behind them (plane_exps).
-  // The rows of dL are those of dL[b][m] 2^Wexp[m]: they meet rows of W without their scale
+  // dLT [2 ldb/32][M][64 bytes], dL [2 ldM/32][B][64 bytes], scaled by rows (largest_exp of rows and top).
+  // The rows of dL are those of dL[b][m] 2^Wexp[m]: they meet rows of W without their scale.  Where *flag is SPLIT_WIDE: as
+  // planes of three bf16 terms, 3 for 2, without scales
   int planes;
   const void* dslT;     // the sum-unit rows M..Mx-1 of dLT, [Mx - M][ldb] in the dtype of h
-  int* big;             // planes: set to 1 when an element is infinite or NaN
+  int* flag;            // planes: SPLIT_*, raised for the elements
   int* top;             // planes: scratch [ldb], cleared (k_grad_exps)
+  int* rows;            // planes: scratch [M], cleared
+  const unsigned* weights;      // planes: of h's rows in the planes of h^T (launch_transpose) [ldb]
+  const int* cols;      // planes: counts of the columns of [W; Wsum] (launch_split_rows)
   int* Wexp;            // planes: exponents of the rows of W and, behind them, of Wsum [Mx] (launch_transpose, along_rows)
-  const int* wild;      // planes: the flag of the forward pass that has split W; set, it sets *big; or nullptr
   // 1 (staged, bf16): no dL; dLT [ldb/32][ldM][64 bytes], the sum-unit rows and zeros behind the others; and rows tail_row ..
   // ldM - 1 of [W; Wsum; 0], [ldM][d], are copied to `tail`
   int rows_only;
@@ -334,6 +341,10 @@ struct GradPhiArgs {
   void* tail;
 };
 hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st);
+// (planes) what has to come first: which positions have a gradient; and, once h^T and [W; Wsum] are split, the scales of the rows
+// of both and whether the terms do
+hipError_t launch_live_positions(const GradPhiArgs& a, hipStream_t st);
+hipError_t launch_grad_exps(const GradPhiArgs& a, hipStream_t st);
 // n ints set to 0 by a kernel
 hipError_t launch_clear(int* p, long long n, hipStream_t st);
 
@@ -367,16 +378,17 @@ struct GemmArgs {
   // partials in a fixed order into C (single output buffer only)
   int ksplit; int kchunk; float* partial;
   int planes;           // fp32 only: As and Bs hold two fp16 terms per value, [2 K/32][rows][64 bytes]
-  const int* Ae;        // ... and these the exponents of their rows (nullptr: 0)
+  const int* Atop;      // ... and these the largest elements of A's rows (largest_exp), and the exponents of B's (nullptr: 0)
   const int* Be;
+  const int* flag;      // planes: where SPLIT_WIDE is set they are three bf16 terms, 3 for 2 (in Bk.chunk as well), without exponents
   // operands given along their rows instead, their K rows of M and N columns: both (bf16), or the second one beside A's planes.
   // base nullptr: as above
   KRows Ak, Bk;
 };
 hipError_t launch_gemm_tn(const GemmArgs& a, int dtype, hipStream_t st);
-// After two products of planes: where *big is set, forms every result that is not finite anew as an fp32 sum of the
-// whole values (see split2).  Single output buffer C only.
-hipError_t launch_gemm_nonfinite(const GemmArgs& a, const GemmArgs& b, const int* big, hipStream_t st);
+// After two products of planes: where *flag is SPLIT_WIDE and SPLIT_WHOLE, forms every result that is not finite anew as an fp32
+// sum of the whole values (see split3).  Single output buffer C only.
+hipError_t launch_gemm_nonfinite(const GemmArgs& a, const GemmArgs& b, const int* flag, hipStream_t st);
 // number of K splits that fills the 256 CUs best for an M x N output (1: none)
 inline int gemm_ksplit(int M, int N, int K) {
   const long long tiles = (long long)((M + 255) / 256) * ((N + 255) / 256);
@@ -402,7 +414,10 @@ struct TransposeArgs {
   int stage_rows;
   // 1 (fp32, stage_rows set, col0 = 0, Rpad a multiple of 32): two fp16 terms per value, [2 columns/32][stage_rows][64 bytes]
   int planes;
-  int* big;             // planes: set to 1 when an element is infinite or NaN
+  int* flag;            // planes: SPLIT_*
+  // planes, the transpose: src's rows whose `live` is 0 are zeros in the planes and none of the largest values of dst's
+  // rows; `weights` gets the sums of their scaled magnitudes.  Both [Rpad], 0 beyond R
+  const int* live; unsigned* weights;
   // planes: rows of dst get scales of their own, left behind the planes (plane_exps); src^T in fp32 goes to plain, [C][ld_plain],
   // columns up to Rpad
   void* plain; long long ld_plain;
@@ -412,6 +427,7 @@ struct TransposeArgs {
   int along_rows;
   const void* src2; int R2; int row0;
   int* exps;
+  int* cols;            // counts of its columns (launch_split_rows)
 };
 hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t st);
 
@@ -431,6 +447,7 @@ struct CircuitBwdArgs {
   float* G;              // scratch [L][r][r]
   float* Gpart;          // scratch: per block of LAYER_GRAD_ROWS rows, [steps][r][r] outer-product partials
                          // (shared layers) or [L*r*r] column sums (bias gradient of layers computed from h)
+  int* clear; int nclear;       // ints set to 0 for the launches that follow (which saves a launch of its own)
   // layers of every position (computed from h): lay_nat / lay_tr hold [rows][L][r][r] and the
   // gradient w.r.t. the logits of position b goes to dlog[b*ld_dlog + (l*r + z)*r + z'] in the
   // dtype of h (dlog_cols columns, zero beyond L*r*r); dlayers then receives the column sums
@@ -558,6 +575,9 @@ constexpr int SPLIT_ZERO_ROW = -100000;
 __device__ __forceinline__ int split_exp(float largest) {
   return largest > 0.f ? __builtin_amdgcn_frexp_expf(largest) - 15 : SPLIT_ZERO_ROW;
 }
+// the same from its bits, which are an integer like any other to an atomic.  (0: as for fp32's smallest value, which is what a
+// row may hold whose scaled largest is below that.)
+__device__ __forceinline__ int largest_exp(int bits) { return __builtin_amdgcn_frexp_expf(__uint_as_float((unsigned)max(bits, 1))) - 15; }
 
 __device__ __forceinline__ float neg_inf() { return -__builtin_inff(); }
 

@@ -238,6 +238,7 @@ struct TileFeed {
   // KR: the rows of srdH that are left, in stages, and where it goes on from there
   i32x4_t srdT;
   int hleft;
+  unsigned hterm;                                    // three terms: the distance of two of them (hleft: how many are issued)
 
   __device__ __forceinline__ void issue_one(int q, int buf) {   // q-th wave-load of this wave for one stage
     __builtin_assume(wave >= 0 && wave < TL::NW);    // (which loads are W's and which exist is then known per q, mostly)
@@ -265,7 +266,12 @@ struct TileFeed {
     if constexpr (KR == 0) kofs += SB;
     if constexpr (WPACK || KR == 3) kofsW += wstep;
     kofsH += hstep;
-    if constexpr (KR != 0 && SPLIT != 0) hstep = kofs - hstep;       // (kofs: the distance of two terms and back, constant here)
+    // (kofs: from the first term of 32 rows to that of the next, constant here)
+    if constexpr (KR != 0 && SPLIT == 2) hstep = kofs - hstep;
+    if constexpr (KR != 0 && SPLIT == 3) {
+      hleft = hleft == 2 ? 0 : hleft + 1;
+      hstep = hleft == 2 ? kofs - 2 * hterm : hterm;
+    }
     if constexpr (KR != 0 && SPLIT == 0) {
       const bool over = --hleft == 0;
 #pragma unroll
@@ -280,13 +286,14 @@ struct TileFeed {
   }
 
   // lane offset of the q-th load of an operand given along its rows: eight rows of 64 columns from column 32 * chunk0 on
+  // (given for two terms)
   __device__ __forceinline__ unsigned row_offset(int wl, const KRows& m, int chunk0, int chunks) {
     const int lane = threadIdx.x & 63;
     const int row = (wl & 3) * 8 + (lane >> 3), c = (lane & 7) ^ (swz_krow(row) << 1);
     const int chunk = min(chunk0 + 2 * (wl >> 2) + (c >> 2), chunks - 1);       // (columns that are not there: any)
-    return (unsigned)chunk * m.chunk + (unsigned)row * m.row + (c & 3) * 16;
+    return (unsigned)chunk * (SPLIT == 3 ? 3 * m.term : m.chunk) + (unsigned)row * m.row + (c & 3) * 16;
   }
-  // KR: columns a0 .. of `ak` (of acols; KR = 3) or rows of the stage-major planes at Ap [2 K/32][arows][64] (KR = 2), columns
+  // KR: columns a0 .. of `ak` (of acols; KR = 3) or rows of the stage-major planes at Ap [SPLIT K/32][arows][64] (KR = 2), columns
   // b0 .. of `bk` (of bcols), rows k0 .. k0 + klen - 1.  a0, b0, k0 and klen are multiples of 32.
   __device__ __forceinline__ void open_rows(const void* Ap, int arows, const KRows& ak, int acols, int a0, const KRows& bk, int bcols, int b0,
                                             int k0, int klen, char* smem) {
@@ -299,14 +306,15 @@ struct TileFeed {
       kofsW = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)k0 * ak.row));
       wstep = (unsigned)__builtin_amdgcn_readfirstlane((int)(32u * ak.row));
     } else {
-      srdW = make_srd((const char*)Ap + (long long)(k0 / 32) * 2 * arows * 64, (unsigned)((long long)klen * 4 * arows));
+      srdW = make_srd((const char*)Ap + (long long)(k0 / 32) * SPLIT * arows * 64, (unsigned)((long long)klen * 2 * SPLIT * arows));
       kofsW = 0;
       wstep = (unsigned)__builtin_amdgcn_readfirstlane(arows * 64);
     }
     const bool main = k0 < bk.kmain;                   // workgroup-uniform
     srdT = make_srd(bk.tail, bk.tail_bytes);
-    srdH = main ? make_srd(bk.base, bk.bytes) : srdT;
-    hleft = main ? (bk.kmain - k0) / 32 : 0;
+    srdH = main ? make_srd(bk.base, SPLIT == 3 ? bk.bytes / 2 * 3 : bk.bytes) : srdT;
+    hleft = SPLIT == 0 && main ? (bk.kmain - k0) / 32 : 0;
+    hterm = (unsigned)__builtin_amdgcn_readfirstlane((int)bk.term);
     kofsH = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(main ? k0 : k0 - bk.kmain) * bk.row));
     hstep = (unsigned)__builtin_amdgcn_readfirstlane((int)(SPLIT != 0 ? bk.term : 32u * bk.row));
     kofs = (unsigned)__builtin_amdgcn_readfirstlane((int)(32u * bk.row));
@@ -321,8 +329,10 @@ struct TileFeed {
       voff[q + 2] = row_offset(wl, bk, b0 / 32, (bcols + 31) / 32);
     }
     lds0 = (unsigned)(size_t)smem;
-    static_assert(SPLIT != 3, "two terms");
-    if constexpr (SPLIT == 2) {
+    if constexpr (SPLIT == 3) {
+      issue(SPLIT3_SLOT_A0);
+      issue(SPLIT3_SLOT_B);
+    } else if constexpr (SPLIT == 2) {
       issue(SPLIT_SLOT_HI);
       issue(SPLIT_SLOT_LO);
       if (klen > 32) issue(SPLIT_SLOT_HI + 1);

@@ -1211,11 +1211,12 @@ hipError_t launch_pack_rows(const void* src, void* dst, long long slabs, int v, 
 // few values happen to be near 0: more than one in 16 of those that are not 0 (of a row with few of them, any).
 // first: raises SPLIT_STOP beside SPLIT_WIDE.  skip: a caller that has no use for the planes of one matrix where another is
 // SPLIT_WIDE; nothing is done where the launch before has found that, and little more than the reads where this one does.
+// cols: the same counts for every column of the matrix, added up over its rows (for a product whose K runs down the rows).
 constexpr int SPLIT_ROWS = 8, SPLIT_KEEP = 8;        // rows of a workgroup, steps of 512 columns kept in registers
 // (four waves to a SIMD, so that two workgroups share a CU: with one, the same reads take a quarter longer)
 __global__ __launch_bounds__(512, 4) void k_split_rows(const char* __restrict__ src, char* __restrict__ dst, int v, int d,
                                                     long long row_stride, int* __restrict__ exps, int* flag, int guard,
-                                                    long long dst_rows, int rows1, const char* __restrict__ src2, int rows2, int first, int skip) {
+                                                    long long dst_rows, int rows1, const char* __restrict__ src2, int rows2, int first, int skip, int* cols) {
   if (skip && (*flag & SPLIT_STOP) != 0) return;     // (raised by launches before this one only: the same for every wave)
   __shared__ unsigned s_max[8][SPLIT_ROWS];
   __shared__ int s_small[8][SPLIT_ROWS], s_zero[8][SPLIT_ROWS], s_stop;
@@ -1266,7 +1267,9 @@ __global__ __launch_bounds__(512, 4) void k_split_rows(const char* __restrict__ 
   for (int w = 0; w < 8; ++w) m = max(m, s_max[w][rl]);
   const int E = split_exp(__uint_as_float(m));
   int small = 0;                                     // (with those that are 0)
-  auto put = [&](const f32x4_t& y0, const f32x4_t& y1, int k) {
+  unsigned hit = 0;                                  // steps with any (the last bit: of those beyond SPLIT_KEEP)
+  auto put = [&](const f32x4_t& y0, const f32x4_t& y1, int k, int it) {
+    const int before = small;
     if (!live || k >= stages) return;
     struct alignas(16) Oct { unsigned short v[8]; } o[2];
 #pragma unroll
@@ -1277,16 +1280,38 @@ __global__ __launch_bounds__(512, 4) void k_split_rows(const char* __restrict__ 
       split2(y, q);
       o[0].v[c] = q[0]; o[1].v[c] = q[1];
     }
+    hit |= small != before ? 1u << it : 0u;
 #pragma unroll
     for (int p = 0; p < 2; ++p)
       *(Oct*)(out + (2LL * k + p) * srow * 64) = o[p];
   };
 #pragma unroll
-  for (int it = 0; it < SPLIT_KEEP; ++it) put(x[it][0], x[it][1], it * 16 + sub);
+  for (int it = 0; it < SPLIT_KEEP; ++it) put(x[it][0], x[it][1], it * 16 + sub, it);
   const f32x4_t zeros = f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int k = SPLIT_KEEP * 16 + sub; live && k < stages; k += 16)
-    put(read ? *(const f32x4_t*)(s + (long long)k * 128) : zeros, read ? *(const f32x4_t*)(s + (long long)k * 128 + 16) : zeros, k);
+    put(read ? *(const f32x4_t*)(s + (long long)k * 128) : zeros, read ? *(const f32x4_t*)(s + (long long)k * 128 + 16) : zeros, k, SPLIT_KEEP);
   int raise = odd ? SPLIT_WIDE | SPLIT_WHOLE : 0;
+  if (cols != nullptr) {                             // (reads the few stages with small values or zeros once more)
+    // the lanes of a column: those of the eight rows
+    const unsigned long long mine = 0x11111111ull << ((lane & 32) + (lane & 3));
+    unsigned todo = hit;
+    for (int o = 1; o < 64; o <<= 1) todo |= (unsigned)__shfl_xor((int)todo, o);
+    while (todo != 0) {
+      const int it = __builtin_ctz(todo);
+      todo &= todo - 1;
+      for (int k = it * 16 + sub; k < (it < SPLIT_KEEP ? min(stages, it * 16 + 16) : stages); k += 16) {
+        const f32x4_t y[2] = {read ? *(const f32x4_t*)(s + (long long)k * 128) : zeros, read ? *(const f32x4_t*)(s + (long long)k * 128 + 16) : zeros};
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          const bool none = live && y[c >> 2][c & 3] == 0.f;
+          const bool little = live && !none && fabsf(__builtin_amdgcn_ldexpf(y[c >> 2][c & 3], -E)) < SPLIT_SMALL;
+          const int nl = __popcll(__ballot(little) & mine), nz = __popcll(__ballot(none) & mine), at = k * 32 + ch * 8 + c;
+          if (rl == 0 && nl > 0) atomicAdd(cols + at, nl);
+          if (rl == 0 && nz > 0) atomicAdd(cols + d + at, nz);
+        }
+      }
+    }
+  }
   if (guard) {
     auto sum = [&](int y) { y += __shfl_xor(y, 1); y += __shfl_xor(y, 2); return y + __shfl_xor(y, 32); };
     small = sum(small);
@@ -1318,27 +1343,30 @@ __global__ __launch_bounds__(512, 4) void k_split_rows(const char* __restrict__ 
 }
 
 hipError_t launch_split_rows(const void* src, void* dst, long long slabs, int v, int d, long long row_stride, int* exps,
-                             int* flag, int guard, hipStream_t st, long long dst_rows, int rows1, const void* src2, int rows2, int first, int skip) {
+                             int* flag, int guard, hipStream_t st, long long dst_rows, int rows1, const void* src2, int rows2, int first, int skip, int* cols) {
   const long long blocks = slabs * ((v + SPLIT_ROWS - 1) / SPLIT_ROWS);
   hipLaunchKernelGGL(k_split_rows, dim3((unsigned)blocks), dim3(512), 0, st, (const char*)src, (char*)dst, v, d, row_stride, exps,
-                     flag, guard, dst_rows, rows1, (const char*)src2, rows2, first, skip);
+                     flag, guard, dst_rows, rows1, (const char*)src2, rows2, first, skip, cols);
   return hipGetLastError();
 }
 
 // Planes of three bf16 terms: one thread splits 8 columns; four threads read one 128-byte line and write 64 contiguous bytes of
 // each plane, neighbouring rows follow (843 MB of W in 0.43 ms, 4.9 TB/s).  Raises SPLIT_WHOLE (a matrix that k_split_rows has skipped
 // is seen here first).
-__global__ __launch_bounds__(256) void k_split3(const Split3Job j0, const Split3Job j1, int* flag, int mask, int want) {
-  if ((__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & mask) != want) return;
+__global__ __launch_bounds__(256) void k_split3(const Split3Job j0, const Split3Job j1, int* flag, int whole) {
+  const int now = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((now & SPLIT_WIDE) == 0 || (!whole && (now & SPLIT_WHOLE) != 0)) return;
+  const bool done = whole && (now & (SPLIT_DONE | SPLIT_UNDONE)) == SPLIT_DONE;       // (not raised by launches with `whole`)
   bool large = false;
   for (int g = 0; g < 2; ++g) {
     const Split3Job& j = g == 0 ? j0 : j1;
-    const long long per_slab = (long long)j.v * (j.d / 8), total = j.slabs * per_slab;
+    const int row0 = done ? j.done_rows : 0, nrows = j.v - row0;
+    const long long per_slab = (long long)nrows * (j.d / 8), total = j.slabs * per_slab;
     const long long srow = j.dst_rows > 0 ? j.dst_rows : j.v;
     for (long long t = (long long)blockIdx.x * 256 + threadIdx.x; t < total; t += (long long)gridDim.x * 256) {
       const long long slab = t / per_slab;
       const int u = (int)(t - slab * per_slab);
-      const int k = u / (j.v * 4), w = u - k * j.v * 4, row = w >> 2, ch = w & 3;
+      const int k = u / (nrows * 4), w = u - k * nrows * 4, row = row0 + (w >> 2), ch = w & 3;
       const bool second = row >= j.rows1;
       f32x4_t x[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
       if (!second || row - j.rows1 < j.rows2) {
@@ -1361,13 +1389,14 @@ __global__ __launch_bounds__(256) void k_split3(const Split3Job j0, const Split3
       for (int p = 0; p < 3; ++p) *(Oct*)(out + (3LL * k + p) * srow * 64) = o[p];
     }
   }
-  if (large) raise_flag(flag, SPLIT_WHOLE);
+  if (large) raise_flag(flag, whole ? SPLIT_WHOLE : SPLIT_WHOLE | SPLIT_UNDONE);
+  if (!whole && threadIdx.x == 0) raise_flag(flag, SPLIT_DONE);
 }
 
-hipError_t launch_split3(const Split3Job& j0, const Split3Job& j1, int* flag, int mask, int want, hipStream_t st) {
+hipError_t launch_split3(const Split3Job& j0, const Split3Job& j1, int* flag, int whole, hipStream_t st) {
   const long long chunks = std::max(j0.slabs * j0.v * (j0.d / 8), j1.slabs * j1.v * (j1.d / 8));
   // (at most eight workgroups per CU, which walk: mostly there is nothing to do, and many would take long to say so)
-  hipLaunchKernelGGL(k_split3, dim3((unsigned)std::min((chunks + 255) / 256, 2048LL)), dim3(256), 0, st, j0, j1, flag, mask, want);
+  hipLaunchKernelGGL(k_split3, dim3((unsigned)std::min((chunks + 255) / 256, 2048LL)), dim3(256), 0, st, j0, j1, flag, whole);
   return hipGetLastError();
 }
 
@@ -1381,14 +1410,14 @@ static hipError_t launch_split(const UnembedArgs& a0, hipStream_t st) {
   UnembedArgs a = a0;
   const long long slabs = (long long)a.n * a.r;
   if (a.Wexp == nullptr) a.Wexp = plane_exps(a.Wq, slabs * a.v * a.d);
-  hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, st, a.wild);
+  if (!a.cleared) hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, st, a.wild);
   hipError_t e = launch_split_rows(a.h, a.hq, 1, a.B, a.d, a.ld_h * 4, plane_exps(a.hq, (long long)a.B * a.d), a.wild, 1, st, 0, 0x7fffffff,
                                    nullptr, 0, a.three, 0);
-  if (e == hipSuccess) e = launch_split_rows(a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wexp, a.wild, 1, st, a.Wq_rows, 0x7fffffff, nullptr, 0, 0, a.three);
+  if (e == hipSuccess) e = launch_split_rows(a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wexp, a.wild, 1, st, a.Wq_rows, 0x7fffffff, nullptr, 0, 0, a.three, a.cols);
   if (e == hipSuccess && a.three) {
-    const Split3Job jh{a.h, a.hq, 1, a.B, a.d, a.ld_h * 4LL, 0, 0x7fffffff, nullptr, 0};
-    const Split3Job jw{a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wq_rows, 0x7fffffff, nullptr, 0};
-    e = launch_split3(jh, jw, a.wild, SPLIT_WIDE | SPLIT_WHOLE, SPLIT_WIDE, st);
+    const Split3Job jh{a.h, a.hq, 1, a.B, a.d, a.ld_h * 4LL, 0, 0x7fffffff, nullptr, 0, 0};
+    const Split3Job jw{a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wq_rows, 0x7fffffff, nullptr, 0, 0};
+    e = launch_split3(jh, jw, a.wild, 0, st);
   }
   int positions = 256;
   if (e == hipSuccess) e = walk_positions(a, true, positions);
