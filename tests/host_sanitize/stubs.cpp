@@ -77,9 +77,11 @@ hipError_t launch_unembed(const UnembedArgs& a, int dtype, hipStream_t) {
   need(a.W, (u64)a.n * a.r * a.v * a.d * esz(dtype), "unembed W");
   opt(a.Wp, (u64)a.n * a.r * a.v * a.d * esz(dtype), "unembed stage-major W");
   opt(a.hs, (u64)a.B * a.d * esz(dtype), "unembed stage-major h");
-  opt(a.Wq, (u64)a.n * a.r * a.v * a.d * 6, "unembed bf16 terms of W");
-  opt(a.hq, (u64)a.B * a.d * 6, "unembed bf16 terms of h");
+  opt(a.Wq, (a.Wq_rows > 0 ? (u64)a.Wq_rows : (u64)a.n * a.r * a.v) * a.d * 6, "unembed terms of W");
+  opt(a.hq, (u64)a.B * a.d * 6, "unembed terms of h");
+  opt(a.Wexp, (u64)a.n * a.r * a.v * 4, "unembed exponents of W");
   opt(a.wild, 4, "unembed flag");
+  opt(a.cols, (u64)a.d * 8, "unembed counts of W");
   host_check::g_terms |= a.Wq != nullptr;
   host_check::g_staged_h |= a.hs != nullptr;
   host_check::g_table |= a.logphi != nullptr;
@@ -214,6 +216,44 @@ hipError_t launch_unembed_grad(const GradLogitsArgs& a, int dtype, hipStream_t) 
   need(a.dLT, (u64)a.n * a.r * a.v * a.ldb * esz(dtype), "grad dLT");
   return ok();
 }
+static void grad_scales(const GradPhiArgs& a) {
+  need(a.flag, 4, "grad flag");
+  need(a.top, (u64)a.ldb * 4, "grad largest of the positions");
+  need(a.rows, (u64)a.M * 4, "grad largest of the rows");
+  need(a.weights, (u64)a.ldb * 4, "grad weights of the positions");
+  need(a.cols, (u64)a.d * 8, "grad counts of W");
+  need(a.Wexp, (u64)a.Mx * 4, "grad exponents of W");
+}
+hipError_t launch_live_positions(const GradPhiArgs& a, hipStream_t) {
+  need(a.targets, (u64)a.B * a.n * 4, "live targets");
+  need(a.Ge, (u64)a.B * a.n * a.r * 4, "live Ge");
+  if (a.Mx > a.M) need(a.dslT, (u64)(a.Mx - a.M) * a.ldb * 4, "live sum-unit rows");
+  need(a.top, (u64)a.B * 4, "live");
+  return ok();
+}
+hipError_t launch_grad_exps(const GradPhiArgs& a, hipStream_t) {
+  need(a.phiT, (u64)a.M * a.ld_phi * 4, "scales phiT");
+  need(a.targets, (u64)a.B * a.n * 4, "scales targets");
+  need(a.Ge, (u64)a.B * a.n * a.r * 4, "scales Ge");
+  if (a.Mx > a.M) need(a.dslT, (u64)(a.Mx - a.M) * a.ldb * 4, "scales sum-unit rows");
+  grad_scales(a);
+  return ok();
+}
+hipError_t launch_clear(int* p, long long n, hipStream_t) {
+  need(p, (u64)n * 4, "clear");
+  return ok();
+}
+hipError_t launch_split3(const Split3Job& j0, const Split3Job& j1, int* flag, int, hipStream_t) {
+  need(flag, 4, "split flag");
+  for (const Split3Job* j : {&j0, &j1}) {
+    if (j->d % 32 || (j->dst_rows > 0 && j->dst_rows < j->slabs * j->v) || j->done_rows > j->v) { std::fprintf(stderr, "split: another form\n"); std::abort(); }
+    const u64 rows1 = j->slabs * (u64)(j->v < j->rows1 ? j->v : j->rows1);
+    need(j->src, (rows1 - 1) * j->row_stride + (u64)j->d * 4, "split source");
+    if (j->rows2 > 0) need(j->src2, (u64)(j->rows2 - 1) * j->row_stride + (u64)j->d * 4, "split second source");
+    need(j->dst, (j->dst_rows > 0 ? (u64)j->dst_rows : j->slabs * (u64)j->v) * j->d * 6, "split planes");
+  }
+  return ok();
+}
 hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t) {
   need(a.phiT, (u64)a.M * a.ld_phi * 4, "grad phiT");
   need(a.targets, (u64)a.B * a.n * 4, "grad targets");
@@ -221,9 +261,9 @@ hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t) {
   need(a.dLT, (u64)a.Mx * a.ldb * esz(dtype), "grad dLT");
   need(a.dL, (u64)a.B * a.ldM * esz(dtype), "grad dL");
   if (a.planes) {
-    need(a.dLT, (u64)a.M * a.ldb * 6, "grad dLT, bf16 terms");
-    need(a.dL, (u64)a.B * a.ldM * 6, "grad dL, bf16 terms");
-    need(a.big, 4, "grad flag");
+    need(a.dLT, (u64)a.M * a.ldb * 6, "grad dLT, terms");
+    need(a.dL, (u64)a.B * a.ldM * 6, "grad dL, terms");
+    grad_scales(a);
   }
   if (a.Mx > a.M) need(a.dslT, (u64)(a.Mx - a.M) * a.ldb * esz(dtype), "grad sum-unit rows");
   return ok();
@@ -237,8 +277,11 @@ hipError_t launch_gemm_tn(const GemmArgs& a, int dtype, hipStream_t) {
     need(a.As, (u64)a.As_rows * a.K * esz(dtype), "gemm A, stage-major");
   }
   if (a.planes) {
-    need(a.As, (u64)a.As_rows * a.K * 6, "gemm A, bf16 terms");
-    need(a.Bs, (u64)a.N * a.K * 6, "gemm B, bf16 terms");
+    need(a.As, (u64)a.As_rows * a.K * 6, "gemm A, terms");
+    need(a.Bs, (u64)a.N * a.K * 6, "gemm B, terms");
+    need(a.flag, 4, "gemm flag");
+    need(a.Atop, (u64)a.M * 4, "gemm largest of A's rows");
+    opt(a.Be, (u64)a.N * 4, "gemm exponents of B");
   }
   const int r1 = a.M < a.split ? a.M : a.split;
   need(a.C, strided(r1, a.ldc, a.N, 4), "gemm C");
@@ -247,12 +290,12 @@ hipError_t launch_gemm_tn(const GemmArgs& a, int dtype, hipStream_t) {
   if (a.ksplit > 1) need(a.partial, (u64)a.ksplit * a.M * a.ldc * 4, "gemm partial");
   return ok();
 }
-hipError_t launch_gemm_nonfinite(const GemmArgs& a, const GemmArgs& b, const int* big, hipStream_t) {
-  need(big, 4, "gemm flag");
+hipError_t launch_gemm_nonfinite(const GemmArgs& a, const GemmArgs& b, const int* flag, hipStream_t) {
+  need(flag, 4, "gemm flag");
   for (const GemmArgs* g : {&a, &b}) {
     if (!g->planes || g->n2 > 0 || g->split3 < g->M || g->K % 32) { std::fprintf(stderr, "gemm, not finite: another form\n"); std::abort(); }
-    need(g->As, (u64)g->As_rows * g->K * 6, "gemm A, bf16 terms");
-    need(g->Bs, (u64)g->N * g->K * 6, "gemm B, bf16 terms");
+    need(g->As, (u64)g->As_rows * g->K * 6, "gemm A, terms");
+    need(g->Bs, (u64)g->N * g->K * 6, "gemm B, terms");
     need(g->C, strided(g->M, g->ldc, g->N, 4), "gemm C");
   }
   return ok();
@@ -260,12 +303,22 @@ hipError_t launch_gemm_nonfinite(const GemmArgs& a, const GemmArgs& b, const int
 hipError_t launch_transpose(const TransposeArgs& a, int dtype, hipStream_t) {
   if (a.C < 1 || a.Rpad < 1) return hipSuccess;
   need(a.src, strided(a.R, a.ld_src, a.C, esz(dtype)), "transpose src");
-  if (a.stage_rows) {                     // stage-major destination: whole 64-byte stages of stage_rows rows
+  if (a.planes) need(a.flag, 4, "transpose flag");
+  if (a.along_rows) {
+    if (a.R2 > 0) need(a.src2, (u64)a.R2 * a.C * 4, "split second source");
+    need(a.dst, (u64)a.Rpad * a.C * 6, "split planes");
+    need(a.exps, (u64)a.Rpad * 4, "split exponents");
+    need(a.cols, (u64)a.C * 8, "split counts");
+  } else if (a.planes) {
+    need(a.dst, (u64)a.Rpad * a.stage_rows * 6, "transpose planes");
+    need(plane_exps(a.dst, (long long)a.Rpad * a.stage_rows), (u64)a.C * 4, "transpose exponents");
+    need(a.plain, strided(a.C, a.ld_plain, a.Rpad, 4), "transpose plain");
+    need(a.live, (u64)a.Rpad * 4, "transpose live");
+    need(a.weights, (u64)a.Rpad * 4, "transpose weights");
+  } else if (a.stage_rows) {                     // stage-major destination: whole 64-byte stages of stage_rows rows
     const u64 eps = 64 / esz(dtype);
     if (a.stage_rows < a.C) { std::fprintf(stderr, "transpose: bad stage-major destination\n"); std::abort(); }
     need(a.dst, ((u64)a.col0 + a.Rpad + eps - 1) / eps * a.stage_rows * 64, "transpose dst, stage-major");
-    if (a.planes) need(a.dst, ((u64)a.col0 + a.Rpad + 31) / 32 * a.stage_rows * 192, "transpose dst, bf16 terms");
-    if (a.planes) need(a.big, 4, "transpose flag");
   } else {
     need((const char*)a.dst + (u64)a.col0 * esz(dtype), strided(a.C, a.ld_dst, a.Rpad, esz(dtype)), "transpose dst");
   }
@@ -279,7 +332,7 @@ hipError_t launch_circuit_bwd(const CircuitBwdArgs& a, hipStream_t) {
   need(a.coef, rows * a.n * 4, "bwd coef");
   need(a.Ge, rows * a.n * a.r * 4, "bwd Ge");
   need(a.loss, rows * 4, "bwd loss");
-  opt(a.clear, 4, "bwd flag");
+  opt(a.clear, (u64)a.nclear * 4, "bwd cleared");
   if (a.family != MTPC_FF) {
     need(a.logw, rows * a.r * 4, "bwd logw");
     need(a.dslT, (u64)a.r * a.ldb * (a.bf16 ? 2 : 4), "bwd dslT");
