@@ -658,6 +658,7 @@ struct BwdPlan {
   size_t terms;             // flag of the terms; 16 bytes on, what the scales of the terms are decided by (run_backward)
   bool staged;              // the logit gradient stage-major, as the contractions read it
   bool along_rows;          // bf16: the dh contraction reads W and the logit gradient along their rows
+  long long kmain;          // ... W itself up to this row, a multiple of 32
 };
 
 BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly, bool keep_phi, bool split = true) {
@@ -689,10 +690,6 @@ BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly,
             (unsigned long long)hd->d * q.ldb * 6 < lim;
   q.split_fwd = q.split && split_pays(hd);
   const size_t osz = q.split ? 6 : esz;       // bytes per element of the contractions' operands
-  q.dLT = take((size_t)(q.ctx ? q.ldM : q.split ? q.M : q.Mx) * q.ldb * osz);
-  if (q.split) q.terms = take(16 + (size_t)(q.ldb + hd->d) * 8 + (size_t)q.M * 4);
-  q.dslT = q.split ? take((size_t)(q.Mx - q.M) * q.ldb * esz) : q.dLT + (size_t)q.M * q.ldb * esz;
-  q.dL = take(B * q.ldM * osz);
   // (stage-major when one kernel writes every element of both layouts - no layer-logit columns from elsewhere - and one
   // 32-bit buffer resource spans each)
   q.staged = q.split || (keep_phi && !q.ctx && (unsigned long long)q.M * q.ldb * esz < lim && (unsigned long long)B * q.ldM * esz < lim);
@@ -702,10 +699,7 @@ BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly,
     q.kchunk = (int)(((q.ldM + q.ksplit - 1) / q.ksplit + 63) / 64 * 64);
     q.ksplit = (int)((q.ldM + q.kchunk - 1) / q.kchunk);
   }
-  // Operands along their rows: dLT with the sum-unit rows and zeros up to ldM behind the others, which - like the sum-unit rows
-  // in a layout of their own - take the room of the dL that is then not needed.
   if (q.staged && !q.split && hd->dtype == MTPC_BF16 && (unsigned long long)q.ldM * q.ldb * 2 < lim && (unsigned long long)q.ldM * hd->d * 2 < lim) {
-    const size_t own = up(q.dLT + (size_t)q.ldM * q.ldb * 2);
     // What it saves: the transpose of W, the other layout of the gradient (4.2 TB/s) and a launch.  What it costs: a stage of 32 rows
     // takes 0.05 us longer where all CUs are busy (n r v = 327,680, d = 3072, B = 4096: 22.3 ms without, 21.0 ms with it), up to
     // 0.28 us where they wait for their loads (n r v = 2880, d = 1408, B = 2548: 169, 177 us; 804, 1664, 4726: 166, 172 us;
@@ -713,12 +707,16 @@ BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly,
     const double tiles = (double)((hd->B + 255) / 256) * ((hd->d + 255) / 256) * q.ksplit;
     const double stages = std::ceil(tiles / 256) * (q.kchunk / 32);
     const double saved = ((double)q.M * hd->d * 4 + (double)q.M * hd->B * 2) / 4.2e6 + 4;
-    if (own + (size_t)(q.Mx - q.M) * q.ldb * 2 <= q.dL + B * q.ldM * 2 && saved > stages * (tiles >= 256 ? 0.05 : 0.28)) {
-      q.along_rows = true;
-      q.dslT = own;
-    }
+    q.along_rows = saved > stages * (tiles >= 256 ? 0.05 : 0.28);
   }
-  q.WT = take((size_t)hd->d * q.ldM * osz);
+  // Operands along their rows: dLT with the sum-unit rows and zeros up to ldM behind the others (the sum-unit rows in a layout of
+  // their own as well), no dL, and of W only a copy of the rows beyond its whole stages.
+  q.dLT = take((size_t)(q.ctx || q.along_rows ? q.ldM : q.split ? q.M : q.Mx) * q.ldb * osz);
+  if (q.split) q.terms = take(16 + (size_t)(q.ldb + hd->d) * 8 + (size_t)q.M * 4);
+  q.dslT = q.split || q.along_rows ? take((size_t)(q.Mx - q.M) * q.ldb * esz) : q.dLT + (size_t)q.M * q.ldb * esz;
+  if (!q.along_rows) q.dL = take(B * q.ldM * osz);
+  q.kmain = q.M / 32 * 32;
+  q.WT = take((size_t)(q.along_rows ? q.ldM - q.kmain : q.ldM) * hd->d * osz);
   q.hT = take((size_t)hd->d * q.ldb * esz);
   if (q.split_fwd) {                          // (the planes of W are those the dh contraction reads: in WT)
     q.hq = take(B * (size_t)hd->d * 6);
@@ -870,7 +868,6 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
 
   // ---- [W; Wsum] as an operand read along its rows: in fp32 as planes (all rows the forward pass has not split), in bf16 W
   // itself and, in WT, a copy of the rows beyond its whole stages
-  const int kmain = (int)(q.M / 32 * 32);
   if (q.split) {
     TransposeArgs w{};
     w.along_rows = 1; w.planes = 1; w.flag = flag; w.exps = wexp; w.cols = cols;
@@ -888,12 +885,12 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
     g.B = hd->B; g.n = hd->n; g.r = hd->r; g.v = hd->v;
     g.M = q.M; g.Mx = q.Mx; g.ldM = q.ldM; g.ldb = q.ldb;
     g.dl_end = ctx ? q.Mlay : q.ldM;           // the layer-logit columns are written by the reverse pass
-    g.dLT = ws + q.dLT; g.dL = ws + q.dL;
+    g.dLT = ws + q.dLT; g.dL = q.along_rows ? nullptr : ws + q.dL;
     g.staged = q.staged;
     g.planes = q.split; g.flag = flag; g.top = top; g.rows = rows; g.weights = weights; g.cols = cols; g.dslT = ws + q.dslT; g.Wexp = wexp;
     g.rows_only = q.along_rows;
     g.d = hd->d;
-    if (q.along_rows) { g.W = hd->W; g.Wsum = hd->Wsum; g.tail_row = kmain; g.tail = ws + q.WT; }
+    if (q.along_rows) { g.W = hd->W; g.Wsum = hd->Wsum; g.tail_row = (int)q.kmain; g.tail = ws + q.WT; }
     if (q.split) {
       // which terms: the scales of h^T over the positions that have a gradient, those of the gradient, then the planes of all or,
       // where those do not do, three terms of all
@@ -957,10 +954,14 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
 
   // ---- the two contractions
   GemmArgs m{};
-  m.A = ws + q.dL; m.lda = q.ldM; m.M = hd->B;                   // dh[b][k] = sum_m dL[b][m] WT[k][m]
-  m.Bm = ws + q.WT; m.ldb = q.ldM; m.N = hd->d; m.K = (int)q.ldM;
-  m.Bs = wt_staged ? ws + q.WT : nullptr;
-  m.As = q.staged ? ws + q.dL : nullptr; m.As_rows = hd->B;
+  m.lda = q.ldM; m.M = hd->B;                                    // dh[b][k] = sum_m dL[b][m] WT[k][m]
+  m.ldb = q.ldM; m.N = hd->d; m.K = (int)q.ldM;
+  if (!q.along_rows) {
+    m.A = ws + q.dL;
+    m.Bm = ws + q.WT;
+    m.Bs = wt_staged ? ws + q.WT : nullptr;
+    m.As = q.staged ? ws + q.dL : nullptr; m.As_rows = hd->B;
+  }
   m.planes = q.split; m.flag = flag;
   if (q.split) {                                                 // planes of dL; W along its rows
     m.Atop = top;
@@ -970,9 +971,9 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   } else if (q.along_rows) {
     m.Ak.base = ws + q.dLT; m.Ak.row = 64; m.Ak.chunk = (unsigned)(q.ldM * 64); m.Ak.bytes = (unsigned)(q.ldM * q.ldb * 2);
     m.Ak.kmain = (int)q.ldM;
-    m.Bk.base = hd->W; m.Bk.row = (unsigned)hd->d * 2; m.Bk.chunk = 64; m.Bk.bytes = (unsigned)((long long)kmain * hd->d * 2);
-    m.Bk.kmain = kmain;
-    m.Bk.tail = ws + q.WT; m.Bk.tail_bytes = (unsigned)((q.ldM - kmain) * hd->d * 2);
+    m.Bk.base = hd->W; m.Bk.row = (unsigned)hd->d * 2; m.Bk.chunk = 64; m.Bk.bytes = (unsigned)(q.kmain * hd->d * 2);
+    m.Bk.kmain = (int)q.kmain;
+    m.Bk.tail = ws + q.WT; m.Bk.tail_bytes = (unsigned)((q.ldM - q.kmain) * hd->d * 2);
   }
   m.C = dh; m.ldc = hd->d; m.split = hd->B; m.n2 = 0; m.C2 = nullptr; m.split3 = 0x7fffffff; m.C3 = nullptr;
   m.ksplit = q.ksplit; m.kchunk = q.kchunk; m.partial = q.ksplit > 1 ? (float*)(ws + q.partial) : nullptr;

@@ -258,8 +258,9 @@ hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t) {
   need(a.phiT, (u64)a.M * a.ld_phi * 4, "grad phiT");
   need(a.targets, (u64)a.B * a.n * 4, "grad targets");
   need(a.Ge, (u64)a.B * a.n * a.r * 4, "grad Ge");
-  need(a.dLT, (u64)a.Mx * a.ldb * esz(dtype), "grad dLT");
-  need(a.dL, (u64)a.B * a.ldM * esz(dtype), "grad dL");
+  need(a.dLT, (u64)(a.rows_only ? a.ldM : a.Mx) * a.ldb * esz(dtype), "grad dLT");
+  if (!a.rows_only) need(a.dL, (u64)a.B * a.ldM * esz(dtype), "grad dL");
+  else if (a.ldM > a.tail_row) need(a.tail, (u64)(a.ldM - a.tail_row) * a.d * esz(dtype), "grad rows of W beyond its stages");
   if (a.planes) {
     need(a.dLT, (u64)a.M * a.ldb * 6, "grad dLT, terms");
     need(a.dL, (u64)a.B * a.ldM * 6, "grad dL, terms");
@@ -269,8 +270,18 @@ hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t) {
   return ok();
 }
 hipError_t launch_gemm_tn(const GemmArgs& a, int dtype, hipStream_t) {
-  need(a.A, strided(a.M, a.lda, a.K, esz(dtype)), "gemm A");
-  need(a.Bm, strided(a.N, a.ldb, a.K, esz(dtype)), "gemm B");
+  if (a.Ak.base) {                       // both along their rows
+    need(a.Ak.base, (u64)a.K * ((a.M + 31) / 32) * 64, "gemm A, along its rows");
+    need(a.Bk.base, a.Bk.bytes, "gemm B, along its rows");
+    if (a.Bk.tail_bytes) need(a.Bk.tail, a.Bk.tail_bytes, "gemm B, the rows behind");
+    if ((u64)a.Bk.bytes + a.Bk.tail_bytes != (u64)a.K * a.N * 2 || a.Ak.bytes < (u64)a.K * ((a.M + 31) / 32) * 64) {
+      std::fprintf(stderr, "gemm: operands along their rows with other extents\n");
+      std::abort();
+    }
+  } else {
+    need(a.A, strided(a.M, a.lda, a.K, esz(dtype)), "gemm A");
+    need(a.Bm, strided(a.N, a.ldb, a.K, esz(dtype)), "gemm B");
+  }
   opt(a.Bs, (u64)a.N * a.K * esz(dtype), "gemm B, stage-major");
   if (a.As) {
     if (a.As_rows < a.M) { std::fprintf(stderr, "gemm: stage-major A with too few rows\n"); std::abort(); }

@@ -41,9 +41,19 @@ def test_head_asks_for_the_scratch_of_its_own_dtype(family, B, d, n, r, v, dtype
 
 @pytest.mark.parametrize("B,d,n,r,v", [(300, 512, 8, 32, 40), (2048, 3072, 8, 32, 268)])
 def test_sampling_has_no_planes(B, d, n, r, v):
-    """fp32 draws never go through the planes of bf16 terms (6 bytes per element of W): the static scratch holds none, and
+    """fp32 draws never go through the planes of the terms (6 bytes per element of W): the static scratch holds none, and
     sampling from it gives the bits of sampling from a workspace."""
     hd = c_head(B, d, n, r, v, binding.F32)
     planes = 6 * n * r * v * d
     size = lambda op: binding.lib().mtpc_workspace_bytes(binding.CP, op, C.byref(hd), None, 1, 0)
     assert size(binding.OP_SAMPLE) < planes < size(binding.OP_LOGLIK)
+
+
+def test_training_scratch_holds_one_layout_of_the_gradient():
+    """A large bf16 step reads W and the logit gradient along their rows: beside the probabilities and that one layout its scratch
+    has no room for the other layout or a transpose of W, each of the size of dL [B][n r v]."""
+    B, d, n, r, v = 4096, 3072, 16, 64, 320
+    M, layers = n * r * v, binding.mtpc_sumlayers(0x6000, r * r, 0)
+    hd = c_head(B, d, n, r, v, binding.BF16)
+    size = binding.lib().mtpc_workspace_bytes(binding.BTREE, binding.OP_BACKWARD, C.byref(hd), C.byref(layers), 1, 0)
+    assert M * B * 6 < size < M * B * 6 + min(M * B, M * d) * 2
