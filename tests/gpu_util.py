@@ -89,7 +89,7 @@ def synthetic_verifier(inp, logphi, logw, loglayers, drafts, seed):
 def scratch_columns(head, op=0, dtype=0):
     """Bytes by which the scratch of an operation (default: the log-likelihood in fp32) grows with each column of h: 0 where
     the pass over W runs on tiles of fewer than 256 positions, 4 B for the stage-major copy of h that the 256-position tiles
-    read, 6 (B + n r v) for the planes of bf16 terms."""
+    read, 6 (B + n r v) for the planes of the fp32 terms."""
     import ctypes as C
 
     from paper_2511_11346_amd import binding
@@ -102,10 +102,19 @@ def scratch_columns(head, op=0, dtype=0):
 
 
 def takes_terms(head):
-    """Whether the fp32 pass over W is multiplied as bf16 terms (256-position tiles)."""
+    """Whether the fp32 pass over W is multiplied as fp16 terms (tiles of 192 or 256 positions)."""
     assert scratch_columns(head) in (0, 4 * head.B, 6 * (head.B + head.n * head.r * head.v))
     return scratch_columns(head) == 6 * (head.B + head.n * head.r * head.v)
 
 
 def takes_256_positions(head):
     return scratch_columns(head) > 0
+
+
+def takes_row_operands(head):
+    """Whether the bf16 training step reads W and the logit gradient along their rows: its scratch then holds neither the other
+    layout of the gradient nor a transpose of W, as the step that recomputes its logits does beside no probabilities."""
+    from paper_2511_11346_amd import binding
+    up = lambda x: (x + 255) // 256 * 256
+    phi = up(head.n * head.r * head.v * ((head.B + 31) // 32 * 32) * 4)
+    return head.workspace_bytes(binding.OP_BACKWARD, mode=0) - phi != head.workspace_bytes(binding.OP_BACKWARD, mode=1)

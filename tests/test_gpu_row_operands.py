@@ -2,7 +2,8 @@
 logit gradient as they lie in memory, transposed on the way out of LDS.
 
 Sizes: rows of W that end inside a stage of 32 (with and without the rows of the sum units behind them), columns that end
-inside a block of 64 or a tile of 256, positions that end inside a chunk of 32 or a tile, sums long enough to be split.
+inside a block of 64 or a tile of 256, positions that end inside a chunk of 32 or a tile, sums long enough to be split.  In bf16 most
+small steps keep their transposes: the second test has the sizes that do not, and asks.
 
 Tolerance: that of the other gradient tests (check_grad).  Against the plan that recomputes its logits and reads transposed
 copies, dh sums the same bf16 products in the same order of stages, but the probabilities were formed from a
@@ -14,7 +15,7 @@ import torch
 
 import mtpc_inputs as mi
 from oracle import backward as bw
-from gpu_util import make_head
+from gpu_util import make_head, takes_row_operands
 from test_gpu_backward import check_grad
 
 pytestmark = pytest.mark.gpu
@@ -36,3 +37,13 @@ def test_dh_and_the_rest(family, B, d, n, r, v, dtype):
             check_grad(k, other[k], ref[k], dtype)
     again = make_head(inp).loss_backward(tg, cf)
     assert all(torch.equal(again[k], out[k]) for k in out if out[k] is not None)
+
+
+# one tile, 8 stages and a ninth of sum units; positions and columns beyond a tile; 6 tiles; 108 tiles whose sums are split in
+# four, the last part 51 stages of W's own rows and two of the rows behind; the same where W ends with a stage; without
+# sum units; no whole stage at all, and fewer gradients than the padding of their rows
+@pytest.mark.parametrize("family,B,d,n,r,v", [("cp", 70, 96, 3, 5, 17), ("cp", 257, 288, 2, 3, 61), ("hmm", 300, 544, 3, 5, 27), ("cp", 600, 2080, 8, 33, 31),
+                                              ("btree", 289, 3104, 4, 16, 129), ("ff", 97, 3616, 29, 1, 317), ("cp", 33, 32, 1, 2, 2)])
+def test_bf16_steps_along_rows(family, B, d, n, r, v):
+    assert takes_row_operands(make_head(mi.make_inputs(family, B=B, d=d, n=n, r=r, v=v, dtype="bf16", seed=B + d, h_scale=1.0)))
+    test_dh_and_the_rest(family, B, d, n, r, v, "bf16")
