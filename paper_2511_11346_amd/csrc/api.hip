@@ -77,7 +77,9 @@ bool table_in_workspace(const mtpc_head* hd, int S) {      // for a sampling cal
 // fp32 operands of the 256-position tiles as planes of two fp16 terms (launch_unembed), where a pass over all
 // of W is then faster: per round of tiles over the CUs SPLIT_TILE_US against F32_TILE_US (a 320 x 256 tile, 1024
 // columns; B = 2048, n r = 256, d = 3072: 1.83 against 7.29 ms, 3.19 ms through three bf16 terms and six products), against
-// that stand the split of W (4 bytes read and written per element: 0.31 ms there, 5.4 TB/s) and four short launches.
+// that stand the split of W (4 bytes read and written per element: 0.31 ms there, 5.4 TB/s) and the short launches.  Both sides as rounds
+// of 256 positions, which is what the instruction takes; terms may take 192 (walk_positions), so next to the line the instruction
+// keeps a few sizes that they would win.
 constexpr double SPLIT_TILE_US = 90, F32_TILE_US = 304;
 bool split_pays(const mtpc_head* hd) {
   if (hd->dtype != MTPC_F32 || unembed_positions(hd->B, hd->n, hd->r, hd->dtype) != 256) return false;

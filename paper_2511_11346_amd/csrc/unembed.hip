@@ -1131,7 +1131,9 @@ static hipError_t launch_train(const UnembedArgs& a, hipStream_t st) {
 // beyond a multiple of 256, or a last round that is nearly empty.  CP, d = 2048, v = 320, 256 / 192 positions: n r = 512,
 // B = 300 281 / 248 us, B = 570 402 / 349; n r = 128, B = 1100 190 / 167; 5 rounds against 6 (n r = 256, B = 1100) 330 / 324 and, at
 // v = 100 and d = 4096, 10 against 12 575 / 599: not taken.  n r = 96, B = 570, d = 512, two rounds of any width: 53 / 46 /
-// 41 us with 128.  Of 713 sizes (B 140 .. 2000) 385 change: 0.76 to 1.01 of the time, 0.89 in the mean.
+// 41 us with 128.  Of 713 sizes (B 140 .. 2000) 385 change: 0.76 to 1.01 of the time, 0.89 in the mean.  Passes that also store
+// gain less and lose nowhere: of 60 such sizes (B 143 .. 1500, v 60 .. 320) marginals over all tokens, which write the table, take
+// 0.86 to 1.00 of the time with 256 (0.92 in the mean), training steps, which write the probabilities, 0.96 to 1.00; scores 0.77 to 1.01.
 // fp32 terms (`terms`; their ring has four buffers, so 128 positions gain nothing there): 0.87 as well up to 272 rows (n r = 256,
 // B = 570, d = 2048, v = 268 697 / 583 us), 0.68 to 0.78 of the 320-row tile (854 / 657; 5 rounds against 6, B = 1100, 1202 / 1022).
 static hipError_t walk_positions(const UnembedArgs& a, bool terms, int& positions) {

@@ -325,7 +325,7 @@ int main() {
   run_case({MTPC_HMM, MTPC_BF16, 8192, 4096, 8, 32, 320, 1, CTX_PER_LAYER, 0}, true);
   run_case({MTPC_BTREE, MTPC_BF16, 4096, 3072, 16, 64, 320, 1, PER_LAYER, 0}, true);
   run_case({MTPC_BTREE, MTPC_F32, 2048, 3072, 16, 32, 268, 1, CTX_PER_LAYER, 0}, true);
-  // fp32 whose pass over W is multiplied as bf16 terms: planes larger and smaller than the table of the univariate pass,
+  // fp32 whose pass over W is multiplied as terms: planes larger and smaller than the table of the univariate pass,
   // rows of h apart, one unit per layer
   run_case({MTPC_CP, MTPC_F32, 300, 1056, 8, 32, 268, 2, PER_LAYER, 0}, true);
   run_case({MTPC_HMM, MTPC_F32, 4000, 512, 8, 32, 320, 2, PER_LAYER, 544}, true);

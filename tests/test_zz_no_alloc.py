@@ -63,7 +63,7 @@ def test_static_scratch_entry_point_matches_the_sampling_entry_points():
                          [(300, 512, 8, 32, 40, 1, True, True), (300, 512, 8, 32, 8, 1, True, False), (300, 512, 8, 32, 33, 7, True, False),
                           (600, 544, 64, 1, 12, 2, True, False)])
 def test_static_scratch_entry_point_fp32_of_many_tiles(B, d, n, r, v, S, want_prefix, want_table):
-    """fp32 batches of the 256-position tiles, where scoring goes through planes of bf16 terms (which the static
+    """fp32 batches of the 256-position tiles, where scoring goes through planes of fp32 terms (which the static
     scratch has no room for) and sampling must not: with the caller's table, with scores from one kept in the scratch's
     place or a second pass, through buckets, and with one unit per layer."""
     inp = mi.make_inputs("ff" if r == 1 else "cp", B=B, d=d, n=n, r=r, v=v, dtype="f32", seed=46 + v, h_scale=1.0)
