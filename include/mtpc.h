@@ -322,7 +322,7 @@ mtpc_status mtpc_btree_verify(const mtpc_head* head, const mtpc_sumlayers* A, co
  * fp16 terms: 22 bits of it or more, down to 2^-18 of the largest it is scaled beside (the logit gradient of
  * a token over all positions, that of a position over all tokens, a feature of h over the positions that
  * have a gradient, a row of W).  Where more than one in 16 of a feature of h, of a row or of a column of W is
- * below that, or a position's features are next to nothing beside those of the others, all operands go
+ * below that, or a position's features or gradients are next to nothing beside those of the others, all operands go
  * through three bf16 terms, which hold every value whole; results that are not finite are those of fp32 sums.
  * targets: ids in [0, v), or -1 (that variable is summed out and receives no
  * gradient).

@@ -714,7 +714,7 @@ BwdPlan make_bwd_plan(int family, const mtpc_head* hd, const mtpc_sumlayers* ly,
   // Operands along their rows: dLT with the sum-unit rows and zeros up to ldM behind the others (the sum-unit rows in a layout of
   // their own as well), no dL, and of W only a copy of the rows beyond its whole stages.
   q.dLT = take((size_t)(q.ctx || q.along_rows ? q.ldM : q.split ? q.M : q.Mx) * q.ldb * osz);
-  if (q.split) q.terms = take(16 + (size_t)(q.ldb + hd->d) * 8 + (size_t)q.M * 4);
+  if (q.split) q.terms = take(16 + (size_t)(q.ldb + hd->d) * 8 + (size_t)(q.M + q.ldb) * 4);
   q.dslT = q.split || q.along_rows ? take((size_t)(q.Mx - q.M) * q.ldb * esz) : q.dLT + (size_t)q.M * q.ldb * esz;
   if (!q.along_rows) q.dL = take(B * q.ldM * osz);
   q.kmain = q.M / 32 * 32;
@@ -827,6 +827,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   unsigned* const weights = q.split ? (unsigned*)top + q.ldb : nullptr;            // ... and the magnitudes of its row of h
   int* const cols = q.split ? top + 2 * q.ldb : nullptr;                           // per column of W: small values, zeros
   int* const rows = q.split ? cols + 2 * hd->d : nullptr;                          // per row of dLT: its largest element
+  float* const most = q.split ? (float*)(rows + q.M) : nullptr;                    // per position: its largest gradient (not cleared)
   const int nflags = q.split ? (int)(4 + 2 * (q.ldb + hd->d) + q.M) : 0;
   if (q.split_fwd) {
     HIP_TRY(launch_clear(flag, nflags, st));
@@ -889,7 +890,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
     g.dl_end = ctx ? q.Mlay : q.ldM;           // the layer-logit columns are written by the reverse pass
     g.dLT = ws + q.dLT; g.dL = q.along_rows ? nullptr : ws + q.dL;
     g.staged = q.staged;
-    g.planes = q.split; g.flag = flag; g.top = top; g.rows = rows; g.weights = weights; g.cols = cols; g.dslT = ws + q.dslT; g.Wexp = wexp;
+    g.planes = q.split; g.flag = flag; g.top = top; g.rows = rows; g.most = most; g.weights = weights; g.cols = cols; g.dslT = ws + q.dslT; g.Wexp = wexp;
     g.rows_only = q.along_rows;
     g.d = hd->d;
     if (q.along_rows) { g.W = hd->W; g.Wsum = hd->Wsum; g.tail_row = (int)q.kmain; g.tail = ws + q.WT; }

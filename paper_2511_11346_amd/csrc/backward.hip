@@ -197,19 +197,24 @@ __global__ __launch_bounds__(512) void k_transpose_split(const TransposeArgs a, 
 // make them: sqrt(B) times 2^-40 of an average position, as a random walk.  Both stay below 2^-23 where the position's
 // magnitudes add up to 2^-17 of d scales (which a value has of 2^14 to 2^15 units: d / 4), and of sqrt(B) average positions.
 // [W; Wsum] has a scale per row: a column may be small in most rows, which decides about that column of dh.
-__device__ __forceinline__ void check_planes(const GradPhiArgs& a, float (&s_sum)[4], float (&s_cnt)[4]) {
+// The gradient has a scale per token, which is at most the largest of all positions' gradients, so a position may be small in all of them,
+// and a feature that only such positions have makes a column of dW of nothing else.  Its M entries are off by 2^-42 of that largest
+// one, to be compared with the position's own gradients: below 2^-20 of them where those are sqrt(M) 2^-22 of the largest.
+__device__ __forceinline__ void check_planes(const GradPhiArgs& a, float (&s_sum)[4], float (&s_cnt)[4], float (&s_most)[4]) {
   const int tid = threadIdx.x;
-  float sum = 0.f, cnt = 0.f;
+  float sum = 0.f, cnt = 0.f, most = 0.f;
   for (int b = tid; b < a.B; b += 256)
-    if (a.top[b] > 0) { sum += (float)a.weights[b]; cnt += 1.f; }
-  sum = wsum(sum); cnt = wsum(cnt);
-  if ((tid & 63) == 0) { s_sum[tid >> 6] = sum; s_cnt[tid >> 6] = cnt; }
+    if (a.top[b] > 0) { sum += (float)a.weights[b]; cnt += 1.f; most = fmaxf(most, a.most[b]); }
+  sum = wsum(sum); cnt = wsum(cnt); most = wmax(most);
+  if ((tid & 63) == 0) { s_sum[tid >> 6] = sum; s_cnt[tid >> 6] = cnt; s_most[tid >> 6] = most; }
   __syncthreads();
   sum = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
   cnt = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+  most = fmaxf(fmaxf(s_most[0], s_most[1]), fmaxf(s_most[2], s_most[3]));
   const float least = fmaxf((float)a.d * 0.25f, sum / fmaxf(cnt, 1.f) * sqrtf((float)a.B) * 0x1p-17f);
   bool wide = false;
-  for (int b = tid; b < a.B; b += 256) wide |= a.top[b] > 0 && (float)a.weights[b] < least;
+  const float faint = most * sqrtf((float)a.M) * 0x1p-22f;
+  for (int b = tid; b < a.B; b += 256) wide |= a.top[b] > 0 && ((float)a.weights[b] < least || (a.most[b] > 0.f && a.most[b] < faint));
   for (int k = tid; k < a.d; k += 256) wide |= a.cols[k] > ((int)a.ldM - a.cols[a.d + k]) / 16;
   if (wide) raise_flag(a.flag, SPLIT_WIDE);
 }
@@ -270,17 +275,23 @@ __global__ __launch_bounds__(256) void k_grad_rows(const GradPhiArgs a, int rows
   }
 }
 
-// a.top: 1, the least, for a position that has a gradient, else 0.  A wave to a position.  (Before everything that reads the
+// a.top: 1, the least, for a position that has a gradient, else 0, and the largest of its gradients (a.most).  A wave to a position.  (Before everything that reads the
 // probabilities: the transpose of h asks for it, and between k_grad_exps and k_grad_from_phi, which finds what is left of the
 // probabilities in the last cache, that costs the latter a third where they fit.)
 __global__ __launch_bounds__(256) void k_live_positions(const GradPhiArgs a) {
   const int b = blockIdx.x * 4 + (threadIdx.x >> 6), t = threadIdx.x & 63, nr = a.n * a.r;
   if (b >= a.B) return;                              // (all 64)
   bool some = false;
-  for (int i = t; i < nr; i += 64) some |= a.Ge[(long long)b * nr + i] != 0.f && a.targets[(long long)b * a.n + i / a.r] != -1;
+  float most = 0.f;                                  // of the gradients of its evidence
+  for (int i = t; i < nr; i += 64) {
+    const float g = a.targets[(long long)b * a.n + i / a.r] != -1 ? fabsf(a.Ge[(long long)b * nr + i]) : 0.f;
+    some |= g != 0.f;
+    most = fmaxf(most, g);
+  }
   for (int j = t; j < (int)(a.Mx - a.M); j += 64) some |= ((const float*)a.dslT)[j * a.ldb + b] != 0.f;
   some = __any(some);
-  if (t == 0) a.top[b] = some;
+  most = wmax(most);
+  if (t == 0) { a.top[b] = some; a.most[b] = most; }
 }
 
 // What the scales of the two planes that k_grad_from_phi writes (see split2) follow from: the largest magnitude of a row of dLT over
@@ -398,9 +409,9 @@ __global__ __launch_bounds__(256, 4) void k_grad_exps(const GradPhiArgs a, int r
     return;
   }
   if (blockIdx.y > 0) return;
-  __shared__ float s_sum[4], s_cnt[4];
+  __shared__ float s_sum[4], s_cnt[4], s_most[4];
   if (blockIdx.x == gridDim.x - 1) {
-    check_planes(a, s_sum, s_cnt);
+    check_planes(a, s_sum, s_cnt, s_most);
     return;
   }
   const int b = ((int)blockIdx.x - groups) * 16 + (tid >> 4), t = tid & 15;

@@ -329,6 +329,7 @@ struct GradPhiArgs {
   int* flag;            // planes: SPLIT_*, raised for the elements
   int* top;             // planes: scratch [ldb], cleared (k_grad_exps)
   int* rows;            // planes: scratch [M], cleared
+  float* most;          // planes: scratch [B], the largest |Ge| of every position (launch_live_positions)
   const unsigned* weights;      // planes: of h's rows in the planes of h^T (launch_transpose) [ldb]
   const int* cols;      // planes: counts of the columns of [W; Wsum] (launch_split_rows)
   int* Wexp;            // planes: exponents of the rows of W and, behind them, of Wsum [Mx] (launch_transpose, along_rows)

@@ -223,12 +223,14 @@ static void grad_scales(const GradPhiArgs& a) {
   need(a.weights, (u64)a.ldb * 4, "grad weights of the positions");
   need(a.cols, (u64)a.d * 8, "grad counts of W");
   need(a.Wexp, (u64)a.Mx * 4, "grad exponents of W");
+  need(a.most, (u64)a.B * 4, "grad largest of the evidence");
 }
 hipError_t launch_live_positions(const GradPhiArgs& a, hipStream_t) {
   need(a.targets, (u64)a.B * a.n * 4, "live targets");
   need(a.Ge, (u64)a.B * a.n * a.r * 4, "live Ge");
   if (a.Mx > a.M) need(a.dslT, (u64)(a.Mx - a.M) * a.ldb * 4, "live sum-unit rows");
   need(a.top, (u64)a.B * 4, "live");
+  need(a.most, (u64)a.B * 4, "live largest gradients");
   return ok();
 }
 hipError_t launch_grad_exps(const GradPhiArgs& a, hipStream_t) {

@@ -65,6 +65,12 @@ def small_positions(inp, coef, power):
     coef[rest] *= 2.0 ** -power
 
 
+def faint_positions(inp, coef, power):
+    """A few positions whose weight is far below the others', and a feature that only they have."""
+    inp.h[:40, 7] = inp.h[44:, 7] = 0.0
+    coef[40:44] *= 2.0 ** -power
+
+
 def no_features(inp, coef):
     """A position without features and a feature without values."""
     inp.h[100] = 0.0
@@ -90,6 +96,7 @@ CASES = {
     "zero sum units, small W": (zero_sum_units, 2.0 ** -8), "impossible token 2^12": (impossible_token, 12),
     "impossible token 2^24": (impossible_token, 24), "column 2^-14": (weak_column, 14), "column 2^-20": (weak_column, 20), "column 2^-28": (weak_column, 28),
     "small positions 2^-12": (small_positions, 12), "small positions 2^-20": (small_positions, 20), "small positions 2^-26": (small_positions, 26),
+    "faint positions 2^-12": (faint_positions, 12), "faint positions 2^-20": (faint_positions, 20), "faint positions 2^-32": (faint_positions, 32),
     "no features": (no_features,), "no weights": (no_weights, False), "no weights at all": (no_weights, True), "tiny weights": (tiny_weights, 60),
 }
 
