@@ -237,7 +237,7 @@ struct TileFeed {
   int wave, hrows;
   // KR: the rows of srdH that are left, in stages, and where it goes on from there
   i32x4_t srdT;
-  int hleft;
+  int hleft;                                         // (whole values, operands along K: stages that are left before K starts over)
   unsigned hterm;                                    // three terms: the distance of two of them (hleft: how many are issued)
 
   __device__ __forceinline__ void issue_one(int q, int buf) {   // q-th wave-load of this wave for one stage
@@ -263,9 +263,15 @@ struct TileFeed {
     }
   }
   __device__ __forceinline__ void advance() {
-    if constexpr (KR == 0) kofs += SB;
+    if constexpr (KR == 0 && !WPACK) kofs += SB;
     if constexpr (WPACK || KR == 3) kofsW += wstep;
     kofsH += hstep;
+    if constexpr (KR == 0 && SPLIT == 0) {
+      const bool over = --hleft == 0;
+      if constexpr (WPACK) kofsW = over ? 0u : kofsW;
+      else kofs = over ? 0u : kofs;
+      kofsH = over ? 0u : kofsH;
+    }
     // (kofs: from the first term of 32 rows to that of the next, constant here)
     if constexpr (KR != 0 && SPLIT == 2) hstep = kofs - hstep;
     if constexpr (KR != 0 && SPLIT == 3) {
@@ -343,10 +349,11 @@ struct TileFeed {
   }
 
   // Arguments as for tile_gemm.  The ring must be free (no wave still reads it).
+  // first: the stage that the product starts with (whole values only); it goes through all of K from there, over its end to its beginning.
   __device__ __forceinline__ void open(const void* Wp, long long ld_w, const void* hp, long long ld_h,
                                        int B, int d, int v, int slab, int b0, char* smem,
                                        const int* rows = nullptr, int nrows = 0, int rdiv = 1,
-                                       const void* hs = nullptr, int wrows_total = 0, int wrow0 = 0) {
+                                       const void* hs = nullptr, int wrows_total = 0, int wrow0 = 0, int first = 0) {
     const int tid = threadIdx.x, lane = tid & 63;
     wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Two resources: this slab of W (v rows of d, row stride ld_w) and this tile of h (rows b0..).
@@ -379,13 +386,15 @@ struct TileFeed {
       }
     }
     lds0 = (unsigned)(size_t)smem;
-    kofs = 0;
-    kofsW = 0;
-    kofsH = 0;
     // (steps along K of the stage-major operands; uniform over the workgroup, which the register allocator
     // has to be told where they come out of a select)
     hstep = (unsigned)__builtin_amdgcn_readfirstlane((int)(hpk ? (unsigned)B * SB : (unsigned)SB));
     wstep = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(wall ? wrows_total : v) * SB));
+    first = SPLIT == 0 ? __builtin_amdgcn_readfirstlane(first) : 0;
+    kofs = (unsigned)first * SB;
+    kofsW = (unsigned)first * wstep;
+    kofsH = (unsigned)first * hstep;
+    hleft = d * ESZ / SB - first;
     if constexpr (SPLIT == 3) {
       issue(SPLIT3_SLOT_A0);
       issue(SPLIT3_SLOT_B);
@@ -833,9 +842,9 @@ __device__ __forceinline__ void tile_gemm(const void* Wp, long long ld_w, const 
                                           int B, int d, int v, int slab, int b0, char* smem,
                                           typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB - VH / 2],
                                           const int* rows = nullptr, int nrows = 0, int rdiv = 1,
-                                          const void* hs = nullptr, int wrows_total = 0, int wrow0 = 0) {
+                                          const void* hs = nullptr, int wrows_total = 0, int wrow0 = 0, int first = 0) {
   TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, false, VH> feed;
-  feed.open(Wp, ld_w, hp, ld_h, B, d, v, slab, b0, smem, rows, nrows, rdiv, hs, wrows_total, wrow0);
+  feed.open(Wp, ld_w, hp, ld_h, B, d, v, slab, b0, smem, rows, nrows, rdiv, hs, wrows_total, wrow0, first);
   tile_gemm_run(feed, d, smem, acc);
 }
 

@@ -288,7 +288,15 @@ void k_unembed(const UnembedArgs a) {
   tile_of_block(blockIdx.x, nbt, nslab, slab, bt);
   Feed feed;
   const int wrows = SPLIT ? a.Wq_rows : 0;
-  feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab, bt * TL::TP, smem, nullptr, 0, 1, hstaged, wrows, slab * a.v);
+  // Where there is one tile of positions every workgroup streams a slab of its own, and rows of W lie a power of two or nearly that
+  // apart: CUs that all walk K from 0 ask the same few memory channels at a time.  Each slab therefore starts one stage
+  // further than the one before it (W's own rows, n r = 512, v = 320, draft and score, B = 1: 253 -> 233 us, B = 61 320 -> 309;
+  // prefix marginals, B = 200: d = 4096 356 -> 324, 2048 214 -> 193, 3072 286 -> 261; stage-major W, B = 1: 238 -> 236).  Tiles that share
+  // slabs and rows of h in an L2 walk K together, from its beginning (starts that differ: B = 300 .. 1000 the same, B = 4096 and 8192 0.4 % slower).
+  const int stages = SPLIT ? 1 : a.d * (BF16 ? 2 : 4) / SB;
+  auto first_stage = [&](int sl) { return nbt == 1 ? (int)((unsigned)sl % (unsigned)stages) : 0; };
+  feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab, bt * TL::TP, smem, nullptr, 0, 1, hstaged, wrows, slab * a.v,
+            first_stage(slab));
   for (int w = blockIdx.x;;) {
   const int b0 = bt * TL::TP;
   const int wi = slab / a.r, wj = slab - wi * a.r;
@@ -332,7 +340,8 @@ void k_unembed(const UnembedArgs a) {
   if constexpr (WALK)
     if (wnext < ntiles) {
       tile_of_block(wnext, nbt, nslab, slab_next, bt_next);
-      feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab_next, bt_next * TL::TP, smem, nullptr, 0, 1, hstaged, wrows, slab_next * a.v);
+      feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab_next, bt_next * TL::TP, smem, nullptr, 0, 1, hstaged, wrows, slab_next * a.v,
+                first_stage(slab_next));
     }
 
   if constexpr (!SAMPLE) if (a.targets != nullptr) {
@@ -549,8 +558,11 @@ void k_draw_gather(const DrawGatherArgs a) {
   constexpr bool M16 = use_m16<WV, WB, SB, NS, BF16>();
   constexpr int NPB = PB * Frag<M16>::SUB + PH, NVB = VB * Frag<M16>::SUB - VH / 2;
   typename Frag<M16>::blk_t acc[NPB][NVB];
+  // (each bucket's slab from a stage of its own on, as in k_unembed: a sampling call of the tree n r = 1024, d = 3072, B = 4096, 446 -> 439 us
+  // from the stage-major W, 492 -> 486 from its rows; CP n r = 512, d = 4096, B = 1000 281 -> 268)
   tile_gemm<WV, WB, VB, PB, SB, NS, BF16, true, M16, WPACK, false, PH, VH>(WPACK ? a.Wp : a.W, a.d, a.h, a.ld_h, a.B, a.d, a.v, g, 0, smem,
-                                                                       acc, rows, nrows, a.S);
+                                                                       acc, rows, nrows, a.S, nullptr, 0, 0,
+                                                                       (int)((unsigned)g % (unsigned)(a.d * (BF16 ? 2 : 4) / SB)));
   float mx[NPB], lse[NPB];
   tile_lse<WV, WB, VB, PB, SB, NS, M16, PH, VH>(acc, a.v, (float2*)(smem + TL::RED_OFF), mx, lse);
 
