@@ -313,11 +313,17 @@ hipError_t stage_major_h(const mtpc_head* hd, bool have, size_t off, UnembedArgs
 // `draws` (sampling calls of a few positions): the launch that computes the sum units goes on to
 // draw the latents, after the layers those draws read; returns with *draws_done set then.
 // `own_sumunit`: the consumer computes its sum units itself (verification of a few positions).
+// `later`: sum units and shared layers are left to the launch of the pass over W, which computes them beside (launch_unembed_few).
 mtpc_status launch_params(int family, const mtpc_head* hd, const mtpc_sumlayers* ly, const Plan& p,
                           bool nat, bool circ, hipStream_t st, const LatentArgs* draws = nullptr,
-                          bool* draws_done = nullptr, bool own_sumunit = false) {
+                          bool* draws_done = nullptr, bool own_sumunit = false, ParamArgs* later = nullptr) {
   char* ws = (char*)hd->workspace;
   nat = nat && p.has_nat;
+  if (later) {
+    later->h = hd->h; later->ld_h = hd->ld_h; later->B = hd->B; later->d = hd->d; later->r = hd->r;
+    if (family != MTPC_FF) { later->Wsum = hd->Wsum; later->logw = (float*)(ws + p.logw); }
+    own_sumunit = true;
+  }
   const bool fuse = draws != nullptr && family != MTPC_FF && hd->B <= SUMUNIT_SMALL_B;
   if (draws_done) *draws_done = fuse;
   if (family != MTPC_FF && !fuse && !own_sumunit)
@@ -336,8 +342,13 @@ mtpc_status launch_params(int family, const mtpc_head* hd, const mtpc_sumlayers*
   } else if (L > 0) {
     float* out_nat = nat ? (float*)(ws + p.lay_nat) : nullptr;
     float* out_tr = (circ && family == MTPC_BTREE) ? (float*)(ws + p.lay_circ) : nullptr;
-    HIP_TRY(launch_normalise_layers(ly->logits, ly->layer_stride, ly->batch_stride, p.nb, p.Lst, hd->r,
-                                    out_nat, out_tr, st));
+    if (later && (out_nat || out_tr)) {
+      later->logits = ly->logits; later->layer_stride = ly->layer_stride; later->batch_stride = ly->batch_stride;
+      later->nb = p.nb; later->L = p.Lst; later->out_nat = out_nat; later->out_tr = out_tr;
+    } else {
+      HIP_TRY(launch_normalise_layers(ly->logits, ly->layer_stride, ly->batch_stride, p.nb, p.Lst, hd->r,
+                                      out_nat, out_tr, st));
+    }
   }
   if (fuse)
     HIP_TRY(launch_sumunit_latents(hd->h, hd->ld_h, hd->Wsum, hd->d, hd->dtype, (float*)(ws + p.logw), *draws, st));
@@ -367,7 +378,9 @@ mtpc_status run_evidence_op(int family, const mtpc_head* hd, const mtpc_sumlayer
   if (s != MTPC_OK) return s;
   hipStream_t st = (hipStream_t)hd->stream;
   char* ws = (char*)hd->workspace;
-  s = launch_params(family, hd, ly, p, family != MTPC_FF && family != MTPC_CP, true, st);
+  const int few = unembed_few(hd->B, hd->n, hd->r, hd->dtype);
+  ParamArgs beside{};
+  s = launch_params(family, hd, ly, p, family != MTPC_FF && family != MTPC_CP, true, st, nullptr, nullptr, false, few && unembed_few_params(hd->B, hd->n, hd->r, few) ? &beside : nullptr);
   if (s != MTPC_OK) return s;
   UnembedArgs u = unembed_args(hd);
   u.targets = targets; u.T = 1; u.e = (float*)(ws + p.e);
@@ -375,7 +388,7 @@ mtpc_status run_evidence_op(int family, const mtpc_head* hd, const mtpc_sumlayer
   HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, u, st));
   {
     ProfScope prof(st);
-    HIP_TRY(launch_unembed(u, hd->dtype, st));
+    HIP_TRY(few ? launch_unembed_few(u, beside, hd->dtype, st) : launch_unembed(u, hd->dtype, st));
   }
   HIP_TRY(profiled_circuit(circuit_args(family, hd, p, hd->B, 1, out, prefix), st));
   return MTPC_OK;
@@ -388,12 +401,20 @@ mtpc_status run_univariate(int family, const mtpc_head* hd, const mtpc_sumlayers
   if (s != MTPC_OK) return s;
   hipStream_t st = (hipStream_t)hd->stream;
   char* ws = (char*)hd->workspace;
-  s = launch_params(family, hd, ly, p, true, false, st);
+  const int few = (family == MTPC_FF || p.has_table) ? unembed_few(hd->B, hd->n, hd->r, hd->dtype) : 0;
+  ParamArgs beside{};
+  s = launch_params(family, hd, ly, p, true, false, st, nullptr, nullptr, false, few && unembed_few_params(hd->B, hd->n, hd->r, few) ? &beside : nullptr);
   if (s != MTPC_OK) return s;
   UnivariateArgs u{};
   u.h = hd->h; u.ld_h = hd->ld_h; u.W = hd->W;
   u.B = hd->B; u.d = hd->d; u.v = hd->v; u.n = hd->n; u.r = hd->r;
   u.out = out;
+  UnembedArgs t = unembed_args(hd);
+  t.logphi = family == MTPC_FF ? out : (float*)(ws + p.table);
+  if (few) {
+    ProfScope prof(st);
+    HIP_TRY(launch_unembed_few(t, beside, hd->dtype, st));
+  }
   if (family != MTPC_FF) {
     LatentMarginalArgs m{};
     m.family = family; m.B = hd->B; m.n = hd->n; m.r = hd->r;
@@ -408,11 +429,9 @@ mtpc_status run_univariate(int family, const mtpc_head* hd, const mtpc_sumlayers
   // into `out`, which is that table), then the mixture over the r units per token.  A table
   // above 8 GiB is not kept: the slabs of a token are then mixed in registers, on smaller tiles.
   if (family == MTPC_FF || p.has_table) {
-    UnembedArgs t = unembed_args(hd);
-    t.logphi = family == MTPC_FF ? out : (float*)(ws + p.table);
-    split_scratch(hd, p, t);
-    HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, t, st));
-    {
+    if (!few) {
+      split_scratch(hd, p, t);
+      HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, t, st));
       ProfScope prof(st);
       HIP_TRY(launch_unembed(t, hd->dtype, st));
     }
@@ -569,7 +588,9 @@ mtpc_status run_window_scores(int family, const mtpc_head* hd, const mtpc_sumlay
   if (s != MTPC_OK) return s;
   hipStream_t st = (hipStream_t)hd->stream;
   char* ws = (char*)hd->workspace;
-  s = launch_params(family, hd, ly, p, family != MTPC_FF && family != MTPC_CP, true, st);
+  const int few = unembed_few(hd->B, hd->n, hd->r, hd->dtype);
+  ParamArgs beside{};
+  s = launch_params(family, hd, ly, p, family != MTPC_FF && family != MTPC_CP, true, st, nullptr, nullptr, false, few && unembed_few_params(hd->B, hd->n, hd->r, few) ? &beside : nullptr);
   if (s != MTPC_OK) return s;
   UnembedArgs u = unembed_args(hd);
   u.targets = x; u.T = T; u.targets2 = x2; u.T2 = T2; u.e = (float*)(ws + p.e);
@@ -577,7 +598,7 @@ mtpc_status run_window_scores(int family, const mtpc_head* hd, const mtpc_sumlay
   HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, u, st));
   {
     ProfScope prof(st);
-    HIP_TRY(launch_unembed(u, hd->dtype, st));
+    HIP_TRY(few ? launch_unembed_few(u, beside, hd->dtype, st) : launch_unembed(u, hd->dtype, st));
   }
   HIP_TRY(profiled_circuit(circuit_args(family, hd, p, hd->B * (int)TT, (int)TT, out, mode == MTPC_SCORE_PREFIX), st));
   return MTPC_OK;

@@ -53,6 +53,21 @@ struct UnembedArgs {
   int Wq_rows;          // > 0: the planes of W are ONE matrix of so many rows, [2 d/32][Wq_rows][64 bytes], slab after slab
 };
 
+// What a call computes from h and the layer logits alone, before its circuit: log omega (Wsum nullptr: not wanted) and the softmax
+// of shared layers (L = 0: none), as launch_sumunit and launch_normalise_layers.
+struct ParamArgs {
+  const void* h;
+  long long ld_h;
+  const void* Wsum;
+  int B, d, r;
+  float* logw;          // [B][r]
+  const float* logits;
+  long long layer_stride, batch_stride;
+  int nb, L;
+  float* out_nat;
+  float* out_tr;
+};
+
 // Univariate marginals: M[b][i][a] = log sum_j m[b][i][j] phi[b][i][j][a].
 struct UnivariateArgs {
   const void* h;
@@ -86,6 +101,23 @@ struct CtxLayerArgs {
 hipError_t launch_ctx_layers(const CtxLayerArgs& a, int dtype, hipStream_t st);
 
 hipError_t launch_unembed(const UnembedArgs& a, int dtype, hipStream_t st);
+// The same evidence (and table) of calls so small that all tiles of 16 or 32 positions run at once, and the sum units and layers of the
+// call beside them in one launch (where unembed_few_params says so; else p is empty).  No draws, no probabilities.
+hipError_t launch_unembed_few(const UnembedArgs& a, const ParamArgs& p, int dtype, hipStream_t st);
+// Whether the tiles of the sum units run at once with those of W.  If not they would come after them, and take as long.
+inline bool unembed_few_params(int B, int n, int r, int tile) {
+  return ((long long)n * r + 1) * ((B + tile - 1LL) / tile) <= 256;
+}
+// Positions per tile of such a call, 0: none.  fp32, which is bound by its products, takes 16 wherever that fills no more than the 256
+// CUs (B = 64, n = 4, r = 8, d = 256, v = 256 21.3 -> 13.6 us, B = 5, n = 4, r = 20, d = 3072, v = 128 119 -> 49); bf16, as wide a tile as
+// that of k_unembed, gains the launches that it saves (B = 64, n = 4, r = 16, d = 256 18.7 -> 11.7, d = 4096 74.7 -> 68.0) and
+// the head without sum units has none (B = 500, d = 2048: 24.6 / 26.5).
+inline int unembed_few(int B, int n, int r, int dtype) {
+  const long long slabs = (long long)n * r;
+  if (dtype == MTPC_F32) return slabs * ((B + 15LL) / 16) <= 256 ? 16 : slabs * ((B + 31LL) / 32) <= 256 ? 32 : 0;
+  const int tile = B <= 16 ? 16 : 32;
+  return r > 1 && unembed_few_params(B, n, r, tile) ? tile : 0;
+}
 // Positions per tile of the fused kernel.  A decode-sized batch is one tile (W is then read once).  Larger ones
 // take 256, unless fewer are enough or the narrower tiles all run at once on the 256 CUs: a K stage of those is
 // shorter, and that many CUs would stand idle.  Measured with 256 positions and with the width chosen here: FF, n = 8,

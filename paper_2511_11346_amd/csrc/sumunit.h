@@ -89,4 +89,32 @@ __device__ __forceinline__ void sumunit_position(const void* h, long long ld_h, 
   __syncthreads();
 }
 
+// softmax over the last axis of one row (of one r x r layer) of the sum layers, by a wave: row k of layer l of position block b,
+// counted through all nb * L * r of them; the natural copy [k][j], the transposed one [j][k], or both
+__device__ __forceinline__ void normalise_layer_row(const float* logits, long long ls, long long bs, long long row, int L, int r,
+                                                    float* out_nat, float* out_tr) {
+  const int lane = threadIdx.x & 63;
+  const int k = (int)(row % r);
+  const int l = (int)((row / r) % L);
+  const long long b = row / ((long long)r * L);
+  const float* src = logits + b * bs + (long long)l * ls + (long long)k * r;
+  const float x0 = lane < r ? src[lane] : neg_inf();
+  const float x1 = lane + 64 < r ? src[lane + 64] : neg_inf();
+  const float m = group_max(fmaxf(x0, x1), 64);
+  const float ms = (m == neg_inf()) ? 0.f : m;
+  const float e0 = x0 > neg_inf() ? expf(x0 - ms) : 0.f;
+  const float e1 = x1 > neg_inf() ? expf(x1 - ms) : 0.f;
+  const float tot = group_sum(e0 + e1, 64);
+  const float inv = tot > 0.f ? 1.f / tot : 0.f;
+  const long long base = (b * L + l) * (long long)r * r;
+  if (out_nat) {
+    if (lane < r) out_nat[base + (long long)k * r + lane] = e0 * inv;
+    if (lane + 64 < r) out_nat[base + (long long)k * r + lane + 64] = e1 * inv;
+  }
+  if (out_tr) {
+    if (lane < r) out_tr[base + (long long)lane * r + k] = e0 * inv;
+    if (lane + 64 < r) out_tr[base + (long long)(lane + 64) * r + k] = e1 * inv;
+  }
+}
+
 }  // namespace mtpc

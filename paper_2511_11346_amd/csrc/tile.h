@@ -194,6 +194,14 @@ __device__ __forceinline__ int swz(int row) {
 // banks, so with f = swizzle of rows k, 4+k, 8+k, 12+k the chunks f(k), f(12+k), 1^f(4+k),
 // 1^f(8+k) must differ: f = (0, 3, 2, 1).
 __device__ __forceinline__ int swz16(int row) { return (0 - (row >> 2)) & 3; }
+// The same for 128-byte rows: two neighbours fill the 64 banks, so rows 2 apart share theirs, and of the eight even (or odd) rows of a
+// cycle's 16 lanes four read chunk c and the others c ^ 1: f(row) = row / 2 makes f(0, 2, 12, 14) and 1 ^ f(4, 6, 8, 10), and the other
+// cycle's f(4, 6, 8, 10) and 1 ^ f(0, 2, 12, 14), eight different chunks each.
+template <int CPR>
+__device__ __forceinline__ int swz16(int row) {
+  if constexpr (CPR == 4) return swz16(row);
+  else return (row >> 1) & 7;
+}
 
 // LDS image of an operand given along its rows (KRows): per 64 columns a block of 32 rows of 128 bytes, whose 32-byte pieces (16 columns) are XOR-swizzled so
 // that the eight pieces that half a wave reads at once - four neighbouring rows, and the four eight rows on - lie in
@@ -221,8 +229,9 @@ constexpr int SPLIT3_SLOT_A0 = 0, SPLIT3_SLOT_C = 2, SPLIT3_SLOT_B = 3;
 // has returned) before it turns to the epilogue of the one it has just multiplied.
 // SPLIT: the operands are fp32 matrices as planes of two fp16 (2) or three bf16 (3) terms (see tile_gemm_run_split).
 // KR: operands given along their rows (KRows, open_rows): 2 the one of the tile's columns, 3 both; tiles of 256 x 256.
+// ROT: K may start anywhere (open's `first`).
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER = false, bool M16 = false,
-          bool WPACK = false, bool STREAMW = false, int PH = 0, int SPLIT = 0, int VH = 0, int KR = 0>
+          bool WPACK = false, bool STREAMW = false, int PH = 0, int SPLIT = 0, int VH = 0, int KR = 0, bool ROT = false>
 struct TileFeed {
   using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
   static constexpr int ESZ = BF16 ? 2 : 4;
@@ -237,7 +246,7 @@ struct TileFeed {
   int wave, hrows;
   // KR: the rows of srdH that are left, in stages, and where it goes on from there
   i32x4_t srdT;
-  int hleft;                                         // (whole values, operands along K: stages that are left before K starts over)
+  int hleft;                                         // (ROT: stages that are left before K starts over)
   unsigned hterm;                                    // three terms: the distance of two of them (hleft: how many are issued)
 
   __device__ __forceinline__ void issue_one(int q, int buf) {   // q-th wave-load of this wave for one stage
@@ -266,7 +275,8 @@ struct TileFeed {
     if constexpr (KR == 0 && !WPACK) kofs += SB;
     if constexpr (WPACK || KR == 3) kofsW += wstep;
     kofsH += hstep;
-    if constexpr (KR == 0 && SPLIT == 0) {
+    if constexpr (ROT) {
+      static_assert(KR == 0 && SPLIT == 0, "whole values along K");
       const bool over = --hleft == 0;
       if constexpr (WPACK) kofsW = over ? 0u : kofsW;
       else kofs = over ? 0u : kofs;
@@ -349,7 +359,7 @@ struct TileFeed {
   }
 
   // Arguments as for tile_gemm.  The ring must be free (no wave still reads it).
-  // first: the stage that the product starts with (whole values only); it goes through all of K from there, over its end to its beginning.
+  // first (ROT): the stage that the product starts with; it goes through all of K from there, over its end to its beginning.
   __device__ __forceinline__ void open(const void* Wp, long long ld_w, const void* hp, long long ld_h,
                                        int B, int d, int v, int slab, int b0, char* smem,
                                        const int* rows = nullptr, int nrows = 0, int rdiv = 1,
@@ -377,7 +387,7 @@ struct TileFeed {
     for (int q = 0; q < TL::LPW; ++q) {
       const int wl = min(wave + q * TL::NW, TL::NWL - 1);
       const int row = wl * TL::RPL + lane / CPR;
-      const int ch = (lane % CPR) ^ (M16 ? swz16(row) : swz<CPR>(row));
+      const int ch = (lane % CPR) ^ (M16 ? swz16<CPR>(row) : swz<CPR>(row));
       if (row < TL::TV) voff[q] = (unsigned)((wall ? wrow0 : 0) + min(row, v - 1)) * (WPACK ? (unsigned)SB : (unsigned)(ld_w * ESZ)) + ch * 16;
       else {
         int hr = min(row - TL::TV, hrows - 1);
@@ -390,11 +400,11 @@ struct TileFeed {
     // has to be told where they come out of a select)
     hstep = (unsigned)__builtin_amdgcn_readfirstlane((int)(hpk ? (unsigned)B * SB : (unsigned)SB));
     wstep = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(wall ? wrows_total : v) * SB));
-    first = SPLIT == 0 ? __builtin_amdgcn_readfirstlane(first) : 0;
+    first = ROT ? __builtin_amdgcn_readfirstlane(first) : 0;
     kofs = (unsigned)first * SB;
     kofsW = (unsigned)first * wstep;
     kofsH = (unsigned)first * hstep;
-    hleft = d * ESZ / SB - first;
+    if constexpr (ROT) hleft = d * ESZ / SB - first;
     if constexpr (SPLIT == 3) {
       issue(SPLIT3_SLOT_A0);
       issue(SPLIT3_SLOT_B);
@@ -410,10 +420,19 @@ struct TileFeed {
   }
 };
 
+// The stage that a slab's product starts with where every workgroup streams a slab of its own: one further than the slab before
+// it.  Rows of W lie a power of two or nearly that apart, and CUs that all walk K from 0 ask the same few memory channels at a
+// time (W's own rows, n r = 512, v = 320, draft and score, B = 1: 253 -> 233 us, B = 61 320 -> 309; prefix marginals,
+// B = 200: d = 4096 356 -> 324, 2048 214 -> 193, 3072 286 -> 261; stage-major W, B = 1: 238 -> 236).  Rows of less than 4 KB spread
+// over the channels by themselves (n r = 256, B = 1: d = 1024 39.6 us either way, d = 2048 86 -> 63).
+__device__ __forceinline__ int first_stage(int slab, int row_bytes, int SB) {
+  return row_bytes < 4096 ? 0 : (int)((unsigned)slab % (unsigned)(row_bytes / SB));
+}
+
 // The product of a tile whose feed is open: on return every wave holds its VB x PB accumulator blocks and
 // all waves have passed a barrier (the ring is free).
-template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER, bool M16, bool WPACK, bool STREAMW, int PH, int VH, int KR>
-__device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, 0, VH, KR>& feed,
+template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER, bool M16, bool WPACK, bool STREAMW, int PH, int VH, int KR, bool ROT>
+__device__ __forceinline__ void tile_gemm_run(TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, 0, VH, KR, ROT>& feed,
                                               int d, char* smem,
                                               typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB - VH / 2]) {
   using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
@@ -837,13 +856,13 @@ __device__ __forceinline__ void tile_unscale(f32x4_t (&acc)[NPB][NVB], const int
 // STREAMW: every byte of W is read once by the whole launch (one tile of positions): loaded with the
 // non-temporal hint.
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER = false, bool M16 = false,
-          bool WPACK = false, bool STREAMW = false, int PH = 0, int VH = 0>
+          bool WPACK = false, bool STREAMW = false, int PH = 0, int VH = 0, bool ROT = false>
 __device__ __forceinline__ void tile_gemm(const void* Wp, long long ld_w, const void* hp, long long ld_h,
                                           int B, int d, int v, int slab, int b0, char* smem,
                                           typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB - VH / 2],
                                           const int* rows = nullptr, int nrows = 0, int rdiv = 1,
                                           const void* hs = nullptr, int wrows_total = 0, int wrow0 = 0, int first = 0) {
-  TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, false, VH> feed;
+  TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, 0, VH, 0, ROT> feed;
   feed.open(Wp, ld_w, hp, ld_h, B, d, v, slab, b0, smem, rows, nrows, rdiv, hs, wrows_total, wrow0, first);
   tile_gemm_run(feed, d, smem, acc);
 }

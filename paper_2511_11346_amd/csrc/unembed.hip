@@ -14,6 +14,7 @@
 // a ring of NS stages with unpadded, XOR-swizzled rows; fragments are read with
 // conflict-free 16-byte LDS loads one half-step ahead of the MFMAs using them.
 #include "tile.h"
+#include "sumunit.h"
 
 namespace mtpc {
 
@@ -277,7 +278,8 @@ void k_unembed(const UnembedArgs a) {
   // softmax statistics are taken, instead of after a workgroup launch with the matrix pipe idle.
   // Every other instantiation has one tile per workgroup and leaves the loop after it.
   constexpr bool WALK = unembed_walks_tiles<WB, SAMPLE>();
-  using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, STREAM, PH, SPLIT, VH>;
+  constexpr bool ROT = SPLIT == 0 && (STREAM || WB != 1);      // (tiles that a launch may have one row of)
+  using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, STREAM, PH, SPLIT, VH, 0, ROT>;
   const void* const hstaged = SPLIT ? a.hq : (WB != 1 && SB == H_STAGE_BYTES) ? a.hs : nullptr;
   const void* const Wfeed = SPLIT ? a.Wq : WPACK ? a.Wp : a.W;
   const int dfeed = SPLIT != 0 ? SPLIT * a.d : a.d;   // 16-bit columns of the planes
@@ -288,15 +290,11 @@ void k_unembed(const UnembedArgs a) {
   tile_of_block(blockIdx.x, nbt, nslab, slab, bt);
   Feed feed;
   const int wrows = SPLIT ? a.Wq_rows : 0;
-  // Where there is one tile of positions every workgroup streams a slab of its own, and rows of W lie a power of two or nearly that
-  // apart: CUs that all walk K from 0 ask the same few memory channels at a time.  Each slab therefore starts one stage
-  // further than the one before it (W's own rows, n r = 512, v = 320, draft and score, B = 1: 253 -> 233 us, B = 61 320 -> 309;
-  // prefix marginals, B = 200: d = 4096 356 -> 324, 2048 214 -> 193, 3072 286 -> 261; stage-major W, B = 1: 238 -> 236).  Tiles that share
-  // slabs and rows of h in an L2 walk K together, from its beginning (starts that differ: B = 300 .. 1000 the same, B = 4096 and 8192 0.4 % slower).
-  const int stages = SPLIT ? 1 : a.d * (BF16 ? 2 : 4) / SB;
-  auto first_stage = [&](int sl) { return nbt == 1 ? (int)((unsigned)sl % (unsigned)stages) : 0; };
+  // One tile of positions: every workgroup streams a slab of its own.  Tiles that share slabs and rows of h in an L2 walk K together,
+  // from its beginning (starts that differ: B = 300 .. 1000 the same, B = 4096 and 8192 0.4 % slower).
+  auto first = [&](int sl) { return ROT && nbt == 1 ? first_stage(sl, a.d * (BF16 ? 2 : 4), SB) : 0; };
   feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab, bt * TL::TP, smem, nullptr, 0, 1, hstaged, wrows, slab * a.v,
-            first_stage(slab));
+            first(slab));
   for (int w = blockIdx.x;;) {
   const int b0 = bt * TL::TP;
   const int wi = slab / a.r, wj = slab - wi * a.r;
@@ -341,7 +339,7 @@ void k_unembed(const UnembedArgs a) {
     if (wnext < ntiles) {
       tile_of_block(wnext, nbt, nslab, slab_next, bt_next);
       feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab_next, bt_next * TL::TP, smem, nullptr, 0, 1, hstaged, wrows, slab_next * a.v,
-                first_stage(slab_next));
+                first(slab_next));
     }
 
   if constexpr (!SAMPLE) if (a.targets != nullptr) {
@@ -558,11 +556,11 @@ void k_draw_gather(const DrawGatherArgs a) {
   constexpr bool M16 = use_m16<WV, WB, SB, NS, BF16>();
   constexpr int NPB = PB * Frag<M16>::SUB + PH, NVB = VB * Frag<M16>::SUB - VH / 2;
   typename Frag<M16>::blk_t acc[NPB][NVB];
-  // (each bucket's slab from a stage of its own on, as in k_unembed: a sampling call of the tree n r = 1024, d = 3072, B = 4096, 446 -> 439 us
+  // (each bucket's slab from a stage of its own on: a sampling call of the tree n r = 1024, d = 3072, B = 4096, 446 -> 439 us
   // from the stage-major W, 492 -> 486 from its rows; CP n r = 512, d = 4096, B = 1000 281 -> 268)
-  tile_gemm<WV, WB, VB, PB, SB, NS, BF16, true, M16, WPACK, false, PH, VH>(WPACK ? a.Wp : a.W, a.d, a.h, a.ld_h, a.B, a.d, a.v, g, 0, smem,
+  tile_gemm<WV, WB, VB, PB, SB, NS, BF16, true, M16, WPACK, false, PH, VH, true>(WPACK ? a.Wp : a.W, a.d, a.h, a.ld_h, a.B, a.d, a.v, g, 0, smem,
                                                                        acc, rows, nrows, a.S, nullptr, 0, 0,
-                                                                       (int)((unsigned)g % (unsigned)(a.d * (BF16 ? 2 : 4) / SB)));
+                                                                       first_stage(g, a.d * (BF16 ? 2 : 4), SB));
   float mx[NPB], lse[NPB];
   tile_lse<WV, WB, VB, PB, SB, NS, M16, PH, VH>(acc, a.v, (float2*)(smem + TL::RED_OFF), mx, lse);
 
@@ -1439,6 +1437,224 @@ static hipError_t launch_split(const UnembedArgs& a0, hipStream_t st) {
     e = positions == 192 ? launch_train<true, false, true, 2, 1, 1>(a, st) : launch_train<true, false, true, 2>(a, st);
   if (e == hipSuccess && a.three) e = launch_train<true, false, true, 3>(a, st);
   return e != hipSuccess ? e : launch_dt<false, false>(a, st);
+}
+
+// ---- calls of few tiles --------------------------------------------------------------------------------------
+// A call whose tiles all run at once is bound by its launches, by the latency of its loads and, in fp32, by the products of the CUs that
+// it uses.  So the workgroups behind those of the slabs compute what else the circuit needs, in the same launch: a tile of sum
+// units is a slab of r rows whose normalised logits are all kept, and of the layers a wave takes a row.  fp32 takes 16 positions
+// to a tile, half of the narrowest tile of k_unembed, on twice the CUs.
+// WV waves of 32 vocabulary rows each, 16 NPB positions; plain ring, as in tile_gemm_run.
+// (Operands straight into registers cost four times the loads' time: the four lanes that a load serves at once
+// are then in four rows, 63 cycles for 1 KB.)
+template <bool BF16, int WV, int RB, int NPB, int SB, int NS, bool STREAM>
+__global__ __launch_bounds__(WV * 64)
+void k_unembed_few(const UnembedArgs a, const ParamArgs p) {
+  constexpr int PB = NPB / 2, PH = NPB % 2;
+  using TL = Tile<WV, 1, RB / 2, PB, SB, NS, PH>;
+  constexpr int ESZ = BF16 ? 2 : 4;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int l15 = lane & 15, lq = lane >> 4;
+  const int nbt = (a.B + TL::TP - 1) / TL::TP, ntiles = a.n * a.r * nbt, nsum = p.Wsum != nullptr ? nbt : 0;
+  const int w = blockIdx.x;
+  if (w >= ntiles + nsum) {
+    const long long row = (long long)(w - ntiles - nsum) * WV + wave;
+    if (row < (long long)p.nb * p.L * p.r) normalise_layer_row(p.logits, p.layer_stride, p.batch_stride, row, p.L, p.r, p.out_nat, p.out_tr);
+    return;
+  }
+  const bool sum = w >= ntiles;                      // workgroup-uniform
+  int slab = 0, bt = w - ntiles;
+  if (!sum) tile_of_block(w, nbt, a.n * a.r, slab, bt);
+  const int b0 = bt * TL::TP, rows = sum ? p.r : a.v;
+  const int wi = slab / a.r, wj = slab - wi * a.r;
+  const int KI = a.d * ESZ / SB;
+  TileFeed<WV, 1, RB / 2, PB, SB, NS, BF16, false, true, false, STREAM, PH, 0, 0, 0, STREAM> feed;
+  // (one tile of positions: slabs from different stages on, and W as a stream, as in k_unembed)
+  feed.open(sum ? p.Wsum : a.W, a.d, a.h, a.ld_h, a.B, a.d, rows, slab, b0, smem, nullptr, 0, 1, nullptr, 0, 0,
+                STREAM ? first_stage(slab, a.d * ESZ, SB) : 0);
+  // this lane's target of the first windows: fetched while nothing depends on it
+  const int T = sum || a.targets == nullptr ? 0 : a.T, TT = T == 0 ? 0 : T + a.T2;
+  auto target = [&](int b, int t) {
+    return t < T ? a.targets[((long long)b * T + t) * a.n + wi] : a.targets2[((long long)b * a.T2 + (t - T)) * a.n + wi];
+  };
+  int x0[NPB];
+#pragma unroll
+  for (int pb = 0; pb < NPB; ++pb) {
+    const int b = b0 + pb * 16 + l15;
+    x0[pb] = TT > 0 && b < a.B ? target(b, 0) : -1;
+  }
+  f32x4_t acc[NPB][RB];
+#pragma unroll
+  for (int pb = 0; pb < NPB; ++pb)
+#pragma unroll
+    for (int i = 0; i < RB; ++i) acc[pb][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // chunk 4 ks + lq of a row lies at ^ (64 ks)
+  const int row0 = wave * RB * 16;
+  const int sw = swz16<TL::CPR>(l15);
+  const int a_off = (row0 + l15) * SB + ((lq ^ sw) << 4), b_off = (TL::TV + l15) * SB + ((lq ^ sw) << 4);
+  const bool busy = row0 < rows;                     // wave-uniform
+  auto stage = [&](int it) {
+    const char* const cur = smem + (it % NS) * TL::STAGE;
+    i32x4_t fa[SB / 64][RB], fb[SB / 64][NPB];
+#pragma unroll
+    for (int ks = 0; ks < SB / 64; ++ks) {
+#pragma unroll
+      for (int pb = 0; pb < NPB; ++pb) fb[ks][pb] = *(const i32x4_t*)(cur + ((b_off + pb * 16 * SB) ^ (ks * 64)));
+#pragma unroll
+      for (int i = 0; i < RB; ++i) fa[ks][i] = *(const i32x4_t*)(cur + ((a_off + i * 16 * SB) ^ (ks * 64)));
+    }
+#pragma unroll
+    for (int ks = 0; ks < SB / 64; ++ks) {
+      if constexpr (BF16) {
+#pragma unroll
+        for (int pb = 0; pb < NPB; ++pb)
+#pragma unroll
+          for (int i = 0; i < RB; ++i) mma_step<true>(acc[pb][i], fa[ks][i], fb[ks][pb]);
+      } else {
+        // lane group lq holds columns 4 lq .. 4 lq + 3 of both operands: product t takes one of each
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int pb = 0; pb < NPB; ++pb)
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+              acc[pb][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4_t, fa[ks][i])[t],
+                                                                __builtin_bit_cast(f32x4_t, fb[ks][pb])[t], acc[pb][i], 0, 0, 0);
+      }
+    }
+  };
+  const int KM = max(KI - (NS - 1), 0);              // iterations that still issue a stage
+  int it = 0;
+  for (; it < KM; ++it) {
+    MTPC_WAIT_VMCNT((NS - 2) * TL::PER);
+    __syncthreads();                                 // stage `it` landed everywhere, nobody reads stage it-1 any more
+    feed.issue((it + NS - 1) % NS);
+    if (busy) stage(it);
+  }
+  for (; it < KI; ++it) {
+    MTPC_WAIT_VMCNT(0);
+    __syncthreads();
+    if (busy) stage(it);
+  }
+  // softmax statistics of the columns: this lane holds rows rbase + 16 i + t of column 16 pb + l15
+  const int rbase = row0 + 4 * lq;
+  constexpr float LOG2E = 1.4426950408889634f;
+  float2* const red = (float2*)(smem + TL::RED_OFF); // [WV][TP]
+  float lse[NPB];
+#pragma unroll
+  for (int pb = 0; pb < NPB; ++pb) {
+    float m = neg_inf(), s = 0.f;
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (rbase + i * 16 + t < rows) m = fmaxf(m, acc[pb][i][t]);
+    m = Frag<true>::across(m, [](float x, float y) { return fmaxf(x, y); });
+    const float ms2 = m == neg_inf() ? 0.f : -m * LOG2E;
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (rbase + i * 16 + t < rows) s += __builtin_amdgcn_exp2f(fmaf(acc[pb][i][t], LOG2E, ms2));
+    s = Frag<true>::across(s, [](float x, float y) { return x + y; });
+    if (lq == 0) red[wave * TL::TP + pb * 16 + l15] = make_float2(m, s);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int pb = 0; pb < NPB; ++pb) {
+    float M = neg_inf(), Z = 0.f;
+#pragma unroll
+    for (int q = 0; q < WV; ++q) M = fmaxf(M, red[q * TL::TP + pb * 16 + l15].x);
+#pragma unroll
+    for (int q = 0; q < WV; ++q) {
+      const float2 y = red[q * TL::TP + pb * 16 + l15];
+      if (y.y > 0.f) Z += y.y * __expf(y.x - M);
+    }
+    lse[pb] = M + __logf(Z);
+  }
+#pragma unroll
+  for (int pb = 0; pb < NPB; ++pb) {
+    const int b = b0 + pb * 16 + l15;
+    if (b >= a.B) continue;
+    if (sum) {
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          if (rbase + i * 16 + t < rows) p.logw[(long long)b * p.r + rbase + i * 16 + t] = acc[pb][i][t] - lse[pb];
+      continue;
+    }
+    for (int t = 0; t < TT; ++t) {
+      const int x = t == 0 ? x0[pb] : target(b, t);
+      float* const dst = a.e + (((long long)b * TT + t) * a.n + wi) * a.r + wj;
+      if (x < 0 || x >= a.v) {
+        if (threadIdx.x < 16) *dst = x == -1 ? 0.f : __builtin_nanf("");
+      } else {
+        const int xr = x - rbase;
+        if (xr >= 0 && xr < RB * 16 && (xr & 12) == 0) {
+          const bool t0 = xr & 1, t1 = xr & 2;
+          float y = 0.f;
+#pragma unroll
+          for (int i = 0; i < RB; ++i) {
+            const float c0 = t0 ? acc[pb][i][1] : acc[pb][i][0], c1 = t0 ? acc[pb][i][3] : acc[pb][i][2];
+            y = (xr >> 4) == i ? (t1 ? c1 : c0) : y;
+          }
+          *dst = y - lse[pb];
+        }
+      }
+    }
+    if (a.logphi != nullptr) {
+      float* const dst = a.logphi + (((long long)b * a.n + wi) * a.r + wj) * a.v;
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        const int row = rbase + i * 16;
+        if ((a.v & 3) == 0) {
+          if (row < a.v)
+            *(f32x4_t*)(dst + row) = f32x4_t{acc[pb][i][0] - lse[pb], acc[pb][i][1] - lse[pb], acc[pb][i][2] - lse[pb], acc[pb][i][3] - lse[pb]};
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            if (row + t < a.v) dst[row + t] = acc[pb][i][t] - lse[pb];
+        }
+      }
+    }
+  }
+}
+
+template <bool BF16, int WV, int RB, int NPB, int SB, int NS, bool STREAM = false>
+static hipError_t launch_few_cfg(const UnembedArgs& a, const ParamArgs& p, hipStream_t st) {
+  using TL = Tile<WV, 1, RB / 2, NPB / 2, SB, NS, NPB % 2>;
+  const int nbt = (a.B + TL::TP - 1) / TL::TP;
+  // Each slab is read once: as a stream, where W is too large for the 256 MB cache to keep much of it from one call to the next (n r =
+  // 252, v = 320, B = 1, 165 MB: 37.7 / 33.7 us; 21 MB, n r = 64, B = 30, called again 18.4 / 23.6).
+  if constexpr (!STREAM)
+    if (nbt == 1 && (long long)a.n * a.r * a.v * a.d * (BF16 ? 2 : 4) > (128LL << 20))
+      return launch_few_cfg<BF16, WV, RB, NPB, SB, NS, true>(a, p, st);
+  constexpr auto kern = k_unembed_few<BF16, WV, RB, NPB, SB, NS, STREAM>;
+  if (hipError_t e = allow_lds<kern>(TL::SMEM); e != hipSuccess) return e;
+  const long long lrows = (long long)p.nb * p.L * p.r;
+  const long long grid = ((long long)a.n * a.r + (p.Wsum != nullptr)) * nbt + (lrows + WV - 1) / WV;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(TL::NT), TL::SMEM, st, a, p);
+  return hipGetLastError();
+}
+
+// Rows per wave: 32 in fp32, whose products then spread over the SIMDs; 64 in bf16, which reads half as many fragments of h for it.
+template <bool BF16, int NPB>
+static hipError_t launch_few_rows(const UnembedArgs& a, const ParamArgs& p, hipStream_t st) {
+  constexpr int RB = BF16 ? 4 : 2, W = BF16 ? 1 : 2;
+  const int need = std::max(a.v, p.Wsum != nullptr ? p.r : 0);
+  if (a.d * (BF16 ? 2 : 4) % 128 != 0) return launch_few_cfg<BF16, 5 * W, RB, NPB, 64, 4>(a, p, st);
+  if (need > 256) return launch_few_cfg<BF16, 5 * W, RB, NPB, 128, 3>(a, p, st);
+  if (need > 128) return launch_few_cfg<BF16, 4 * W, RB, NPB, 128, 4>(a, p, st);
+  return launch_few_cfg<BF16, 2 * W, RB, NPB, 128, 4>(a, p, st);
+}
+
+hipError_t launch_unembed_few(const UnembedArgs& a, const ParamArgs& p, int dtype, hipStream_t st) {
+  const int tile = unembed_few(a.B, a.n, a.r, dtype);
+  if (a.zleaf != nullptr || a.phiT != nullptr || a.v > 320 || p.r > 128 || tile == 0) return hipErrorInvalidValue;
+  if (dtype == MTPC_F32) return tile == 16 ? launch_few_rows<false, 1>(a, p, st) : launch_few_rows<false, 2>(a, p, st);
+  return tile == 16 ? launch_few_rows<true, 1>(a, p, st) : launch_few_rows<true, 2>(a, p, st);
 }
 
 hipError_t launch_unembed(const UnembedArgs& a, int dtype, hipStream_t st) {

@@ -98,6 +98,11 @@ hipError_t launch_unembed(const UnembedArgs& a, int dtype, hipStream_t) {
   opt(a.phiT, (u64)a.n * a.r * a.v * a.ld_phi * 4, "unembed phiT");
   return ok();
 }
+hipError_t launch_unembed_few(const UnembedArgs& a, const ParamArgs& p, int dtype, hipStream_t st) {
+  if (p.Wsum) launch_sumunit(p.h, p.ld_h, p.Wsum, p.B, p.d, p.r, dtype, p.logw, st);
+  if (p.L > 0) launch_normalise_layers(p.logits, p.layer_stride, p.batch_stride, p.nb, p.L, p.r, p.out_nat, p.out_tr, st);
+  return launch_unembed(a, dtype, st);
+}
 hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t) {
   need(a.h, strided(a.B, a.ld_h, a.d, esz(dtype)), "univariate h");
   need(a.W, (u64)a.n * a.r * a.v * a.d * esz(dtype), "univariate W");
