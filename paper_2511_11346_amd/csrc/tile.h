@@ -422,8 +422,8 @@ struct TileFeed {
 
 // The stage that a slab's product starts with where every workgroup streams a slab of its own: one further than the slab before
 // it.  Rows of W lie a power of two or nearly that apart, and CUs that all walk K from 0 ask the same few memory channels at a
-// time (W's own rows, n r = 512, v = 320, draft and score, B = 1: 253 -> 233 us, B = 61 320 -> 309; prefix marginals,
-// B = 200: d = 4096 356 -> 324, 2048 214 -> 193, 3072 286 -> 261; stage-major W, B = 1: 238 -> 236).  Rows of less than 4 KB spread
+// time (prefix marginals, n r = 512, v = 320, W's own rows, B = 200: d = 4096 356 -> 324 us, 2048 214 -> 193, 3072 286 -> 261, B = 100
+// 280 -> 271).  Rows of less than 4 KB spread
 // over the channels by themselves (n r = 256, B = 1: d = 1024 39.6 us either way, d = 2048 86 -> 63).
 __device__ __forceinline__ int first_stage(int slab, int row_bytes, int SB) {
   return row_bytes < 4096 ? 0 : (int)((unsigned)slab % (unsigned)(row_bytes / SB));
@@ -856,14 +856,14 @@ __device__ __forceinline__ void tile_unscale(f32x4_t (&acc)[NPB][NVB], const int
 // STREAMW: every byte of W is read once by the whole launch (one tile of positions): loaded with the
 // non-temporal hint.
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool GATHER = false, bool M16 = false,
-          bool WPACK = false, bool STREAMW = false, int PH = 0, int VH = 0, bool ROT = false>
+          bool WPACK = false, bool STREAMW = false, int PH = 0, int VH = 0>
 __device__ __forceinline__ void tile_gemm(const void* Wp, long long ld_w, const void* hp, long long ld_h,
                                           int B, int d, int v, int slab, int b0, char* smem,
                                           typename Frag<M16>::blk_t (&acc)[PB * Frag<M16>::SUB + PH][VB * Frag<M16>::SUB - VH / 2],
                                           const int* rows = nullptr, int nrows = 0, int rdiv = 1,
-                                          const void* hs = nullptr, int wrows_total = 0, int wrow0 = 0, int first = 0) {
-  TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, 0, VH, 0, ROT> feed;
-  feed.open(Wp, ld_w, hp, ld_h, B, d, v, slab, b0, smem, rows, nrows, rdiv, hs, wrows_total, wrow0, first);
+                                          const void* hs = nullptr, int wrows_total = 0, int wrow0 = 0) {
+  TileFeed<WV, WB, VB, PB, SB, NS, BF16, GATHER, M16, WPACK, STREAMW, PH, 0, VH> feed;
+  feed.open(Wp, ld_w, hp, ld_h, B, d, v, slab, b0, smem, rows, nrows, rdiv, hs, wrows_total, wrow0);
   tile_gemm_run(feed, d, smem, acc);
 }
 

@@ -278,7 +278,7 @@ void k_unembed(const UnembedArgs a) {
   // softmax statistics are taken, instead of after a workgroup launch with the matrix pipe idle.
   // Every other instantiation has one tile per workgroup and leaves the loop after it.
   constexpr bool WALK = unembed_walks_tiles<WB, SAMPLE>();
-  constexpr bool ROT = SPLIT == 0 && (STREAM || WB != 1);      // (tiles that a launch may have one row of)
+  constexpr bool ROT = SPLIT == 0 && !SAMPLE && (STREAM || WB != 1);      // (tiles that a launch may have one row of)
   using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, STREAM, PH, SPLIT, VH, 0, ROT>;
   const void* const hstaged = SPLIT ? a.hq : (WB != 1 && SB == H_STAGE_BYTES) ? a.hs : nullptr;
   const void* const Wfeed = SPLIT ? a.Wq : WPACK ? a.Wp : a.W;
@@ -291,7 +291,9 @@ void k_unembed(const UnembedArgs a) {
   Feed feed;
   const int wrows = SPLIT ? a.Wq_rows : 0;
   // One tile of positions: every workgroup streams a slab of its own.  Tiles that share slabs and rows of h in an L2 walk K together,
-  // from its beginning (starts that differ: B = 300 .. 1000 the same, B = 4096 and 8192 0.4 % slower).
+  // from its beginning (starts that differ: B = 300 .. 1000 the same, B = 4096 and 8192 0.4 % slower).  Passes that draw do as well: with
+  // sums in another order one token in 30,000 falls on the other side of its uniform, and a draft of a given seed is to stay what it
+  // was (draft and score, B = 61, W's own rows, 320 / 309 us; the gathered draws of n r = 1024, B = 4096 446 / 439).
   auto first = [&](int sl) { return ROT && nbt == 1 ? first_stage(sl, a.d * (BF16 ? 2 : 4), SB) : 0; };
   feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab, bt * TL::TP, smem, nullptr, 0, 1, hstaged, wrows, slab * a.v,
             first(slab));
@@ -556,11 +558,8 @@ void k_draw_gather(const DrawGatherArgs a) {
   constexpr bool M16 = use_m16<WV, WB, SB, NS, BF16>();
   constexpr int NPB = PB * Frag<M16>::SUB + PH, NVB = VB * Frag<M16>::SUB - VH / 2;
   typename Frag<M16>::blk_t acc[NPB][NVB];
-  // (each bucket's slab from a stage of its own on: a sampling call of the tree n r = 1024, d = 3072, B = 4096, 446 -> 439 us
-  // from the stage-major W, 492 -> 486 from its rows; CP n r = 512, d = 4096, B = 1000 281 -> 268)
-  tile_gemm<WV, WB, VB, PB, SB, NS, BF16, true, M16, WPACK, false, PH, VH, true>(WPACK ? a.Wp : a.W, a.d, a.h, a.ld_h, a.B, a.d, a.v, g, 0, smem,
-                                                                       acc, rows, nrows, a.S, nullptr, 0, 0,
-                                                                       first_stage(g, a.d * (BF16 ? 2 : 4), SB));
+  tile_gemm<WV, WB, VB, PB, SB, NS, BF16, true, M16, WPACK, false, PH, VH>(WPACK ? a.Wp : a.W, a.d, a.h, a.ld_h, a.B, a.d, a.v, g, 0, smem,
+                                                                       acc, rows, nrows, a.S);
   float mx[NPB], lse[NPB];
   tile_lse<WV, WB, VB, PB, SB, NS, M16, PH, VH>(acc, a.v, (float2*)(smem + TL::RED_OFF), mx, lse);
 

@@ -1,16 +1,15 @@
-"""GPU parity of passes over W whose slabs begin at different stages of K (one tile of positions, and the gathered draws): one
+"""GPU parity of passes over W whose slabs begin at different stages of K (one tile of positions): one
 stage in all, fewer stages than the ring has buffers, fewer and more than there are slabs, on every tile that streams W,
 from W's own rows and from either stage-major copy of it (the same bits).
 
-Tolerance: as in test_gpu_tile_positions, sums of d <= 1056 products."""
+Tolerance: as in test_gpu_tile_positions, sums of d <= 2080 products."""
 import numpy as np
 import pytest
 import torch
 
 import mtpc_inputs as mi
 from oracle import mtpc_oracle as oc
-from oracle import philox
-from gpu_util import compare_drafts, make_head
+from gpu_util import make_head
 
 pytestmark = pytest.mark.gpu
 
@@ -18,7 +17,7 @@ LOG = 4e-5
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("d", [32, 64, 96, 192, 1056])
+@pytest.mark.parametrize("d", [32, 96, 2048, 2080])
 @pytest.mark.parametrize("B,r", [(1, 11), (40, 11), (64, 70), (100, 11), (129, 70), (200, 70), (256, 70)])
 def test_scores(B, r, d, dtype):
     inp = mi.make_inputs("cp", B=B, d=d, n=4, r=r, v=61, dtype=dtype, seed=B + d, h_scale=1.0)
@@ -31,16 +30,3 @@ def test_scores(B, r, d, dtype):
         head.pack_W()
         assert torch.equal(head.prefix_marginals(tg), got)
 
-
-@pytest.mark.parametrize("packed", [False, True])
-@pytest.mark.parametrize("d", [32, 96, 1056])
-@pytest.mark.parametrize("B", [70, 700])
-def test_gathered_draws(B, d, packed):
-    inp = mi.make_inputs("cp", B=B, d=d, n=4, r=35, v=61, dtype="bf16", seed=B + d, h_scale=1.0)
-    logphi, logw, _ = oc._params("cp", inp.h, inp.W, inp.Wsum, None)
-    od, ol, margin = oc.sample_from("cp", logphi, logw, None, philox.uniforms(B, 1, 5, seed=3), with_margin=True)
-    head = make_head(inp)
-    if packed:
-        head.pack_W()
-    gd, gl, _ = head.sample(1, seed=3)
-    compare_drafts(gd, gl, od, ol, margin)
