@@ -360,7 +360,7 @@ CircuitArgs circuit_args(int family, const mtpc_head* hd, const Plan& p, int row
   char* ws = (char*)hd->workspace;
   CircuitArgs c{};
   c.family = family; c.rows = rows; c.T = T; c.n = hd->n; c.r = hd->r;
-  c.e = (const float*)(ws + p.e);
+  c.e = (float*)(ws + p.e);
   c.logw = family == MTPC_FF ? nullptr : (const float*)(ws + p.logw);
   c.layers = n_layers(family, hd->n) > 0 ? (const float*)(ws + p.lay_circ) : nullptr;
   c.layers_nat = (c.layers && family == MTPC_BTREE && p.nb == 1 && p.has_nat) ? (const float*)(ws + p.lay_nat) : nullptr;
@@ -563,13 +563,9 @@ mtpc_status run_sample(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
     HIP_TRY(launch_unembed(u2, hd->dtype, st));
   }
   if (want_prefix) {
-    if (table_scores) {
-      GatherArgs g{};
-      g.B = hd->B; g.S = S; g.v = hd->v; g.n = hd->n; g.r = hd->r;
-      g.x = drafts; g.e = (float*)(ws + p.e);
-      HIP_TRY(launch_gather_table(g, table, st));
-    }
-    HIP_TRY(profiled_circuit(circuit_args(family, hd, p, hd->B * S, S, prefix_logq, 1), st));
+    CircuitArgs c = circuit_args(family, hd, p, hd->B * S, S, prefix_logq, 1);
+    if (table_scores) { c.table = table; c.x = drafts; c.v = hd->v; }
+    HIP_TRY(profiled_circuit(c, st));
   }
   return MTPC_OK;
 }
@@ -618,11 +614,9 @@ mtpc_status run_table_scores(int family, const mtpc_head* hd, const mtpc_sumlaye
   char* ws = (char*)hd->workspace;
   s = launch_params(family, hd, ly, p, family != MTPC_FF && family != MTPC_CP, true, st);
   if (s != MTPC_OK) return s;
-  GatherArgs g{};
-  g.B = hd->B; g.S = T; g.v = hd->v; g.n = hd->n; g.r = hd->r;
-  g.x = x; g.e = (float*)(ws + p.e);
-  HIP_TRY(launch_gather_table(g, logphi, st));
-  HIP_TRY(profiled_circuit(circuit_args(family, hd, p, hd->B * T, T, out, mode == MTPC_SCORE_PREFIX), st));
+  CircuitArgs c = circuit_args(family, hd, p, hd->B * T, T, out, mode == MTPC_SCORE_PREFIX);
+  c.table = logphi; c.x = x; c.v = hd->v;
+  HIP_TRY(profiled_circuit(c, st));
   return MTPC_OK;
 }
 

@@ -2,6 +2,7 @@
 // layers on the evidence e[rows][n][r], latent draws of the ancestral sampler,
 // latent marginals, and the table lookup that scores drafts.
 // All of them touch O(B n r) or O(L r^2) data; none is a roofline concern.
+#include <algorithm>
 #include <type_traits>
 
 #include "mtpc_internal.h"
@@ -799,122 +800,282 @@ static hipError_t launch_btree_static(const CircuitArgs& a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// Few rows (decode-sized calls): the HMM chain and the binary tree are chains of
-// dependent r x r products, and with one group per row every product waits for its
-// layer to come from L2.  Here ONE WORKGROUP owns a row: all layers of the row, its
-// evidence and log omega are fetched into LDS with every load in flight at once, then
-//  - binary tree: the nodes of a level are evaluated side by side by the workgroup's
-//    groups (one barrier per level), and the n prefix marginals - each a walk from a
-//    leaf to the root of at most log2 n products - are dealt to the groups;
-//  - HMM: one group runs the forward recursion out of LDS.
-// One unit per lane (r <= 64).  LDS: layers L*r*r + evidence n*r + nodes (n-1)*r +
-// log omega r + one exchange row of r floats per group.
+// Few rows (decode-sized calls), up to 64 units: what counts is the latency of one row, a chain of dependent r x r products (HMM, binary
+// tree).  ONE WORKGROUP owns a row: all layers of the row, its evidence - rows of e, or looked up in the table of input
+// units - and log omega are fetched into LDS with every load in flight at once, then
+//  - binary tree: the nodes of a level are evaluated side by side by the workgroup's waves (one barrier per level), and the
+//    n prefix marginals - each a walk from a leaf to the root of at most log2 n products - are dealt to them;
+//  - HMM: one wave runs the forward recursion on linear values.  All exponentials of the evidence are taken before the chain, all
+//    logarithms of its sums after it; what is left of a step is one product, one sum over the units and a scaling by a power of two;
+//  - CP: the prefixes' sums, in double, and their log-sum-exps side by side.
+// A wave forms a product with all of its lanes: lane (k, part) sums the terms j = part, part + P, ... of output k (neighbouring
+// rows of the layer: no bank conflicts), the operand comes back from LDS 16 bytes at a time, the parts meet in lane swaps.
+// Before (groups of 32 lanes, a logarithm and two exponentials to a step, evidence through a launch of its own), after, us: HMM n = 16, r = 32,
+// 61 rows from the table 34.5 -> 13.7; CP, one row from the table 14.9 -> 5.0; tree n = 16, r = 32, 200 rows 26 -> 12.
+// G: r rounded up to a power of two, at least 8.
+// LDS: see circuit_row_smem.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_circuit_row(const CircuitArgs a, int G) {
+constexpr int ROW_SCALE = 64;      // the HMM's values sum to 2^64 .. 2^65: what is kept of a unit reaches 2^-149 and no result overflows
+// P: parts.  One where rows outnumber the CUs and a product is small: a wave then forms 64 / G of them side by side.
+template <int G, int P>
+__global__ __launch_bounds__(1024) void k_circuit_row(const CircuitArgs a) {
+  constexpr int JP = G / P;
+  static_assert(P == 64 / G || P == 1, "a wave, or groups of G lanes, to a product");
   extern __shared__ __align__(16) float rsm[];
-  const int n = a.n, r = a.r, tid = threadIdx.x;
-  const int NG = 256 / G, gi = tid / G, g = tid % G;
+  const int n = a.n, r = a.r, tid = threadIdx.x, NT = blockDim.x, NW = NT / (G * P);
+  const int lane = tid % (G * P), wave = tid / (G * P), k = tid % G, part = lane / G;      // (wave: or group of lanes)
   const long long row = blockIdx.x;
   const long long pos = row / a.T;
-  const int Lst = a.L;                                   // stored layers (1: shared by all steps / nodes)
+  const bool hmm = a.family == MTPC_HMM, tree = a.family == MTPC_BTREE;
+  const int Lst = (hmm || tree) && a.layers ? a.L : 0;   // stored layers (1: shared by all steps / nodes)
   const int lstep = Lst > 1 ? r * r : 0;
-  float* s_lay = rsm;                                    // [Lst][j][k]
-  float* s_ev = s_lay + (size_t)Lst * r * r;             // [n][r]
-  float* s_nodes = s_ev + (size_t)n * r;                 // [n-1][r] (binary tree)
-  float* s_lw = s_nodes + (size_t)(n - 1) * r;           // [r]
-  float* s_sh = s_lw + r + (size_t)gi * r;               // this group's exchange row
-  int* s_bad = (int*)(s_lw + r + (size_t)NG * r);
+  float* s_x = rsm;                                      // [threads] operands of the products
+  float* s_lay = s_x + NT;                          // [Lst][j][k]
+  float* s_ev = s_lay + (((size_t)Lst * r * r + 3) & ~(size_t)3);   // [n][r]
+  float* s_w = s_ev + (size_t)n * r;                     // [n][r] HMM: exp(evidence - its maximum); tree: node values
+  float* s_lw = s_w + (hmm || tree ? (size_t)n * r : 0); // [r]
+  float* s_max = s_lw + r;                               // [n] HMM: the maxima
+  float* s_sum = s_max + n;                              // [n] HMM: sums of the steps, and their exponents
+  int* s_exp = (int*)(s_sum + n);
+  int* s_bad = s_exp + n;
+  const float ninf = neg_inf();
+  const bool live = k < r;
 
+  // ---- everything into LDS
   const float* lay = a.layers;
   if (a.contextual && lay) lay += pos * (long long)Lst * r * r;
-  const float* ev = a.e + row * (long long)n * r;
-  const int nlay = lay ? Lst * r * r : 0;
+  const int nlay = Lst * r * r;
   if ((nlay & 3) == 0 && (((size_t)lay) & 15) == 0) {
-    // 16-byte loads, four per thread in flight
-    const float4* src = (const float4*)lay;
-    float4* dst = (float4*)s_lay;
+    const f32x4_t* src = (const f32x4_t*)lay;
+    f32x4_t* dst = (f32x4_t*)s_lay;
     const int nq = nlay >> 2;
-    for (int t0 = 0; t0 < nq; t0 += 4 * 256) {
-      float4 tmp[4];
+    for (int t0 = 0; t0 < nq; t0 += 4 * NT) {
+      f32x4_t tmp[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) tmp[u] = src[min(t0 + u * 256 + tid, nq - 1)];
+      for (int u = 0; u < 4; ++u) tmp[u] = src[min(t0 + u * NT + tid, nq - 1)];
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (t0 + u * 256 + tid < nq) dst[t0 + u * 256 + tid] = tmp[u];
+        if (t0 + u * NT + tid < nq) dst[t0 + u * NT + tid] = tmp[u];
     }
   } else {
-    for (int t0 = 0; t0 < nlay; t0 += 8 * 256) {         // eight loads per thread in flight
+    for (int t0 = 0; t0 < nlay; t0 += 8 * NT) {
       float tmp[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) tmp[u] = lay[min(t0 + u * 256 + tid, nlay - 1)];
+      for (int u = 0; u < 8; ++u) tmp[u] = lay[min(t0 + u * NT + tid, nlay - 1)];
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (t0 + u * 256 + tid < nlay) s_lay[t0 + u * 256 + tid] = tmp[u];
+        if (t0 + u * NT + tid < nlay) s_lay[t0 + u * NT + tid] = tmp[u];
     }
   }
-  for (int t = tid; t < n * r; t += 256) s_ev[t] = ev[t];
-  if (tid < r) s_lw[tid] = a.logw[pos * r + tid];
-  __syncthreads();
-  // an id outside [-1, v) left NaN in every unit of its window position: poison what observes it
-  if (gi == 0) {
-    const int fb = first_nan_position(s_ev, n, r, g, G);
-    if (g == 0) *s_bad = fb;
+  if (tid == 0) *s_bad = n;
+  const float lw0 = a.logw != nullptr && live ? a.logw[pos * r + k] : ninf;
+  const int step = NT / G;                               // groups of G lanes take a token each
+  for (int i = tid / G; i < n; i += step) {
+    if (!live) continue;
+    float e;
+    if (a.table != nullptr) {
+      const int x = a.x[row * n + i];
+      if (x >= 0 && x < a.v) e = a.table[((pos * n + i) * r + k) * a.v + x];
+      else e = x == -1 ? 0.f : __builtin_nanf("");
+    } else {
+      e = a.e[(row * n + i) * r + k];
+    }
+    s_ev[i * r + k] = e;
   }
   __syncthreads();
-  const int first_bad = *s_bad;
-  const float ninf = neg_inf();
-  auto emit = [&](int i, float v) {
-    if (g != 0) return;
-    if (i >= first_bad) v = __builtin_nanf("");
+  // an id outside [-1, v) leaves NaN in every unit of its window position: poison what observes it
+  for (int i = tid; i < n; i += NT)
+    if (s_ev[i * r] != s_ev[i * r]) atomicMin(s_bad, i);
+
+  // ---- reductions over the G units (every lane gets the result), and over the parts of an output
+  auto both16 = [](float x, float& p, float& q) {
+    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    p = __uint_as_float(t[0]); q = __uint_as_float(t[1]);
+  };
+  auto both32 = [](float x, float& p, float& q) {
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    p = __uint_as_float(t[0]); q = __uint_as_float(t[1]);
+  };
+  auto over_units = [&](float x, auto op) {
+    x = op(x, __int_as_float(dpp_move<0xB1>(__float_as_int(x))));     // (as group_reduce)
+    x = op(x, __int_as_float(dpp_move<0x4E>(__float_as_int(x))));
+    x = op(x, __int_as_float(dpp_move<0x141>(__float_as_int(x))));
+    if constexpr (G >= 16) x = op(x, __int_as_float(dpp_move<0x140>(__float_as_int(x))));
+    if constexpr (G >= 32) { float p, q; both16(x, p, q); x = op(p, q); }
+    if constexpr (G >= 64) { float p, q; both32(x, p, q); x = op(p, q); }
+    return x;
+  };
+  auto sum_units = [&](float x) { return over_units(x, [](float y, float z) { return y + z; }); };
+  auto max_units = [&](float x) { return over_units(x, [](float y, float z) { return fmaxf(y, z); }); };
+  auto sum_parts = [&](float x) {
+    if constexpr (P > 1) {
+      if constexpr (G <= 8) x += __int_as_float(dpp_move<0x128>(__float_as_int(x)));    // row_ror:8
+      if constexpr (G <= 16) { float p, q; both16(x, p, q); x = p + q; }
+      if constexpr (G <= 32) { float p, q; both32(x, p, q); x = p + q; }
+    }
+    return x;
+  };
+  float* const xs = s_x + wave * (G * P);
+  // this lane's share of a layer (what multiplies no unit: any), in registers before the operand is there; 64 units: from LDS beside it
+  constexpr bool AHEAD = JP <= 16;
+  struct Weights { float w[AHEAD ? JP : 1]; const float* p; };
+  auto weights = [&](const float* Wl) {
+    Weights o;
+    o.p = Wl + min(k, r - 1);
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int u = 0; u < JP; ++u) o.w[u] = o.p[min(part + P * u, r - 1) * r];
+    }
+    return o;
+  };
+  // sum_j x_j W[j][k]; x is this lane's unit k's, 0 for k >= r
+  auto product = [&](float x, const Weights& w) {
+    if (part == 0) xs[(k % P) * JP + k / P] = x;
+    __builtin_amdgcn_wave_barrier();
+    constexpr int C = JP < 4 ? JP : 4, U = JP < 16 ? JP : 16;          // sums side by side; terms at a time
+    float acc[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[c] = 0.f;
+#pragma unroll 1
+    for (int u0 = 0; u0 < JP; u0 += U) {
+      float xv[U], wv[U];
+#pragma unroll
+      for (int u = 0; u < U; u += C) {
+        if constexpr (C == 4) {
+          const f32x4_t t = *(const f32x4_t*)(xs + part * JP + u0 + u);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) xv[u + c] = t[c];
+        } else {
+          xv[u] = xs[part * JP + u0 + u];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) wv[u] = AHEAD ? w.w[AHEAD ? u : 0] : w.p[min(part + P * (u0 + u), r - 1) * r];
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc[u % C] = fmaf(xv[u], wv[u], acc[u % C]);
+    }
+    __builtin_amdgcn_wave_barrier();
+    float y = acc[0];
+    if constexpr (C == 4) y = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    return sum_parts(y);
+  };
+  auto emit = [&](int i, float v) {                      // (by one lane)
+    if (i >= *s_bad) v = __builtin_nanf("");
     if (a.prefix) a.out[row * n + i] = v;
     else if (i == n - 1) a.out[row] = v;
   };
-  auto lse = [&](float x) {
-    const float m = group_max(x, G);
-    if (m == ninf) return m;
-    return m + __logf(group_sum(g < r ? __expf(x - m) : 0.f, G));
-  };
-  auto leaf = [&](int i) { return g < r ? s_ev[i * r + g] : ninf; };
-  const float lw = g < r ? s_lw[g] : ninf;
 
-  if (a.family == MTPC_HMM) {
-    if (gi != 0) return;                                 // (no workgroup barrier below)
-    // the message stays relative to its largest unit, the magnitude taken out is summed in double
-    float alpha[1] = {lw + leaf(0)};
-    double scale = 0.0;
+  if (a.family == MTPC_FF) {
+    __syncthreads();
+    if (tid < n) {
+      double acc = 0.0;                                  // (one rounding of the whole, not one per token)
+      for (int i = 0; i <= tid; ++i) acc += (double)s_ev[i * r];
+      emit(tid, (float)acc);
+    }
+    return;
+  }
+  if (a.family == MTPC_CP) {
+    __syncthreads();
+    for (int i = tid / G; i < n; i += step) {
+      double s = (double)lw0;
+      if (live)
+        for (int t = 0; t <= i; ++t) s += (double)s_ev[t * r + k];
+      const float m = max_units(live ? (float)s : ninf);
+      const float z = sum_units(live && m != ninf ? __expf((float)(s - (double)m)) : 0.f);
+      if (k == 0) emit(i, m == ninf ? m : (float)((double)m + (double)__logf(z)));
+    }
+    return;
+  }
+
+  if (hmm) {
+    for (int i = tid / G; i < n; i += step) {
+      const float e = live ? s_ev[i * r + k] : ninf;
+      const float m = max_units(e), ms = m == ninf ? 0.f : m;
+      if (live) s_w[i * r + k] = expf(e - ms);
+      if (k == 0) s_max[i] = ms;
+    }
+    __syncthreads();
+    if (wave != 0) return;                               // (no workgroup barrier below)
+    // x_k 2^E exp(the maxima so far) is the forward message; the product with a layer keeps its sum
+    const float lm = max_units(lw0), lms = lm == ninf ? 0.f : lm;
+    float x = live ? __builtin_amdgcn_ldexpf(expf(lw0 - lms), ROW_SCALE) : 0.f;
+    int E = -ROW_SCALE;
+    Weights w{};
+    if (n > 1) w = weights(s_lay);
     for (int i = 0; i < n; ++i) {
+      const int ic = i * r + min(k, r - 1);
+      const float ew = s_w[ic];
+      float y = x;
       if (i > 0) {
-        sum_layer_lds<1>(alpha, s_lay + (size_t)(i - 1) * lstep, s_sh, g, r, G);
-        alpha[0] += leaf(i);
+        y = product(x, w);
+        if (i < n - 1) w = weights(s_lay + (size_t)i * lstep);
       }
-      const float m = group_max(alpha[0], G);
-      if (m != ninf) { alpha[0] -= m; scale += (double)m; }
-      if (a.prefix || i == n - 1)                        // largest unit 0 (or all -inf: log 0)
-        emit(i, (float)(scale + (double)__logf(group_sum(g < r ? __expf(alpha[0]) : 0.f, G))));
+      float c = live ? y * ew : 0.f;
+      float s = sum_units(c);
+      if (s < 0x1p34f) {
+        // the units that are left have next to none of the evidence (or none: all results from here on are -inf): exponentials
+        // relative to the largest product
+        const float l = live && y > 0.f ? logf(y) + s_ev[ic] : ninf;
+        const float lmax = max_units(l);
+        if (lmax != ninf) {
+          c = __builtin_amdgcn_ldexpf(expf(l - lmax), ROW_SCALE);
+          s = sum_units(c);
+          E -= ROW_SCALE;
+          if (lane == 0) s_max[i] = lmax;
+        }
+      }
+      if (lane == 0) { s_sum[i] = s; s_exp[i] = E; }
+      const int sh = s > 0.f ? ROW_SCALE + 1 - __builtin_amdgcn_frexp_expf(s) : 0;
+      x = __builtin_amdgcn_ldexpf(c, sh);
+      E -= sh;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (lane < n) {
+      double M = (double)lms;
+      for (int t = 0; t <= lane; ++t) M += (double)s_max[t];
+      emit(lane, (float)(M + (double)s_exp[lane] * 0.69314718055994530942 + (double)logf(s_sum[lane])));
     }
     return;
   }
 
   // ---- binary tree, heap order: inner nodes 0..n-2, leaf i at n-1+i
-  auto full_value = [&](int c) {                         // child fully observed
-    if (c >= n - 1) return leaf(c - (n - 1));
-    return g < r ? s_nodes[c * r + g] : ninf;
+  float* const s_nodes = s_w;
+  if (tid < r) s_lw[tid] = lw0;                          // (tid = k)
+  __syncthreads();
+  // c_k <- log sum_j W[j][k] exp(c_j)
+  auto sum_layer = [&](float c, int m) {
+    const Weights w = weights(s_lay + (size_t)(m - 1) * lstep);
+    const float mx = max_units(c);
+    const float y = product(live ? __expf(c - (mx == ninf ? 0.f : mx)) : 0.f, w);
+    return live ? mx + __logf(y) : ninf;                 // -inf + log 0 = -inf
   };
+  auto lse = [&](float x) {
+    const float m = max_units(x);
+    if (m == ninf) return m;
+    return m + __logf(sum_units(live ? __expf(x - m) : 0.f));
+  };
+  auto full_value = [&](int c) {                         // child fully observed
+    if (!live) return ninf;
+    return c >= n - 1 ? s_ev[(c - (n - 1)) * r + k] : s_nodes[c * r + k];
+  };
+  const float lw = live ? s_lw[k] : ninf;
   for (int lo = (n >> 1) - 1; lo >= 1; lo = (lo - 1) >> 1) {   // levels bottom-up: nodes lo .. 2*lo
-    for (int m = lo + gi; m <= 2 * lo; m += NG) {
-      float c[1] = {full_value(2 * m + 1) + full_value(2 * m + 2)};
-      sum_layer_lds<1>(c, s_lay + (size_t)(m - 1) * lstep, s_sh, g, r, G);
-      if (g < r) s_nodes[m * r + g] = c[0];
+    for (int m = lo + wave; m <= 2 * lo; m += NW) {
+      const float c = sum_layer(full_value(2 * m + 1) + full_value(2 * m + 2), m);
+      if (part == 0 && live) s_nodes[m * r + k] = c;
     }
     __syncthreads();
   }
   if (!a.prefix) {
-    if (gi == 0) emit(n - 1, lse(full_value(1) + full_value(2) + lw));
+    if (wave == 0) {
+      const float v = lse(full_value(1) + full_value(2) + lw);
+      if (lane == 0) emit(n - 1, v);
+    }
     return;
   }
   // prefix i: a subtree without observed leaf is 1, a fully observed one its stored value;
   // only the nodes whose leaf range straddles the boundary are evaluated again
-  for (int i = gi; i < n; i += NG) {
+  for (int i = wave; i < n; i += NW) {
     float pv = 0.f;                 // value of the straddling child on the path so far
     int idx = n - 1 + i, size = 1;
     while (idx > 0) {
@@ -925,54 +1086,67 @@ __global__ __launch_bounds__(256) void k_circuit_row(const CircuitArgs a, int G)
       const int cl = 2 * m + 1, cr = cl + 1, half = size >> 1;
       const int l_last = first + half - 1, r_first = first + half;
       const float lv = (l_last <= i) ? full_value(cl) : pv;
-      const float rv = (r_first > i) ? (g < r ? 0.f : ninf) : (last <= i ? full_value(cr) : pv);
-      float c[1] = {lv + rv};
+      const float rv = (r_first > i) ? (live ? 0.f : ninf) : (last <= i ? full_value(cr) : pv);
       if (m > 0) {
-        sum_layer_lds<1>(c, s_lay + (size_t)(m - 1) * lstep, s_sh, g, r, G);
-        pv = c[0];
+        pv = sum_layer(lv + rv, m);
       } else {
-        emit(i, lse(c[0] + lw));
+        const float v = lse(lv + rv + lw);
+        if (lane == 0) emit(i, v);
       }
       idx = m;
     }
   }
 }
 
-// LDS of k_circuit_row in bytes (0: the shape is not served)
-static size_t circuit_row_smem(const CircuitArgs& a, int G) {
-  if (a.r > 64 || (a.family != MTPC_HMM && a.family != MTPC_BTREE)) return 0;
-  const int L = a.family == MTPC_HMM ? a.n - 1 : a.n - 2;
-  if (L > 0 && !a.layers) return 0;
-  const size_t fl = (size_t)(L > 0 ? a.L : 0) * a.r * a.r + (size_t)a.n * a.r + (size_t)(a.n - 1) * a.r + a.r +
-                    (size_t)(256 / G) * a.r + 4;
+// Rows that k_circuit_row takes, its threads and its LDS.  HMM and tree: their products wait for layers from the L2 elsewhere.  CP: as many
+// rows as there are CUs, beyond which a row to a group of lanes (k_circuit) keeps more of them in flight; FF the same where its
+// evidence is in the table.
+static bool circuit_row_narrow(const CircuitArgs& a) { return a.family == MTPC_BTREE && a.rows > 256 && a.r <= 16; }
+static int circuit_row_threads(const CircuitArgs& a) {
+  return a.family == MTPC_BTREE && !circuit_row_narrow(a) ? std::min(1024, std::max(256, a.n * 64)) : 256;
+}
+static size_t circuit_row_smem(const CircuitArgs& a) {
+  const bool lay = a.family == MTPC_HMM || a.family == MTPC_BTREE;
+  const size_t fl = (size_t)circuit_row_threads(a) + (lay && a.layers ? (size_t)a.L * a.r * a.r + 4 : 0) + (size_t)a.n * a.r * (lay ? 2 : 1) + a.r +
+                    (size_t)a.n * 3 + 4;
   return fl * 4;
 }
+static bool circuit_row_serves(const CircuitArgs& a) {
+  if (a.r > 64) return false;
+  if (a.family != MTPC_HMM && a.family != MTPC_BTREE) return a.rows <= 256 && (a.family == MTPC_CP || a.table != nullptr);
+  const int L = a.family == MTPC_HMM ? a.n - 1 : a.n - 2;
+  return a.rows <= 2048 && (L <= 0 || a.layers) && circuit_row_smem(a) <= 156 * 1024;
+}
 
-static hipError_t launch_circuit_row(const CircuitArgs& a, int G, size_t smem, hipStream_t st) {
-  static size_t attr = 0;                                // largest dynamic LDS size granted so far
-  if (smem > attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_circuit_row, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)smem);
-    if (e != hipSuccess) return e;
-    attr = smem;
-  }
-  hipLaunchKernelGGL(k_circuit_row, dim3((unsigned)a.rows), dim3(256), smem, st, a, G);
+template <int G, int P>
+static hipError_t launch_circuit_row_g(const CircuitArgs& a, hipStream_t st) {
+  constexpr auto kern = k_circuit_row<G, P>;
+  if (hipError_t e = allow_lds<kern>(156 * 1024); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)a.rows), dim3(circuit_row_threads(a)), circuit_row_smem(a), st, a);
   return hipGetLastError();
+}
+static hipError_t launch_circuit_row(const CircuitArgs& a, hipStream_t st) {
+  const bool narrow = circuit_row_narrow(a);
+  if (a.r <= 8) return narrow ? launch_circuit_row_g<8, 1>(a, st) : launch_circuit_row_g<8, 8>(a, st);
+  if (a.r <= 16) return narrow ? launch_circuit_row_g<16, 1>(a, st) : launch_circuit_row_g<16, 4>(a, st);
+  return a.r <= 32 ? launch_circuit_row_g<32, 2>(a, st) : launch_circuit_row_g<64, 1>(a, st);
 }
 
 hipError_t launch_circuit(const CircuitArgs& a, hipStream_t st) {
-  // decode-sized calls of the families with r x r layers: one workgroup per row
-  if (a.rows <= 2048 && (a.family == MTPC_HMM || a.family == MTPC_BTREE)) {
-    int G = 1;
-    while (G < a.r && G < 64) G <<= 1;
-    const size_t need = circuit_row_smem(a, G);
-    if (need != 0 && need <= 144 * 1024) return launch_circuit_row(a, G, need, st);
+  if (circuit_row_serves(a)) return launch_circuit_row(a, st);
+  if (a.table != nullptr) {                              // the other kernels read rows of e
+    GatherArgs g{};
+    g.B = a.rows / a.T; g.S = a.T; g.v = a.v; g.n = a.n; g.r = a.r;
+    g.x = a.x; g.e = a.e;
+    if (hipError_t e = launch_gather_table(g, a.table, st); e != hipSuccess) return e;
   }
+  // (tree, fewer than 256 rows whose layers do not fit beside each other: the kernels that share layers among rows all the same - r = 64,
+  // n = 16, B = 8 258 -> 98 us with the one, r = 60 258 -> 210 with the other)
   // batching rows pays when sum layers are shared and there are rows to batch;
   // the batched BTree node store must still fit one group into 48 KiB of LDS
   // (measured: the tree's many dependent node evaluations gain from sharing weight
   // loads; the HMM chain prefers more, narrower groups)
-  if (a.family == MTPC_BTREE && !a.contextual && a.n > 2 && a.rows >= 256) {
+  if (a.family == MTPC_BTREE && !a.contextual && a.n > 2) {
     const size_t mfma = btree_mfma_smem(a);
     if (mfma != 0 && mfma <= 150 * 1024) return launch_btree_mfma(a, mfma, st);
     const size_t need = btree_static_smem(a);

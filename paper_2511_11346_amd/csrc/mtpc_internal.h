@@ -189,7 +189,10 @@ struct CircuitArgs {
   int rows;             // B*T evidence rows
   int T;                // rows per position (logw / contextual layers are indexed by row / T)
   int n, r;
-  const float* e;       // [rows][n][r]
+  float* e;             // [rows][n][r]: the evidence, or (table set) room for it
+  const float* table;   // nullptr, or log phi [B][n][r][v], whose entries at the tokens x [rows][n] are the evidence
+  const int* x;
+  int v;
   const float* logw;    // [B][r] (nullptr for FF)
   const float* layers;  // normalised linear probabilities, HMM: [nb][L][j][j'], BTree: [nb][L][j][k] (transposed)
   const float* layers_nat;  // BTree with shared layers: the same in natural layout [L][k][j], or nullptr

@@ -119,6 +119,10 @@ hipError_t launch_univariate_table(const UnivariateArgs& a, const float* logphi,
 hipError_t launch_circuit(const CircuitArgs& a, hipStream_t) {
   const u64 pos = (u64)a.rows / a.T;
   need(a.e, (u64)a.rows * a.n * a.r * 4, "circuit e");
+  if (a.table) {
+    need(a.table, pos * a.n * a.r * a.v * 4, "circuit table");
+    need(a.x, (u64)a.rows * a.n * 4, "circuit tokens");
+  }
   if (a.family != MTPC_FF) need(a.logw, pos * a.r * 4, "circuit logw");
   if (a.layers) need(a.layers, (a.contextual ? pos : 1) * (u64)a.L * a.r * a.r * 4, "circuit layers");
   if (a.layers_nat) need(a.layers_nat, (u64)a.L * a.r * a.r * 4, "circuit layers (natural layout)");
