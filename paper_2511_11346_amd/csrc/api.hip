@@ -297,19 +297,19 @@ UnembedArgs unembed_args(const mtpc_head* hd) {
 void split_scratch(const mtpc_head* hd, const Plan& p, UnembedArgs& u) {
   if (!p.has_split) return;
   char* ws = (char*)hd->workspace;
-  u.Wq = ws + p.Wq; u.hq = ws + p.hq; u.wild = (int*)(ws + p.wild); u.three = 1;
+  u.Wq = ws + p.Wq; u.hq = ws + p.hq; u.wild = (int*)(ws + p.wild); u.three = 1; u.cleared = 1;      // (launch_params)
 }
 
-// the stage-major copy of h into the workspace (when the plan has room for it) and into the arguments
-hipError_t stage_major_h(const mtpc_head* hd, bool have, size_t off, UnembedArgs& u, hipStream_t st) {
-  if (!have) return hipSuccess;
-  const int esz = hd->dtype == MTPC_BF16 ? 2 : 4;
-  void* dst = (char*)hd->workspace + off;
-  u.hs = dst;
-  return launch_pack_rows(hd->h, dst, 1, hd->B, hd->d * esz, (long long)hd->ld_h * esz, H_STAGE_BYTES, st);
+// what a call's parameters are computed from; and the stage-major copy of h, where `hs` is its place
+ParamArgs param_args(const mtpc_head* hd, void* hs) {
+  ParamArgs g{};
+  g.h = hd->h; g.ld_h = hd->ld_h; g.B = hd->B; g.d = hd->d; g.r = hd->r;
+  g.hs = hs; g.row_bytes = hd->d * (hd->dtype == MTPC_BF16 ? 2 : 4);
+  return g;
 }
 
-// sum-unit parameters shared by all ops
+// The parameters shared by all ops - sum units, sum layers -, the stage-major copy of h, and the flag of the fp32 terms: one launch, and one
+// more for layers computed from h.
 // `draws` (sampling calls of a few positions): the launch that computes the sum units goes on to
 // draw the latents, after the layers those draws read; returns with *draws_done set then.
 // `own_sumunit`: the consumer computes its sum units itself (verification of a few positions).
@@ -319,16 +319,11 @@ mtpc_status launch_params(int family, const mtpc_head* hd, const mtpc_sumlayers*
                           bool* draws_done = nullptr, bool own_sumunit = false, ParamArgs* later = nullptr) {
   char* ws = (char*)hd->workspace;
   nat = nat && p.has_nat;
-  if (later) {
-    later->h = hd->h; later->ld_h = hd->ld_h; later->B = hd->B; later->d = hd->d; later->r = hd->r;
-    if (family != MTPC_FF) { later->Wsum = hd->Wsum; later->logw = (float*)(ws + p.logw); }
-    own_sumunit = true;
-  }
   const bool fuse = draws != nullptr && family != MTPC_FF && hd->B <= SUMUNIT_SMALL_B;
   if (draws_done) *draws_done = fuse;
-  if (family != MTPC_FF && !fuse && !own_sumunit)
-    HIP_TRY(launch_sumunit(hd->h, hd->ld_h, hd->Wsum, hd->B, hd->d, hd->r, hd->dtype,
-                           (float*)(ws + p.logw), st));
+  ParamArgs g = param_args(hd, p.has_hs ? ws + p.hs : nullptr);
+  if (family != MTPC_FF && !fuse && !own_sumunit) { g.Wsum = hd->Wsum; g.logw = (float*)(ws + p.logw); }
+  if (p.has_split) { g.clear = (int*)(ws + p.wild); g.nclear = 1; }
   const int L = n_layers(family, hd->n);
   if (L > 0 && ly->R != nullptr) {
     CtxLayerArgs c{};
@@ -340,18 +335,22 @@ mtpc_status launch_params(int family, const mtpc_head* hd, const mtpc_sumlayers*
     c.out_tr = (circ && family == MTPC_BTREE) ? (float*)(ws + p.lay_circ) : nullptr;
     if (c.out_nat || c.out_tr) HIP_TRY(launch_ctx_layers(c, hd->dtype, st));
   } else if (L > 0) {
-    float* out_nat = nat ? (float*)(ws + p.lay_nat) : nullptr;
-    float* out_tr = (circ && family == MTPC_BTREE) ? (float*)(ws + p.lay_circ) : nullptr;
-    if (later && (out_nat || out_tr)) {
-      later->logits = ly->logits; later->layer_stride = ly->layer_stride; later->batch_stride = ly->batch_stride;
-      later->nb = p.nb; later->L = p.Lst; later->out_nat = out_nat; later->out_tr = out_tr;
-    } else {
-      HIP_TRY(launch_normalise_layers(ly->logits, ly->layer_stride, ly->batch_stride, p.nb, p.Lst, hd->r,
-                                      out_nat, out_tr, st));
+    g.out_nat = nat ? (float*)(ws + p.lay_nat) : nullptr;
+    g.out_tr = (circ && family == MTPC_BTREE) ? (float*)(ws + p.lay_circ) : nullptr;
+    if (g.out_nat || g.out_tr) {
+      g.logits = ly->logits; g.layer_stride = ly->layer_stride; g.batch_stride = ly->batch_stride;
+      g.nb = p.nb; g.L = p.Lst;
     }
   }
-  if (fuse)
-    HIP_TRY(launch_sumunit_latents(hd->h, hd->ld_h, hd->Wsum, hd->d, hd->dtype, (float*)(ws + p.logw), *draws, st));
+  // (a batch this small has neither a copy of h nor terms in its plan)
+  const bool together = fuse && sumunit_latents_layers(hd->r, g.nb, g.L) && !g.hs && !g.clear;
+  if (later) *later = g;
+  else if (!together) HIP_TRY(launch_call_params(g, hd->dtype, st));
+  if (fuse) {
+    if (!together) g.L = 0;
+    g.Wsum = hd->Wsum; g.logw = (float*)(ws + p.logw);
+    HIP_TRY(launch_sumunit_latents(g, hd->dtype, *draws, st));
+  }
   return MTPC_OK;
 }
 
@@ -385,7 +384,7 @@ mtpc_status run_evidence_op(int family, const mtpc_head* hd, const mtpc_sumlayer
   UnembedArgs u = unembed_args(hd);
   u.targets = targets; u.T = 1; u.e = (float*)(ws + p.e);
   split_scratch(hd, p, u);
-  HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, u, st));
+  if (p.has_hs) u.hs = ws + p.hs;
   {
     ProfScope prof(st);
     HIP_TRY(few ? launch_unembed_few(u, beside, hd->dtype, st) : launch_unembed(u, hd->dtype, st));
@@ -431,7 +430,7 @@ mtpc_status run_univariate(int family, const mtpc_head* hd, const mtpc_sumlayers
   if (family == MTPC_FF || p.has_table) {
     if (!few) {
       split_scratch(hd, p, t);
-      HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, t, st));
+      if (p.has_hs) t.hs = ws + p.hs;
       ProfScope prof(st);
       HIP_TRY(launch_unembed(t, hd->dtype, st));
     }
@@ -473,7 +472,7 @@ mtpc_status run_sample(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
   // fused pass with the drafts as targets.
   //   Rows      - k_rows_logits on the n slabs a draft needs, k_draw_table on the compact result
   enum class Draw { InKernel, Buckets, FromTable, Rows };
-  const void* hs_ready = nullptr;            // the stage-major copy of h, once a launch of this call has made it
+  const void* const hs = p.has_hs ? ws + p.hs : nullptr;
   const size_t esz = hd->dtype == MTPC_BF16 ? 2 : 4;
   const bool span_ok = (unsigned long long)hd->B * (unsigned long long)hd->ld_h * esz <= 0xffffffffull;
   const Draw draw = (!want_prefix && !logphi && few_drafts(hd, S)) ? Draw::Rows
@@ -536,8 +535,7 @@ mtpc_status run_sample(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
   } else {
     UnembedArgs u = unembed_args(hd);
     u.logphi = table;
-    HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, u, st));
-    hs_ready = u.hs;
+    u.hs = hs;
     if (draw == Draw::InKernel) {
       u.zleaf = la.zleaf; u.S = S; u.drafts = drafts;
       u.seed_lo = seed_lo; u.seed_hi = seed_hi; u.offset = offset; u.greedy = greedy;
@@ -557,8 +555,7 @@ mtpc_status run_sample(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
   if (want_prefix && !table_scores) {
     UnembedArgs u2 = unembed_args(hd);
     u2.targets = drafts; u2.T = S; u2.e = (float*)(ws + p.e);
-    if (hs_ready != nullptr) u2.hs = hs_ready;
-    else HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, u2, st));
+    u2.hs = hs;
     ProfScope prof(st);
     HIP_TRY(launch_unembed(u2, hd->dtype, st));
   }
@@ -591,7 +588,7 @@ mtpc_status run_window_scores(int family, const mtpc_head* hd, const mtpc_sumlay
   UnembedArgs u = unembed_args(hd);
   u.targets = x; u.T = T; u.targets2 = x2; u.T2 = T2; u.e = (float*)(ws + p.e);
   split_scratch(hd, p, u);
-  HIP_TRY(stage_major_h(hd, p.has_hs, p.hs, u, st));
+  if (p.has_hs) u.hs = ws + p.hs;
   {
     ProfScope prof(st);
     HIP_TRY(few ? launch_unembed_few(u, beside, hd->dtype, st) : launch_unembed(u, hd->dtype, st));
@@ -634,8 +631,10 @@ mtpc_status run_verify(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
   const int L = n_layers(family, hd->n);
   // a few positions: each position's workgroup computes its own sum units
   const bool own = family != MTPC_FF && hd->B <= SUMUNIT_SMALL_B;
+  // ... and, where its layers fit beside each other in LDS, normalises those itself
+  const bool in_lds = verify_rows(family, hd->B, hd->n, hd->r, p.Lst, hd->v), raw = in_lds && L > 0 && ly->R == nullptr;
   if (mode == MTPC_VERIFY_SAMPLING) {
-    s = launch_params(family, hd, ly, p, true, family == MTPC_BTREE, st, nullptr, nullptr, own);
+    s = launch_params(family, hd, ly, p, !raw, family == MTPC_BTREE && !in_lds, st, nullptr, nullptr, own);
     if (s != MTPC_OK) return s;
   }
   VerifyArgs a{};
@@ -643,8 +642,9 @@ mtpc_status run_verify(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
   a.logphi = logphi; a.drafts = drafts; a.prefix = prefix_logq; a.p = pver;
   a.logw = (family == MTPC_FF || own) ? nullptr : (const float*)(ws + p.logw);
   if (own) { a.h = hd->h; a.ld_h = hd->ld_h; a.Wsum = hd->Wsum; a.d = hd->d; a.bf16 = hd->dtype == MTPC_BF16; }
-  a.lay_nat = L > 0 ? (const float*)(ws + p.lay_nat) : nullptr;
-  a.lay_tr = (L > 0 && family == MTPC_BTREE) ? (const float*)(ws + p.lay_circ) : nullptr;
+  a.lay_nat = L > 0 && !raw ? (const float*)(ws + p.lay_nat) : nullptr;
+  a.lay_tr = (L > 0 && family == MTPC_BTREE && !in_lds) ? (const float*)(ws + p.lay_circ) : nullptr;
+  if (raw) { a.raw = ly->logits; a.raw_layer_stride = ly->layer_stride; a.raw_batch_stride = ly->batch_stride; }
   a.L = p.Lst; a.contextual = p.nb > 1;
   a.seed_lo = (uint32_t)(seed & 0xffffffffu); a.seed_hi = (uint32_t)(seed >> 32); a.offset = offset;
   a.accepted = accepted; a.token = token;
@@ -816,8 +816,8 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   const long long rr = (long long)hd->r * hd->r;
 
   // ---- parameters and forward pass
-  if (family != MTPC_FF)
-    HIP_TRY(launch_sumunit(hd->h, hd->ld_h, hd->Wsum, hd->B, hd->d, hd->r, hd->dtype, (float*)(ws + q.logw), st));
+  ParamArgs pr = param_args(hd, q.has_hs ? ws + q.hs : nullptr);
+  if (family != MTPC_FF) { pr.Wsum = hd->Wsum; pr.logw = (float*)(ws + q.logw); }
   if (ctx) {
     CtxLayerArgs cl{};
     cl.h = hd->h; cl.ld_h = hd->ld_h; cl.R = ly->R; cl.R_layer_stride = ly->R_layer_stride;
@@ -825,12 +825,10 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
     cl.B = hd->B; cl.d = hd->d; cl.r = hd->r; cl.L = q.Lst;
     cl.out_nat = (float*)(ws + q.lay_nat); cl.out_tr = nullptr;
     HIP_TRY(launch_ctx_layers(cl, hd->dtype, st));
-  } else if (q.perpos) {
-    HIP_TRY(launch_normalise_layers(ly->logits, ly->layer_stride, ly->batch_stride, hd->B, q.Lst, hd->r,
-                                    (float*)(ws + q.lay_nat), nullptr, st));
   } else if (L > 0) {
-    HIP_TRY(launch_normalise_layers(ly->logits, ly->layer_stride, 0, 1, q.Lst, hd->r,
-                                    (float*)(ws + q.lay_nat), (float*)(ws + q.lay_tr), st));
+    pr.logits = ly->logits; pr.layer_stride = ly->layer_stride; pr.batch_stride = q.perpos ? ly->batch_stride : 0;
+    pr.nb = q.perpos ? hd->B : 1; pr.L = q.Lst;
+    pr.out_nat = (float*)(ws + q.lay_nat); pr.out_tr = q.perpos ? nullptr : (float*)(ws + q.lay_tr);
   }
   UnembedArgs u = unembed_args(hd);
   u.targets = targets; u.T = 1; u.e = (float*)(ws + q.e);
@@ -845,11 +843,12 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   float* const most = q.split ? (float*)(rows + q.M) : nullptr;                    // per position: its largest gradient (not cleared)
   const int nflags = q.split ? (int)(4 + 2 * (q.ldb + hd->d) + q.M) : 0;
   if (q.split_fwd) {
-    HIP_TRY(launch_clear(flag, nflags, st));
+    pr.clear = flag; pr.nclear = nflags;
     u.Wq = ws + q.WT; u.Wq_rows = (int)q.ldM; u.Wexp = wexp; u.cols = cols;
     u.hq = ws + q.hq; u.wild = flag; u.cleared = 1; u.three = 1;
   }
-  HIP_TRY(stage_major_h(hd, q.has_hs, q.hs, u, st));
+  HIP_TRY(launch_call_params(pr, hd->dtype, st));
+  if (q.has_hs) u.hs = ws + q.hs;
   HIP_TRY(launch_unembed(u, hd->dtype, st));
 
   // ---- reverse pass through the circuit

@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "mtpc_internal.h"
+#include "rowops.h"
 #include "sumunit.h"
 
 namespace mtpc {
@@ -31,7 +32,8 @@ __device__ __forceinline__ int first_nan_position(const float* e, int n, int r, 
   return group_min(fb, G);
 }
 
-__device__ void draft_latents(const LatentArgs& a, int b, int s, const float* lw, int lane);
+template <bool RAW = false>
+__device__ __forceinline__ void draft_latents(const LatentArgs& a, int b, int s, const float* lw, const float* lay, int lane);
 
 // ---------------------------------------------------------------------------
 // log omega[b,:] = log_softmax(Wsum h[b])   (Sec. 3.3, sum unit parameters)
@@ -40,60 +42,74 @@ __device__ void draft_latents(const LatentArgs& a, int b, int s, const float* lw
 // computed (Alg. 1, top-down; one wave per draft) - one launch and one dependent round trip less
 // on the decode path.  Many positions go through the MFMA tile kernel instead.
 // ---------------------------------------------------------------------------
+// Beside them, or alone (no Wsum), the other parameters of the call.
+// ---------------------------------------------------------------------------
 template <bool BF16>
-__global__ __launch_bounds__(1024) void k_sumunit(const void* h, long long ld_h, const void* Wsum,
-                                                  int B, int d, int r, float* logw, const LatentArgs la) {
+__global__ __launch_bounds__(1024) void k_sumunit(const ParamArgs p, const LatentArgs la) {
   __shared__ float sc[128];
   const int b = blockIdx.x;
-  sumunit_position<BF16, 16>(h, ld_h, Wsum, b, d, r, sc);
-  if ((int)threadIdx.x < r) logw[(long long)b * r + threadIdx.x] = sc[threadIdx.x];
-  if (la.zleaf != nullptr)
-    for (int s = threadIdx.x >> 6; s < la.S; s += 16) draft_latents(la, b, s, sc, threadIdx.x & 63);
+  if (b >= p.B) {
+    params_beside<1024>(p, b - p.B);
+    return;
+  }
+  sumunit_position<BF16, 16>(p.h, p.ld_h, p.Wsum, b, p.d, p.r, sc);
+  if ((int)threadIdx.x < p.r) p.logw[(long long)b * p.r + threadIdx.x] = sc[threadIdx.x];
+  if (la.zleaf == nullptr) return;
+  const float* lay = la.layers;
+  if (la.contextual && lay) lay += (long long)b * la.L * p.r * p.r;
+  for (int s = threadIdx.x >> 6; s < la.S; s += 16) draft_latents(la, b, s, sc, lay, threadIdx.x & 63);
 }
 
-static hipError_t launch_sumunit_small(const void* h, long long ld_h, const void* Wsum, int B, int d, int r,
-                                       int dtype, float* logw, const LatentArgs& la, hipStream_t st) {
-  dim3 grid(B), block(1024);
-  if (dtype == MTPC_BF16)
-    hipLaunchKernelGGL(k_sumunit<true>, grid, block, 0, st, h, ld_h, Wsum, B, d, r, logw, la);
-  else
-    hipLaunchKernelGGL(k_sumunit<false>, grid, block, 0, st, h, ld_h, Wsum, B, d, r, logw, la);
+// The same where the draws read layers shared by all positions that no launch has normalised yet: a workgroup stages their logits in
+// LDS and normalises the few rows that its draws meet (all of them would take it 8 us).  The copies that later launches read
+// are made beside.
+template <bool BF16>
+__global__ __launch_bounds__(1024) void k_sumunit_layers(const ParamArgs p, const LatentArgs la) {
+  extern __shared__ __align__(16) float s_lay[];         // [L][k][j]
+  __shared__ float sc[128];
+  const int b = blockIdx.x, tid = threadIdx.x, rr = p.r * p.r;
+  if (b >= p.B) {
+    params_beside<1024>(p, b - p.B);
+    return;
+  }
+  for (int l = 0; l < p.L; ++l)
+    for (int q = tid; q < rr; q += 1024) s_lay[l * rr + q] = p.logits[l * p.layer_stride + q];
+  sumunit_position<BF16, 16>(p.h, p.ld_h, p.Wsum, b, p.d, p.r, sc);
+  if (tid < p.r) p.logw[(long long)b * p.r + tid] = sc[tid];
+  for (int s = tid >> 6; s < la.S; s += 16) draft_latents<true>(la, b, s, sc, s_lay, tid & 63);
+}
+__global__ __launch_bounds__(256) void k_params(const ParamArgs p) { params_beside<256>(p, blockIdx.x); }
+
+static hipError_t launch_sumunit_small(const ParamArgs& p, int dtype, const LatentArgs& la, hipStream_t st) {
+  const dim3 grid((unsigned)(p.B + param_blocks(p, 1024))), block(1024);
+  if (dtype == MTPC_BF16) hipLaunchKernelGGL(k_sumunit<true>, grid, block, 0, st, p, la);
+  else hipLaunchKernelGGL(k_sumunit<false>, grid, block, 0, st, p, la);
   return hipGetLastError();
 }
 
-hipError_t launch_sumunit(const void* h, long long ld_h, const void* Wsum, int B, int d, int r,
-                          int dtype, float* logw, hipStream_t st) {
-  if (B > SUMUNIT_SMALL_B) return launch_sumunit_mfma(h, ld_h, Wsum, B, d, r, dtype, logw, st);
-  LatentArgs none{};
-  return launch_sumunit_small(h, ld_h, Wsum, B, d, r, dtype, logw, none, st);
-}
-
-// sum units and latent draws in one launch (B <= SUMUNIT_SMALL_B, a family with sum units; the
-// normalised layers the draws of the HMM / binary tree read must be complete before it)
-hipError_t launch_sumunit_latents(const void* h, long long ld_h, const void* Wsum, int d, int dtype, float* logw,
-                                  const LatentArgs& la, hipStream_t st) {
-  return launch_sumunit_small(h, ld_h, Wsum, la.B, d, la.r, dtype, logw, la, st);
-}
-
-// ---------------------------------------------------------------------------
-// softmax over the last axis of every r x r sum layer -> linear probabilities
-// one wave per sum unit (row k of layer l of position-block b); the natural copy
-// [k][j], the transposed one [j][k], or both from one launch
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_normalise_layers(const float* logits, long long ls,
-                                                          long long bs, int nb, int L, int r,
-                                                          float* out_nat, float* out_tr) {
-  const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row < (long long)nb * L * r) normalise_layer_row(logits, ls, bs, row, L, r, out_nat, out_tr);
-}
-
-hipError_t launch_normalise_layers(const float* logits, long long layer_stride, long long batch_stride,
-                                   int nb, int L, int r, float* out_nat, float* out_tr, hipStream_t st) {
-  const long long nrows = (long long)nb * L * r;
-  if (nrows == 0 || (!out_nat && !out_tr)) return hipSuccess;
-  hipLaunchKernelGGL(k_normalise_layers, dim3((unsigned)((nrows + 3) / 4)), dim3(256), 0, st, logits,
-                     layer_stride, batch_stride, nb, L, r, out_nat, out_tr);
+hipError_t launch_call_params(const ParamArgs& p, int dtype, hipStream_t st) {
+  if (p.Wsum != nullptr) {
+    if (p.B > SUMUNIT_SMALL_B) return launch_params_mfma(p, dtype, st);
+    LatentArgs none{};
+    return launch_sumunit_small(p, dtype, none, st);
+  }
+  const long long blocks = param_blocks(p, 256);
+  if (blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_params, dim3((unsigned)blocks), dim3(256), 0, st, p);
   return hipGetLastError();
+}
+
+template <bool BF16>
+static hipError_t launch_sumunit_layers(const ParamArgs& p, const LatentArgs& la, hipStream_t st) {
+  constexpr auto kern = k_sumunit_layers<BF16>;
+  if (hipError_t e = allow_lds<kern>(128 * 1024); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.B + param_blocks(p, 1024))), dim3(1024), (size_t)p.L * p.r * p.r * 4, st, p, la);
+  return hipGetLastError();
+}
+
+hipError_t launch_sumunit_latents(const ParamArgs& p, int dtype, const LatentArgs& la, hipStream_t st) {
+  if (p.L > 0) return dtype == MTPC_BF16 ? launch_sumunit_layers<true>(p, la, st) : launch_sumunit_layers<false>(p, la, st);
+  return launch_sumunit_small(p, dtype, la, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -815,12 +831,9 @@ static hipError_t launch_btree_static(const CircuitArgs& a, hipStream_t st) {
 // G: r rounded up to a power of two, at least 8.
 // LDS: see circuit_row_smem.
 // ---------------------------------------------------------------------------
-constexpr int ROW_SCALE = 64;      // the HMM's values sum to 2^64 .. 2^65: what is kept of a unit reaches 2^-149 and no result overflows
 // P: parts.  One where rows outnumber the CUs and a product is small: a wave then forms 64 / G of them side by side.
 template <int G, int P>
 __global__ __launch_bounds__(1024) void k_circuit_row(const CircuitArgs a) {
-  constexpr int JP = G / P;
-  static_assert(P == 64 / G || P == 1, "a wave, or groups of G lanes, to a product");
   extern __shared__ __align__(16) float rsm[];
   const int n = a.n, r = a.r, tid = threadIdx.x, NT = blockDim.x, NW = NT / (G * P);
   const int lane = tid % (G * P), wave = tid / (G * P), k = tid % G, part = lane / G;      // (wave: or group of lanes)
@@ -841,124 +854,65 @@ __global__ __launch_bounds__(1024) void k_circuit_row(const CircuitArgs a) {
   const float ninf = neg_inf();
   const bool live = k < r;
 
-  // ---- everything into LDS
+  // ---- everything into LDS, the evidence of the first tokens looked up while layers are on their way
   const float* lay = a.layers;
   if (a.contextual && lay) lay += pos * (long long)Lst * r * r;
-  const int nlay = Lst * r * r;
-  if ((nlay & 3) == 0 && (((size_t)lay) & 15) == 0) {
-    const f32x4_t* src = (const f32x4_t*)lay;
-    f32x4_t* dst = (f32x4_t*)s_lay;
-    const int nq = nlay >> 2;
-    for (int t0 = 0; t0 < nq; t0 += 4 * NT) {
-      f32x4_t tmp[4];
+  const int nlay = Lst * r * r, gi = tid / G, step = NT / G, kc = min(k, r - 1);          // groups of G lanes take a token each
+  auto token = [&](int i) { return a.table != nullptr ? a.x[row * n + min(i, n - 1)] : 0; };
+  auto evidence = [&](int i, int x) {
+    i = min(i, n - 1);
+    if (a.table == nullptr) return a.e[(row * n + i) * r + kc];
+    const float t = a.table[((pos * n + i) * r + kc) * a.v + min(max(x, 0), a.v - 1)];
+    return x >= 0 && x < a.v ? t : x == -1 ? 0.f : __builtin_nanf("");
+  };
+  const bool vec = (nlay & 3) == 0 && (((size_t)lay) & 15) == 0;
+  const f32x4_t* const src = (const f32x4_t*)lay;
+  f32x4_t* const dst = (f32x4_t*)s_lay;
+  const int nq = vec ? nlay >> 2 : 0;
+  const float lw0 = a.logw != nullptr && live ? a.logw[pos * r + k] : ninf;
+  const int x0 = token(gi), x1 = token(gi + step);
+  f32x4_t tmp[8];
+  auto load = [&](int t0) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) tmp[u] = src[min(t0 + u * NT + tid, nq - 1)];
+    for (int u = 0; u < 8; ++u) tmp[u] = src[min(t0 + u * NT + tid, nq - 1)];
+  };
+  auto put = [&](int t0) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (t0 + u * NT + tid < nq) dst[t0 + u * NT + tid] = tmp[u];
-    }
-  } else {
-    for (int t0 = 0; t0 < nlay; t0 += 8 * NT) {
-      float tmp[8];
+    for (int u = 0; u < 8; ++u)
+      if (t0 + u * NT + tid < nq) dst[t0 + u * NT + tid] = tmp[u];
+  };
+  if (nq > 0) load(0);
+  const float e0 = evidence(gi, x0), e1 = evidence(gi + step, x1);
+  if (nq > 0) {
+    put(0);
+    for (int t0 = 8 * NT; t0 < nq; t0 += 8 * NT) { load(t0); put(t0); }
+  }
+  for (int t0 = 0; !vec && t0 < nlay; t0 += 8 * NT) {
+    float one[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) tmp[u] = lay[min(t0 + u * NT + tid, nlay - 1)];
+    for (int u = 0; u < 8; ++u) one[u] = lay[min(t0 + u * NT + tid, nlay - 1)];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (t0 + u * NT + tid < nlay) s_lay[t0 + u * NT + tid] = tmp[u];
-    }
+    for (int u = 0; u < 8; ++u)
+      if (t0 + u * NT + tid < nlay) s_lay[t0 + u * NT + tid] = one[u];
   }
   if (tid == 0) *s_bad = n;
-  const float lw0 = a.logw != nullptr && live ? a.logw[pos * r + k] : ninf;
-  const int step = NT / G;                               // groups of G lanes take a token each
-  for (int i = tid / G; i < n; i += step) {
-    if (!live) continue;
-    float e;
-    if (a.table != nullptr) {
-      const int x = a.x[row * n + i];
-      if (x >= 0 && x < a.v) e = a.table[((pos * n + i) * r + k) * a.v + x];
-      else e = x == -1 ? 0.f : __builtin_nanf("");
-    } else {
-      e = a.e[(row * n + i) * r + k];
-    }
-    s_ev[i * r + k] = e;
+  if (live && gi < n) s_ev[gi * r + k] = e0;
+  if (live && gi + step < n) s_ev[(gi + step) * r + k] = e1;
+  for (int i = gi + 2 * step; i < n; i += step) {
+    const float e = evidence(i, token(i));
+    if (live) s_ev[i * r + k] = e;
   }
   __syncthreads();
   // an id outside [-1, v) leaves NaN in every unit of its window position: poison what observes it
   for (int i = tid; i < n; i += NT)
     if (s_ev[i * r] != s_ev[i * r]) atomicMin(s_bad, i);
 
-  // ---- reductions over the G units (every lane gets the result), and over the parts of an output
-  auto both16 = [](float x, float& p, float& q) {
-    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    p = __uint_as_float(t[0]); q = __uint_as_float(t[1]);
-  };
-  auto both32 = [](float x, float& p, float& q) {
-    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    p = __uint_as_float(t[0]); q = __uint_as_float(t[1]);
-  };
-  auto over_units = [&](float x, auto op) {
-    x = op(x, __int_as_float(dpp_move<0xB1>(__float_as_int(x))));     // (as group_reduce)
-    x = op(x, __int_as_float(dpp_move<0x4E>(__float_as_int(x))));
-    x = op(x, __int_as_float(dpp_move<0x141>(__float_as_int(x))));
-    if constexpr (G >= 16) x = op(x, __int_as_float(dpp_move<0x140>(__float_as_int(x))));
-    if constexpr (G >= 32) { float p, q; both16(x, p, q); x = op(p, q); }
-    if constexpr (G >= 64) { float p, q; both32(x, p, q); x = op(p, q); }
-    return x;
-  };
-  auto sum_units = [&](float x) { return over_units(x, [](float y, float z) { return y + z; }); };
-  auto max_units = [&](float x) { return over_units(x, [](float y, float z) { return fmaxf(y, z); }); };
-  auto sum_parts = [&](float x) {
-    if constexpr (P > 1) {
-      if constexpr (G <= 8) x += __int_as_float(dpp_move<0x128>(__float_as_int(x)));    // row_ror:8
-      if constexpr (G <= 16) { float p, q; both16(x, p, q); x = p + q; }
-      if constexpr (G <= 32) { float p, q; both32(x, p, q); x = p + q; }
-    }
-    return x;
-  };
+  using Ops = RowOps<G, P>;
+  auto sum_units = [](float x) { return Ops::sum_units(x); };
+  auto max_units = [](float x) { return Ops::max_units(x); };
   float* const xs = s_x + wave * (G * P);
-  // this lane's share of a layer (what multiplies no unit: any), in registers before the operand is there; 64 units: from LDS beside it
-  constexpr bool AHEAD = JP <= 16;
-  struct Weights { float w[AHEAD ? JP : 1]; const float* p; };
-  auto weights = [&](const float* Wl) {
-    Weights o;
-    o.p = Wl + min(k, r - 1);
-    if constexpr (AHEAD) {
-#pragma unroll
-      for (int u = 0; u < JP; ++u) o.w[u] = o.p[min(part + P * u, r - 1) * r];
-    }
-    return o;
-  };
-  // sum_j x_j W[j][k]; x is this lane's unit k's, 0 for k >= r
-  auto product = [&](float x, const Weights& w) {
-    if (part == 0) xs[(k % P) * JP + k / P] = x;
-    __builtin_amdgcn_wave_barrier();
-    constexpr int C = JP < 4 ? JP : 4, U = JP < 16 ? JP : 16;          // sums side by side; terms at a time
-    float acc[C];
-#pragma unroll
-    for (int c = 0; c < C; ++c) acc[c] = 0.f;
-#pragma unroll 1
-    for (int u0 = 0; u0 < JP; u0 += U) {
-      float xv[U], wv[U];
-#pragma unroll
-      for (int u = 0; u < U; u += C) {
-        if constexpr (C == 4) {
-          const f32x4_t t = *(const f32x4_t*)(xs + part * JP + u0 + u);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) xv[u + c] = t[c];
-        } else {
-          xv[u] = xs[part * JP + u0 + u];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) wv[u] = AHEAD ? w.w[AHEAD ? u : 0] : w.p[min(part + P * (u0 + u), r - 1) * r];
-#pragma unroll
-      for (int u = 0; u < U; ++u) acc[u % C] = fmaf(xv[u], wv[u], acc[u % C]);
-    }
-    __builtin_amdgcn_wave_barrier();
-    float y = acc[0];
-    if constexpr (C == 4) y = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-    return sum_parts(y);
-  };
+  auto weights = [&](const float* Wl) { return Ops::weights(Wl, k, part, r, r, 1); };
+  auto product = [&](float x, const typename Ops::Weights& w) { return Ops::product(x, w, xs, k, part, r, r); };
   auto emit = [&](int i, float v) {                      // (by one lane)
     if (i >= *s_bad) v = __builtin_nanf("");
     if (a.prefix) a.out[row * n + i] = v;
@@ -1000,7 +954,7 @@ __global__ __launch_bounds__(1024) void k_circuit_row(const CircuitArgs a) {
     const float lm = max_units(lw0), lms = lm == ninf ? 0.f : lm;
     float x = live ? __builtin_amdgcn_ldexpf(expf(lw0 - lms), ROW_SCALE) : 0.f;
     int E = -ROW_SCALE;
-    Weights w{};
+    typename Ops::Weights w{};
     if (n > 1) w = weights(s_lay);
     for (int i = 0; i < n; ++i) {
       const int ic = i * r + min(k, r - 1);
@@ -1010,24 +964,11 @@ __global__ __launch_bounds__(1024) void k_circuit_row(const CircuitArgs a) {
         y = product(x, w);
         if (i < n - 1) w = weights(s_lay + (size_t)i * lstep);
       }
-      float c = live ? y * ew : 0.f;
-      float s = sum_units(c);
-      if (s < 0x1p34f) {
-        // the units that are left have next to none of the evidence (or none: all results from here on are -inf): exponentials
-        // relative to the largest product
-        const float l = live && y > 0.f ? logf(y) + s_ev[ic] : ninf;
-        const float lmax = max_units(l);
-        if (lmax != ninf) {
-          c = __builtin_amdgcn_ldexpf(expf(l - lmax), ROW_SCALE);
-          s = sum_units(c);
-          E -= ROW_SCALE;
-          if (lane == 0) s_max[i] = lmax;
-        }
-      }
-      if (lane == 0) { s_sum[i] = s; s_exp[i] = E; }
-      const int sh = s > 0.f ? ROW_SCALE + 1 - __builtin_amdgcn_frexp_expf(s) : 0;
-      x = __builtin_amdgcn_ldexpf(c, sh);
-      E -= sh;
+      float s, taken = s_max[i];
+      int shift;
+      x = observe<Ops>(y, ew, s_ev[ic], live, s, E, shift, taken);
+      if (lane == 0) { s_sum[i] = s; s_exp[i] = E; s_max[i] = taken; }
+      E -= shift;
     }
     __builtin_amdgcn_wave_barrier();
     if (lane < n) {
@@ -1044,7 +985,7 @@ __global__ __launch_bounds__(1024) void k_circuit_row(const CircuitArgs a) {
   __syncthreads();
   // c_k <- log sum_j W[j][k] exp(c_j)
   auto sum_layer = [&](float c, int m) {
-    const Weights w = weights(s_lay + (size_t)(m - 1) * lstep);
+    const typename Ops::Weights w = weights(s_lay + (size_t)(m - 1) * lstep);
     const float mx = max_units(c);
     const float y = product(live ? __expf(c - (mx == ninf ? 0.f : mx)) : 0.f, w);
     return live ? mx + __logf(y) : ninf;                 // -inf + log 0 = -inf
@@ -1165,10 +1106,8 @@ hipError_t launch_circuit(const CircuitArgs& a, hipStream_t st) {
 // last unit with positive weight.  The result is wave-uniform, so the next sum
 // unit's row is again one coalesced load.
 // ---------------------------------------------------------------------------
-// Inclusive scan over the 64 lanes in double.  Inside a row of 16 lanes the four steps are DPP
-// row shifts (lanes without a source read zero), then the row totals travel over the LDS crossbar:
-// the last lane of the previous row, and after that the last lane of the row before it, which by
-// then holds the total of two rows.
+// Inclusive scan over the first r (64 at most) of the 64 lanes in double.  Inside a row of 16 lanes the four steps are DPP
+// row shifts (lanes without a source read zero); the rows' totals come back as scalars, none where r does not reach beyond the first row.
 template <int CTRL>
 __device__ __forceinline__ double dpp_move_f64(double x) {
   const long long v = __double_as_longlong(x);
@@ -1176,25 +1115,34 @@ __device__ __forceinline__ double dpp_move_f64(double x) {
   const unsigned hi = (unsigned)dpp_move<CTRL>((int)(unsigned)((unsigned long long)v >> 32));
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
-__device__ __forceinline__ double wave_scan_incl(double x, int lane) {
+__device__ __forceinline__ double readlane_f64(double x, int lane) {
+  const long long v = __double_as_longlong(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v & 0xffffffffll), lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)((unsigned long long)v >> 32), lane);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_scan_incl(double x, int lane, int r) {
   x += dpp_move_f64<0x111>(x);      // row_shr:1
   x += dpp_move_f64<0x112>(x);      // row_shr:2
   x += dpp_move_f64<0x114>(x);      // row_shr:4
   x += dpp_move_f64<0x118>(x);      // row_shr:8
+  if (r <= 16) return x;
+  // the row before first, then the sum of those before that
   const int row = lane >> 4;
-  const double t1 = __shfl(x, max(16 * row - 1, 0));
-  if (row >= 1) x += t1;
-  const double t2 = __shfl(x, max(16 * row - 17, 0));
-  if (row >= 2) x += t2;
+  const double t0 = readlane_f64(x, 15);
+  if (r <= 32) return row == 1 ? x + t0 : x;
+  const double t1 = readlane_f64(x, 31), t2 = readlane_f64(x, 47);
+  if (row >= 1) x += row == 1 ? t0 : row == 2 ? t1 : t2;
+  if (row >= 2) x += row == 2 ? t0 : t1 + t0;
   return x;
 }
 __device__ __forceinline__ int wave_draw(float p0, float p1, int r, float u, int lane) {
   const bool in0 = lane < r, in1 = lane + 64 < r;
-  const double c0 = wave_scan_incl(in0 ? (double)p0 : 0.0, lane);
+  const double c0 = wave_scan_incl(in0 ? (double)p0 : 0.0, lane, r);
   unsigned long long m = __ballot(in0 && (double)u < c0);
   if (m) return __ffsll((long long)m) - 1;
   if (r > 64) {
-    const double c1 = __shfl(c0, 63) + wave_scan_incl(in1 ? (double)p1 : 0.0, lane);
+    const double c1 = __shfl(c0, 63) + wave_scan_incl(in1 ? (double)p1 : 0.0, lane, 64);
     m = __ballot(in1 && (double)u < c1);
     if (m) return 64 + __ffsll((long long)m) - 1;
     m = __ballot(in1 && p1 > 0.f);
@@ -1218,20 +1166,24 @@ __device__ __forceinline__ int wave_argmax(float p0, float p1, int r, int lane) 
   return arg;
 }
 
-// the latents of draft (b, s) by one wave; lw: the position's log omega (global or LDS)
-__device__ void draft_latents(const LatentArgs& a, int b, int s, const float* lw, int lane) {
+// the latents of draft (b, s) by one wave; lw: the position's log omega, lay: its layers (both in memory or LDS; RAW: their logits)
+template <bool RAW>
+__device__ __forceinline__ void draft_latents(const LatentArgs& a, int b, int s, const float* lw, const float* lay, int lane) {
   const long long t = (long long)b * a.S + s;
   const int n = a.n, r = a.r;
   int* zl = a.zleaf + t * n;
-  const float* lay = a.layers;
-  if (a.contextual && lay) lay += (long long)b * a.L * r * r;
   const long long lstep = (a.L > 1) ? (long long)r * r : 0;
-  auto U = [&](int lat) {
-    return philox_uniform(a.seed_lo, a.seed_hi, a.offset, (uint32_t)b, (uint32_t)s, (uint32_t)(n + lat));
-  };
-  auto draw_row = [&](const float* row, int lat) {      // row of normalised linear weights
-    const float p0 = lane < r ? row[lane] : 0.f;
-    const float p1 = lane + 64 < r ? row[lane + 64] : 0.f;
+  // (all uniforms at once, before the chain of draws that uses them: at most 64)
+  const float uniforms = philox_uniform(a.seed_lo, a.seed_hi, a.offset, (uint32_t)b, (uint32_t)s, (uint32_t)(n + lane));
+  auto U = [&](int lat) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(uniforms), lat)); };
+  auto draw_row = [&](const float* row, int lat) {      // row of normalised linear weights, or normalised here (as normalise_layer_row)
+    float p0 = lane < r ? row[lane] : RAW ? neg_inf() : 0.f;
+    float p1 = lane + 64 < r ? row[lane + 64] : 0.f;
+    if constexpr (RAW) {                                // (r <= 64)
+      const float m = group_max(p0, 64), ms = m == neg_inf() ? 0.f : m;
+      const float e = p0 > neg_inf() ? expf(p0 - ms) : 0.f, tot = group_sum(e, 64);
+      p0 = e * (tot > 0.f ? 1.f / tot : 0.f);
+    }
     return a.greedy ? wave_argmax(p0, p1, r, lane) : wave_draw(p0, p1, r, U(lat), lane);
   };
   const float q0 = lane < r ? expf(lw[lane]) : 0.f, q1 = lane + 64 < r ? expf(lw[lane + 64]) : 0.f;
@@ -1253,7 +1205,7 @@ __device__ void draft_latents(const LatentArgs& a, int b, int s, const float* lw
     int* L = a.latents + t * (n - 1);
     int mine = z0;                                      // latent of node `lane` (n - 1 <= 63 nodes)
     for (int m = 1; m < n - 1; ++m) {
-      const int zp = __shfl(mine, (m - 1) >> 1);
+      const int zp = __builtin_amdgcn_readlane(mine, (m - 1) >> 1);
       const int z = draw_row(lay + (long long)(m - 1) * lstep + (long long)zp * r, m);
       if (lane == m) mine = z;
     }
@@ -1274,7 +1226,9 @@ __global__ __launch_bounds__(256) void k_latents(const LatentArgs a) {
     for (int i = lane; i < a.n; i += 64) zl[i] = 0;
     return;
   }
-  draft_latents(a, b, s, a.logw + (long long)b * a.r, lane);
+  const float* lay = a.layers;
+  if (a.contextual && lay) lay += (long long)b * a.L * a.r * a.r;
+  draft_latents(a, b, s, a.logw + (long long)b * a.r, lay, lane);
 }
 
 hipError_t launch_latents(const LatentArgs& a, hipStream_t st) {

@@ -53,20 +53,28 @@ struct UnembedArgs {
   int Wq_rows;          // > 0: the planes of W are ONE matrix of so many rows, [2 d/32][Wq_rows][64 bytes], slab after slab
 };
 
-// What a call computes from h and the layer logits alone, before its circuit: log omega (Wsum nullptr: not wanted) and the softmax
-// of shared layers (L = 0: none), as launch_sumunit and launch_normalise_layers.
+// What a call computes from h and the layer logits alone, before its circuit: log omega (Wsum nullptr: not wanted), the softmax of
+// shared layers (L = 0: none), the stage-major copy of h (hs nullptr: none), and ints set to 0 for the launches that follow.  They do not depend
+// on each other: one launch.
 struct ParamArgs {
   const void* h;
   long long ld_h;
   const void* Wsum;
   int B, d, r;
-  float* logw;          // [B][r]
+  float* logw;          // [B][r]: log omega[b][:] = log_softmax(Wsum h[b])
+  // softmax over the last axis of r x r logits -> linear probabilities.  logits[b*batch_stride + l*layer_stride + k*r + j];
+  // out_nat[((b*L + l)*r + k)*r + j] and / or the same transposed, out_tr[((b*L + l)*r + j)*r + k] (either may be nullptr)
   const float* logits;
   long long layer_stride, batch_stride;
   int nb, L;
   float* out_nat;
   float* out_tr;
+  void* hs;             // [row_bytes / 64][B][64 bytes]
+  int row_bytes;        // of h
+  int* clear;
+  long long nclear;
 };
+hipError_t launch_call_params(const ParamArgs& p, int dtype, hipStream_t st);
 
 // Univariate marginals: M[b][i][a] = log sum_j m[b][i][j] phi[b][i][j][a].
 struct UnivariateArgs {
@@ -172,17 +180,8 @@ struct Split3Job {
 hipError_t launch_split3(const Split3Job& j0, const Split3Job& j1, int* flag, int whole, hipStream_t st);
 
 // ---- small kernels (circuits.hip) -----------------------------------------
-// log omega[b][:] = log_softmax(Wsum h[b])
-hipError_t launch_sumunit(const void* h, long long ld_h, const void* Wsum, int B, int d, int r,
-                          int dtype, float* logw, hipStream_t st);
-// same result through the MFMA tile kernel (unembed.hip); used when B is large
-hipError_t launch_sumunit_mfma(const void* h, long long ld_h, const void* Wsum, int B, int d, int r,
-                               int dtype, float* logw, hipStream_t st);
-// softmax over the last axis of r x r logits -> linear probabilities.
-// in: logits[(b*bs) + l*ls + k*r + j]; out_nat[((b*L + l)*r + k)*r + j] and / or the same
-// transposed, out_tr[((b*L + l)*r + j)*r + k] (either may be nullptr).
-hipError_t launch_normalise_layers(const float* logits, long long layer_stride, long long batch_stride,
-                                   int nb, int L, int r, float* out_nat, float* out_tr, hipStream_t st);
+// launch_call_params of more than SUMUNIT_SMALL_B positions with sum units (unembed.hip)
+hipError_t launch_params_mfma(const ParamArgs& p, int dtype, hipStream_t st);
 
 struct CircuitArgs {
   int family;           // mtpc_family
@@ -219,10 +218,11 @@ struct LatentArgs {
 hipError_t launch_latents(const LatentArgs& a, hipStream_t st);
 // batches up to this many positions compute their sum units one workgroup per position
 constexpr int SUMUNIT_SMALL_B = 128;
-// the same draws in the launch that computes log omega (B <= SUMUNIT_SMALL_B, families with sum
-// units): writes logw [B][r] and the latents; the normalised layers must be complete before it
-hipError_t launch_sumunit_latents(const void* h, long long ld_h, const void* Wsum, int d, int dtype, float* logw,
-                                  const LatentArgs& a, hipStream_t st);
+// The same draws in the launch that computes log omega (B <= SUMUNIT_SMALL_B, families with sum
+// units): writes logw [B][r] and the latents.  The normalised layers a.layers must be complete before it - or (sumunit_latents_layers)
+// they come out of p.logits in the same launch, which draws from a copy in LDS and writes p.out_nat and p.out_tr; a.layers is not read then.
+hipError_t launch_sumunit_latents(const ParamArgs& p, int dtype, const LatentArgs& a, hipStream_t st);
+inline bool sumunit_latents_layers(int r, int nb, int L) { return nb == 1 && L > 0 && r <= 64 && (size_t)L * r * r * 4 <= 128 * 1024; }
 
 // log marginal of the latent that indexes each leaf: logm[b][i][j]
 struct LatentMarginalArgs {
@@ -320,13 +320,24 @@ struct VerifyArgs {
   const void* Wsum;
   int d, bf16;
   const float* lay_nat; // normalised linear layers [nb][L][k][j]
-  const float* lay_tr;  // the same transposed [nb][L][j][k] (BTree only)
+  const float* lay_tr;  // the same transposed [nb][L][j][k] (BTree only, not where verify_rows)
+  const float* raw;     // verify_rows: nullptr, or the logits of the layers, which the kernel normalises itself (no lay_nat then)
+  long long raw_layer_stride, raw_batch_stride;
   int L, contextual;
   uint32_t seed_lo, seed_hi, offset;
   int* accepted;        // [B]
   int* token;           // [B]
 };
 hipError_t launch_verify(const VerifyArgs& a, hipStream_t st);
+// Whether the verification of a few positions keeps a position's layers in LDS (k_verify_row); L: stored layers.  LDS in floats
+constexpr int VERIFY_ROW_THREADS = 1024;
+inline size_t verify_row_floats(int family, int n, int r, int L, int v) {
+  const bool lay = family == MTPC_HMM || family == MTPC_BTREE;
+  return VERIFY_ROW_THREADS * 2 + (lay ? (size_t)L * r * (r + 1) : 0) + (size_t)n * r * (lay ? 2 : 1) + n + 2 * (size_t)r + (size_t)v;
+}
+inline bool verify_rows(int family, int B, int n, int r, int L, int v) {
+  return B <= 256 && r <= 64 && verify_row_floats(family, n, r, L > 0 ? L : 0, v) * 4 <= 152 * 1024;
+}
 
 // ---- training step (grad.hip, backward.hip) ----------------------------------
 // Recompute pass: dLT[(i*r+j)*v + a][b] = Ge[b][i][j] * (1[a == x_bi] - phi[b,i,j,a]) in the

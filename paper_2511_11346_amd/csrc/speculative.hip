@@ -11,9 +11,11 @@
 //   3. one draw from max(0, p - q) / Z (or from p after n acceptances).
 // Everything is O(n r^2 + r v) per position and latency-bound; matrix-vector
 // products use all 256 threads so that every layer costs one memory round trip.
+#include <algorithm>
 #include <climits>
 
 #include "mtpc_internal.h"
+#include "rowops.h"
 #include "sumunit.h"
 
 namespace mtpc {
@@ -364,12 +366,273 @@ __global__ __launch_bounds__(256) void k_verify(const VerifyArgs a, int G) {
   }
 }
 
+// The same for a few positions (verify_rows), bound by the latency of one: whatever does not depend on the rejected position is fetched
+// before it is known - acceptance tests, evidence of all drafted tokens, sum units, and the logits of all layers, of which those that turn out
+// to be needed are then normalised in LDS (no launch for that) -, and the message to the rejected position is formed out of LDS, by one wave (HMM: linear values, as
+// in k_circuit_row) or (binary tree, observed subtrees) a wave to a node.  G as in RowOps.
+// HMM n = 16, r = 32, v = 320, B = 61: VERIFY_HMM us, CP B = 1 VERIFY_CP us.
+template <int G>
+__global__ __launch_bounds__(VERIFY_ROW_THREADS) void k_verify_row(const VerifyArgs a) {
+  using Ops = RowOps<G, 64 / G>;
+  constexpr int NT = VERIFY_ROW_THREADS, NW = NT / 64;
+  extern __shared__ __align__(16) float vsm[];
+  __shared__ float s_lw[128];
+  __shared__ int s_j;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k = lane % G, part = lane / G;
+  const int n = a.n, r = a.r, v = a.v, rs = r + 1;            // (rows of r + 1: either way through a layer meets all banks)
+  const bool hmm = a.family == MTPC_HMM, tree = a.family == MTPC_BTREE, live = k < r;
+  const int L = hmm || tree ? a.L : 0, lstep = L > 1 ? r * rs : 0;
+  const float ninf = neg_inf();
+  float* const xs = vsm + wave * 64;                          // [waves][64] operands of the products
+  float* const s_part = vsm + NT;                             // [NT] parts of the mixture
+  float* const s_lay = s_part + NT;                           // [L][r][rs]
+  float* const s_e = s_lay + (size_t)L * r * rs;              // [n][r] evidence of the drafted tokens
+  float* const s_w = s_e + (size_t)n * r;                     // [n][r] HMM: its exponentials; tree: node values
+  float* const s_max = s_w + (hmm || tree ? (size_t)n * r : 0);     // [n]
+  float* const s_lam = s_max + n;                             // [r] weights of the mixture
+  float* const s_m = s_lam + 2 * r;                           // [v] weights of the final draw
+  const int* x = a.drafts + (long long)b * n;
+  const float* phi = a.logphi + (long long)b * n * r * v;
+  const float* pv = a.p + (long long)b * (n + 1) * v;
+  // ids outside [0, v) are the caller's error; clamping keeps every access in bounds
+  auto tok_at = [&](int i) { return min(max(x[i], 0), v - 1); };
+
+  // ---- 1. acceptance tests, evidence, layers, sum units
+  if (wave == 0) {
+    bool rej = false;
+    if (lane < n) {
+      const float lq = a.prefix[(long long)b * n + lane] - (lane > 0 ? a.prefix[(long long)b * n + lane - 1] : 0.f);
+      const float ratio = pv[(long long)lane * v + tok_at(lane)] / __expf(lq);
+      rej = philox_uniform(a.seed_lo, a.seed_hi, a.offset, (uint32_t)b, VERIFY_DRAFT_INDEX, (uint32_t)lane) > ratio;
+    }
+    const unsigned long long m = __ballot(rej);
+    if (lane == 0) s_j = m ? __ffsll((long long)m) - 1 : n;
+  }
+  // a group of G lanes to a token, and to a row of a layer, sixteen rows in flight; the first tokens' evidence is looked up while the
+  // rows are on their way
+  const int gi = tid / G, kc = min(k, r - 1);
+  constexpr int NG = NT / G, E = G / 16 > 0 ? G / 16 : 1;     // (64 tokens)
+  int tok[E];
+#pragma unroll
+  for (int u = 0; u < E; ++u) tok[u] = tok_at(min(gi + u * NG, n - 1));
+  const float* const src = a.raw != nullptr ? a.raw + (long long)b * a.raw_batch_stride : a.lay_nat + (a.contextual ? (long long)b * L * r * r : 0);
+  const long long layer_stride = a.raw != nullptr ? a.raw_layer_stride : (long long)r * r;
+  const int rows = L * r;
+  const bool dense = L <= 1 || layer_stride == (long long)r * r;        // (rows one behind the other)
+  auto load_rows = [&](int q0, float (&y)[16]) {
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int q = min(q0 + u * NG, rows - 1);
+      y[u] = dense ? src[q * r + kc] : src[q / r * layer_stride + q % r * r + kc];
+    }
+  };
+  auto put_rows = [&](int q0, const float (&y)[16]) {
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (live && q0 + u * NG < rows) s_lay[(q0 + u * NG) * rs + k] = y[u];
+  };
+  float y[16], ev[E];
+  if (rows > 0) load_rows(gi, y);
+#pragma unroll
+  for (int u = 0; u < E; ++u) ev[u] = phi[(long long)(min(gi + u * NG, n - 1) * r + kc) * v + tok[u]];
+  if (rows > 0) {
+    put_rows(gi, y);
+    for (int q0 = gi + 16 * NG; q0 < rows; q0 += 16 * NG) {
+      load_rows(q0, y);
+      put_rows(q0, y);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < E; ++u)
+    if (live && gi + u * NG < n) s_e[(gi + u * NG) * r + k] = ev[u];
+  if (a.family == MTPC_FF) {
+    if (tid < r) s_lw[tid] = 0.f;
+  } else if (a.h != nullptr) {
+    if (a.bf16) sumunit_position<true, NW>(a.h, a.ld_h, a.Wsum, b, a.d, r, s_lw);
+    else sumunit_position<false, NW>(a.h, a.ld_h, a.Wsum, b, a.d, r, s_lw);
+  } else if (tid < r) {
+    s_lw[tid] = a.logw[(long long)b * r + tid];
+  }
+  __syncthreads();
+  const int j = s_j;
+  int lg = 0;
+  while ((1 << lg) < n) ++lg;
+  if (a.raw != nullptr && j < n) {
+    // the layers that the message will meet, normalised in place (as normalise_layer_row): all of them would be 8 us of it
+    auto met = [&](int l) {
+      if (hmm) return l < j;                                  // (one layer for all steps: l = 0)
+      if (L == 1) return true;
+      const int m = l + 1, lev = 31 - __clz(m + 1), span = n >> lev, at = m + 1 - (1 << lev);     // leaves at * span ..
+      return at * span <= j;                                  // left of leaf j, or over it
+    };
+    for (int q = gi; q < rows; q += NG) {
+      if (!met(q / r)) continue;
+      const float z = live ? s_lay[q * rs + k] : ninf, m = Ops::max_units(z), ms = m == ninf ? 0.f : m;
+      const float e = z > ninf ? expf(z - ms) : 0.f, tot = Ops::sum_units(e);
+      if (live) s_lay[q * rs + k] = e * (tot > 0.f ? 1.f / tot : 0.f);
+    }
+    __syncthreads();
+  }
+
+  // ---- 2. weights of the final draw into s_m
+  if (j == n) {
+    for (int t = tid; t < v; t += NT) s_m[t] = pv[(long long)n * v + t];
+  } else {
+    const int vr = (v + 63) / 64 * 64, zparts = NT / vr, t = tid % vr, zp = tid / vr;
+    float pt = 0.f;
+    if (tid < v) pt = pv[(long long)j * v + tid];             // (v <= 320; fetched while the weights are formed)
+    const float lw = live ? s_lw[k] : ninf;
+    float c = lw;                                             // log-domain message into leaf j (first wave)
+    bool linear = false;
+    float lam = 0.f;
+    if (a.family == MTPC_CP) {
+      if (wave == 0 && live)
+        for (int i = 0; i < j; ++i) c += s_e[i * r + k];
+    } else if (hmm) {
+      for (int i = tid / G; i < j; i += NT / G) {
+        const float e = live ? s_e[i * r + k] : ninf;
+        const float m = Ops::max_units(e), ms = m == ninf ? 0.f : m;
+        if (live) s_w[i * r + k] = expf(e - ms);
+      }
+      __syncthreads();
+      if (wave == 0 && j > 0) {
+        linear = true;
+        const float lm = Ops::max_units(lw);
+        float y = live ? __builtin_amdgcn_ldexpf(expf(lw - (lm == ninf ? 0.f : lm)), ROW_SCALE) : 0.f;
+        for (int i = 0; i < j; ++i) {                         // observe token i, predict state i + 1
+          const int ic = i * r + min(k, r - 1);
+          const typename Ops::Weights w = Ops::weights(s_lay + (size_t)i * lstep, k, part, r, rs, 1);
+          float s, taken;
+          int exponent = 0, shift;
+          const float z = observe<Ops>(y, s_w[ic], s_e[ic], live, s, exponent, shift, taken);
+          y = Ops::product(z, w, xs, k, part, r, rs);
+        }
+        lam = live ? y : 0.f;
+      }
+    } else if (tree) {
+      // heap order: inner nodes 0..n-2, leaf i at n-1+i
+      auto value = [&](int q) {                               // fully observed child q
+        if (!live) return ninf;
+        return q >= n - 1 ? s_e[(q - (n - 1)) * r + k] : s_w[q * r + k];
+      };
+      auto layer = [&](float y, const typename Ops::Weights& w, int sj) {
+        const float mx = Ops::max_units(y);
+        const float o = Ops::product(live ? __expf(y - (mx == ninf ? 0.f : mx)) : 0.f, w, xs, k, part, r, sj);
+        return live ? mx + __logf(o) : ninf;                  // log 0 = -inf
+      };
+      for (int lev = lg - 1; lev >= 1; --lev) {               // bottom-up: the nodes whose leaves all lie left of leaf j
+        const int span = n >> lev, first = (1 << lev) - 1, count = j / span;
+        for (int q = wave; q < count; q += NW) {
+          const int m = first + q;
+          const float o = layer(value(2 * m + 1) + value(2 * m + 2), Ops::weights(s_lay + (size_t)(m - 1) * lstep, k, part, r, 1, rs), 1);
+          if (part == 0 && live) s_w[m * r + k] = o;
+        }
+        __syncthreads();
+      }
+      if (wave == 0) {
+        // top-down along the path: D_child[t] = (sum_k D_node[k] A_node[k][t]) * sibling[t]
+        for (int lev = 0; lev < lg; ++lev) {
+          // child of the path node at this level: the node (or leaf) one level down that covers leaf j
+          const int q = lev + 1 < lg ? (1 << (lev + 1)) - 1 + (j >> (lg - lev - 1)) : n - 1 + j;
+          const int node = (q - 1) >> 1;
+          if (node > 0) c = layer(c, Ops::weights(s_lay + (size_t)(node - 1) * lstep, k, part, r, rs, 1), rs);
+          if ((q & 1) == 0) c += value(q - 1);                // left sibling: leaves < j, observed; right: nothing, = 1
+        }
+      }
+    }
+    if (wave == 0) {                                          // lambda = softmax(c), or the linear values over their sum
+      const float most = Ops::max_units(c);                   // (of all lanes: not behind a condition on `live`)
+      if (!linear) lam = live ? __expf(c - most) : 0.f;
+      const float tot = Ops::sum_units(lam);
+      if (part == 0 && live) s_lam[k] = lam / tot;
+    }
+    __syncthreads();
+    // q(a | x_1..x_j) = sum_z lambda_z phi[j][z][a];  weights max(0, p - q)
+    float q = 0.f;
+    if (zp < zparts && t < v) {
+      const float* col = phi + (long long)j * r * v + t;
+      for (int z0 = zp; z0 < r; z0 += 16 * zparts) {          // 16 rows of the table in flight: none beyond r
+        float lp[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+          if (z0 + u * zparts < r) lp[u] = col[(long long)(z0 + u * zparts) * v];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+          if (z0 + u * zparts < r) q = fmaf(s_lam[z0 + u * zparts], __expf(lp[u]), q);
+      }
+      s_part[zp * vr + t] = q;
+    }
+    __syncthreads();
+    if (tid < v) {
+      float sum = 0.f;
+      for (int w = 0; w < zparts; ++w) sum += s_part[w * vr + tid];
+      s_m[tid] = fmaxf(0.f, pt - sum);
+    }
+  }
+  __syncthreads();
+  if (wave != 0) return;
+
+  // ---- 3. inverse-CDF draw from s_m / Z, consecutive ids per lane
+  constexpr int VPL = 5;                                      // v <= 320
+  const int C = (v + 63) / 64;
+  float m[VPL], ls = 0.f, incl = 0.f, total = 0.f;
+  for (int pass = 0; pass < 2; ++pass) {
+    ls = 0.f;
+#pragma unroll
+    for (int q = 0; q < VPL; ++q) {
+      const int t = lane * C + q;
+      // p == q at the rejected position: the adjusted distribution is undefined, draw from p
+      m[q] = q < C && t < v ? (pass == 0 ? s_m[t] : pv[(long long)j * v + t]) : 0.f;
+      ls += m[q];
+    }
+    incl = ls;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const float up = __shfl_up(incl, o);
+      if (lane >= o) incl += up;
+    }
+    total = __shfl(incl, 63);
+    if (total > 0.f || j == n) break;
+  }
+  const float tgt = philox_uniform(a.seed_lo, a.seed_hi, a.offset, (uint32_t)b, VERIFY_DRAFT_INDEX, (uint32_t)n) * total;
+  float run = incl - ls;
+  int first = INT_MAX, last = -1;
+#pragma unroll
+  for (int q = 0; q < VPL; ++q) {
+    run += m[q];
+    if (q < C && first == INT_MAX && tgt < run) first = lane * C + q;
+    if (m[q] > 0.f) last = lane * C + q;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    first = min(first, __shfl_xor(first, o));
+    last = max(last, __shfl_xor(last, o));
+  }
+  if (lane == 0) {
+    a.accepted[b] = j;
+    a.token[b] = first < v ? first : max(last, 0);
+  }
+}
+
+template <int G>
+hipError_t launch_verify_row(const VerifyArgs& a, hipStream_t st) {
+  if (hipError_t e = allow_lds<k_verify_row<G>>(152 * 1024); e != hipSuccess) return e;
+  const int L = a.family == MTPC_HMM || a.family == MTPC_BTREE ? std::max(a.L, 0) : 0;
+  hipLaunchKernelGGL(k_verify_row<G>, dim3(a.B), dim3(VERIFY_ROW_THREADS), verify_row_floats(a.family, a.n, a.r, L, a.v) * 4, st, a);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_verify(const VerifyArgs& a, hipStream_t st) {
   if (a.mode == MTPC_VERIFY_GREEDY) {
     hipLaunchKernelGGL(k_verify_greedy, dim3(a.B), dim3(a.n < 16 ? (a.n + 1) * 64 : 1024), 0, st, a);
     return hipGetLastError();
+  }
+  if (verify_rows(a.family, a.B, a.n, a.r, a.L, a.v)) {
+    if (a.r <= 8) return launch_verify_row<8>(a, st);
+    if (a.r <= 16) return launch_verify_row<16>(a, st);
+    return a.r <= 32 ? launch_verify_row<32>(a, st) : launch_verify_row<64>(a, st);
   }
   int G = 1;
   while (G < a.r) G <<= 1;                                   // r <= 128 -> at least two column groups

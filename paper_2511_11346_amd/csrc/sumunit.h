@@ -117,4 +117,44 @@ __device__ __forceinline__ void normalise_layer_row(const float* logits, long lo
   }
 }
 
+// What stands beside the sum units in the launch of a call's parameters: workgroup w of those behind theirs, NT threads each.
+constexpr int PARAM_COPIES = 4, PARAM_CLEARS = 16;       // 16-byte pieces of h, and ints, of a thread
+inline __host__ __device__ long long param_blocks_copy(const ParamArgs& p, int NT) {
+  return p.hs == nullptr ? 0 : ((long long)p.B * (p.row_bytes / 16) + NT * PARAM_COPIES - 1) / (NT * PARAM_COPIES);
+}
+inline __host__ __device__ long long param_blocks_layers(const ParamArgs& p, int NT) { return ((long long)p.nb * p.L * p.r + NT / 64 - 1) / (NT / 64); }
+inline long long param_blocks(const ParamArgs& p, int NT) {
+  return param_blocks_copy(p, NT) + param_blocks_layers(p, NT) + (p.nclear + NT * PARAM_CLEARS - 1) / (NT * PARAM_CLEARS);
+}
+template <int NT>
+__device__ __forceinline__ void params_beside(const ParamArgs& p, long long w) {
+  const int tid = threadIdx.x;
+  const long long copies = param_blocks_copy(p, NT), layers = param_blocks_layers(p, NT);
+  if (w < copies) {
+    // (as k_pack_rows: neighbouring threads read 64 bytes of neighbouring rows and write one run)
+    const long long total = (long long)p.B * (p.row_bytes / 16);
+    const long long t0 = w * (NT * PARAM_COPIES) + tid;
+    const unsigned stage_chunks = (unsigned)p.B * 4;
+    const long long row_stride = p.ld_h * (p.row_bytes / p.d);
+    i32x4_t x[PARAM_COPIES];
+#pragma unroll
+    for (int c = 0; c < PARAM_COPIES; ++c) {
+      const unsigned t = (unsigned)min(t0 + c * NT, total - 1);      // (of less than 4 GiB of h)
+      const unsigned stage = t / stage_chunks, u = t - stage * stage_chunks;
+      x[c] = *(const i32x4_t*)((const char*)p.h + (long long)(u >> 2) * row_stride + (long long)stage * 64 + (u & 3) * 16);
+    }
+#pragma unroll
+    for (int c = 0; c < PARAM_COPIES; ++c)
+      if (t0 + c * NT < total) *(i32x4_t*)((char*)p.hs + (t0 + c * NT) * 16) = x[c];
+  } else if (w < copies + layers) {
+    const long long row = (w - copies) * (NT / 64) + (tid >> 6);
+    if (row < (long long)p.nb * p.L * p.r) normalise_layer_row(p.logits, p.layer_stride, p.batch_stride, row, p.L, p.r, p.out_nat, p.out_tr);
+  } else {
+    const long long t0 = (w - copies - layers) * (NT * PARAM_CLEARS) + tid;
+#pragma unroll
+    for (int c = 0; c < PARAM_CLEARS; ++c)
+      if (t0 + c * NT < p.nclear) p.clear[t0 + c * NT] = 0;
+  }
+}
+
 }  // namespace mtpc

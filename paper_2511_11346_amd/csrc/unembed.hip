@@ -631,75 +631,93 @@ hipError_t launch_draw_gather(const DrawGatherArgs& a, int dtype, hipStream_t st
 
 // Sum-unit parameters for many positions (Sec. 3.3): log omega[b,:] = log_softmax(Wsum h[b]), r <= 16 RB units,
 // 16 PB positions per workgroup.  The product is small and its chain over d long, so the waves (sixteen, or eight
-// where their partial sums would not fit in LDS) deal its 64-byte steps among themselves (together a contiguous
-// piece of every row), straight from memory into registers with U
-// steps in flight, and their partial sums are added through LDS in a fixed order.  (As one wave that walks all
-// of d through an LDS ring, 32 positions to a workgroup: 22 us for any B up to 4096 at d = 4096 bf16, r = 32, 57 us
-// in fp32 - 0.35 us per 128 bytes of a row, a barrier and a chain of LDS read and product each.)
-// What limits it then is the rate at which a CU takes in operand rows: loads that are not needed cost as much as those
-// that are (d = 1152 bf16, 36 steps over 16 waves, steps beyond d loaded all the same: 7.5 us more for a batch of 1000).
-constexpr int sumunit_waves(int RB, int PB) { return RB * PB <= 2 ? 16 : 8; }
-template <int RB, int PB, bool BF16, int NW>
+// where their partial sums and buffers would not fit in LDS) deal its 64-byte steps among themselves (together a contiguous
+// piece of every row), each through LDS buffers of its own with U steps in flight and no barrier, and their partial sums are
+// added through LDS in a fixed order.
+// What limits it is the rate at which a CU takes in operand rows, so every load is 16 whole 64-byte pieces of rows, straight into LDS: as
+// fragments in registers four neighbouring lanes ask for four rows, and a load takes four times as long (r = 32, d = 4096 bf16, B = 200:
+// 15 -> 11 us with the layers and the copy of h beside it, 25 in three launches; fp32, B = 2048, d = 3072 26 -> 21; as one wave that walks all of d 22 and 57).  Steps that are not there are not loaded.
+// The workgroups behind those of the positions see to the call's other parameters.
+template <int RB, int PB, bool BF16, int NW, int U>
 __global__ __launch_bounds__(NW * 64)
-void k_sumunit_mfma(const void* h, long long ld_h, const void* Wsum, int B, int d, int r, float* logw) {
-  constexpr int ESZ = BF16 ? 2 : 4, U = RB + PB <= 3 ? 8 : RB + PB <= 5 ? 6 : 3;
+void k_sumunit_mfma(const ParamArgs p) {
+  constexpr int ESZ = BF16 ? 2 : 4, NB = RB + PB;
   constexpr int PS = PB * 16 + 1;                    // (odd stride: the lanes of a reduction read different banks)
-  __shared__ float part[NW][RB * 16 * PS];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int PART = RB * 16 * PS;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int nsum = (p.B + PB * 16 - 1) / (PB * 16);
+  if ((int)blockIdx.x >= nsum) {
+    params_beside<NW * 64>(p, (int)blockIdx.x - nsum);
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int l15 = lane & 15, lq = lane >> 4;
-  const int b0 = blockIdx.x * PB * 16;
-  const int steps = d * ESZ / 64;
-  const char* pw[RB];
-  const char* ph[PB];
+  const int b0 = blockIdx.x * PB * 16, r = p.r;
+  const int steps = p.d * ESZ / 64, mine = (steps - wave + NW - 1) / NW;      // (0: fewer steps than waves)
+  const int hspan = min(p.B - b0, PB * 16);
+  const i32x4_t srdW = make_srd(p.Wsum, (unsigned)((long long)r * p.d * ESZ));
+  const i32x4_t srdH = make_srd((const char*)p.h + (long long)b0 * p.ld_h * ESZ, (unsigned)((long long)(hspan - 1) * p.ld_h * ESZ + (long long)p.d * ESZ));
+  // this lane's 16 bytes of a block of 16 rows, swizzled for the fragment reads (swz16)
+  const int lrow = lane >> 2, lch = ((lane & 3) ^ swz16(lrow)) * 16;
+  unsigned voff[NB];
 #pragma unroll
-  for (int i = 0; i < RB; ++i) pw[i] = (const char*)Wsum + (long long)min(i * 16 + l15, r - 1) * d * ESZ + lq * 16;
+  for (int i = 0; i < NB; ++i)
+    voff[i] = i < RB ? (unsigned)min(i * 16 + lrow, r - 1) * (unsigned)(p.d * ESZ) + lch
+                     : (unsigned)min((i - RB) * 16 + lrow, hspan - 1) * (unsigned)(p.ld_h * ESZ) + lch;
+  char* const ring = smem + wave * (min(U, (steps + NW - 1) / NW) * NB * 1024);      // (of as many steps as a wave has, or U)
+  const unsigned lds0 = (unsigned)(size_t)ring;
+  auto issue = [&](int j) {
+    const unsigned so = (unsigned)(wave + j * NW) * 64, at = lds0 + (unsigned)(j % U) * (NB * 1024);
 #pragma unroll
-  for (int i = 0; i < PB; ++i) ph[i] = (const char*)h + (long long)min(b0 + i * 16 + l15, B - 1) * ld_h * ESZ + lq * 16;
+    for (int i = 0; i < NB; ++i) load_to_lds(voff[i], i < RB ? srdW : srdH, so, at + i * 1024);
+  };
   f32x4_t acc[PB][RB];
 #pragma unroll
-  for (int p = 0; p < PB; ++p)
+  for (int q = 0; q < PB; ++q)
 #pragma unroll
-    for (int i = 0; i < RB; ++i) acc[p][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  for (int s0 = wave; s0 < steps; s0 += NW * U) {
-    i32x4_t fw[U][RB], fh[U][PB];
+    for (int i = 0; i < RB; ++i) acc[q][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < min(U, mine); ++j) issue(j);
+  const int frag = l15 * 64 + ((lq ^ swz16(l15)) << 4);
+  for (int j = 0; j < mine; ++j) {
+    // step j has landed (a wave's loads arrive in their order; the last U - 1 steps wait for all that are left)
+    if (j + U <= mine) MTPC_WAIT_VMCNT((U - 1) * NB); else MTPC_WAIT_VMCNT(0);
+    __builtin_amdgcn_sched_barrier(0);
+    const char* const cur = ring + (j % U) * (NB * 1024) + frag;
+    i32x4_t fw[RB], fh[PB];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      // (steps beyond d are neither loaded nor multiplied: wave-uniform, all others in flight together)
-      if (s0 + u * NW >= steps) continue;
-      const long long o = (long long)(s0 + u * NW) * 64;
+    for (int i = 0; i < RB; ++i) fw[i] = *(const i32x4_t*)(cur + i * 1024);
 #pragma unroll
-      for (int i = 0; i < PB; ++i) fh[u][i] = *(const i32x4_t*)(ph[i] + o);
+    for (int q = 0; q < PB; ++q) fh[q] = *(const i32x4_t*)(cur + (RB + q) * 1024);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): read, before its buffer takes step j + U
+    __builtin_amdgcn_sched_barrier(0);
+    if (j + U < mine) issue(j + U);
 #pragma unroll
-      for (int i = 0; i < RB; ++i) fw[u][i] = *(const i32x4_t*)(pw[i] + o);
-    }
+    for (int q = 0; q < PB; ++q)
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (s0 + u * NW >= steps) continue;
+      for (int i = 0; i < RB; ++i) {
+        if constexpr (BF16) mma_step<true>(acc[q][i], fw[i], fh[q]);
+        else {
+          // lane group lq holds columns 4 lq .. 4 lq + 3 of both operands: product t takes one of each
+          const f32x4_t x = __builtin_bit_cast(f32x4_t, fw[i]), y = __builtin_bit_cast(f32x4_t, fh[q]);
 #pragma unroll
-      for (int p = 0; p < PB; ++p)
-#pragma unroll
-        for (int i = 0; i < RB; ++i) {
-          if constexpr (BF16) mma_step<true>(acc[p][i], fw[u][i], fh[u][p]);
-          else {
-            // lane group lq holds columns 4 lq .. 4 lq + 3 of both operands: product t takes one of each
-            const f32x4_t x = __builtin_bit_cast(f32x4_t, fw[u][i]), y = __builtin_bit_cast(f32x4_t, fh[u][p]);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) acc[p][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t], y[t], acc[p][i], 0, 0, 0);
-          }
+          for (int t = 0; t < 4; ++t) acc[q][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t], y[t], acc[q][i], 0, 0, 0);
         }
-    }
+      }
   }
+  __syncthreads();                                   // all buffers are read: the partial sums take their place
+  float* const part = (float*)smem;                  // [NW][PART]
 #pragma unroll
-  for (int p = 0; p < PB; ++p)
+  for (int q = 0; q < PB; ++q)
 #pragma unroll
     for (int i = 0; i < RB; ++i)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) part[wave][(i * 16 + 4 * lq + t) * PS + p * 16 + l15] = acc[p][i][t];
+      for (int t = 0; t < 4; ++t) part[wave * PART + (i * 16 + 4 * lq + t) * PS + q * 16 + l15] = acc[q][i][t];
   __syncthreads();
   // 32 lanes per position, units j, j + 32, ...
   const int j = threadIdx.x & 31;
   constexpr int Q = (RB + 1) / 2;
-  for (int p = threadIdx.x >> 5; p < PB * 16 && b0 + p < B; p += NW * 2) {
+  for (int q0 = threadIdx.x >> 5; q0 < PB * 16 && b0 + q0 < p.B; q0 += NW * 2) {
     float x[Q], m = neg_inf();
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -708,7 +726,7 @@ void k_sumunit_mfma(const void* h, long long ld_h, const void* Wsum, int B, int 
       if (u < r) {
         float sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) sum += part[w][u * PS + p];
+        for (int w = 0; w < NW; ++w) sum += part[w * PART + u * PS + q0];
         x[q] = sum;
       }
       m = fmaxf(m, x[q]);
@@ -722,21 +740,30 @@ void k_sumunit_mfma(const void* h, long long ld_h, const void* Wsum, int B, int 
     const float lse = m + __logf(group_sum(e, 32));
 #pragma unroll
     for (int q = 0; q < Q; ++q)
-      if (j + 32 * q < r) logw[(long long)(b0 + p) * r + j + 32 * q] = x[q] - lse;
+      if (j + 32 * q < r) p.logw[(long long)(b0 + q0) * r + j + 32 * q] = x[q] - lse;
   }
+}
+
+template <int RB, int PB, bool BF16, int NW>
+static hipError_t launch_sumunit_mfma_nw(const ParamArgs& p, hipStream_t st) {
+  constexpr int NB = RB + PB, most = 148 / (NB * NW);          // steps in flight: what fits in LDS, up to eight
+  constexpr int U = most < 8 ? most : 8;
+  static_assert(U >= 2 && (U - 1) * NB <= 63, "a ring, and a wait that counts its loads");
+  constexpr int part = NW * RB * 16 * (PB * 16 + 1) * 4, most_smem = std::max(part, NW * U * NB * 1024);
+  static_assert(most_smem <= 160 * 1024, "LDS budget of one CU");
+  constexpr auto kern = k_sumunit_mfma<RB, PB, BF16, NW, U>;
+  if (hipError_t e = allow_lds<kern>(most_smem); e != hipSuccess) return e;
+  const int steps = p.d * (BF16 ? 2 : 4) / 64, smem = std::max(part, NW * std::min(U, (steps + NW - 1) / NW) * NB * 1024);
+  const long long grid = (p.B + PB * 16 - 1) / (PB * 16) + param_blocks(p, NW * 64);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), smem, st, p);
+  return hipGetLastError();
 }
 
 // (rows of at most 32 steps: four waves have all of them in flight, more would only add partial sums)
 template <int RB, int PB, bool BF16>
-static hipError_t launch_sumunit_mfma_cfg(const void* h, long long ld_h, const void* Wsum, int B, int d,
-                                          int r, float* logw, hipStream_t st) {
-  constexpr int NW = sumunit_waves(RB, PB);
-  const dim3 grid((B + PB * 16 - 1) / (PB * 16));
-  if (d * (BF16 ? 2 : 4) / 64 <= 32)
-    hipLaunchKernelGGL((k_sumunit_mfma<RB, PB, BF16, 4>), grid, dim3(256), 0, st, h, ld_h, Wsum, B, d, r, logw);
-  else
-    hipLaunchKernelGGL((k_sumunit_mfma<RB, PB, BF16, NW>), grid, dim3(NW * 64), 0, st, h, ld_h, Wsum, B, d, r, logw);
-  return hipGetLastError();
+static hipError_t launch_sumunit_mfma_cfg(const ParamArgs& p, hipStream_t st) {
+  if (p.d * (BF16 ? 2 : 4) / 64 <= 32) return launch_sumunit_mfma_nw<RB, PB, BF16, 4>(p, st);
+  return launch_sumunit_mfma_nw<RB, PB, BF16, RB * PB <= 2 ? 16 : 8>(p, st);
 }
 
 // The same for many units over long rows in bf16: the tile machinery with Wsum as the only "slab" (r <= 128 rows), 32
@@ -779,24 +806,17 @@ static hipError_t launch_sumunit_ring(const void* h, long long ld_h, const void*
 // 500 positions, r = 128, d = 544 25.5 / 27.1 us with the ring), longer ones are not (d = 1216 39.9 / 37.5, d = 4096 91.3 / 81.4;
 // 8000 positions 855 / 823).
 template <bool BF16>
-static hipError_t launch_sumunit_mfma_dt(const void* h, long long ld_h, const void* Wsum, int B, int d,
-                                         int r, float* logw, hipStream_t st) {
-  const bool wide = B > 4096;
-  if (BF16 && r > 64 && d > 1024)
-    return d % 64 == 0 ? launch_sumunit_ring<128>(h, ld_h, Wsum, B, d, r, logw, st) : launch_sumunit_ring<64>(h, ld_h, Wsum, B, d, r, logw, st);
-  if (r <= 16) return wide ? launch_sumunit_mfma_cfg<1, 2, BF16>(h, ld_h, Wsum, B, d, r, logw, st)
-                           : launch_sumunit_mfma_cfg<1, 1, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
-  if (r <= 32) return wide ? launch_sumunit_mfma_cfg<2, 2, BF16>(h, ld_h, Wsum, B, d, r, logw, st)
-                           : launch_sumunit_mfma_cfg<2, 1, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
-  if (r <= 64) return wide ? launch_sumunit_mfma_cfg<4, 2, BF16>(h, ld_h, Wsum, B, d, r, logw, st)
-                           : launch_sumunit_mfma_cfg<4, 1, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
-  return launch_sumunit_mfma_cfg<8, 1, BF16>(h, ld_h, Wsum, B, d, r, logw, st);
+static hipError_t launch_sumunit_mfma_dt(const ParamArgs& p, hipStream_t st) {
+  const bool wide = p.B > 4096;
+  const int r = p.r;
+  if (r <= 16) return wide ? launch_sumunit_mfma_cfg<1, 2, BF16>(p, st) : launch_sumunit_mfma_cfg<1, 1, BF16>(p, st);
+  if (r <= 32) return wide ? launch_sumunit_mfma_cfg<2, 2, BF16>(p, st) : launch_sumunit_mfma_cfg<2, 1, BF16>(p, st);
+  if (r <= 64) return wide ? launch_sumunit_mfma_cfg<4, 2, BF16>(p, st) : launch_sumunit_mfma_cfg<4, 1, BF16>(p, st);
+  return launch_sumunit_mfma_cfg<8, 1, BF16>(p, st);
 }
 
-hipError_t launch_sumunit_mfma(const void* h, long long ld_h, const void* Wsum, int B, int d, int r,
-                               int dtype, float* logw, hipStream_t st) {
-  return dtype == MTPC_BF16 ? launch_sumunit_mfma_dt<true>(h, ld_h, Wsum, B, d, r, logw, st)
-                            : launch_sumunit_mfma_dt<false>(h, ld_h, Wsum, B, d, r, logw, st);
+hipError_t launch_params_mfma(const ParamArgs& p, int dtype, hipStream_t st) {
+  return dtype == MTPC_BF16 ? launch_sumunit_mfma_dt<true>(p, st) : launch_sumunit_mfma_dt<false>(p, st);
 }
 
 // Contextual sum layers (Sec. 3.3, sum unit parameters): every sum unit (layer l,

@@ -46,22 +46,31 @@ static u64 strided(u64 rows, long long ld, u64 cols, u64 es) { return rows ? ((r
 static int nlat(int family, int n) { return family == MTPC_FF ? 0 : family == MTPC_CP ? 1 : family == MTPC_HMM ? n : n - 1; }
 static hipError_t ok() { ++host_check::g_launches; return hipSuccess; }
 
-hipError_t launch_sumunit(const void* h, long long ld_h, const void* Wsum, int B, int d, int r, int dtype, float* logw,
+static hipError_t launch_sumunit(const void* h, long long ld_h, const void* Wsum, int B, int d, int r, int dtype, float* logw,
                           hipStream_t) {
   need(h, strided(B, ld_h, d, esz(dtype)), "sumunit h");
   need(Wsum, (u64)r * d * esz(dtype), "sumunit Wsum");
   need(logw, (u64)B * r * 4, "sumunit logw");
   return ok();
 }
-hipError_t launch_sumunit_mfma(const void* h, long long ld_h, const void* Wsum, int B, int d, int r, int dtype,
-                               float* logw, hipStream_t st) {
-  return launch_sumunit(h, ld_h, Wsum, B, d, r, dtype, logw, st);
-}
-hipError_t launch_normalise_layers(const float* logits, long long ls, long long bs, int nb, int L, int r, float* out_nat,
+static hipError_t launch_normalise_layers(const float* logits, long long ls, long long bs, int nb, int L, int r, float* out_nat,
                                    float* out_tr, hipStream_t) {
   need(logits, ((u64)(nb - 1) * bs + (u64)(L - 1) * ls + (u64)r * r) * 4, "normalise logits");
   opt(out_nat, (u64)nb * L * r * r * 4, "normalise out_nat");
   opt(out_tr, (u64)nb * L * r * r * 4, "normalise out_tr");
+  return ok();
+}
+hipError_t launch_call_params(const ParamArgs& p, int dtype, hipStream_t st) {
+  const int before = host_check::g_launches;
+  if (p.Wsum) launch_sumunit(p.h, p.ld_h, p.Wsum, p.B, p.d, p.r, dtype, p.logw, st);
+  if (p.L > 0) launch_normalise_layers(p.logits, p.layer_stride, p.batch_stride, p.nb, p.L, p.r, p.out_nat, p.out_tr, st);
+  if (p.hs) {
+    need(p.h, strided(p.B, p.ld_h, p.d, esz(dtype)), "copy of h: source");
+    need(p.hs, (u64)p.B * p.row_bytes, "copy of h");
+    if ((u64)p.row_bytes != (u64)p.d * esz(dtype)) { std::fprintf(stderr, "copy of h: rows of another length\n"); std::abort(); }
+  }
+  if (p.nclear > 0) need(p.clear, (u64)p.nclear * 4, "ints to clear");
+  host_check::g_launches = before;
   return ok();
 }
 hipError_t launch_ctx_layers(const CtxLayerArgs& a, int dtype, hipStream_t) {
@@ -137,10 +146,10 @@ hipError_t launch_latents(const LatentArgs& a, hipStream_t) {
   opt(a.zero, (u64)a.nzero * 4, "latents: counters to clear");
   return ok();
 }
-hipError_t launch_sumunit_latents(const void* h, long long ld_h, const void* Wsum, int d, int dtype, float* logw,
-                                  const LatentArgs& a, hipStream_t st) {
-  if (a.B > SUMUNIT_SMALL_B || a.family == MTPC_FF) { std::fprintf(stderr, "fused sum units + latents outside their range\n"); std::abort(); }
-  launch_sumunit(h, ld_h, Wsum, a.B, d, a.r, dtype, logw, st);
+hipError_t launch_sumunit_latents(const ParamArgs& p, int dtype, const LatentArgs& a, hipStream_t st) {
+  if (a.B > SUMUNIT_SMALL_B || a.family == MTPC_FF || p.B != a.B || p.r != a.r) { std::fprintf(stderr, "fused sum units + latents outside their range\n"); std::abort(); }
+  if (p.L > 0 && (!sumunit_latents_layers(p.r, p.nb, p.L) || p.L != a.L)) { std::fprintf(stderr, "fused layers outside their range\n"); std::abort(); }
+  launch_call_params(p, dtype, st);
   --host_check::g_launches;
   return launch_latents(a, st);
 }
@@ -212,6 +221,8 @@ hipError_t launch_verify(const VerifyArgs& a, hipStream_t) {
     const u64 lay = (a.contextual ? (u64)a.B : 1) * a.L * a.r * a.r * 4;
     if (a.lay_nat) need(a.lay_nat, lay, "verify lay_nat");
     if (a.lay_tr) need(a.lay_tr, lay, "verify lay_tr");
+    if (a.raw) need(a.raw, ((u64)(a.contextual ? a.B - 1 : 0) * a.raw_batch_stride + (u64)(a.L - 1) * a.raw_layer_stride + (u64)a.r * a.r) * 4, "verify layer logits");
+    if (a.L > 0 && !a.raw && !a.lay_nat) { std::fprintf(stderr, "verify: no layers\n"); std::abort(); }
   }
   need(a.accepted, (u64)a.B * 4, "verify accepted");
   need(a.token, (u64)a.B * 4, "verify token");
