@@ -883,6 +883,7 @@ __global__ __launch_bounds__(1024) void k_circuit_row(const CircuitArgs a) {
   };
   if (nq > 0) load(0);
   const float e0 = evidence(gi, x0), e1 = evidence(gi + step, x1);
+  __builtin_amdgcn_sched_barrier(0);                     // (all of these in flight before the first is waited for)
   if (nq > 0) {
     put(0);
     for (int t0 = 8 * NT; t0 < nq; t0 += 8 * NT) { load(t0); put(t0); }
@@ -1174,7 +1175,7 @@ __device__ __forceinline__ void draft_latents(const LatentArgs& a, int b, int s,
   int* zl = a.zleaf + t * n;
   const long long lstep = (a.L > 1) ? (long long)r * r : 0;
   // (all uniforms at once, before the chain of draws that uses them: at most 64)
-  const float uniforms = philox_uniform(a.seed_lo, a.seed_hi, a.offset, (uint32_t)b, (uint32_t)s, (uint32_t)(n + lane));
+  const float uniforms = a.greedy ? 0.f : philox_uniform(a.seed_lo, a.seed_hi, a.offset, (uint32_t)b, (uint32_t)s, (uint32_t)(n + lane));
   auto U = [&](int lat) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(uniforms), lat)); };
   auto draw_row = [&](const float* row, int lat) {      // row of normalised linear weights, or normalised here (as normalise_layer_row)
     float p0 = lane < r ? row[lane] : RAW ? neg_inf() : 0.f;
@@ -1445,7 +1446,7 @@ template <bool BF16>
 __global__ __launch_bounds__(256) void k_rows_logits(const RowLogitArgs a) {
   constexpr int ESZ = BF16 ? 2 : 4;
   constexpr int EPC = 16 / ESZ;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const long long di = blockIdx.x;                       // (b, s, i) flattened
   const int i = (int)(di % a.n);
   const long long b = di / a.n / a.S;
@@ -1456,24 +1457,23 @@ __global__ __launch_bounds__(256) void k_rows_logits(const RowLogitArgs a) {
   const int nch = a.d / EPC;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
   for (int c0 = 0; c0 < nch; c0 += 512) {
-    i32x4_t hv[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int c = c0 + t * 64 + lane;
-      const i32x4_t x = *(const i32x4_t*)(hb + (long long)min(c, nch - 1) * 16);
-      hv[t] = c < nch ? x : i32x4_t{0, 0, 0, 0};
-    }
+    // all of the loads in flight together (the barrier: sumunit_position)
+    const int at = (c0 + lane) * 16;
+    i32x4_t hv[8], wv[4][8];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const char* wr = Wz + (long long)min(row0 + q, a.v - 1) * a.d * ESZ;
+      const RowLoad wl(Wz + (long long)min(row0 + q, a.v - 1) * a.d * ESZ, a.d * ESZ);
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        // unconditional (clamped) loads so that all of them are in flight together;
-        // chunks beyond d meet a zero hv
-        const int c = min(c0 + t * 64 + lane, nch - 1);
-        acc[q] += dot_chunk<BF16>(*(const i32x4_t*)(wr + (long long)c * 16), hv[t]);
-      }
+      for (int t = 0; t < 8; ++t) wv[q][t] = wl(at + t * 1024);
     }
+    const RowLoad hl(hb, a.d * ESZ);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) hv[t] = hl(at + t * 1024);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int t = 0; t < 8; ++t) acc[q] += dot_chunk<BF16>(wv[q][t], hv[t]);
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {

@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256) void k_verify(const VerifyArgs a, int G) {
 // before it is known - acceptance tests, evidence of all drafted tokens, sum units, and the logits of all layers, of which those that turn out
 // to be needed are then normalised in LDS (no launch for that) -, and the message to the rejected position is formed out of LDS, by one wave (HMM: linear values, as
 // in k_circuit_row) or (binary tree, observed subtrees) a wave to a node.  G as in RowOps.
-// HMM n = 16, r = 32, v = 320, B = 61: VERIFY_HMM us, CP B = 1 VERIFY_CP us.
+// HMM n = 16, r = 32, v = 320, B = 61: 28.9 (with the launch that normalised its layers) -> 20.3 us, CP B = 1 17.5 -> 10.4.
 template <int G>
 __global__ __launch_bounds__(VERIFY_ROW_THREADS) void k_verify_row(const VerifyArgs a) {
   using Ops = RowOps<G, 64 / G>;
@@ -435,6 +435,7 @@ __global__ __launch_bounds__(VERIFY_ROW_THREADS) void k_verify_row(const VerifyA
   if (rows > 0) load_rows(gi, y);
 #pragma unroll
   for (int u = 0; u < E; ++u) ev[u] = phi[(long long)(min(gi + u * NG, n - 1) * r + kc) * v + tok[u]];
+  __builtin_amdgcn_sched_barrier(0);                          // (all of these in flight before the first is waited for)
   if (rows > 0) {
     put_rows(gi, y);
     for (int q0 = gi + 16 * NG; q0 < rows; q0 += 16 * NG) {
@@ -556,6 +557,7 @@ __global__ __launch_bounds__(VERIFY_ROW_THREADS) void k_verify_row(const VerifyA
 #pragma unroll
         for (int u = 0; u < 16; ++u)
           if (z0 + u * zparts < r) lp[u] = col[(long long)(z0 + u * zparts) * v];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < 16; ++u)
           if (z0 + u * zparts < r) q = fmaf(s_lam[z0 + u * zparts], __expf(lp[u]), q);
