@@ -414,7 +414,10 @@ mtpc_status run_univariate(int family, const mtpc_head* hd, const mtpc_sumlayers
     ProfScope prof(st);
     HIP_TRY(launch_unembed_few(t, beside, hd->dtype, st));
   }
-  if (family != MTPC_FF) {
+  if (family == MTPC_CP) {                                // one latent, whose weights every token has
+    u.logm = (const float*)(ws + p.logw);
+    u.logm_b = hd->r;
+  } else if (family != MTPC_FF) {
     LatentMarginalArgs m{};
     m.family = family; m.B = hd->B; m.n = hd->n; m.r = hd->r;
     m.logw = (const float*)(ws + p.logw);
@@ -423,6 +426,8 @@ mtpc_status run_univariate(int family, const mtpc_head* hd, const mtpc_sumlayers
     m.logm = (float*)(ws + p.logm);
     HIP_TRY(launch_latent_marginals(m, st));
     u.logm = m.logm;
+    u.logm_b = (long long)hd->n * hd->r;
+    u.logm_i = hd->r;
   }
   // One pass of the evidence kernel that only writes log phi (the head without sum units: straight
   // into `out`, which is that table), then the mixture over the r units per token.  A table

@@ -1240,12 +1240,12 @@ hipError_t launch_latents(const LatentArgs& a, hipStream_t st) {
 
 // ---------------------------------------------------------------------------
 // log marginal of the latent that indexes leaf i (for univariate marginals):
-// CP: omega; HMM: omega T_1 ... T_i; BTree: top-down products to the leaf's parent
+// HMM: omega T_1 ... T_i; BTree: top-down products to the leaf's parent (CP: omega itself, which the mixture reads)
 // one thread per (position, unit); r <= 128 values exchanged through LDS.  A chain of matrix-vector products,
 // each bound by the latency of its layer: up to 32 rows of it in flight at once, in whole groups of eight (then four, two
 // and one), in the same order of sums as a loop of dependent loads.  No load beyond r: with the 32 always issued,
 // clamped, a chain of small layers paid for them (univariate marginals over 16 tokens, d = 256, us,
-// loop / 32 clamped / this: HMM n = 8, B = 1000, r = 32 119 / 86 / 82, r = 8 35 / 36 / 31; tree n = 16, B = 1000, r = 8
+// loop / 32 clamped / this, r <= 32 since then as below: HMM n = 8, B = 1000, r = 32 119 / 86 / 82, r = 8 35 / 36 / 31; tree n = 16, B = 1000, r = 8
 // 53 / 66 / 53, B = 27, r = 3 21 / 29 / 21).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float column_dot(const float* x, const float* __restrict__ T, int r, int j) {
@@ -1278,55 +1278,60 @@ __device__ __forceinline__ float column_dot(const float* x, const float* __restr
   return s;
 }
 
-__global__ void k_latent_marginals(const LatentMarginalArgs a) {
-  extern __shared__ float lsm[];          // 2 * n * r floats: node marginals (linear)
-  const int b = blockIdx.x, j = threadIdx.x, n = a.n, r = a.r;
+// Every node's message is its parent's (HMM: the node before it) times the node's layer.  Bound by the latency of that chain: a layer
+// does not depend on it, so with up to R units a lane holds its column of the next one while this one's product is formed, and
+// logarithms follow at the end (a step waited for its layer: HMM n = 8, r = 32, B = 1000 12.7 -> 10.9 us; with the mixture below,
+// n = 16, B = 61, d = 256 65.7 -> 56.5 us a call).  R = 0: any r, a column fetched when its turn comes (64 of them ahead would leave
+// one wave to a SIMD).
+template <int R>
+__global__ __launch_bounds__(R ? 64 : 128) void k_latent_marginals(const LatentMarginalArgs a) {
+  extern __shared__ __align__(16) float lsm[];          // node marginals (linear), rows of R (or r)
+  const int b = blockIdx.x, j = threadIdx.x, n = a.n, r = a.r, pitch = R ? R : r;
   const float* lay = a.layers;
   if (a.contextual && lay) lay += (long long)b * a.L * r * r;
   const long long lstep = (a.L > 1) ? (long long)r * r : 0;
   float* out = a.logm + (long long)b * n * r;
-  const float w = (j < r) ? expf(a.logw[(long long)b * r + j]) : 0.f;
-  if (a.family == MTPC_CP) {
-    if (j < r) for (int i = 0; i < n; ++i) out[i * r + j] = a.logw[(long long)b * r + j];
-    return;
-  }
-  if (a.family == MTPC_HMM) {
-    float* cur = lsm;
-    float* nxt = lsm + r;
-    if (j < r) { cur[j] = w; out[j] = logf(w); }
+  const bool hmm = a.family == MTPC_HMM;
+  const int nodes = hmm ? n : n - 1;                     // (binary tree: inner nodes, heap order)
+  const float w0 = (j < r) ? expf(a.logw[(long long)b * r + j]) : 0.f;
+  if (j < pitch) lsm[j] = w0;
+  if constexpr (R > 0) {
+    float w[R], next[R];
+    auto fetch = [&](int m, float (&c)[R]) {
+      const float* T = lay + (m - 1) * lstep;
+#pragma unroll
+      for (int k = 0; k < R; ++k) c[k] = T[min(k, r - 1) * r + min(j, r - 1)];
+    };
+    if (nodes > 1) fetch(1, w);
     __syncthreads();
-    for (int i = 1; i < n; ++i) {
+    for (int m = 1; m < nodes; ++m) {
+      fetch(min(m + 1, nodes - 1), next);
+      __builtin_amdgcn_sched_barrier(0);
+      const float* x = lsm + (hmm ? m - 1 : (m - 1) >> 1) * R;
       float s = 0.f;
-      if (j < r) {
-        s = column_dot(cur, lay + (long long)(i - 1) * lstep, r, j);
-        nxt[j] = s;
-        out[i * r + j] = logf(s);
-      }
+#pragma unroll
+      for (int k = 0; k < R; ++k) s = fmaf(x[k], w[k], s);              // (x[r ..] is 0)
+      if (j < R) lsm[m * R + j] = j < r ? s : 0.f;
+#pragma unroll
+      for (int k = 0; k < R; ++k) w[k] = next[k];
       __syncthreads();
-      float* t = cur; cur = nxt; nxt = t;
     }
-    return;
-  }
-  // BTree: marginal of every inner node's latent, heap order
-  if (j < r) lsm[j] = w;
-  __syncthreads();
-  for (int m = 1; m < n - 1; ++m) {
-    if (j < r) {
-      const float* A = lay + (long long)(m - 1) * lstep;
-      const float* par = lsm + (size_t)((m - 1) >> 1) * r;
-      lsm[(size_t)m * r + j] = column_dot(par, A, r, j);
-    }
+  } else {
     __syncthreads();
+    for (int m = 1; m < nodes; ++m) {
+      if (j < r) lsm[m * r + j] = column_dot(lsm + (hmm ? m - 1 : (m - 1) >> 1) * r, lay + (m - 1) * lstep, r, j);
+      __syncthreads();
+    }
   }
   if (j < r)
-    for (int i = 0; i < n; ++i) out[i * r + j] = logf(lsm[(size_t)((n - 2 + i) >> 1) * r + j]);
+    for (int i = 0; i < n; ++i) out[i * r + j] = logf(lsm[(hmm ? i : (n - 2 + i) >> 1) * pitch + j]);
 }
 
 hipError_t launch_latent_marginals(const LatentMarginalArgs& a, hipStream_t st) {
-  int threads = 64;
-  while (threads < a.r) threads <<= 1;
-  const size_t smem = (size_t)(a.n > 2 ? a.n : 2) * a.r * 4;
-  hipLaunchKernelGGL(k_latent_marginals, dim3(a.B), dim3(threads), smem, st, a);
+  if (a.r <= 8) hipLaunchKernelGGL(k_latent_marginals<8>, dim3(a.B), dim3(64), (size_t)a.n * 8 * 4, st, a);
+  else if (a.r <= 16) hipLaunchKernelGGL(k_latent_marginals<16>, dim3(a.B), dim3(64), (size_t)a.n * 16 * 4, st, a);
+  else if (a.r <= 32) hipLaunchKernelGGL(k_latent_marginals<32>, dim3(a.B), dim3(64), (size_t)a.n * 32 * 4, st, a);
+  else hipLaunchKernelGGL(k_latent_marginals<0>, dim3(a.B), dim3(128), (size_t)a.n * a.r * 4, st, a);
   return hipGetLastError();
 }
 
@@ -1543,39 +1548,45 @@ hipError_t launch_dwsum(const void* gT, const void* hT, long long ldb, int r, in
 // Univariate marginals (App. B.1) from the table of normalised input units:
 //   M[b][i][a] = log sum_j exp(logm[b][i][j] + log phi[b][i][j][a]).
 // One wave per (b, i); lane l holds tokens l, l + 64, ...; the r rows of the table are read
-// once, front to back (whole 256-byte segments), into a running maximum and a sum relative to it.
-__global__ __launch_bounds__(256) void k_univariate_table(const float* logphi, const float* logm, float* out,
-                                                          long long tokens, int r, int v) {
+// once, front to back (whole 256-byte segments), into a running maximum and a sum relative to it.  Bound by those reads: JB rows
+// are in flight together, as the weights come out of registers (a load of each between the rows' made the compiler wait for every
+// row before the next: whole calls, CP, d = 256, v = 268, n = 16, r = 8, B = 2000 184.8 -> 176.2 us, r = 64, B = 100 110.3 -> 102.6).
+__global__ __launch_bounds__(256) void k_univariate_table(const UnivariateArgs a, const float* logphi) {
   constexpr int VPL = 5;                      // v <= 320
-  const int lane = threadIdx.x & 63;
-  const long long t = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);       // (b, i) flattened
-  if (t >= tokens) return;
+  constexpr int JB = 8;                       // rows fetched together
+  const int lane = threadIdx.x & 63, r = a.r, v = a.v;
+  const long long t = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);       // (b, i) flattened
+  if (t >= (long long)a.B * a.n) return;
   const float* rows = logphi + t * r * v;
+  const float* lm = a.logm + (t / a.n) * a.logm_b + (t % a.n) * a.logm_i;
+  const float lm0 = lane < r ? lm[lane] : neg_inf(), lm1 = lane + 64 < r ? lm[lane + 64] : neg_inf();
   float m[VPL], s[VPL];
 #pragma unroll
   for (int q = 0; q < VPL; ++q) { m[q] = neg_inf(); s[q] = 0.f; }
-  constexpr int JB = 4;                       // rows fetched together
   for (int j0 = 0; j0 < r; j0 += JB) {
     float x[JB][VPL];
 #pragma unroll
     for (int u = 0; u < JB; ++u) {
-      const int j = min(j0 + u, r - 1);
-      const float lm = (j0 + u < r) ? (logm ? logm[t * r + j] : 0.f) : neg_inf();
+      const float* row = rows + (long long)min(j0 + u, r - 1) * v;
 #pragma unroll
-      for (int q = 0; q < VPL; ++q) {
-        const int k = lane + 64 * q;
-        x[u][q] = lm + rows[(long long)j * v + min(k, v - 1)];
-      }
+      for (int q = 0; q < VPL; ++q) x[u][q] = row[min(lane + 64 * q, v - 1)];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < JB; ++u) {            // (lanes from r on hold -inf, and j0 is a multiple of JB)
+      const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(j0 < 64 ? lm0 : lm1), (j0 & 63) + u));
+#pragma unroll
+      for (int q = 0; q < VPL; ++q) x[u][q] += w;
     }
 #pragma unroll
     for (int q = 0; q < VPL; ++q) {
       float mm = m[q];
 #pragma unroll
       for (int u = 0; u < JB; ++u) mm = fmaxf(mm, x[u][q]);
-      if (mm == neg_inf()) continue;          // only terms of probability zero so far
-      float ss = s[q] * __expf(m[q] - mm);    // (m = -inf: s = 0, exp(-inf) = 0)
+      const float ms = mm == neg_inf() ? 0.f : mm;       // only terms of probability zero so far: exp(-inf) = 0
+      float ss = s[q] * __expf(m[q] - ms);
 #pragma unroll
-      for (int u = 0; u < JB; ++u) ss += __expf(x[u][q] - mm);
+      for (int u = 0; u < JB; ++u) ss += __expf(x[u][q] - ms);
       m[q] = mm;
       s[q] = ss;
     }
@@ -1583,14 +1594,13 @@ __global__ __launch_bounds__(256) void k_univariate_table(const float* logphi, c
 #pragma unroll
   for (int q = 0; q < VPL; ++q) {
     const int k = lane + 64 * q;
-    if (k < v) out[t * v + k] = s[q] > 0.f ? m[q] + __logf(s[q]) : neg_inf();
+    if (k < v) a.out[t * v + k] = s[q] > 0.f ? m[q] + __logf(s[q]) : neg_inf();
   }
 }
 
 hipError_t launch_univariate_table(const UnivariateArgs& a, const float* logphi, hipStream_t st) {
   const long long tokens = (long long)a.B * a.n;
-  hipLaunchKernelGGL(k_univariate_table, dim3((unsigned)((tokens + 3) / 4)), dim3(256), 0, st, logphi, a.logm, a.out,
-                     tokens, a.r, a.v);
+  hipLaunchKernelGGL(k_univariate_table, dim3((unsigned)((tokens + 3) / 4)), dim3(256), 0, st, a, logphi);
   return hipGetLastError();
 }
 

@@ -82,7 +82,8 @@ struct UnivariateArgs {
   long long ld_h;
   const void* W;
   int B, d, v, n, r;
-  const float* logm;    // [B][n][r] log marginal of the latent indexing leaf i (nullptr: r == 1)
+  const float* logm;    // log marginal of the latent indexing leaf i: r values at b * logm_b + i * logm_i
+  long long logm_b, logm_i;
   float* out;           // [B][n][v]
 };
 

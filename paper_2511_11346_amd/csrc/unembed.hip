@@ -1041,7 +1041,7 @@ void k_univariate(const UnivariateArgs a) {
 #pragma unroll
     for (int pb = 0; pb < NPB; ++pb) {
       const int b = min(b0 + wb * PB * 32 + pb * FR::BR + lcol, a.B - 1);
-      const float lm = a.logm ? a.logm[((long long)b * a.n + wi) * a.r + j] : 0.f;
+      const float lm = a.logm[b * a.logm_b + wi * a.logm_i + j];
       // m_j phi_j = 2^((l - lse_j + log m_j) log2 e): one fused multiply-add and one v_exp per logit
       constexpr float LOG2E = 1.4426950408889634f;
       const float shift = (lm - lse[pb]) * LOG2E;

@@ -115,13 +115,13 @@ hipError_t launch_unembed_few(const UnembedArgs& a, const ParamArgs& p, int dtyp
 hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t) {
   need(a.h, strided(a.B, a.ld_h, a.d, esz(dtype)), "univariate h");
   need(a.W, (u64)a.n * a.r * a.v * a.d * esz(dtype), "univariate W");
-  opt(a.logm, (u64)a.B * a.n * a.r * 4, "univariate logm");
+  need(a.logm, (u64)((a.B - 1) * a.logm_b + (a.n - 1) * a.logm_i + a.r) * 4, "univariate logm");
   need(a.out, (u64)a.B * a.n * a.v * 4, "univariate out");
   return ok();
 }
 hipError_t launch_univariate_table(const UnivariateArgs& a, const float* logphi, hipStream_t) {
   need(logphi, (u64)a.B * a.n * a.r * a.v * 4, "univariate table");
-  opt(a.logm, (u64)a.B * a.n * a.r * 4, "univariate logm");
+  need(a.logm, (u64)((a.B - 1) * a.logm_b + (a.n - 1) * a.logm_i + a.r) * 4, "univariate logm");
   need(a.out, (u64)a.B * a.n * a.v * 4, "univariate out");
   return ok();
 }
