@@ -297,7 +297,7 @@ UnembedArgs unembed_args(const mtpc_head* hd) {
 void split_scratch(const mtpc_head* hd, const Plan& p, UnembedArgs& u) {
   if (!p.has_split) return;
   char* ws = (char*)hd->workspace;
-  u.Wq = ws + p.Wq; u.hq = ws + p.hq; u.wild = (int*)(ws + p.wild); u.three = 1; u.cleared = 1;      // (launch_params)
+  u.Wq = ws + p.Wq; u.hq = ws + p.hq; u.wild = (int*)(ws + p.wild); u.three = 1;      // (launch_params clears the flag)
 }
 
 // what a call's parameters are computed from; and the stage-major copy of h, where `hs` is its place
@@ -501,8 +501,8 @@ mtpc_status run_sample(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
   bool drawn = false;
   s = launch_params(family, hd, ly, p, true, want_prefix, st, &la, &drawn);
   if (s != MTPC_OK) return s;
-  if (!drawn) HIP_TRY(launch_latents(la, st));
-
+  // (factorised: nothing to draw, and only the buckets read which unit it would be; greedy, d = 256, v = 268, n = 8, B = 1 22.3 -> 19.7 us)
+  if (!drawn && (family != MTPC_FF || draw == Draw::Buckets)) HIP_TRY(launch_latents(la, st));
 
   const bool table_scores = want_prefix && draw != Draw::Buckets && (logphi != nullptr || p.has_table);
   float* table = logphi ? logphi : (table_scores ? (float*)(ws + p.table) : nullptr);
@@ -850,7 +850,7 @@ mtpc_status run_backward(int family, const mtpc_head* hd, const mtpc_sumlayers* 
   if (q.split_fwd) {
     pr.clear = flag; pr.nclear = nflags;
     u.Wq = ws + q.WT; u.Wq_rows = (int)q.ldM; u.Wexp = wexp; u.cols = cols;
-    u.hq = ws + q.hq; u.wild = flag; u.cleared = 1; u.three = 1;
+    u.hq = ws + q.hq; u.wild = flag; u.three = 1;
   }
   HIP_TRY(launch_call_params(pr, hd->dtype, st));
   if (q.has_hs) u.hs = ws + q.hs;

@@ -1389,11 +1389,6 @@ hipError_t launch_grad_exps(const GradPhiArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_clear(int* p, long long n, hipStream_t st) {
-  hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (float*)p, n);
-  return hipGetLastError();
-}
-
 hipError_t launch_circuit_bwd(const CircuitBwdArgs& a, hipStream_t st) {
   const long long rows = a.dslT ? a.ldb : a.rows;
   const int r = a.r;

@@ -1373,9 +1373,12 @@ __global__ __launch_bounds__(256) void k_draw_table(const DrawArgs a) {
   const long long bs = di / a.n;
   const long long b = bs / a.S;
   const int s = (int)(bs - b * a.S);
-  const int z = a.zleaf[di];
   // rows of the full table, or (compact) one row of unnormalised logits per token
-  const float* row = a.compact ? a.logphi + di * a.v : a.logphi + ((b * a.n + i) * a.r + z) * a.v;
+  const float* row = a.logphi + di * a.v;
+  if (!a.compact) {
+    const int z = a.r == 1 ? 0 : a.zleaf[di];
+    row = a.logphi + ((b * a.n + i) * a.r + z) * a.v;
+  }
   float lg[VPL], vals[VPL];
   float mx = neg_inf();
 #pragma unroll

@@ -48,7 +48,6 @@ struct UnembedArgs {
   int* wild;
   int* Wexp;            // where the exponents of W's rows go, [n*r*v], or nullptr: behind its planes
   int three;            // operands without SPLIT_WHOLE that are SPLIT_WIDE go through three bf16 terms, in the same scratch
-  int cleared;          // the flag is 0 already
   int* cols;            // counts of the columns of W (launch_split_rows), or nullptr
   int Wq_rows;          // > 0: the planes of W are ONE matrix of so many rows, [2 d/32][Wq_rows][64 bytes], slab after slab
 };
@@ -394,7 +393,6 @@ hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st)
 hipError_t launch_live_positions(const GradPhiArgs& a, hipStream_t st);
 hipError_t launch_grad_exps(const GradPhiArgs& a, hipStream_t st);
 // n ints set to 0 by a kernel
-hipError_t launch_clear(int* p, long long n, hipStream_t st);
 
 // An operand of a contraction given along its rows: K runs down the rows, columns lie in chunks of 32 (64 bytes).  Element
 // (k, 32 c + x) is at base + c * chunk + k * row + 2 x; rows from kmain (a multiple of 32) on come from `tail` instead,

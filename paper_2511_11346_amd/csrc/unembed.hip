@@ -469,10 +469,11 @@ void k_unembed(const UnembedArgs a) {
     // training-sized tiles: the tokens of all columns at once, one pass per draft (only tiles in which some
     // position draws token wi of that draft from component wj)
     if (a.zleaf == nullptr) return;
+    const bool one = a.r == 1;                         // (zleaf is 0 throughout, and not written)
     for (int s = 0; s < a.S; ++s) {
       auto need = [&](int p) {
         const long long b = b0 + p;
-        return b < a.B && a.zleaf[(b * a.S + s) * a.n + wi] == wj;
+        return b < a.B && (one || a.zleaf[(b * a.S + s) * a.n + wi] == wj);
       };
       bool any = false;
       for (int p = tid; p < TL::TP; p += TL::NT) any |= need(p);
@@ -484,6 +485,7 @@ void k_unembed(const UnembedArgs a) {
     }
   } else if constexpr (SAMPLE) {
     if (a.zleaf == nullptr) return;
+    const bool one = a.r == 1;                         // (zleaf is 0 throughout, and not written)
     // ---- which positions of this tile draw token wi from component wj?
     int* misc = (int*)(smem + TL::MISC_OFF);
     int* s_cnt = misc;
@@ -495,7 +497,7 @@ void k_unembed(const UnembedArgs a) {
       bool need = false;
       if (b < a.B)
         for (int s = 0; s < a.S; ++s)
-          need |= (a.zleaf[((long long)b * a.S + s) * a.n + wi] == wj);
+          need |= one || a.zleaf[((long long)b * a.S + s) * a.n + wi] == wj;
       if (need) s_list[atomicAdd(s_cnt, 1)] = p;
     }
     __syncthreads();
@@ -505,7 +507,7 @@ void k_unembed(const UnembedArgs a) {
       const int b = b0 + p;
       for (int s = 0; s < a.S; ++s) {
         const long long di = ((long long)b * a.S + s) * a.n + wi;
-        if (a.zleaf[di] != wj) continue;
+        if (!one && a.zleaf[di] != wj) continue;
         int tok;
         bool writer;
         if (a.greedy) {
@@ -766,45 +768,8 @@ static hipError_t launch_sumunit_mfma_cfg(const ParamArgs& p, hipStream_t st) {
   return launch_sumunit_mfma_nw<RB, PB, BF16, RB * PB <= 2 ? 16 : 8>(p, st);
 }
 
-// The same for many units over long rows in bf16: the tile machinery with Wsum as the only "slab" (r <= 128 rows), 32
-// positions to a workgroup, every operand row through LDS once per workgroup.  In registers the 128 rows of Wsum are
-// read anew for every 16 positions, and that is what a CU is then busy with.
-template <int SB>
-__global__ __launch_bounds__(128)
-void k_sumunit_ring(const void* h, long long ld_h, const void* Wsum, int B, int d, int r, float* logw) {
-  using TL = Tile<2, 1, 2, 1, SB, 4>;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int l31 = lane & 31, lhalf = lane >> 5;
-  const int b0 = blockIdx.x * TL::TP;
-  f32x16_t acc[1][2];
-  tile_gemm<2, 1, 2, 1, SB, 4, true>(Wsum, d, h, ld_h, B, d, r, 0, b0, smem, acc);
-  float mx[1], lse[1];
-  tile_lse<2, 1, 2, 1, SB, 4>(acc, r, (float2*)(smem + TL::RED_OFF), mx, lse);
-  const int b = b0 + l31;
-  if (b >= B) return;
-#pragma unroll
-  for (int vb = 0; vb < 2; ++vb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int row = wv * 64 + 4 * lhalf + vb * 32 + 8 * (i >> 2) + (i & 3);
-      if (row < r) logw[(long long)b * r + row] = acc[0][vb][i] - lse[0];
-    }
-}
-
-template <int SB>
-static hipError_t launch_sumunit_ring(const void* h, long long ld_h, const void* Wsum, int B, int d, int r, float* logw,
-                                      hipStream_t st) {
-  using TL = Tile<2, 1, 2, 1, SB, 4>;
-  if (hipError_t e = allow_lds<k_sumunit_ring<SB>>(TL::SMEM); e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sumunit_ring<SB>, dim3((B + TL::TP - 1) / TL::TP), dim3(TL::NT), TL::SMEM, st, h, ld_h, Wsum, B, d, r, logw);
-  return hipGetLastError();
-}
-
 // 16 positions per workgroup as long as those fill the 256 CUs at most once, else 32: Wsum is then read from the
-// L2s half as often.  bf16, more than 64 units: rows of up to 32 steps are as fast or faster this way (a one-token call of
-// 500 positions, r = 128, d = 544 25.5 / 27.1 us with the ring), longer ones are not (d = 1216 39.9 / 37.5, d = 4096 91.3 / 81.4;
-// 8000 positions 855 / 823).
+// L2s half as often.
 template <bool BF16>
 static hipError_t launch_sumunit_mfma_dt(const ParamArgs& p, hipStream_t st) {
   const bool wide = p.B > 4096;
@@ -1431,8 +1396,6 @@ hipError_t launch_split3(const Split3Job& j0, const Split3Job& j1, int* flag, in
   return hipGetLastError();
 }
 
-__global__ void k_clear_flag(int* flag) { *flag = 0; }
-
 // fp32 operands through their fp16 terms.  Operands that those would not do justice go through three bf16 terms, which cost
 // 1.7 times as much (see tile_gemm_run_split), and what those cannot take stays with the fp32 instruction: which of the
 // three launches does the work is known on the device only, the others' workgroups leave at once (2 to 3 us each, as the split
@@ -1441,7 +1404,6 @@ static hipError_t launch_split(const UnembedArgs& a0, hipStream_t st) {
   UnembedArgs a = a0;
   const long long slabs = (long long)a.n * a.r;
   if (a.Wexp == nullptr) a.Wexp = plane_exps(a.Wq, slabs * a.v * a.d);
-  if (!a.cleared) hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, st, a.wild);
   hipError_t e = launch_split_rows(a.h, a.hq, 1, a.B, a.d, a.ld_h * 4, plane_exps(a.hq, (long long)a.B * a.d), a.wild, 1, st, 0, 0x7fffffff,
                                    nullptr, 0, a.three, 0);
   if (e == hipSuccess) e = launch_split_rows(a.W, a.Wq, slabs, a.v, a.d, a.d * 4LL, a.Wexp, a.wild, 1, st, a.Wq_rows, 0x7fffffff, nullptr, 0, 0, a.three, a.cols);

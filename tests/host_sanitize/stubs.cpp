@@ -261,10 +261,6 @@ hipError_t launch_grad_exps(const GradPhiArgs& a, hipStream_t) {
   grad_scales(a);
   return ok();
 }
-hipError_t launch_clear(int* p, long long n, hipStream_t) {
-  need(p, (u64)n * 4, "clear");
-  return ok();
-}
 hipError_t launch_split3(const Split3Job& j0, const Split3Job& j1, int* flag, int, hipStream_t) {
   need(flag, 4, "split flag");
   for (const Split3Job* j : {&j0, &j1}) {
