@@ -185,7 +185,7 @@ class Head:
         hd.W = self.W.data_ptr()
         hd.Wsum = self.Wsum.data_ptr() if self.Wsum is not None else None
         hd.workspace, hd.workspace_bytes = self._ws.data_ptr(), self._ws.numel()
-        hd.stream = torch.cuda.current_stream(self.h.device).cuda_stream
+        hd.stream = torch._C._cuda_getCurrentRawStream(self.h.get_device())     # (a Stream object: 2.0 us instead of 0.15)
         hd.W_stage_major = self.W_stage_major.data_ptr() if self.W_stage_major is not None else None
         hd.W_stage_bytes = self.W_stage_bytes
         return hd
@@ -268,7 +268,7 @@ class Head:
         hd.W = self.W.data_ptr()
         hd.Wsum = self.Wsum.data_ptr() if self.Wsum is not None else None
         hd.workspace, hd.workspace_bytes = None, 0
-        hd.stream = torch.cuda.current_stream(self.h.device).cuda_stream
+        hd.stream = torch._C._cuda_getCurrentRawStream(self.h.get_device())     # (a Stream object: 2.0 us instead of 0.15)
         hd.W_stage_major = self.W_stage_major.data_ptr() if self.W_stage_major is not None else None
         hd.W_stage_bytes = self.W_stage_bytes
         _check(lib().mtpc_sample_static(FAMILY[self.family], C.byref(hd), self._layers_ref(), S, seed, offset,
