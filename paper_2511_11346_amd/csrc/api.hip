@@ -498,8 +498,10 @@ mtpc_status run_sample(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
     la.zero = (int*)(ws + p.bk_count);
     la.nzero = hd->n * hd->r;
   }
-  bool drawn = false;
-  s = launch_params(family, hd, ly, p, true, want_prefix, st, &la, &drawn);
+  // (the passes over a few slabs below a CP need no other parameters)
+  bool drawn = draw == Draw::Rows && family == MTPC_CP && rows_latents((long long)hd->B * S, hd->d, hd->v, hd->n, hd->r, hd->dtype);
+  const bool in_rows = drawn;
+  if (!drawn) s = launch_params(family, hd, ly, p, true, want_prefix, st, &la, &drawn);
   if (s != MTPC_OK) return s;
   // (factorised: nothing to draw, and only the buckets read which unit it would be; greedy, d = 256, v = 268, n = 8, B = 1 22.3 -> 19.7 us)
   if (!drawn && (family != MTPC_FF || draw == Draw::Buckets)) HIP_TRY(launch_latents(la, st));
@@ -512,7 +514,8 @@ mtpc_status run_sample(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
     rl.h = hd->h; rl.ld_h = hd->ld_h; rl.W = hd->W;
     rl.B = hd->B; rl.S = S; rl.d = hd->d; rl.v = hd->v; rl.n = hd->n; rl.r = hd->r;
     rl.zleaf = la.zleaf; rl.out = (float*)(ws + p.rowlogits);
-    HIP_TRY(launch_rows_logits(rl, hd->dtype, st));
+    const RowLatentArgs own{hd->Wsum, seed_lo, seed_hi, offset, greedy, la.latents};
+    HIP_TRY(in_rows ? launch_rows_latents(rl, own, hd->dtype, st) : launch_rows_logits(rl, hd->dtype, st));
     DrawArgs dr{};
     dr.B = hd->B; dr.S = S; dr.v = hd->v; dr.n = hd->n; dr.r = hd->r;
     dr.logphi = rl.out; dr.zleaf = la.zleaf; dr.drafts = drafts; dr.compact = 1;

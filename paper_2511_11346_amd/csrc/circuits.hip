@@ -1450,18 +1450,15 @@ __global__ __launch_bounds__(256) void k_draw_table(const DrawArgs a) {
 // hidden vector stays in registers); the rows go to a compact table [B*S*n][v] that
 // k_draw_table reads.  B*S*n*v*d products and as many bytes of W instead of a pass over all of it.
 // ---------------------------------------------------------------------------
+// (draft (b, s), token i) = di, logits row0 .. row0 + 3 of the slab of unit z, by a wave
 template <bool BF16>
-__global__ __launch_bounds__(256) void k_rows_logits(const RowLogitArgs a) {
+__device__ __forceinline__ void rows_logits(const RowLogitArgs& a, long long di, int z, int row0, int lane) {
   constexpr int ESZ = BF16 ? 2 : 4;
   constexpr int EPC = 16 / ESZ;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const long long di = blockIdx.x;                       // (b, s, i) flattened
   const int i = (int)(di % a.n);
   const long long b = di / a.n / a.S;
-  const int z = min(max(a.zleaf[di], 0), a.r - 1);
   const char* hb = (const char*)a.h + b * a.ld_h * ESZ;
   const char* Wz = (const char*)a.W + ((long long)(i * a.r + z) * a.v) * a.d * ESZ;
-  const int row0 = blockIdx.y * 16 + wave * 4;
   const int nch = a.d / EPC;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
   for (int c0 = 0; c0 < nch; c0 += 512) {
@@ -1488,6 +1485,47 @@ __global__ __launch_bounds__(256) void k_rows_logits(const RowLogitArgs a) {
     const float val = wave_sum(acc[q]);
     if (lane == 0 && row0 + q < a.v) a.out[di * a.v + row0 + q] = val;
   }
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(256) void k_rows_logits(const RowLogitArgs a) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const long long di = blockIdx.x;                       // (b, s, i) flattened
+  rows_logits<BF16>(a, di, min(max(a.zleaf[di], 0), a.r - 1), blockIdx.y * 16 + wave * 4, lane);
+}
+
+// Below a CP, whose one latent is drawn from the sum units: a workgroup of eight waves, 32 logits, first computes those
+// units, as all others do.  They read Wsum out of the L2s, which takes less than a launch that does it once, by one workgroup for
+// each position, and leaves the chip idle meanwhile (n = 16, v = 320, r = 32, d = 4096, B = 1, a greedy draft and its verification:
+// 24.5 -> 21.9 us, d = 256 24.2 -> 19.5).
+template <bool BF16>
+__global__ __launch_bounds__(512) void k_rows_latents(const RowLogitArgs a, const RowLatentArgs l) {
+  __shared__ float sc[128];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const long long di = blockIdx.x;                       // (b, s, i) flattened
+  const int b = (int)(di / a.n / a.S), s = (int)(di / a.n % a.S);
+  sumunit_position<BF16, 8>(a.h, a.ld_h, l.Wsum, b, a.d, a.r, sc);
+  const float q0 = lane < a.r ? expf(sc[lane]) : 0.f, q1 = lane + 64 < a.r ? expf(sc[lane + 64]) : 0.f;        // (as draft_latents)
+  const int drawn = l.greedy ? wave_argmax(q0, q1, a.r, lane)
+                             : wave_draw(q0, q1, a.r, philox_uniform(l.seed_lo, l.seed_hi, l.offset, (uint32_t)b, (uint32_t)s, (uint32_t)a.n), lane);
+  const int z = __builtin_amdgcn_readfirstlane(min(max(drawn, 0), a.r - 1));
+  if (blockIdx.y == 0 && threadIdx.x == 0 && di % a.n == 0) l.latents[di / a.n] = drawn;
+  rows_logits<BF16>(a, di, z, blockIdx.y * 32 + wave * 4, lane);
+}
+
+// As long as every workgroup has a CU to itself (draft and verification, r = 64, v = 256, n = 8, d = 1024, bf16, 64 workgroups to a
+// position: B = 4 23.8 -> 21.6 us, B = 8 26.3 -> 34.0; v = 320, n = 16, B = 1 23.8 -> 22.1, B = 2 25.4 -> 34.3), and up to 64 MB
+// of Wsum out of the L2s together (r = 64, d = 4096, B = 1: bf16, 84 MB, 26.2 with and without).
+bool rows_latents(long long drafts, int d, int v, int n, int r, int dtype) {
+  const long long groups = drafts * n * ((v + 31) / 32);
+  return groups <= 256 && groups * r * d * (dtype == MTPC_BF16 ? 2 : 4) <= 64ll << 20;
+}
+
+hipError_t launch_rows_latents(const RowLogitArgs& a, const RowLatentArgs& l, int dtype, hipStream_t st) {
+  const dim3 grid((unsigned)((long long)a.B * a.S * a.n), (unsigned)((a.v + 31) / 32));
+  if (dtype == MTPC_BF16) hipLaunchKernelGGL(k_rows_latents<true>, grid, dim3(512), 0, st, a, l);
+  else hipLaunchKernelGGL(k_rows_latents<false>, grid, dim3(512), 0, st, a, l);
+  return hipGetLastError();
 }
 
 hipError_t launch_rows_logits(const RowLogitArgs& a, int dtype, hipStream_t st) {

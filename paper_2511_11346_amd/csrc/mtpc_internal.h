@@ -266,6 +266,16 @@ struct RowLogitArgs {
   float* out;           // [B*S*n][v]
 };
 hipError_t launch_rows_logits(const RowLogitArgs& a, int dtype, hipStream_t st);
+// The same below a CP (zleaf unused): every workgroup computes the sum units of its position and draws the draft's latent by itself;
+// the latents are also left in `latents` [B][S].  Where rows_latents() says so.
+struct RowLatentArgs {
+  const void* Wsum;
+  uint32_t seed_lo, seed_hi, offset;
+  int greedy;
+  int* latents;
+};
+hipError_t launch_rows_latents(const RowLogitArgs& a, const RowLatentArgs& la, int dtype, hipStream_t st);
+bool rows_latents(long long drafts, int d, int v, int n, int r, int dtype);
 
 // Buckets of the (b, s, i) triples by (i, selected input unit): bucket g = i*r + z holds
 // list[row_off[g] .. row_off[g+1]) = the draft rows b*S+s whose token i comes from unit z

@@ -49,7 +49,7 @@ __device__ __forceinline__ void sumunit_position(const void* h, long long ld_h, 
                                                  float* sc) {
   constexpr int ESZ = BF16 ? 2 : 4;
   constexpr int EPC = 16 / ESZ;
-  constexpr int Q = NW > 4 ? 2 : 4;
+  constexpr int Q = NW > 8 ? 2 : 4;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const char* hb = (const char*)h + (long long)b * ld_h * ESZ;
   const int nch = d / EPC;
