@@ -72,8 +72,16 @@ __global__ __launch_bounds__(1024) void k_sumunit_layers(const ParamArgs p, cons
     params_beside<1024>(p, b - p.B);
     return;
   }
-  for (int l = 0; l < p.L; ++l)
-    for (int q = tid; q < rr; q += 1024) s_lay[l * rr + q] = p.logits[l * p.layer_stride + q];
+  for (int q = tid; q < rr; q += 1024)
+    for (int l0 = 0; l0 < p.L; l0 += 8) {                 // (eight layers in flight: each waited for the one before; HMM n = 16, r = 32, B = 61 17.7 -> 16.9 us)
+      float x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = p.logits[min(l0 + u, p.L - 1) * p.layer_stride + q];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (l0 + u < p.L) s_lay[(l0 + u) * rr + q] = x[u];
+    }
   sumunit_position<BF16, 16>(p.h, p.ld_h, p.Wsum, b, p.d, p.r, sc);
   if (tid < p.r) p.logw[(long long)b * p.r + tid] = sc[tid];
   for (int s = tid >> 6; s < la.S; s += 16) draft_latents<true>(la, b, s, sc, s_lay, tid & 63);
