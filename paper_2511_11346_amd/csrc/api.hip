@@ -475,7 +475,7 @@ mtpc_status run_sample(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
   //   FromTable - the fused kernel only writes the caller's table, k_draw_table reads it
   // and how the drafts are scored: from the table when there is one, else by one more
   // fused pass with the drafts as targets.
-  //   Rows      - k_rows_logits on the n slabs a draft needs, k_draw_table on the compact result
+  //   Rows      - k_rows_logits (k_rows_latents) on the n slabs a draft needs, k_draw_table on the compact result
   enum class Draw { InKernel, Buckets, FromTable, Rows };
   const void* const hs = p.has_hs ? ws + p.hs : nullptr;
   const size_t esz = hd->dtype == MTPC_BF16 ? 2 : 4;

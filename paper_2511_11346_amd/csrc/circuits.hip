@@ -40,9 +40,8 @@ __device__ __forceinline__ void draft_latents(const LatentArgs& a, int b, int s,
 // Few positions: one workgroup of 16 waves per position (sumunit_position).  With la.zleaf set the
 // workgroup goes on to draw the latents of the position's drafts from the weights it has just
 // computed (Alg. 1, top-down; one wave per draft) - one launch and one dependent round trip less
-// on the decode path.  Many positions go through the MFMA tile kernel instead.
-// ---------------------------------------------------------------------------
-// Beside them, or alone (no Wsum), the other parameters of the call.
+// on the decode path.  Many positions go through k_sumunit_mfma instead.
+// Workgroups behind theirs, or k_params alone (no Wsum), make the other parameters of the call (params_beside).
 // ---------------------------------------------------------------------------
 template <bool BF16>
 __global__ __launch_bounds__(1024) void k_sumunit(const ParamArgs p, const LatentArgs la) {

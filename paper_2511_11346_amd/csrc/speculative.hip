@@ -9,8 +9,10 @@
 //      tree: product of layer-transposed messages down the path to the leaf, with
 //      fully observed left siblings evaluated bottom-up and right siblings = 1);
 //   3. one draw from max(0, p - q) / Z (or from p after n acceptances).
-// Everything is O(n r^2 + r v) per position and latency-bound; matrix-vector
-// products use all 256 threads so that every layer costs one memory round trip.
+// Everything is O(n r^2 + r v) per position and latency-bound: k_verify_row fetches
+// whatever a rejection may need before it knows where there is one; k_verify, where
+// that does not fit, spreads a matrix-vector product over all 256 threads so that every
+// layer costs one memory round trip.
 #include <algorithm>
 #include <climits>
 
