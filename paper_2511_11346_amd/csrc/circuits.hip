@@ -828,7 +828,7 @@ static hipError_t launch_btree_static(const CircuitArgs& a, hipStream_t st) {
 // units - and log omega are fetched into LDS with every load in flight at once, then
 //  - binary tree: the nodes of a level are evaluated side by side by the workgroup's waves (one barrier per level), and the
 //    n prefix marginals - each a walk from a leaf to the root of at most log2 n products - are dealt to them;
-//  - HMM: one wave runs the forward recursion on linear values.  All exponentials of the evidence are taken before the chain, all
+//  - HMM: one wave runs the forward recursion on linear values.  All exponentials of the evidence behind the first token are taken before the chain, all
 //    logarithms of its sums after it; what is left of a step is one product, one sum over the units and a scaling by a power of two;
 //  - CP: the prefixes' sums, in double, and their log-sum-exps side by side.
 // A wave forms a product with all of its lanes: lane (k, part) sums the terms j = part, part + P, ... of output k (neighbouring
@@ -852,7 +852,7 @@ __global__ __launch_bounds__(1024) void k_circuit_row(const CircuitArgs a) {
   float* s_x = rsm;                                      // [threads] operands of the products
   float* s_lay = s_x + NT;                          // [Lst][j][k]
   float* s_ev = s_lay + (((size_t)Lst * r * r + 3) & ~(size_t)3);   // [n][r]
-  float* s_w = s_ev + (size_t)n * r;                     // [n][r] HMM: exp(evidence - its maximum); tree: node values
+  float* s_w = s_ev + (size_t)n * r;                     // [n][r] HMM: scaled exp(evidence - its maximum); tree: node values
   float* s_lw = s_w + (hmm || tree ? (size_t)n * r : 0); // [r]
   float* s_max = s_lw + r;                               // [n] HMM: the maxima
   float* s_sum = s_max + n;                              // [n] HMM: sums of the steps, and their exponents
@@ -953,34 +953,33 @@ __global__ __launch_bounds__(1024) void k_circuit_row(const CircuitArgs a) {
     for (int i = tid / G; i < n; i += step) {
       const float e = live ? s_ev[i * r + k] : ninf;
       const float m = max_units(e), ms = m == ninf ? 0.f : m;
-      if (live) s_w[i * r + k] = expf(e - ms);
+      if (live) s_w[i * r + k] = scaled_exp(e - ms, ROW_EVIDENCE);
       if (k == 0) s_max[i] = ms;
     }
     __syncthreads();
     if (wave != 0) return;                               // (no workgroup barrier below)
-    // x_k 2^E exp(the maxima so far) is the forward message; the product with a layer keeps its sum
-    const float lm = max_units(lw0), lms = lm == ninf ? 0.f : lm;
-    float x = live ? __builtin_amdgcn_ldexpf(expf(lw0 - lms), ROW_SCALE) : 0.f;
-    int E = -ROW_SCALE;
+    // x_k 2^E exp(what has been taken out so far) is the forward message; the product with a layer keeps its sum
+    float x = 0.f;
+    int E = 0;
     typename Ops::Weights w{};
     if (n > 1) w = weights(s_lay);
     for (int i = 0; i < n; ++i) {
       const int ic = i * r + min(k, r - 1);
-      const float ew = s_w[ic];
-      float y = x;
-      if (i > 0) {
-        y = product(x, w);
-        if (i < n - 1) w = weights(s_lay + (size_t)i * lstep);
-      }
       float s, taken = s_max[i];
       int shift;
-      x = observe<Ops>(y, ew, s_ev[ic], live, s, E, shift, taken);
+      if (i == 0) {
+        x = observe_first<Ops>(lw0, s_ev[ic], live, s, E, shift, taken);
+      } else {
+        const float ew = s_w[ic], y = product(x, w);
+        if (i < n - 1) w = weights(s_lay + (size_t)i * lstep);
+        x = observe<Ops>(y, ew, s_ev[ic], live, s, E, shift, taken);
+      }
       if (lane == 0) { s_sum[i] = s; s_exp[i] = E; s_max[i] = taken; }
       E -= shift;
     }
     __builtin_amdgcn_wave_barrier();
     if (lane < n) {
-      double M = (double)lms;
+      double M = 0.0;
       for (int t = 0; t <= lane; ++t) M += (double)s_max[t];
       emit(lane, (float)(M + (double)s_exp[lane] * 0.69314718055994530942 + (double)logf(s_sum[lane])));
     }

@@ -89,29 +89,56 @@ struct RowOps {
   }
 };
 
-// The HMM's forward message on linear values: x_k 2^exponent times the exponentials of what has been taken out of it before.
-// SCALE: its values sum to 2^64 .. 2^65, so that what is kept of a unit reaches 2^-149 and no result overflows
-constexpr int ROW_SCALE = 64;
-// One observation: y (unit k's, 0 for k >= r) times exp(evidence).  ew: exp(evidence - its maximum `taken`), e: the evidence itself.  Returns
-// the scaled product, its sum before that in s (whose exponent is `exponent` still), and counts the scaling in `shift`.
+// The HMM's forward message on linear values: x_k 2^exponent times the exponentials of what has been taken out of it before.  Its values
+// sum to 2^ROW_SCALE .. 2^(ROW_SCALE + 1), and the exponentials of the evidence, relative to its largest, come times 2^ROW_EVIDENCE: no
+// result overflows, and units down to 2^-126 of the largest keep their precision through a step, which is what a chain of logarithms
+// whose products are formed relative to the largest unit keeps.
+constexpr int ROW_SCALE = 32, ROW_EVIDENCE = 64;
+// exp(d) 2^scale, d <= 0: the scale goes in before a small exponential underflows
+__device__ __forceinline__ float scaled_exp(float d, int scale) {
+  const bool low = d < -64.f;
+  const float t = __builtin_amdgcn_ldexpf(expf(low ? 0.5f * d : d), low ? scale / 2 : scale);
+  return low ? t * t : t;
+}
+// values c with sum s > 0 to the message's scale; 2^shift is what they were multiplied with
+__device__ __forceinline__ float to_row_scale(float c, float s, int& shift) {
+  shift = s > 0.f ? ROW_SCALE + 1 - __builtin_amdgcn_frexp_expf(s) : 0;
+  return __builtin_amdgcn_ldexpf(c, shift);
+}
+// The first observation, out of logarithms: root weights and evidence may be further apart than any linear values reach, and yet
+// make up for each other.  lw, e: unit k's.  Returns the scaled message, its sum before the scaling in s (whose exponent is `exponent`
+// still), what it was scaled by in `shift` and the largest logarithm in `taken`.
+template <class Ops>
+__device__ __forceinline__ float observe_first(float lw, float e, bool live, float& s, int& exponent, int& shift, float& taken) {
+  const double l = (double)lw + (double)e;                   // (one rounding, of what is left relative to the largest)
+  const float most = Ops::max_units(live ? (float)l : neg_inf());
+  taken = most == neg_inf() ? 0.f : most;
+  const float c = live ? scaled_exp((float)(l - (double)taken), ROW_SCALE) : 0.f;
+  s = Ops::sum_units(c);
+  exponent = -ROW_SCALE;
+  return to_row_scale(c, s, shift);
+}
+// One observation: y (unit k's, 0 for k >= r) times exp(evidence).  ew: exp(evidence - its maximum `taken`) 2^ROW_EVIDENCE, e: the
+// evidence itself.  The rest as above.
 template <class Ops>
 __device__ __forceinline__ float observe(float y, float ew, float e, bool live, float& s, int& exponent, int& shift, float& taken) {
   float c = live ? y * ew : 0.f;
   s = Ops::sum_units(c);
-  if (s < 0x1p34f) {
+  exponent -= ROW_EVIDENCE;
+  if (s < 0x1p40f) {
     // the units that are left have next to none of the evidence (or none: nothing is left of the row): exponentials relative to
-    // the largest product
+    // the largest product.  (From 2^40 on what a linear evidence of less than 2^-126 makes of a unit, 2^-93 at the most, is
+    // less than 2^-126 of the largest.)
     const float l = live && y > 0.f ? logf(y) + e : neg_inf();
     const float most = Ops::max_units(l);
     if (most != neg_inf()) {
-      c = __builtin_amdgcn_ldexpf(expf(l - most), ROW_SCALE);
+      c = scaled_exp(l - most, ROW_SCALE);
       s = Ops::sum_units(c);
-      exponent -= ROW_SCALE;
+      exponent += ROW_EVIDENCE - ROW_SCALE;
       taken = most;
     }
   }
-  shift = s > 0.f ? ROW_SCALE + 1 - __builtin_amdgcn_frexp_expf(s) : 0;
-  return __builtin_amdgcn_ldexpf(c, shift);
+  return to_row_scale(c, s, shift);
 }
 
 }  // namespace mtpc

@@ -495,19 +495,19 @@ __global__ __launch_bounds__(VERIFY_ROW_THREADS) void k_verify_row(const VerifyA
       for (int i = tid / G; i < j; i += NT / G) {
         const float e = live ? s_e[i * r + k] : ninf;
         const float m = Ops::max_units(e), ms = m == ninf ? 0.f : m;
-        if (live) s_w[i * r + k] = expf(e - ms);
+        if (live) s_w[i * r + k] = scaled_exp(e - ms, ROW_EVIDENCE);
       }
       __syncthreads();
       if (wave == 0 && j > 0) {
         linear = true;
-        const float lm = Ops::max_units(lw);
-        float y = live ? __builtin_amdgcn_ldexpf(expf(lw - (lm == ninf ? 0.f : lm)), ROW_SCALE) : 0.f;
+        float y = 0.f;
         for (int i = 0; i < j; ++i) {                         // observe token i, predict state i + 1
           const int ic = i * r + min(k, r - 1);
           const typename Ops::Weights w = Ops::weights(s_lay + (size_t)i * lstep, k, part, r, rs, 1);
           float s, taken;
           int exponent = 0, shift;
-          const float z = observe<Ops>(y, s_w[ic], s_e[ic], live, s, exponent, shift, taken);
+          const float z = i == 0 ? observe_first<Ops>(lw, s_e[ic], live, s, exponent, shift, taken)
+                                 : observe<Ops>(y, s_w[ic], s_e[ic], live, s, exponent, shift, taken);
           y = Ops::product(z, w, xs, k, part, r, rs);
         }
         lam = live ? y : 0.f;
