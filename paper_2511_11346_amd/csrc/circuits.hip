@@ -981,7 +981,10 @@ __global__ __launch_bounds__(1024) void k_circuit_row(const CircuitArgs a) {
     if (lane < n) {
       double M = 0.0;
       for (int t = 0; t <= lane; ++t) M += (double)s_max[t];
-      emit(lane, (float)(M + (double)s_exp[lane] * 0.69314718055994530942 + (double)logf(s_sum[lane])));
+      // (the logarithm of the sum's mantissa, at most 0.7: that of the whole sum, 28 to 67, would be rounded by up to 2^-18 before it is added)
+      const float s = s_sum[lane];
+      const int e2 = s_exp[lane] + __builtin_amdgcn_frexp_expf(s);
+      emit(lane, (float)(M + (double)e2 * 0.69314718055994530942 + (double)logf(__builtin_amdgcn_frexp_mantf(s))));
     }
     return;
   }

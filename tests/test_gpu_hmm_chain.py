@@ -84,3 +84,18 @@ def test_verification(n, r, B):
     safe = margin >= 2e-4
     assert safe.sum() >= 0.9 * B
     assert np.array_equal(tok.cpu().numpy()[safe], want_tok[safe])
+
+@pytest.mark.parametrize("n,r", [(1, 8), (2, 32), (3, 32), (8, 16), (16, 32)])
+def test_scores_carry_one_rounding(n, r):
+    """Evidence as a byte model has it.  The result's own rounding is 2^-24 of it at the most, 3.4e-8 in the mean square; the steps before
+    it (linear values, errors of some 2^-24 each, in a magnitude of 5 a step) add less than that."""
+    B, v = 235, 3
+    inp = mi.make_inputs("hmm", B=B, d=32, n=n, r=r, v=v, dtype="f32", seed=n + r, h_scale=1.0)
+    inp.Wsum[:] = 0.0                                       # (weights 1 / r: none of their error is in what is measured)
+    logphi = (np.random.default_rng(r).standard_normal((B, n, r, v)) - 5.5).astype(np.float32)
+    logw, logT = oc.sum_unit(inp.h, inp.Wsum), oc.sum_layers(inp.layers)
+    want = oc.prefix_marginals_from("hmm", logphi.astype(np.float64), logw, logT, inp.targets)
+    got = make_head(inp).table_scores(torch.from_numpy(logphi).cuda(), torch.from_numpy(inp.targets).cuda()[:, None].contiguous(), prefix=True)
+    rel = (got.cpu().numpy()[:, 0].astype(np.float64) - want) / want
+    print(f"n={n} r={r}: relative error rms {np.sqrt(np.mean(rel ** 2)):.2e}, max {np.abs(rel).max():.2e}")
+    assert np.sqrt(np.mean(rel ** 2)) <= 6e-8
