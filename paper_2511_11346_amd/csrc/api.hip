@@ -543,6 +543,7 @@ mtpc_status run_sample(int family, const mtpc_head* hd, const mtpc_sumlayers* ly
   } else {
     UnembedArgs u = unembed_args(hd);
     u.logphi = table;
+    u.drawn = draw == Draw::FromTable;
     u.hs = hs;
     if (draw == Draw::InKernel) {
       u.zleaf = la.zleaf; u.S = S; u.drafts = drafts;

@@ -38,6 +38,7 @@ struct UnembedArgs {
   uint32_t seed_lo, seed_hi, offset;
   int greedy;           // 1: every draw is replaced by the most likely outcome (no random numbers)
   float* logphi;        // [B][n][r][v] normalised logits of every slab, or nullptr
+  int drawn;            // tokens are drawn from logphi: sums in the order of the passes that draw
   float* phiT;          // [n*r*v][ld_phi] softmax probabilities, transposed, or nullptr (evidence kernel only)
   long long ld_phi;
   // fp32 operands of 256-position tiles, multiplied as two fp16 terms each (split_pays): scratch that

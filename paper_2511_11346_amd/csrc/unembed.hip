@@ -291,10 +291,11 @@ void k_unembed(const UnembedArgs a) {
   Feed feed;
   const int wrows = SPLIT ? a.Wq_rows : 0;
   // One tile of positions: every workgroup streams a slab of its own.  Tiles that share slabs and rows of h in an L2 walk K together,
-  // from its beginning (starts that differ: B = 300 .. 1000 the same, B = 4096 and 8192 0.4 % slower).  Passes that draw do as well: with
-  // sums in another order one token in 30,000 falls on the other side of its uniform, and a draft of a given seed is to stay what it
-  // was (draft and score, B = 61, W's own rows, 320 / 309 us; the gathered draws of n r = 1024, B = 4096 446 / 439).
-  auto first = [&](int sl) { return ROT && nbt == 1 ? first_stage(sl, a.d * (BF16 ? 2 : 4), SB) : 0; };
+  // from its beginning (starts that differ: B = 300 .. 1000 the same, B = 4096 and 8192 0.4 % slower).  Passes that draw, or fill a table
+  // that tokens are drawn from, do as well: with sums in another order one token in 30,000 falls on the other side of its uniform, and
+  // a draft of a given seed is to stay what it was (draft and score, B = 61, W's own rows, 320 / 309 us; the gathered draws of n r = 1024,
+  // B = 4096 446 / 439; draft, table, scores and verification, n r = 256, d = 2048, B = 256 171 / 152).
+  auto first = [&](int sl) { return ROT && nbt == 1 && !a.drawn ? first_stage(sl, a.d * (BF16 ? 2 : 4), SB) : 0; };
   feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab, bt * TL::TP, smem, nullptr, 0, 1, hstaged, wrows, slab * a.v,
             first(slab));
   for (int w = blockIdx.x;;) {
