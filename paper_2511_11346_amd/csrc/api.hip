@@ -322,7 +322,7 @@ mtpc_status launch_params(int family, const mtpc_head* hd, const mtpc_sumlayers*
   const bool fuse = draws != nullptr && family != MTPC_FF && hd->B <= SUMUNIT_SMALL_B;
   if (draws_done) *draws_done = fuse;
   ParamArgs g = param_args(hd, p.has_hs ? ws + p.hs : nullptr);
-  if (family != MTPC_FF && !fuse && !own_sumunit) { g.Wsum = hd->Wsum; g.logw = (float*)(ws + p.logw); }
+  if (family != MTPC_FF && !fuse && !own_sumunit) { g.Wsum = hd->Wsum; g.logw = (float*)(ws + p.logw); g.draws = draws != nullptr; }
   if (p.has_split) { g.clear = (int*)(ws + p.wild); g.nclear = 1; }
   const int L = n_layers(family, hd->n);
   if (L > 0 && ly->R != nullptr) {

@@ -62,6 +62,7 @@ struct ParamArgs {
   const void* Wsum;
   int B, d, r;
   float* logw;          // [B][r]: log omega[b][:] = log_softmax(Wsum h[b])
+  int draws;            // latents are drawn from log omega: its sums in one order whatever is fastest
   // softmax over the last axis of r x r logits -> linear probabilities.  logits[b*batch_stride + l*layer_stride + k*r + j];
   // out_nat[((b*L + l)*r + k)*r + j] and / or the same transposed, out_tr[((b*L + l)*r + j)*r + k] (either may be nullptr)
   const float* logits;

@@ -769,12 +769,54 @@ static hipError_t launch_sumunit_mfma_cfg(const ParamArgs& p, hipStream_t st) {
   return launch_sumunit_mfma_nw<RB, PB, BF16, RB * PB <= 2 ? 16 : 8>(p, st);
 }
 
+// The same for many units over long rows in bf16: the tile machinery with Wsum as the only "slab" (r <= 128 rows), 32
+// positions to a workgroup, every operand row through LDS once per workgroup, K in one chain.
+template <int SB>
+__global__ __launch_bounds__(128)
+void k_sumunit_ring(const void* h, long long ld_h, const void* Wsum, int B, int d, int r, float* logw) {
+  using TL = Tile<2, 1, 2, 1, SB, 4>;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int l31 = lane & 31, lhalf = lane >> 5;
+  const int b0 = blockIdx.x * TL::TP;
+  f32x16_t acc[1][2];
+  tile_gemm<2, 1, 2, 1, SB, 4, true>(Wsum, d, h, ld_h, B, d, r, 0, b0, smem, acc);
+  float mx[1], lse[1];
+  tile_lse<2, 1, 2, 1, SB, 4>(acc, r, (float2*)(smem + TL::RED_OFF), mx, lse);
+  const int b = b0 + l31;
+  if (b >= B) return;
+#pragma unroll
+  for (int vb = 0; vb < 2; ++vb)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int row = wv * 64 + 4 * lhalf + vb * 32 + 8 * (i >> 2) + (i & 3);
+      if (row < r) logw[(long long)b * r + row] = acc[0][vb][i] - lse[0];
+    }
+}
+
+// (the other parameters by a launch of their own: this kernel's LDS leaves two of its workgroups to a CU, too few to copy h - r = 128,
+// d = 4096, B = 8192, a one-token call 847 us instead of 836 -, and behind it, so that the copy is in the last cache when W's pass begins)
+template <int SB>
+static hipError_t launch_sumunit_ring(const ParamArgs& p, hipStream_t st) {
+  using TL = Tile<2, 1, 2, 1, SB, 4>;
+  if (hipError_t e = allow_lds<k_sumunit_ring<SB>>(TL::SMEM); e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_sumunit_ring<SB>, dim3((p.B + TL::TP - 1) / TL::TP), dim3(TL::NT), TL::SMEM, st, p.h, p.ld_h, p.Wsum, p.B, p.d, p.r, p.logw);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  ParamArgs rest = p;
+  rest.Wsum = nullptr;
+  return launch_call_params(rest, MTPC_BF16, st);
+}
+
 // 16 positions per workgroup as long as those fill the 256 CUs at most once, else 32: Wsum is then read from the
-// L2s half as often.
+// L2s half as often.  bf16, more than 64 units, rows of more than 32 steps, and latents to be drawn: the ring above, in whose order the
+// weights of a seed's drafts have always been summed.  For scores it is the slower one up to 4000 positions and little faster beyond (one-token
+// calls, ring / this, r = 128: d = 4096, B = 500 79 / 73 us, 3000 329 / 326, 8192 850 / 870; d = 2048, B = 129 41 / 34, 2000 128 / 124, 8192 468 / 476;
+// v = 320, B = 8000, d = 4096 1905 / 1920).
 template <bool BF16>
 static hipError_t launch_sumunit_mfma_dt(const ParamArgs& p, hipStream_t st) {
   const bool wide = p.B > 4096;
   const int r = p.r;
+  if (BF16 && p.draws && r > 64 && p.d > 1024) return p.d % 64 == 0 ? launch_sumunit_ring<128>(p, st) : launch_sumunit_ring<64>(p, st);
   if (r <= 16) return wide ? launch_sumunit_mfma_cfg<1, 2, BF16>(p, st) : launch_sumunit_mfma_cfg<1, 1, BF16>(p, st);
   if (r <= 32) return wide ? launch_sumunit_mfma_cfg<2, 2, BF16>(p, st) : launch_sumunit_mfma_cfg<2, 1, BF16>(p, st);
   if (r <= 64) return wide ? launch_sumunit_mfma_cfg<4, 2, BF16>(p, st) : launch_sumunit_mfma_cfg<4, 1, BF16>(p, st);
