@@ -942,9 +942,9 @@ __global__ __launch_bounds__(1024) void k_circuit_row(const CircuitArgs a) {
       double s = (double)lw0;
       if (live)
         for (int t = 0; t <= i; ++t) s += (double)s_ev[t * r + k];
-      const float m = max_units(live ? (float)s : ninf);
-      const float z = sum_units(live && m != ninf ? __expf((float)(s - (double)m)) : 0.f);
-      if (k == 0) emit(i, m == ninf ? m : (float)((double)m + (double)__logf(z)));
+      const float m = max_units(live ? (float)s : ninf), ms = m == ninf ? 0.f : m;      // (-inf: all of them are, or NaN)
+      const float z = sum_units(live ? __expf((float)(s - (double)ms)) : 0.f);
+      if (k == 0) emit(i, (float)((double)ms + (double)__logf(z)));
     }
     return;
   }
