@@ -12,6 +12,10 @@ from typing import Optional
 
 import torch
 
+# The handle of a device's current stream as it is (0.15 us; out of a Stream object made for it 2.0).  torch's name for that is its own
+# affair: without it, the object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream(device).cuda_stream)
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmtpc.so")
 
@@ -185,7 +189,7 @@ class Head:
         hd.W = self.W.data_ptr()
         hd.Wsum = self.Wsum.data_ptr() if self.Wsum is not None else None
         hd.workspace, hd.workspace_bytes = self._ws.data_ptr(), self._ws.numel()
-        hd.stream = torch._C._cuda_getCurrentRawStream(self.h.get_device())     # (a Stream object: 2.0 us instead of 0.15)
+        hd.stream = _raw_stream(self.h.get_device())
         hd.W_stage_major = self.W_stage_major.data_ptr() if self.W_stage_major is not None else None
         hd.W_stage_bytes = self.W_stage_bytes
         return hd
@@ -268,7 +272,7 @@ class Head:
         hd.W = self.W.data_ptr()
         hd.Wsum = self.Wsum.data_ptr() if self.Wsum is not None else None
         hd.workspace, hd.workspace_bytes = None, 0
-        hd.stream = torch._C._cuda_getCurrentRawStream(self.h.get_device())     # (a Stream object: 2.0 us instead of 0.15)
+        hd.stream = _raw_stream(self.h.get_device())
         hd.W_stage_major = self.W_stage_major.data_ptr() if self.W_stage_major is not None else None
         hd.W_stage_bytes = self.W_stage_bytes
         _check(lib().mtpc_sample_static(FAMILY[self.family], C.byref(hd), self._layers_ref(), S, seed, offset,
