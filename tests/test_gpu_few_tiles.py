@@ -55,8 +55,8 @@ def test_layers_of_every_position(family, dtype):
     tol_check(got, oc.prefix_marginals_from(family, logphi, logw, ll, inp.targets), dtype, family)
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 2048), ("f32", 1024)])
-@pytest.mark.parametrize("B", [1, 16])
+@pytest.mark.parametrize("dtype,d", [("bf16", 2048), ("f32", 1024), ("bf16", 2080)])       # (the last in 64-byte stages)
+@pytest.mark.parametrize("B", [1, 16, 17, 32])
 def test_a_vocabulary_that_is_streamed(B, d, dtype):
     """More than 128 MB of W and one tile of positions: read as a stream, slabs from different stages of K on."""
     inp = mi.make_inputs("cp", B=B, d=d, n=4, r=36, v=300, dtype=dtype, seed=B, h_scale=1.0)
