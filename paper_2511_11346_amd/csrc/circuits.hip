@@ -1522,14 +1522,6 @@ __global__ __launch_bounds__(512) void k_rows_latents(const RowLogitArgs a, cons
   rows_logits<BF16>(a, di, z, blockIdx.y * 32 + wave * 4, lane);
 }
 
-// As long as every workgroup has a CU to itself (draft and verification, r = 64, v = 256, n = 8, d = 1024, bf16, 64 workgroups to a
-// position: B = 4 23.8 -> 21.6 us, B = 8 26.3 -> 34.0; v = 320, n = 16, B = 1 23.8 -> 22.1, B = 2 25.4 -> 34.3), and up to 64 MB
-// of Wsum out of the L2s together (r = 64, d = 4096, B = 1: bf16, 84 MB, 26.2 with and without).
-bool rows_latents(long long drafts, int d, int v, int n, int r, int dtype) {
-  const long long groups = drafts * n * ((v + 31) / 32);
-  return groups <= 256 && groups * r * d * (dtype == MTPC_BF16 ? 2 : 4) <= 64ll << 20;
-}
-
 hipError_t launch_rows_latents(const RowLogitArgs& a, const RowLatentArgs& l, int dtype, hipStream_t st) {
   const dim3 grid((unsigned)((long long)a.B * a.S * a.n), (unsigned)((a.v + 31) / 32));
   if (dtype == MTPC_BF16) hipLaunchKernelGGL(k_rows_latents<true>, grid, dim3(512), 0, st, a, l);

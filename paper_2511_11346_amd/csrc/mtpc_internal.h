@@ -277,7 +277,13 @@ struct RowLatentArgs {
   int* latents;
 };
 hipError_t launch_rows_latents(const RowLogitArgs& a, const RowLatentArgs& la, int dtype, hipStream_t st);
-bool rows_latents(long long drafts, int d, int v, int n, int r, int dtype);
+// As long as every workgroup has a CU to itself (draft and verification, r = 64, v = 256, n = 8, d = 1024, bf16, 64 workgroups to a
+// position: B = 4 23.8 -> 21.6 us, B = 8 26.3 -> 34.0; v = 320, n = 16, B = 1 23.8 -> 22.1, B = 2 25.4 -> 34.3), and up to 64 MB
+// of Wsum out of the L2s together (r = 64, d = 4096, B = 1: bf16, 84 MB, 26.2 with and without).
+inline bool rows_latents(long long drafts, int d, int v, int n, int r, int dtype) {
+  const long long groups = drafts * n * ((v + 31) / 32);
+  return groups <= 256 && groups * r * d * (dtype == MTPC_BF16 ? 2 : 4) <= 64ll << 20;
+}
 
 // Buckets of the (b, s, i) triples by (i, selected input unit): bucket g = i*r + z holds
 // list[row_off[g] .. row_off[g+1]) = the draft rows b*S+s whose token i comes from unit z
@@ -404,7 +410,6 @@ hipError_t launch_grad_from_phi(const GradPhiArgs& a, int dtype, hipStream_t st)
 // of both and whether the terms do
 hipError_t launch_live_positions(const GradPhiArgs& a, hipStream_t st);
 hipError_t launch_grad_exps(const GradPhiArgs& a, hipStream_t st);
-// n ints set to 0 by a kernel
 
 // An operand of a contraction given along its rows: K runs down the rows, columns lie in chunks of 32 (64 bytes).  Element
 // (k, 32 c + x) is at base + c * chunk + k * row + 2 x; rows from kmain (a multiple of 32) on come from `tail` instead,

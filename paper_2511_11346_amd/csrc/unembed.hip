@@ -1668,7 +1668,8 @@ template <bool BF16, int NPB>
 static hipError_t launch_few_rows(const UnembedArgs& a, const ParamArgs& p, hipStream_t st) {
   constexpr int RB = BF16 ? 4 : 2, W = BF16 ? 1 : 2;
   const int need = std::max(a.v, p.Wsum != nullptr ? p.r : 0);
-  if (a.d * (BF16 ? 2 : 4) % 128 != 0) return launch_few_cfg<BF16, 5 * W, RB, NPB, 64, 4>(a, p, st);
+  if constexpr (BF16)                                // (d is a multiple of 32: fp32 rows always are of whole 128-byte stages)
+    if (a.d % 64 != 0) return launch_few_cfg<BF16, 5 * W, RB, NPB, 64, 4>(a, p, st);
   if (need > 256) return launch_few_cfg<BF16, 5 * W, RB, NPB, 128, 3>(a, p, st);
   if (need > 128) return launch_few_cfg<BF16, 4 * W, RB, NPB, 128, 4>(a, p, st);
   return launch_few_cfg<BF16, 2 * W, RB, NPB, 128, 4>(a, p, st);

@@ -186,10 +186,6 @@ hipError_t launch_rows_latents(const RowLogitArgs& a, const RowLatentArgs& l, in
   need(a.out, (u64)a.B * a.S * a.n * a.v * 4, "rows out");
   return ok();
 }
-bool rows_latents(long long drafts, int d, int v, int n, int r, int dtype) {
-  const long long groups = drafts * n * ((v + 31) / 32);
-  return groups <= 256 && groups * r * d * (int)esz(dtype) <= 64ll << 20;
-}
 static void bucket_arrays(const int* row_off, const int* tile_off, const int* tile_bucket, const int* list, u64 B, u64 S,
                           u64 n, u64 r, u64 tile) {
   need(row_off, (n * r + 1) * 4, "bucket row_off");
