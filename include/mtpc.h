@@ -72,19 +72,23 @@ typedef struct {
   void* workspace;        /* device scratch, >= mtpc_workspace_bytes(...)                 */
   size_t workspace_bytes;
   void* stream;           /* hipStream_t                                                  */
-  const void* W_stage_major; /* optional (NULL: none): the copy of W that mtpc_pack_weights makes.   */
-                          /* The pass over all of W in mtpc_*_sample / *_greedy_draft /         */
+  const void* W_stage_major; /* optional (NULL: none): the copy of W that mtpc_pack_weights makes.  */
+                          /* The pass over all of W in mtpc_*_sample / *_greedy_draft /          */
                           /* *_loglik / *_marginals / *_window_scores / *_loss_backward reads it */
-                          /* instead of W when its stages are the ones that pass uses: 128      */
-                          /* bytes for B <= 64, 64 bytes for larger batches (same results, bit  */
-                          /* for bit; 3-5 % less time), and so do the token draws of a larger   */
-                          /* batch (each from its one slab; 64-byte stages, 6-8 % less time).   */
-                          /* A copy with the other stage size is ignored, and so is any by a    */
-                          /* batch of 33 to 64 positions of few tiles (n r <= 128 in fp32,      */
-                          /* <= 32 in bf16), and by the scoring calls and the training step     */
-                          /* where fp32 is multiplied as fp16 terms (mtpc_workspace_bytes;      */
-                          /* draws read it all the same).  W must be valid as well: every       */
-                          /* other path reads W.                                                */
+                          /* instead of W when its stages are the ones that pass uses: 128       */
+                          /* bytes for B <= 64, 64 bytes for larger batches (same results, bit   */
+                          /* for bit; 3-5 % less time, 7-9 % for some hundred positions, 1-4 %   */
+                          /* for B <= 8, but 3 % more for sampling at B = 33 to 64), and so do   */
+                          /* the token draws of a larger batch (each from its one slab; 64-byte  */
+                          /* stages, 6-8 % less time).  A copy with the other stage size is      */
+                          /* ignored, and so is any by a batch of 33 to 64 positions of few      */
+                          /* tiles (n r <= 128 in fp32, <= 32 in bf16), by loglik, marginals and */
+                          /* window_scores whose tiles all run at once (n r ceil(B / 32) <= 256  */
+                          /* in fp32, (n r + 1) ceil(B / 32) <= 256 and r > 1 in bf16: those are */
+                          /* faster from W's rows), and by the scoring calls and the training    */
+                          /* step where fp32 is multiplied as fp16 terms (mtpc_workspace_bytes;  */
+                          /* draws read it all the same).  W must be valid as well: every other  */
+                          /* path reads W.                                                       */
   int32_t W_stage_bytes;  /* stage size of that copy: 128 (also meant by 0) or 64               */
 } mtpc_head;
 

@@ -169,8 +169,8 @@ class Head:
         """Make the stage-major copy of W (for serving, W fixed) and use it from now on: the pass over
         all of W reads it instead of W's rows.  The stage size has to be the one that pass uses for this
         head's batch (the default): 128 bytes up to 64 positions, 64 bytes above.  Costs one more buffer
-        of the size of W.  Scoring in fp32 where that is multiplied as fp16 terms does not read it (include/mtpc.h,
-        W_stage_major): for that the buffer is of use to draws only."""
+        of the size of W.  Scoring in fp32 where that is multiplied as fp16 terms, and scoring so few tiles that all run at
+        once, does not read it (include/mtpc.h, W_stage_major): for that the buffer is of use to draws only."""
         buf = torch.empty_like(self.W)
         hd = self._head(256)
         hd.W_stage_major = None

@@ -121,7 +121,9 @@ inline bool unembed_few_params(int B, int n, int r, int tile) {
 // Positions per tile of such a call, 0: none.  fp32, which is bound by its products, takes 16 wherever that fills no more than the 256
 // CUs (B = 64, n = 4, r = 8, d = 256, v = 256 21.3 -> 13.6 us, B = 5, n = 4, r = 20, d = 3072, v = 128 119 -> 49); bf16, as wide a tile as
 // that of k_unembed, gains the launches that it saves (B = 64, n = 4, r = 16, d = 256 18.7 -> 11.7, d = 4096 74.7 -> 68.0) and
-// the head without sum units has none (B = 500, d = 2048: 24.6 / 26.5).
+// the head without sum units has none (B = 500, d = 2048: 24.6 / 26.5).  A stage-major copy of W is not read: calls from the copy through
+// k_unembed are slower than these from W's own rows (bf16, n r = 248, v = 320, d = 4096, B = 1 111 / 98 us, n r = 64, B = 64 72 / 67, d = 256 21 / 10; n r =
+// 192, v = 256, d = 2048, B = 32 44 / 36; 1.09 to 2.2 times as long at 99 sizes in bf16 and fp32).
 inline int unembed_few(int B, int n, int r, int dtype) {
   const long long slabs = (long long)n * r;
   if (dtype == MTPC_F32) return slabs * ((B + 15LL) / 16) <= 256 ? 16 : slabs * ((B + 31LL) / 32) <= 256 ? 32 : 0;

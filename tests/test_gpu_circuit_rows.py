@@ -65,3 +65,16 @@ def test_evidence_far_apart(family, r):
     assert np.array_equal(np.isneginf(got), np.isneginf(want))
     ok = np.isfinite(want)
     assert np.all(np.abs(got - want)[ok] <= 1e-4 + 4 * 2.0 ** -23 * np.abs(want[ok]))
+
+
+@pytest.mark.parametrize("B", [1, 3, 17, 255])
+@pytest.mark.parametrize("n,r", [(16, 60), (32, 40), (16, 64), (64, 32)])
+def test_few_rows_of_trees_whose_layers_do_not_fit(n, r, B):
+    inp = mi.make_inputs("btree", B=B, d=32, n=n, r=r, v=5, dtype="f32", seed=n + r, h_scale=1.0)
+    logphi, logw, lay = oc._params("btree", inp.h, inp.W, inp.Wsum, inp.layers)
+    x = inp.targets.astype(np.int32).copy()
+    x[0, 0], x[-1, -1] = -1, 5                              # summed out, no such id
+    head, tx = make_head(inp), torch.from_numpy(x).cuda()
+    got = head.prefix_marginals(tx)
+    tol_check(got.cpu().numpy(), oc.prefix_marginals_from("btree", logphi, logw, lay, x), "f32", "prefix")
+    tol_check(head.loglik(tx).cpu().numpy(), got[:, -1].cpu().numpy(), "f32", "log-likelihood")
