@@ -51,6 +51,8 @@ struct UnembedArgs {
   int three;            // operands without SPLIT_WHOLE that are SPLIT_WIDE go through three bf16 terms, in the same scratch
   int* cols;            // counts of the columns of W (launch_split_rows), or nullptr
   int Wq_rows;          // > 0: the planes of W are ONE matrix of so many rows, [2 d/32][Wq_rows][64 bytes], slab after slab
+  // the launch's own: stages of K that slabs start at in turn, or 0 (all at its beginning), and their reciprocal (first_stage)
+  unsigned first_stages, first_reciprocal;
 };
 
 // What a call computes from h and the layer logits alone, before its circuit: log omega (Wsum nullptr: not wanted), the softmax of
@@ -129,6 +131,18 @@ inline int unembed_few(int B, int n, int r, int dtype) {
   if (dtype == MTPC_F32) return slabs * ((B + 15LL) / 16) <= 256 ? 16 : slabs * ((B + 31LL) / 32) <= 256 ? 32 : 0;
   const int tile = B <= 16 ? 16 : 32;
   return r > 1 && unembed_few_params(B, n, r, tile) ? tile : 0;
+}
+// Whether slabs that are each streamed by a workgroup of their own (one tile of `positions`) start at different stages of K.  Rows of W
+// lie row_bytes apart, and CUs that all walk K from 0 ask the same few memory channels at a time where that is a multiple of a
+// large power of two, or next to one.  Log-likelihoods, own rows, the same beginning / different ones: n r = 512, v = 268, B = 1 and v = 320, B = 100,
+// d = 2048 129 / 94 us and 162 / 143, 3072 136 / 135 and 203 / 201, 4096 175 / 174 and 256 / 248; n r = 320, v = 256, B = 64, d = 2048 99 / 78, 4096 166 / 138, 4064
+// (8192 - 64 bytes) 276 / 233.  Others spread over the channels by themselves, and wrapping round only costs: v = 320, B = 40, d = 2592 224 / 241,
+// 3744 0.92, B = 64, d = 3360 0.94, B = 100, d = 2240 0.93 of the speed, few more than 1.02.  Tiles of more positions, which ask for W in 64-byte halves of lines,
+// gain wherever rows are of whole lines (B = 256, d = 2112 to 4096 1.04 to 1.14, B = 160 0.99 to 1.06) and lose nothing elsewhere (0.99 to 1.01).
+// Rows of less than 4 KB: nothing (n r = 256, B = 1, d = 1024 39.6 us either way).
+inline bool starts_differ(long long row_bytes, int positions) {
+  const long long off = row_bytes % 8192;
+  return row_bytes >= 4096 && (positions > 128 || row_bytes % 2048 == 0 || off <= 64 || off >= 8192 - 64);
 }
 // Positions per tile of the fused kernel.  A decode-sized batch is one tile (W is then read once).  Larger ones
 // take 256, unless fewer are enough or the narrower tiles all run at once on the 256 CUs: a K stage of those is

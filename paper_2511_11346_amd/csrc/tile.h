@@ -420,13 +420,10 @@ struct TileFeed {
   }
 };
 
-// The stage that a slab's product starts with where every workgroup streams a slab of its own: one further than the slab before
-// it.  Rows of W lie a power of two or nearly that apart, and CUs that all walk K from 0 ask the same few memory channels at a
-// time (prefix marginals, n r = 512, v = 320, W's own rows, B = 200: d = 4096 356 -> 324 us, 2048 214 -> 193, 3072 286 -> 261, B = 100
-// 280 -> 271).  Rows of less than 4 KB spread
-// over the channels by themselves (n r = 256, B = 1: d = 1024 39.6 us either way, d = 2048 86 -> 63).
-__device__ __forceinline__ int first_stage(int slab, int row_bytes, int SB) {
-  return row_bytes < 4096 ? 0 : (int)((unsigned)slab % (unsigned)(row_bytes / SB));
+// The stage that a slab's product starts with where every workgroup streams a slab of its own (starts_differ): one further than the
+// slab before it, slab mod stages by the reciprocal of `stages`, 2^32 / stages rounded up.  stages = 0: the beginning.
+__device__ __forceinline__ int first_stage(unsigned slab, unsigned stages, unsigned reciprocal) {
+  return stages == 0 ? 0 : (int)(slab - __umulhi(slab, reciprocal) * stages);
 }
 
 // The product of a tile whose feed is open: on return every wave holds its VB x PB accumulator blocks and

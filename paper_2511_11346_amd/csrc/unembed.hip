@@ -250,8 +250,9 @@ constexpr bool unembed_walks_tiles() { return !SAMPLE && WB != 1; }
 // scales of fp16 terms' rows that come out of the result behind it, is the bf16 kernel's.
 // STREAM: one tile of positions, so that every byte of W is read once (loaded with the non-temporal hint).
 // PH: 16 more positions per wave (Tile).
+// ROT: slabs may start at different stages of K (UnembedArgs::first_stages).
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, int SPLIT = 0, int VH = 0,
-          bool STREAM = false, int PH = 0>
+          bool STREAM = false, int PH = 0, bool ROT = SPLIT == 0 && !SAMPLE && WB != 1>
 __global__ __launch_bounds__(WV * WB * 64)
 void k_unembed(const UnembedArgs a) {
   // of the launches over the same fp32 operands one does the work (see launch_split)
@@ -278,7 +279,6 @@ void k_unembed(const UnembedArgs a) {
   // softmax statistics are taken, instead of after a workgroup launch with the matrix pipe idle.
   // Every other instantiation has one tile per workgroup and leaves the loop after it.
   constexpr bool WALK = unembed_walks_tiles<WB, SAMPLE>();
-  constexpr bool ROT = SPLIT == 0 && !SAMPLE && (STREAM || WB != 1);      // (tiles that a launch may have one row of)
   using Feed = TileFeed<WV, WB, VB, PB, SB, NS, BF16, false, M16, WPACK, STREAM, PH, SPLIT, VH, 0, ROT>;
   const void* const hstaged = SPLIT ? a.hq : (WB != 1 && SB == H_STAGE_BYTES) ? a.hs : nullptr;
   const void* const Wfeed = SPLIT ? a.Wq : WPACK ? a.Wp : a.W;
@@ -290,12 +290,13 @@ void k_unembed(const UnembedArgs a) {
   tile_of_block(blockIdx.x, nbt, nslab, slab, bt);
   Feed feed;
   const int wrows = SPLIT ? a.Wq_rows : 0;
-  // One tile of positions: every workgroup streams a slab of its own.  Tiles that share slabs and rows of h in an L2 walk K together,
-  // from its beginning (starts that differ: B = 300 .. 1000 the same, B = 4096 and 8192 0.4 % slower).  Passes that draw, or fill a table
-  // that tokens are drawn from, do as well: with sums in another order one token in 30,000 falls on the other side of its uniform, and
-  // a draft of a given seed is to stay what it was (draft and score, B = 61, W's own rows, 320 / 309 us; the gathered draws of n r = 1024,
-  // B = 4096 446 / 439; draft, table, scores and verification, n r = 256, d = 2048, B = 256 171 / 152).
-  auto first = [&](int sl) { return ROT && nbt == 1 && !a.drawn ? first_stage(sl, a.d * (BF16 ? 2 : 4), SB) : 0; };
+  // One tile of positions: every workgroup streams a slab of its own, and where W's rows ask for it (starts_differ) from a stage of
+  // its own on.  Tiles that share slabs and rows of h in an L2 walk K together, from its beginning (starts that differ: B = 300 .. 1000
+  // the same, B = 4096 and 8192 0.4 % slower).  Passes that draw, or fill a table that tokens are drawn from, do as well: with sums in
+  // another order one token in 30,000 falls on the other side of its uniform, and a draft of a given seed is to stay what it was (draft
+  // and score, B = 61, W's own rows, 320 / 309 us; the gathered draws of n r = 1024, B = 4096 446 / 439; draft, table, scores and
+  // verification, n r = 256, d = 2048, B = 256 171 / 152).
+  auto first = [&](int sl) { return ROT ? first_stage(sl, a.first_stages, a.first_reciprocal) : 0; };
   feed.open(Wfeed, dfeed, a.h, a.ld_h, a.B, dfeed, a.v, slab, bt * TL::TP, smem, nullptr, 0, 1, hstaged, wrows, slab * a.v,
             first(slab));
   for (int w = blockIdx.x;;) {
@@ -1101,15 +1102,24 @@ hipError_t launch_univariate(const UnivariateArgs& a, int dtype, hipStream_t st)
   return dtype == MTPC_BF16 ? launch_uni_dt<true>(a, st) : launch_uni_dt<false>(a, st);
 }
 
+// (of launches with one tile of positions)
+static void set_first_stages(UnembedArgs& a, int row_bytes, int SB, int positions) {
+  if (a.drawn || !starts_differ(row_bytes, positions)) return;
+  a.first_stages = (unsigned)(row_bytes / SB);
+  a.first_reciprocal = (unsigned)(((1ull << 32) + a.first_stages - 1) / a.first_stages);     // (exact below 2^32 / stages, far beyond n r)
+}
+
 template <int WV, int WB, int VB, int PB, int SB, int NS, bool BF16, bool SAMPLE, bool WPACK = false, int SPLIT = 0, int VH = 0,
-          bool STREAM = false, int PH = 0>
-static hipError_t launch_cfg(const UnembedArgs& a, hipStream_t st) {
+          bool STREAM = false, int PH = 0, bool ROT = SPLIT == 0 && !SAMPLE && WB != 1>
+static hipError_t launch_cfg(UnembedArgs a, hipStream_t st) {
   using TL = Tile<WV, WB, VB, PB, SB, NS, PH, VH>;
-  constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK, SPLIT, VH, STREAM, PH>;
+  constexpr auto kern = k_unembed<WV, WB, VB, PB, SB, NS, BF16, SAMPLE, WPACK, SPLIT, VH, STREAM, PH, ROT>;
   constexpr int smem = TL::SMEM + (SPLIT == 2 ? TL::ROWS * 4 : 0);
   static_assert(smem <= 160 * 1024, "LDS budget of one CU");
   if (hipError_t e = allow_lds<kern>(smem); e != hipSuccess) return e;
   const int nbt = (a.B + TL::TP - 1) / TL::TP;
+  if constexpr (ROT)
+    if (nbt == 1) set_first_stages(a, a.d * (BF16 ? 2 : 4), SB, TL::TP);
   int grid = nbt * a.n * a.r;
   if constexpr (unembed_walks_tiles<WB, SAMPLE>()) {
     // one workgroup per CU (the ring takes most of a CU's LDS, so no two share one), a multiple of the
@@ -1134,14 +1144,21 @@ static hipError_t launch_dec(const UnembedArgs& a, int row_bytes, hipStream_t st
     // beside them has both in use, 2 x 146 MB at n r = 96, v = 256, d = 2976 where 256 MB are cached: draft and score, B = 126
     // 142 / 93 us)
     if (a.Wp != nullptr && a.Wp_stage == 64) return launch_cfg<WV, 1, 2, PB, 64, 4, BF16, SAMPLE, true>(a, st);
-    return row_bytes % 128 == 0 ? launch_cfg<WV, 1, 2, PB, 128, 3, BF16, SAMPLE>(a, st)
-                                : launch_cfg<WV, 1, 2, PB, 64, 4, BF16, SAMPLE>(a, st);
+    if constexpr (BF16)                              // (fp32 rows always are of whole 128-byte stages)
+      if (row_bytes % 128 != 0) return launch_cfg<WV, 1, 2, PB, 64, 4, BF16, SAMPLE>(a, st);
+    return launch_cfg<WV, 1, 2, PB, 128, 3, BF16, SAMPLE>(a, st);
   }
-  if (row_bytes % 128 == 0) {
-    if (a.Wp != nullptr && a.Wp_stage == 128) return launch_cfg<WV, 1, 2, PB, 128, 3, BF16, SAMPLE, true, false, 0, true>(a, st);
-    return launch_cfg<WV, 1, 2, PB, 128, 3, BF16, SAMPLE, false, false, 0, true>(a, st);
-  }
-  return launch_cfg<WV, 1, 2, PB, 64, 4, BF16, SAMPLE, false, false, 0, true>(a, st);
+  auto stream = [&](auto rot) {
+    constexpr bool ROT = decltype(rot)::value;
+    if constexpr (BF16)
+      if (row_bytes % 128 != 0) return launch_cfg<WV, 1, 2, PB, 64, 4, BF16, SAMPLE, false, 0, 0, true, 0, ROT>(a, st);
+    if (a.Wp != nullptr && a.Wp_stage == 128) return launch_cfg<WV, 1, 2, PB, 128, 3, BF16, SAMPLE, true, 0, 0, true, 0, ROT>(a, st);
+    return launch_cfg<WV, 1, 2, PB, 128, 3, BF16, SAMPLE, false, 0, 0, true, 0, ROT>(a, st);
+  };
+  // (a kernel of its own: what the wrapping round takes of small calls, FF, 24 positions, d = 640, 9.6 / 9.3 us)
+  if constexpr (!SAMPLE)
+    if (!a.drawn && starts_differ(row_bytes, PB * 32)) return stream(std::true_type{});
+  return stream(std::false_type{});
 }
 
 // Tiles of 256 (PB = 2), 192 (PB = PH = 1) or 128 positions of the fewest rows that hold the vocabulary (a K stage costs what its rows
@@ -1496,7 +1513,7 @@ void k_unembed_few(const UnembedArgs a, const ParamArgs p) {
   TileFeed<WV, 1, RB / 2, PB, SB, NS, BF16, false, true, false, STREAM, PH, 0, 0, 0, STREAM> feed;
   // (one tile of positions: slabs from different stages on, and W as a stream, as in k_unembed)
   feed.open(sum ? p.Wsum : a.W, a.d, a.h, a.ld_h, a.B, a.d, rows, slab, b0, smem, nullptr, 0, 1, nullptr, 0, 0,
-                STREAM ? first_stage(slab, a.d * ESZ, SB) : 0);
+            STREAM ? first_stage(slab, a.first_stages, a.first_reciprocal) : 0);
   // this lane's target of the first windows: fetched while nothing depends on it
   const int T = sum || a.targets == nullptr ? 0 : a.T, TT = T == 0 ? 0 : T + a.T2;
   auto target = [&](int b, int t) {
@@ -1647,7 +1664,7 @@ void k_unembed_few(const UnembedArgs a, const ParamArgs p) {
 }
 
 template <bool BF16, int WV, int RB, int NPB, int SB, int NS, bool STREAM = false>
-static hipError_t launch_few_cfg(const UnembedArgs& a, const ParamArgs& p, hipStream_t st) {
+static hipError_t launch_few_cfg(UnembedArgs a, const ParamArgs& p, hipStream_t st) {
   using TL = Tile<WV, 1, RB / 2, NPB / 2, SB, NS, NPB % 2>;
   const int nbt = (a.B + TL::TP - 1) / TL::TP;
   // Each slab is read once: as a stream, where W is too large for the 256 MB cache to keep much of it from one call to the next (n r =
@@ -1655,6 +1672,7 @@ static hipError_t launch_few_cfg(const UnembedArgs& a, const ParamArgs& p, hipSt
   if constexpr (!STREAM)
     if (nbt == 1 && (long long)a.n * a.r * a.v * a.d * (BF16 ? 2 : 4) > (128LL << 20))
       return launch_few_cfg<BF16, WV, RB, NPB, SB, NS, true>(a, p, st);
+  if constexpr (STREAM) set_first_stages(a, a.d * (BF16 ? 2 : 4), SB, TL::TP);
   constexpr auto kern = k_unembed_few<BF16, WV, RB, NPB, SB, NS, STREAM>;
   if (hipError_t e = allow_lds<kern>(TL::SMEM); e != hipSuccess) return e;
   const long long lrows = (long long)p.nb * p.L * p.r;
